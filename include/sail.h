@@ -214,8 +214,8 @@ sail_status sail_read_chi2(sail_problem_t p, double *out, void *stream);
  * the population's residues between its mean and minimum, which drive the
  * self-cooling prescription of Sec. 2.4 (residues in the unit of Sec. 3).
  * If lo or hi is NaN the ensemble minimum / maximum is used.
- * counts: host, n_bins uint64.  Allocates and frees a device buffer for the
- * counts on every call. */
+ * counts: host, n_bins uint64.  The device buffer of the counts is allocated
+ * on the first call (again when n_bins grows) and kept with the walkers. */
 sail_status sail_read_chi2_hist(sail_problem_t p, int n_bins, double lo, double hi, uint64_t *counts,
                                 void *stream);
 

@@ -1858,13 +1858,60 @@ __global__ __launch_bounds__(kBranchThreads) void k_branch_final(BranchArgs a, B
 // --------------------------------------------------------------------------
 // Outputs (Eq. residue-average over the walkers; chi^2 histogram)
 // --------------------------------------------------------------------------
-__global__ void k_mean_spectrum(int n_walkers, int n_omega, const double *b, const double *gsc, double *out)
+// Ensemble mean, bound by reading the spectra once: a workgroup takes kMeanBins
+// bins (256-byte row segments) of up to kMeanSpan walkers, kMeanRows of them
+// side by side, each thread its walkers in ascending order, the row sums added
+// pairwise through LDS.  Populations of more than kMeanSpan walkers leave one
+// partial sum per span, so that all compute units read (one workgroup per bin
+// tile took 50 us over 64 MiB: a quarter of the compute units), and a second
+// launch adds them in order.
+// 512 bins x 16384 walkers: 4.0 ms with one thread per bin, 12 us (5.6 TB/s) and 4 us
+// for the second launch now.
+constexpr int kMeanBins = 32, kMeanRows = 32, kMeanSpan = 512;
+
+int mean_spans(int n_walkers) { return (n_walkers + kMeanSpan - 1) / kMeanSpan; }
+
+__global__ __launch_bounds__(kMeanBins * kMeanRows) void k_mean_spectrum(int n_walkers, int n_omega, const double *b,
+                                                                         const double *gsc, double *out)
+{
+    __shared__ double part[kMeanRows][kMeanBins];
+    const int c = threadIdx.x % kMeanBins, r = threadIdx.x / kMeanBins;
+    const int j = blockIdx.x * kMeanBins + c;
+    const int l0 = blockIdx.y * kMeanSpan, l1 = min(l0 + kMeanSpan, n_walkers);
+    double s = 0.0;
+    if (j < n_omega) {
+#pragma unroll 8
+        for (int l = l0 + r; l < l1; l += kMeanRows) s = fma(gsc[l], b[(size_t)l * n_omega + j], s);
+    }
+    part[r][c] = s;
+    for (int h = kMeanRows / 2; h >= 1; h >>= 1) {
+        __syncthreads();
+        if (r < h) part[r][c] += part[r + h][c];
+    }
+    if (r == 0 && j < n_omega)
+        out[(size_t)blockIdx.y * n_omega + j] = gridDim.y > 1 ? part[0][c] : part[0][c] / (double)n_walkers;
+}
+
+__global__ void k_mean_sum(int n_walkers, int n_omega, int spans, const double *part, double *out)
 {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n_omega) return;
-    double s = 0.0;
-    for (int l = 0; l < n_walkers; ++l) s += gsc[l] * b[(size_t)l * n_omega + j];
+    double s = part[j];
+#pragma unroll 8
+    for (int i = 1; i < spans; ++i) s += part[(size_t)i * n_omega + j];
     out[j] = s / (double)n_walkers;
+}
+
+// part: [mean_spans(n_walkers)][n_omega], may not overlap out
+void launch_mean_spectrum(int n_walkers, int n_omega, const double *b, const double *gsc, double *part, double *out,
+                          hipStream_t stream)
+{
+    const int spans = mean_spans(n_walkers);
+    hipLaunchKernelGGL(k_mean_spectrum, dim3((unsigned)((n_omega + kMeanBins - 1) / kMeanBins), (unsigned)spans),
+                       dim3(kMeanBins * kMeanRows), 0, stream, n_walkers, n_omega, b, gsc, spans > 1 ? part : out);
+    if (spans > 1)
+        hipLaunchKernelGGL(k_mean_sum, dim3((unsigned)((n_omega + 255) / 256)), dim3(256), 0, stream, n_walkers,
+                           n_omega, spans, (const double *)part, out);
 }
 
 // Self-cooling temperature of block b (Sec. 2.4; reading: boil at the mean
@@ -1910,10 +1957,22 @@ __global__ void k_self_cool(const double *chi2, int n, int b, int boil, int cool
     for (int k = k0 + (int)threadIdx.x; k < k1; k += (int)blockDim.x) Tabs[k] = Tb;
 }
 
-__global__ void k_minmax(int n, const double *v, double *out)
+constexpr int kHistMaxBins = 4096, kHistThreads = 256, kMinMaxThreads = 1024;
+
+// Clears n words with vector stores (a kernel node, unlike a memset, is safe
+// to record into a captured graph).
+__global__ void k_zero_u64(int n, unsigned long long *v)
 {
-    __shared__ double red[kThreads / 64];
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) v[i] = 0ull;
+}
+
+// Smallest and largest of n values, one workgroup (16384 values: 28 us with 256
+// threads, 5 us with 1024; latency, four values in flight per thread).
+__global__ __launch_bounds__(kMinMaxThreads) void k_minmax(int n, const double *v, double *out)
+{
+    __shared__ double red[kMinMaxThreads / 64];
     double lo = INFINITY, hi = -INFINITY;
+#pragma unroll 4
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         lo = fmin(lo, v[i]);
         hi = fmax(hi, v[i]);
@@ -1926,21 +1985,45 @@ __global__ void k_minmax(int n, const double *v, double *out)
     }
 }
 
-__global__ void k_chi2_hist(int n, const double *chi2, int n_bins, double lo, double hi, const double *range,
-                            unsigned long long *counts)
+// Histogram of log10 chi^2: counts first in the workgroup's LDS, so that the
+// few bins of a population's residues meet in LDS rather than in one memory
+// word (16384 residues in 64 bins: 43 us with one global atomic per residue,
+// 4 us now).
+__global__ __launch_bounds__(kHistThreads) void k_chi2_hist(int n, const double *chi2, int n_bins, double lo, double hi,
+                                                           const double *range, unsigned long long *counts)
 {
-    const int l = blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= n) return;
+    __shared__ unsigned int local[kHistMaxBins];
+    for (int i = threadIdx.x; i < n_bins; i += blockDim.x) local[i] = 0u;
+    __syncthreads();
     if (range) {
         if (lo != lo) lo = log10(range[0]);
         if (hi != hi) hi = log10(range[1]);
     }
-    const double v = log10(chi2[l]);
     const double width = hi - lo;
-    int bin = (width > 0.0) ? (int)floor((v - lo) / width * (double)n_bins) : 0;
-    if (!(v == v)) bin = 0;
-    bin = max(0, min(n_bins - 1, bin));
-    atomicAdd(counts + bin, 1ull);
+    for (int l = blockIdx.x * blockDim.x + threadIdx.x; l < n; l += gridDim.x * blockDim.x) {
+        const double v = log10(chi2[l]);
+        int bin = (width > 0.0) ? (int)floor((v - lo) / width * (double)n_bins) : 0;
+        if (!(v == v)) bin = 0;
+        bin = max(0, min(n_bins - 1, bin));
+        atomicAdd(local + bin, 1u);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n_bins; i += blockDim.x)
+        if (local[i]) atomicAdd(counts + i, (unsigned long long)local[i]);
+}
+
+// Clears the counts, finds the range where it is asked for (into range) and
+// counts; range: two doubles, counts: n_bins words on the device.
+hipError_t launch_chi2_hist(int n, const double *chi2, int n_bins, double lo, double hi, double *range,
+                            unsigned long long *counts, hipStream_t stream)
+{
+    hipLaunchKernelGGL(k_zero_u64, dim3((n_bins + kThreads - 1) / kThreads), dim3(kThreads), 0, stream, n_bins, counts);
+    const bool need_range = (lo != lo) || (hi != hi);
+    if (need_range) hipLaunchKernelGGL(k_minmax, dim3(1), dim3(kMinMaxThreads), 0, stream, n, chi2, range);
+    const int blocks = std::min(64, (n + kHistThreads - 1) / kHistThreads);
+    hipLaunchKernelGGL(k_chi2_hist, dim3(blocks), dim3(kHistThreads), 0, stream, n, chi2, n_bins, lo, hi,
+                       need_range ? (const double *)range : nullptr, counts);
+    return hipGetLastError();
 }
 
 // Scratch of the allocation-free histogram (sail_read_chi2_hist_noalloc):
@@ -1949,16 +2032,9 @@ __global__ void k_chi2_hist(int n, const double *chi2, int n_bins, double lo, do
 // device the library runs on holds one copy until the process ends.  In host
 // code this name is only a stand-in for the symbol: kernels receive the
 // address hipGetSymbolAddress returns for the current device.
-constexpr int kNoAllocMaxBins = 4096;
+constexpr int kNoAllocMaxBins = kHistMaxBins;
 constexpr int kScratchRangeWords = 32;
 static __device__ __align__(256) unsigned long long scratch[kScratchRangeWords + kNoAllocMaxBins];
-
-// Clears n words with vector stores (a kernel node, unlike a memset, is safe
-// to record into a captured graph).
-__global__ void k_zero_u64(int n, unsigned long long *v)
-{
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) v[i] = 0ull;
-}
 
 // --------------------------------------------------------------------------
 // Host side
@@ -2126,6 +2202,9 @@ struct sail_problem {
     double *d_b = nullptr, *d_gsc = nullptr, *d_ginv = nullptr, *d_chi2 = nullptr, *d_rate = nullptr;
     void *d_Phi = nullptr;  // in the loop precision
     double *d_a0 = nullptr, *d_tmp = nullptr, *d_teff = nullptr;  // d_teff: imprint strength of the last event
+    double *d_part = nullptr;               // partial sums of the averaged spectrum
+    unsigned long long *d_hist = nullptr;   // counts of the residue histogram, kept from its first call
+    int cap_hist = 0;
     int32_t *d_m = nullptr, *d_targets = nullptr, *d_donors = nullptr, *d_npairs = nullptr;
     BranchTree *d_tree = nullptr;  // state of the parallel Delta search
     // events
@@ -2166,13 +2245,14 @@ struct sail_problem {
     void free_walkers()
     {
         dfree(d_b); dfree(d_Phi); dfree(d_gsc); dfree(d_ginv); dfree(d_chi2); dfree(d_rate);
-        dfree(d_a0); dfree(d_tmp); dfree(d_teff); dfree(d_m); dfree(d_targets); dfree(d_donors); dfree(d_npairs);
+        dfree(d_a0); dfree(d_tmp); dfree(d_teff); dfree(d_part); dfree(d_hist); dfree(d_m); dfree(d_targets); dfree(d_donors); dfree(d_npairs);
         dfree(d_tree);
         dfree(d_ev_delta); dfree(d_ev_pr); dfree(d_ev_z); dfree(d_ev_status); dfree(d_ev_m);
         dfree(d_ev_gap); dfree(d_ev_bracket);
         free_watch();
         free_block_log();
         cap_events = 0;
+        cap_hist = 0;
         n_walkers = 0;
     }
     void free_block_log()
@@ -3484,9 +3564,8 @@ void serve(sail_server *S)
                     ++it;
                     continue;
                 }
-                hipLaunchKernelGGL(k_mean_spectrum, dim3((unsigned)((j->omega.size() + 255) / 256)), dim3(256), 0,
-                                   S->stream, j->n_walkers, (int)j->omega.size(), (const double *)j->p->d_b,
-                                   (const double *)j->p->d_gsc, j->d_mean);
+                launch_mean_spectrum(j->n_walkers, (int)j->omega.size(), j->p->d_b, j->p->d_gsc, j->p->d_part, j->d_mean,
+                                     S->stream);
                 (void)hipEventRecord(j->done, S->stream);
                 j->state = kFinishing;
                 S->finishing.push_back(j);
@@ -3592,7 +3671,7 @@ size_t sail_footprint_bytes(int n_omega, int n_tau, int n_walkers, int precision
     max_padding(n_tau, precision, &ntp, &lanes);
     const size_t No = (size_t)n_omega, Nw = (size_t)n_walkers;
     const size_t walkers = sizeof(double) * Nw * (No + 4) + rsz * Nw * ntp + sizeof(int32_t) * (3 * Nw + 4) +
-                           sizeof(double) * (No + std::max<size_t>(No, 64)) + 64 * (4 * sizeof(double) + 2 * sizeof(int32_t)) +
+                           sizeof(double) * (No + std::max<size_t>(No, 64) + No * (size_t)mean_spans(n_walkers)) + 64 * (4 * sizeof(double) + 2 * sizeof(int32_t)) +
                            sizeof(BranchTree);
     return table_bytes(n_omega, n_tau, precision) + walkers;
 }
@@ -3805,7 +3884,8 @@ sail_status sail_walkers_init(sail_problem_t p, int n_walkers, uint64_t seed, in
     p->d_Phi = phi;
     if ((st = dalloc(&p->d_b, (size_t)n_walkers * No)) || (st = dalloc(&p->d_gsc, n_walkers)) || (st = dalloc(&p->d_ginv, n_walkers)) ||
         (st = dalloc(&p->d_chi2, n_walkers)) || (st = dalloc(&p->d_rate, n_walkers)) || (st = dalloc(&p->d_a0, No)) ||
-        (st = dalloc(&p->d_tmp, std::max(No, 64))) || (st = dalloc(&p->d_teff, 1)) || (st = dalloc(&p->d_m, n_walkers)) || (st = dalloc(&p->d_targets, n_walkers)) ||
+        (st = dalloc(&p->d_tmp, std::max(No, 64))) || (st = dalloc(&p->d_teff, 1)) ||
+        (st = dalloc(&p->d_part, (size_t)mean_spans(n_walkers) * No)) || (st = dalloc(&p->d_m, n_walkers)) || (st = dalloc(&p->d_targets, n_walkers)) ||
         (st = dalloc(&p->d_donors, n_walkers)) || (st = dalloc(&p->d_npairs, 4)) || (st = dalloc(&p->d_tree, 1))) {
         p->free_walkers();
         return st;
@@ -4129,8 +4209,7 @@ sail_status sail_read_spectrum(sail_problem_t p, double *out, void *stream_)
     hipStream_t stream = (hipStream_t)stream_;
     SAIL_HIP(hipSetDevice(p->device));
     // d_tmp holds max(64, n_omega) doubles (allocated with the walkers)
-    hipLaunchKernelGGL(k_mean_spectrum, dim3((p->n_omega + 255) / 256), dim3(256), 0, stream, p->n_walkers, p->n_omega,
-                       (const double *)p->d_b, (const double *)p->d_gsc, p->d_tmp);
+    launch_mean_spectrum(p->n_walkers, p->n_omega, p->d_b, p->d_gsc, p->d_part, p->d_tmp, stream);
     SAIL_HIP(hipGetLastError());
     SAIL_HIP(hipMemcpyAsync(out, p->d_tmp, sizeof(double) * p->n_omega, hipMemcpyDeviceToHost, stream));
     SAIL_HIP(hipStreamSynchronize(stream));
@@ -4152,18 +4231,7 @@ sail_status sail_read_chi2_hist_noalloc(sail_problem_t p, int n_bins, double lo,
     if (st) return st;
     double *range = (double *)sc;
     unsigned long long *d_counts = sc + kScratchRangeWords;
-    // the array keeps the previous call's counts: clear the bins this call uses
-    hipLaunchKernelGGL(k_zero_u64, dim3((n_bins + kThreads - 1) / kThreads), dim3(kThreads), 0, stream, n_bins, d_counts);
-    SAIL_HIP(hipGetLastError());
-    const bool need_range = (lo != lo) || (hi != hi);
-    if (need_range) {
-        hipLaunchKernelGGL(k_minmax, dim3(1), dim3(kThreads), 0, stream, p->n_walkers, (const double *)p->d_chi2, range);
-        SAIL_HIP(hipGetLastError());
-    }
-    hipLaunchKernelGGL(k_chi2_hist, dim3((p->n_walkers + 255) / 256), dim3(256), 0, stream, p->n_walkers,
-                       (const double *)p->d_chi2, n_bins, lo, hi, need_range ? (const double *)range : nullptr,
-                       d_counts);
-    SAIL_HIP(hipGetLastError());
+    SAIL_HIP(launch_chi2_hist(p->n_walkers, p->d_chi2, n_bins, lo, hi, range, d_counts, stream));
     SAIL_HIP(hipMemcpyAsync(counts, d_counts, sizeof(uint64_t) * n_bins, hipMemcpyDefault, stream));
     SAIL_HIP(hipStreamSynchronize(stream));
     return SAIL_OK;
@@ -4175,25 +4243,17 @@ sail_status sail_read_chi2_hist(sail_problem_t p, int n_bins, double lo, double 
     if (p->n_walkers == 0) return fail(SAIL_ESTATE, "initialise walkers first");
     hipStream_t stream = (hipStream_t)stream_;
     SAIL_HIP(hipSetDevice(p->device));
-    unsigned long long *d_counts = nullptr;
-    sail_status st = dalloc(&d_counts, n_bins);
-    if (st) return st;
-    hipError_t e = hipMemsetAsync(d_counts, 0, sizeof(unsigned long long) * n_bins, stream);
-    const bool need_range = (lo != lo) || (hi != hi);
-    if (e == hipSuccess && need_range) {
-        hipLaunchKernelGGL(k_minmax, dim3(1), dim3(kThreads), 0, stream, p->n_walkers, (const double *)p->d_chi2, p->d_tmp);
-        e = hipGetLastError();
+    if (n_bins > p->cap_hist) {
+        unsigned long long *d = nullptr;
+        const sail_status st = dalloc(&d, n_bins);
+        if (st) return st;
+        dfree(p->d_hist);
+        p->d_hist = d;
+        p->cap_hist = n_bins;
     }
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_chi2_hist, dim3((p->n_walkers + 255) / 256), dim3(256), 0, stream, p->n_walkers,
-                           (const double *)p->d_chi2, n_bins, lo, hi, need_range ? (const double *)p->d_tmp : nullptr,
-                           d_counts);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) e = hipMemcpyAsync(counts, d_counts, sizeof(uint64_t) * n_bins, hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    dfree(d_counts);
-    if (e != hipSuccess) return fail(SAIL_EDEVICE, hipGetErrorString(e));
+    SAIL_HIP(launch_chi2_hist(p->n_walkers, p->d_chi2, n_bins, lo, hi, p->d_tmp, p->d_hist, stream));
+    SAIL_HIP(hipMemcpyAsync(counts, p->d_hist, sizeof(uint64_t) * n_bins, hipMemcpyDeviceToHost, stream));
+    SAIL_HIP(hipStreamSynchronize(stream));
     return SAIL_OK;
 }
 

@@ -1,0 +1,34 @@
+"""GPU: the read-outs (averaged spectrum, residue histogram) at the edges of
+their tiles and walker spans, against numpy on the walkers' own state."""
+import numpy as np
+import pytest
+
+from paper_1609_07936_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_omega,n_walkers", [(3, 2), (31, 33), (32, 512), (33, 513), (65, 1025), (300, 2049)])
+def test_averaged_spectrum_and_histogram(n_omega, n_walkers):
+    from paper_1609_07936_amd import sail as S
+    tgt = W.Target([1.5, 4.0], [0.4, 0.8], [0.6, 0.4], 10.0)
+    wl = W.make("ro", 10.0, n_omega, W.uniform_tau(0.05, 1.6, 12), tgt, 1e-3, 3, n_walkers, 4, 1e2, 1.0, 100, 100, 5,
+                n_quad=2000)
+    gp = S.Problem(wl.omega, wl.tau, wl.Ft, wl.sigma, wl.m0, wl.m1)
+    gp.init_walkers(n_walkers, 7)
+    gp.run(S.Schedule(np.full(4, 50.0)), 0, 3)  # between resyncs: scales other than 1
+    a, chi2 = gp.read_state()["a"], gp.read_chi2()
+    # both sums add non-negative terms: relative error below one rounding per term and side
+    np.testing.assert_allclose(gp.read_spectrum(), a.mean(axis=0), rtol=2.0 * (n_walkers + 4) * 2.0 ** -53, atol=0)
+    v = np.log10(chi2)
+    for n_bins, lo, hi in ((1, np.nan, np.nan), (7, np.nan, np.nan), (300, v.min() + 0.1 * np.ptp(v), v.max()),
+                           (4096, np.nan, np.nan), (5, np.nan, np.nan)):
+        counts = gp.read_chi2_hist(n_bins, lo, hi)
+        np.testing.assert_array_equal(gp.read_chi2_hist_noalloc(n_bins, lo, hi), counts)
+        assert counts.sum() == n_walkers
+        l, h = v.min() if np.isnan(lo) else lo, v.max() if np.isnan(hi) else hi
+        # a residue within 1e-9 of an inner edge may be counted on either side
+        edges = l + (h - l) * np.arange(1, n_bins) / n_bins
+        below = np.cumsum(counts)[:-1]
+        assert np.all(below >= (v[None, :] < edges[:, None] - 1e-9).sum(axis=1))
+        assert np.all(below <= (v[None, :] < edges[:, None] + 1e-9).sum(axis=1))
