@@ -7,21 +7,23 @@
 //     the exact bin integral of Eq. correlation-model).  The walkers carry
 //     Phi_i = F_i / c_i, so the data become Phit_i = F_i / c_i and the weights
 //     wh_i = c_i^2 / sigma_i^2; chi^2 is unchanged.
-//   * On a uniform tau grid the two columns a proposal needs,
-//     e^{-omega_p tau_i} and e^{-omega_s tau_i}, are generated by the geometric
-//     recurrence e^{-omega (tau_i + d_tau)} = e^{-omega tau_i} e^{-omega d_tau}
-//     from one start value per lane chunk (the power form of
-//     Eq. efficient-correlation-model), so the sweep reads no kernel table.
-//   * A walker occupies L lanes of a wavefront; each lane owns TPL consecutive
-//     tau points and keeps Phi, wh and the proposal's s = dp K_p + ds K_s in
-//     registers.  The residue change is taken from its expansion, whose only
-//     sum over tau that needs the walker is sum_i w_i Phi_i s_i (a butterfly
-//     over the L lanes; every lane ends with the same bits and so takes the
-//     same accept decision); the walker-independent sums come from per-bin and
-//     pair-sum tables, and a commit is Phi = r Phi + s.
+//   * The weighted columns sqrt(wh_i) e^{-omega_j tau_i} of all bins lie, to
+//     rounding, in a space of few dimensions (16 for the benchmark's 512 bins
+//     and 128 times): a Laplace kernel's singular values fall geometrically.
+//     The host builds an orthonormal basis of it, the sweep carries each
+//     walker's coordinates phi of sqrt(wh) Phi in that basis, and sums over
+//     tau become sums over the basis.
+//   * A walker occupies G lanes of a wavefront; lane c holds chunk c mod 4 of
+//     phi in registers.  The residue change is taken from its expansion, whose
+//     only sum that needs the walker is sum_i w_i Phi_i s_i = phi . sigma with
+//     sigma = dp C_p + ds C_s (C_j: column j in the basis; four chunk sums and
+//     a two-step butterfly, so every lane ends with the same bits and takes the
+//     same accept decision, whatever G is); the walker-independent sums come
+//     from per-bin and pair-sum tables, and a commit is phi = r phi + sigma.
 //   * Spectra live in HBM as b_j with a_j = g b_j (a lazy scale g per walker),
-//     so a move touches two coefficients instead of N_omega.  Lane 0 of each
-//     walker owns the spectrum accesses; the scale is folded back at resync.
+//     so a move touches two coefficients instead of N_omega.  Lane c of a
+//     walker owns the spectrum accesses of the proposals it staged; the scale
+//     is folded back at resync.
 //
 // All code is compiled with -ffp-contract=off; fused multiply-adds are
 // written explicitly where wanted, and the scalar move arithmetic keeps the
@@ -41,6 +43,7 @@
 #include <thread>
 #include <mutex>
 #include <tuple>
+#include <type_traits>
 #include <string>
 #include <vector>
 
@@ -143,21 +146,20 @@ __device__ __forceinline__ double staged_threshold(double T, double u)
 // Sweep kernel: sweeps [k0, k1) for every walker (Sec. 2.2, 2.3, 2.7).
 // --------------------------------------------------------------------------
 struct SweepArgs {
-    int n_walkers, n_omega, lanes, log2_lanes, ntau_pad;
+    int n_walkers, n_omega;
     int k0, k1;
     uint32_t key0, key1;
     double A, B, eps0, amp_p, amp_avg;
     int amp_m;
-    const double *omega;  // [N_omega] bin centres
-    const double *z;      // [N_omega] e^{-omega_j d_tau}
-    const void *E0;       // [N_omega][lanes] e^{-omega_j tau_{c TPL}} in the loop precision
-    const void *wh;       // [ntau_pad] weights in the loop precision, 0 on padding
-    void *Phi;            // [N_w][ntau_pad] in the loop precision
+    int chunk;            // basis dimensions per chunk as stored (a multiple of 16 bytes)
+    int columns_lds;      // 1: the workgroup copies the columns to LDS
+    const void *col;      // [N_omega][4][chunk] columns in the basis, loop precision
+    void *phi;            // [N_w][4][chunk] walkers in the basis, loop precision
     // the parts of the residue change that do not depend on the walker (FP64):
     // D_j = sum_i w_i K_ij^2, V_j = sum_i c_i K_ij with c_i = -2 w_i Phit_i, and
     // (G_k, H_k) = sum_i w_i (1, tau_i) e^{-wbar_k tau_i} on the pair sums
     // wbar_k = 2 omega_0 + k d_omega, with C = sum_i w_i Phit_i^2
-    const double *D, *V;  // [N_omega]
+    const double4 *bin;   // [N_omega] (omega_j, D_j, V_j, 0)
     const double2 *GH;    // [2 N_omega - 1]
     double C, w0, dW;
     double *b;            // [N_w][N_omega] spectra up to the lazy scale
@@ -217,33 +219,55 @@ __device__ __forceinline__ void wave_lds_sync()
 }
 
 // Per-proposal quantities that do not depend on the walker state, computed
-// for a batch of L proposals at once (lane c of a walker takes proposal
-// q0 + c) and staged in LDS, in 16-byte pairs: the bins p and s, the deltas
-// dp and ds, the coefficients of the kernel-column recurrences, 1/r, r - 1
-// and r, the accept threshold and the half-width of its uncertainty band,
-// and the walker-independent parts of the residue change, S1 = sum_i w_i s_i^2
-// and S1 + S3 with S3 = sum_i c_i s_i (s_i = dp K_pi + ds K_si).
-// The recurrence coefficients with z = e^{-omega d_tau}: in FP64 dp z_p,
-// ds z_s (second terms of s_i) and z_p + z_s, -z_p z_s (two-term recurrence);
-// in FP32 z_p, z_s (two first-order recurrences).
+// for a batch of G proposals at once (lane c of a walker takes proposal
+// q0 + c) and staged in LDS, read in 16-byte pairs: r - 1, 1/r, the accept
+// threshold, the walker-independent parts of the residue change, S1 =
+// sum_i w_i s_i^2 and S1 + S3 with S3 = sum_i c_i s_i (s_i = dp K_pi + ds K_si),
+// the deltas dp and ds, and the bins, each twice in one word (p | p << 16,
+// s | s << 16).  The bins also stand apart: they are read a proposal earlier
+// than the rest.
 enum : int {
-    kRecPS = 0, kRecDp = 1, kRecDs = 2, kRecC0 = 3, kRecC1 = 4, kRecRinv = 5, kRecRm1 = 6, kRecR = 7,
-    kRecZsum = 8, kRecZprod = 9, kRecThr = 10, kRecTol = 11, kRecT = 12, kRecS1 = 13
+    kRecRm1 = 0, kRecRinv = 1, kRecThr = 2, kRecT = 3, kRecS1 = 4, kRecDp = 5, kRecDs = 6, kRecPS = 7
 };
-constexpr int kRecWords = 14;  // doubles per record
-constexpr int kSweepTables = 4;    // doubles per bin in the sweep's LDS: omega, z, D, V
-constexpr int kPairSumLds = 640;   // grids up to this many bins also keep the pair-sum table in LDS (two workgroups still fit a CU)
-size_t sweep_shmem(int n_omega)
+constexpr int kRecWords = 8;      // doubles per record
+constexpr int kWalkWords = 5;     // doubles per staged step of an index-selection walk: bins, two values, two draws
+constexpr double kNever = -1.7976931348623157e308;  // threshold of a proposal that is never accepted
+// Doubles of LDS per walker, padded against bank conflicts: the records and
+// bins of two batches (one runs while the next is staged), or of one batch and
+// its walk steps.
+constexpr int rec_stride(int G, bool walk) { return (walk ? G * (kRecWords + 1 + kWalkWords) : 2 * G * (kRecWords + 1)) + 2; }
+
+// A split sweep's walker: records of three batches, bins of four, the move
+// width; and a wavefront's masks of shared bins of three batches.
+constexpr int kSplitHits = 3 * 4;
+constexpr int kSplitStride = 3 * 4 * kRecWords + 4 * 4 + 2;
+
+// Basis dimensions per chunk as stored: whole 16-byte words.
+template <typename R>
+constexpr int chunk_stride(int m) { return sizeof(R) == 8 ? (m + 1) & ~1 : (m + 3) & ~3; }
+
+// The sweep kernels are built for these numbers of dimensions per chunk; a
+// larger basis runs the general variant (class 0).
+constexpr int kDims64[4] = {2, 4, 6, 8}, kDims32[4] = {2, 3, 4, 6};
+constexpr int kBasisClasses = 9;
+constexpr int kBasisPad = 12;  // dimensions a basis may be padded by
+constexpr int kPhiRow = 72;    // coordinates per walker up to which the read-out keeps its own rows
+// Dimensions per chunk for a basis of n dimensions.
+int round_dims(int precision, int n)
 {
-    const size_t n = (size_t)n_omega;
-    return sizeof(double) * (kSweepTables * n + (n_omega <= kPairSumLds ? 2 * (2 * n - 1) : 0));
+    const int need = n > 4 ? (n + 3) / 4 : 1;
+    for (int m : precision == SAIL_FP32 ? kDims32 : kDims64)
+        if (need <= m) return m;
+    return need;
+}
+int basis_class(int precision, int m)
+{
+    for (int v : precision == SAIL_FP32 ? kDims32 : kDims64)
+        if (m == v) return v;
+    return 0;
 }
 
-// R is the precision of the residual loop (double: the FP64 path, float:
-// the FP32 variant); moves, positivity, thresholds and chi^2 stay double.
-// LDS for the staged records of a workgroup: 4 wavefronts x (64 / L) walkers x
-// (kRecWords L + 2) doubles, largest for L = 1.
-constexpr int kRecsMax = (kThreads / 64) * 64 * (kRecWords + 2);
+size_t column_bytes(int n_omega, int chunk, size_t rsz) { return (size_t)n_omega * 4 * chunk * rsz; }
 
 // Many problems in one launch: problem q owns workgroups [first[q], first[q + 1]).
 __device__ __forceinline__ int owner_of(const int *first, const int n_jobs, const int b)
@@ -280,38 +304,64 @@ __device__ __forceinline__ void buffer_store_f64(__amdgpu_buffer_rsrc_t r, uint3
     __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, 0);
 }
 
-template <typename R>
-__device__ __forceinline__ R buffer_load_r(__amdgpu_buffer_rsrc_t r, uint32_t off)
+// One lane's chunk of a column: M values in 16-byte loads.
+template <typename R, int M>
+__device__ __forceinline__ void load_chunk(const R *p, R (&v)[M])
 {
-    if constexpr (sizeof(R) == 8) {
-        return buffer_load_f64(r, off);
-    } else {
-        const auto v = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
-        R f;
-        __builtin_memcpy(&f, &v, sizeof f);
-        return f;
+    constexpr int W = 16 / sizeof(R), MS = chunk_stride<R>(M);
+    typedef R vec __attribute__((ext_vector_type(W)));
+#pragma unroll
+    for (int i = 0; i < MS; i += W) {
+        const vec x = *(const vec *)(p + i);
+#pragma unroll
+        for (int t = 0; t < W; ++t)
+            if (i + t < M) v[i + t] = x[t];
     }
 }
 
-// The sweep of one workgroup's walkers: `block` numbers the workgroup within
-// the problem, `recs` and `dyn` are its LDS (records; omega, z and staged start
-// values).
-template <typename R, int TPL, int L, bool TRACE, bool WALK>
-__device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block, double *recs, double *dyn)
+// Lanes qq, qq + G, qq + 2 G, ...: the owners of proposal qq of a batch.
+template <int G>
+__device__ __forceinline__ uint64_t owner_lanes(int qq)
 {
-    constexpr int W = 64 / L;                       // walkers per wavefront
-    constexpr int GSTRIDE = L * kRecWords + 2;      // doubles per walker slot (padded against bank conflicts)
-    static_assert((kThreads / 64) * W * GSTRIDE <= kRecsMax, "record buffer");
-    double *om_s = dyn, *z_s = dyn + a.n_omega, *dg_s = dyn + 2 * a.n_omega, *vg_s = dyn + 3 * a.n_omega;
-    // the pair-sum table in LDS too when the launch's LDS holds it (staging then reads no global memory)
-    const bool gh_lds = a.n_omega <= kPairSumLds;
-    double *g_s = dyn + 4 * a.n_omega, *h_s = g_s + (2 * a.n_omega - 1);
-    const R *E0g = (const R *)a.E0;
-    const R *whg = (const R *)a.wh;
-    R *Phig = (R *)a.Phi;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int c = lane & (L - 1);
-    const int l = (int)(((unsigned)block * (unsigned)kThreads + threadIdx.x) / L);
+    constexpr uint64_t base = G == 4 ? 0x1111111111111111ull : G == 8 ? 0x0101010101010101ull : 0x0001000100010001ull;
+    static_assert(G == 4 || G == 8 || G == 16, "lanes per walker");
+    return base << qq;
+}
+
+// What a launch of the sweep does: uniform selection; the same with the
+// per-proposal trace; index selection by walks (with the trace, if it is on).
+enum : int { kSweepFast = 0, kSweepTraced = 1, kSweepWalk = 2 };
+
+// The sweep of one workgroup's walkers: `block` numbers the workgroup within
+// the problem, `lds` is its LDS (records, then the columns if LDSC, then the
+// walkers' spectra if LDSB).  R is the precision of the residual loop (double:
+// the FP64 path, float: the FP32 variant); moves, positivity, thresholds and
+// chi^2 stay double.  M is the number of basis dimensions a chunk holds; M = 0
+// takes any number, with phi in memory (bases of more than 32 dimensions, which
+// only weights or grids far from a decaying kernel give).
+//
+// SPLIT: half of the workgroup's wavefronts run the walkers' chains, four lanes
+// a walker; the other half, one beside each on the same SIMD, draw and stage
+// the proposals for them.  A chain's proposal is a serial sequence of some
+// hundred instructions, mostly waiting on its own results, so the staging's
+// instructions cost little beside it and a lot within it (512 bins, 16384
+// walkers: @SPLIT@).
+template <typename R, int M, int G, bool LDSC, bool LDSB, int MODE, bool SPLIT>
+__device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block, double *lds)
+{
+    constexpr bool WALK = MODE == kSweepWalk, TRACE = MODE != kSweepFast;
+    constexpr int MR = M > 0 ? M : 1;
+    constexpr int RSTR = SPLIT ? kSplitStride : rec_stride(G, WALK);
+    static_assert(M > 0 || !LDSC, "the general variant reads its columns from memory");
+    static_assert(!SPLIT || (G == 4 && !LDSB && MODE == kSweepFast), "split sweeps: four lanes, spectra in memory");
+    const int nthr = blockDim.x;
+    const int lane = threadIdx.x & 63;
+    const int c = lane & (G - 1), ch = lane & 3;
+    // walkers of the workgroup, and this lane's among them
+    const int half = nthr >> 1;
+    const bool stager = SPLIT && (int)threadIdx.x >= half;
+    const int wpb = (SPLIT ? half : nthr) / G, ws = (int)(stager ? threadIdx.x - half : threadIdx.x) / G;
+    const int l = block * wpb + ws;
     const bool valid = l < a.n_walkers;
     const int lw = valid ? l : a.n_walkers - 1;
     const int No = a.n_omega;
@@ -323,408 +373,689 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
     const double amp_p = a.amp_p, amp_avg = a.amp_avg, eps0 = a.eps0;
     const int amp_m = a.amp_m, walk_len = a.walk_len, wg_sync = a.wg_sync, k1 = a.k1;
     const double *Tsched = a.Tabs;
+    const double4 *bin = a.bin;
     const double2 *GH = a.GH;
     const double cC = a.C, w0x2 = 2.0 * a.w0, dW = a.dW;
-    double *myrec = recs + (wave * W + lane / L) * GSTRIDE;
-    for (int i = threadIdx.x; i < No; i += kThreads) {
-        om_s[i] = a.omega[i];
-        z_s[i] = a.z[i];
-        dg_s[i] = a.D[i];
-        vg_s[i] = a.V[i];
+    const int ms = M > 0 ? chunk_stride<R>(MR) : a.chunk;  // stored dimensions per chunk
+
+    // records, columns and spectra in LDS
+    double *myrec = lds + ws * RSTR;
+    const R *colg = (const R *)a.col;
+    R *col_s = (R *)(lds + wpb * RSTR + (SPLIT ? (wpb >> 4) * kSplitHits : 0));
+    if constexpr (LDSC) {
+        const size_t n16 = (size_t)No * 4 * ms * sizeof(R) / 16;
+        for (size_t i = threadIdx.x; i < n16; i += nthr) ((float4 *)col_s)[i] = ((const float4 *)colg)[i];
     }
-    if (gh_lds) {
-        for (int i = threadIdx.x; i < 2 * No - 1; i += kThreads) {
-            const double2 v = a.GH[i];
-            g_s[i] = v.x;
-            h_s[i] = v.y;
-        }
+    double *spec = (double *)(col_s + (LDSC ? (size_t)No * 4 * ms : 0));
+    double *bsp = spec + ws * No;  // the walker's spectrum
+    if constexpr (LDSB) {
+        const double *bl = a.b + (size_t)lw * No;
+        for (int j = c; j < No; j += G) bsp[j] = bl[j];
     }
     __syncthreads();
-    // spectra and start values through buffer resources: 32-bit offsets
-    // (the library keeps both arrays below 2 GiB, so offset kDropStore lies
-    // past the end of either)
+
+    // spectra in memory through a buffer resource: 32-bit offsets (the library
+    // keeps the array below 2 GiB)
     const __amdgpu_buffer_rsrc_t b_rs = buffer_of(a.b, (uint32_t)((size_t)a.n_walkers * No * sizeof(double)));
-    const __amdgpu_buffer_rsrc_t e0_rs = buffer_of(E0g, (uint32_t)((size_t)No * L * sizeof(R)));
-
-    R Phi[TPL], wh[TPL], sv[TPL];
-    const size_t sbase = (size_t)lw * a.ntau_pad + (size_t)c * TPL;
-#pragma unroll
-    for (int t = 0; t < TPL; ++t) {
-        Phi[t] = Phig[sbase + t];
-        wh[t] = whg[c * TPL + t];
-    }
-    double g = a.gsc[lw], chi2 = a.chi2[lw], rate = a.rate[lw];
-    double ginv = a.ginv[lw];
     const uint32_t brow = (uint32_t)((size_t)lw * No * sizeof(double));  // byte offset of the walker's spectrum
+    auto load_b = [&](const int j) __attribute__((always_inline)) {
+        if constexpr (LDSB) return bsp[j];
+        else return buffer_load_f64(b_rs, brow + ((uint32_t)j << 3));
+    };
 
-    // state of the proposal in flight: indices, deltas, recurrence coefficients,
-    // start values, spectrum values
-    int cp = 0, cs = 0;
-    double cdp = 0.0, cds = 0.0, cc0 = 0.0, cc1 = 0.0, crinv = 1.0, crm1 = 0.0, cr = 1.0, czsum = 2.0, czprod = -1.0;
-    double cT = 0.0, cS1 = 0.0;
-    R cE0p = 0, cE0s = 0;
-    double cbp = 0.0, cbs = 0.0;
+    R phi[MR];
+    R *phig = (R *)a.phi + ((size_t)lw * 4 + ch) * ms;
+    if constexpr (M > 0) load_chunk<R, MR>(phig, phi);
+    double g = a.gsc[lw], chi2 = a.chi2[lw], rate = a.rate[lw], ginv = a.ginv[lw];
     double Q2 = 0.0;  // sum_i w_i Phi_i^2 of the walker, exact at each sweep's start
     int nacc = 0;
     int k = a.k0, q0 = 0;
-    double Tabs = 0.0;  // temperature of sweep k
+    double Tabs = 0.0, yeps = 0.0, thr_T = 0.0;  // temperature and move width of sweep k, thr_tol T
 
-    // S1 = sum_i w_i s_i^2 and S1 + S3 (S3 = sum_i c_i s_i) of the move (p, s,
-    // dp, ds): sum_i w_i K_pi K_si is the pair-sum entry G at wbar = 2 omega_0
-    // + (p + s) d_omega, moved to omega_p + omega_s to first order by H (the
-    // grid is uniform to rounding, so the shift is tiny)
-    auto pair_terms = [&](const int p, const int s, const double dp, const double ds, double &s1_,
+    // Spectra in memory: the proposal this lane owns in the current batch (its
+    // bins' spectrum values here, stored when the batch has ended) and in the
+    // next one, whose values load while the current batch runs; values that
+    // an accepted move of the current batch replaces wait beside them.
+    int op = 0, os = 0, np_ = 0, ns_ = 0;
+    uint32_t ops = 0, nps = 0, nx2 = 0, nx3 = 0;
+    double obp = 0.0, obs = 0.0, nbp = 0.0, nbs = 0.0, fbp = 0.0, fbs = 0.0;
+    uint32_t fp = 0, fs = 0;  // not 0: fbp, fbs replace nbp, nbs (words, not lane masks: they change in few lanes, rarely)
+    uint64_t accm = 0;        // owner lanes whose proposal of the current batch was accepted
+    const uint64_t validm = __builtin_amdgcn_ballot_w64(valid);
+    int buf = 0;              // half of the staging area the current batch reads
+
+    struct Rec {
+        int p, s;
+        uint32_t pp, ss;  // p | p << 16, s | s << 16
+        double rm1, rinv, thr, t, s1, dp, ds;
+        R rp[MR], rs[MR];
+    };
+
+    auto rows = [&](const int p, const int s, Rec &v) __attribute__((always_inline)) {
+        v.p = p;
+        v.s = s;
+        if constexpr (M > 0) {
+            constexpr uint32_t st = (uint32_t)chunk_stride<R>(MR);
+            const uint32_t po = (uint32_t)p * (4 * st) + (uint32_t)ch * st, so = (uint32_t)s * (4 * st) + (uint32_t)ch * st;
+            if constexpr (LDSC) {
+                load_chunk<R, MR>(col_s + po, v.rp);
+                load_chunk<R, MR>(col_s + so, v.rs);
+            } else {
+                load_chunk<R, MR>(colg + po, v.rp);
+                load_chunk<R, MR>(colg + so, v.rs);
+            }
+        }
+    };
+    // staging area of a walker: records of batch slot h, then the bins
+    auto rec_at = [&](const int h, const int qq) __attribute__((always_inline)) { return myrec + (h * G + qq) * kRecWords; };
+    auto bins_at = [&](const int h, const int qq) __attribute__((always_inline)) {
+        return myrec + (SPLIT ? 3 : WALK ? 1 : 2) * G * kRecWords + h * G + qq;
+    };
+    auto fetch = [&](const double *rc, Rec &v) __attribute__((always_inline)) {
+        v.rm1 = rc[kRecRm1];
+        v.rinv = rc[kRecRinv];
+        v.thr = rc[kRecThr];
+        v.t = rc[kRecT];
+        v.s1 = rc[kRecS1];
+        v.dp = rc[kRecDp];
+        v.ds = rc[kRecDs];
+        const double w = rc[kRecPS];
+        v.pp = (uint32_t)__double2loint(w);
+        v.ss = (uint32_t)__double2hiint(w);
+    };
+
+    // Table values of a pair of bins: loaded a batch ahead, so that staging a
+    // record waits for no memory.
+    struct Pair {
+        double4 p, s;
+        double2 gh;
+    };
+    auto load_pair = [&](const int p, const int s, Pair &t) __attribute__((always_inline)) {
+        t.p = bin[p];
+        t.s = bin[s];
+        t.gh = GH[p + s];
+    };
+    // Deltas and walker-independent residue terms of the move (p, s, r): S1 =
+    // sum_i w_i s_i^2 and S1 + S3 (S3 = sum_i c_i s_i); sum_i w_i K_pi K_si is
+    // the pair-sum entry G at wbar = 2 omega_0 + (p + s) d_omega, moved to
+    // omega_p + omega_s to first order by H (the grid is uniform to rounding,
+    // so the shift is tiny).  p = s moves nothing.
+    auto pair_terms = [&](const int p, const int s, const Pair &t, const double r, double &dp, double &ds, double &s1_,
                           double &t_) __attribute__((always_inline)) {
-        const int kk = p + s;
-        double g, h;
-        if (gh_lds) {
-            g = g_s[kk];
-            h = h_s[kk];
-        } else {
-            const double2 v = GH[kk];
-            g = v.x;
-            h = v.y;
-        }
-        const double shift = (om_s[p] + om_s[s]) - (w0x2 + (double)kk * dW);
-        const double mps = g - shift * h;
-        const double S1 = dp * dp * dg_s[p] + 2.0 * dp * ds * mps + ds * ds * dg_s[s];
+        move_deltas(Asum, Bsum, t.p.x, t.s.x, r, dp, ds);
+        dp = p == s ? 0.0 : dp;
+        ds = p == s ? 0.0 : ds;
+        const double shift = (t.p.x + t.s.x) - (w0x2 + (double)(p + s) * dW);
+        const double mps = t.gh.x - shift * t.gh.y;
+        const double S1 = dp * dp * t.p.y + 2.0 * dp * ds * mps + ds * ds * t.s.y;
         s1_ = S1;
-        t_ = S1 + (dp * vg_s[p] + ds * vg_s[s]);
+        t_ = S1 + (dp * t.p.z + ds * t.s.z);
     };
 
-    // loads record qq of the batch and the values it needs from memory
-    auto fetch = [&](const int qq, int &p_, int &s_, double &dp_, double &ds_, double &c0_, double &c1_, double &rinv_,
-                     double &rm1_, double &r_, double &zsum_, double &zprod_, double &t_, double &s1_, R &e0p_, R &e0s_,
-                     double &bp_, double &bs_) __attribute__((always_inline)) {
-        const double *rc = myrec + qq * kRecWords;
-        const double w0 = rc[kRecPS];
-        p_ = __double2loint(w0);
-        s_ = __double2hiint(w0);
-        dp_ = rc[kRecDp];
-        ds_ = rc[kRecDs];
-        c0_ = rc[kRecC0];
-        c1_ = rc[kRecC1];
-        rinv_ = rc[kRecRinv];
-        rm1_ = rc[kRecRm1];
-        r_ = rc[kRecR];
-        t_ = rc[kRecT];
-        s1_ = rc[kRecS1];
-        if constexpr (sizeof(R) == 8) {
-            zsum_ = rc[kRecZsum];
-            zprod_ = rc[kRecZprod];
+    // the uniform draws of proposal q of sweep kk
+    auto draw = [&](const int q, const int kk, int &p, int &s, uint32_t &x2, uint32_t &x3)
+                    __attribute__((always_inline)) {
+        uint32_t x0, x1;
+        philox10((uint32_t)q, (uint32_t)kk, (uint32_t)lw, kStreamProposal, key0, key1, x0, x1, x2, x3);
+        p = index_of(x0, No);
+        s = index_of(x1, No);
+    };
+
+    // writes the bins of this lane's proposal q of a batch (past N_omega: 0, 0)
+    auto stage_bins = [&](const int h, const int q, const int p, const int s) __attribute__((always_inline)) {
+        const bool in = q < No;
+        *bins_at(h, c) = __hiloint2double(in ? s : 0, in ? p : 0);
+    };
+    // writes its record.  Past N_omega the record is a no-op: r = 1, never
+    // accepted.  Straight-line code: it runs in the latencies of the batch
+    // before.
+    auto stage = [&](const int h, const int q, const int p, const int s, const uint32_t x2, const uint32_t x3,
+                     const Pair &pr) __attribute__((always_inline)) {
+        double *rcw = rec_at(h, c);
+        const bool in = q < No;
+        const double ur = u01(x2), ua = u01(x3);
+        // r from the rounded r - 1 (exact for r in [1/2, 2]): both are used
+        const double rm1 = in ? (1.0 - yeps * fma(2.0, ur, -1.0)) - 1.0 : 0.0;  // 2u - 1 is exact either way
+        const double r = rm1 + 1.0;
+        double s1t = 0.0, tt = 0.0, dp = 0.0, ds = 0.0;
+        if constexpr (!WALK) pair_terms(p, s, pr, r, dp, ds, s1t, tt);
+        // u < e^{-dchi2/T}  <=>  dchi2 < -T ln u  (T > 0); p = s is never
+        // accepted
+        const double thr = staged_threshold(Tabs, ua);
+        rcw[kRecRm1] = rm1;
+        rcw[kRecRinv] = recip(r);
+        rcw[kRecThr] = (!in | (!WALK && p == s)) ? kNever : thr;
+        rcw[kRecT] = tt;
+        rcw[kRecS1] = s1t;
+        rcw[kRecDp] = dp;
+        rcw[kRecDs] = ds;
+        rcw[kRecPS] = __hiloint2double((in ? s : 0) * 0x10001, (in ? p : 0) * 0x10001);
+    };
+
+    // Lanes where a half of w is zero, and the smaller of two words by halves.
+    auto zero_half = [&](const uint32_t w) __attribute__((always_inline)) {
+        return __builtin_amdgcn_ballot_w64((w & 0xffffu) == 0u) | __builtin_amdgcn_ballot_w64(w < 0x10000u);
+    };
+    typedef unsigned short half2 __attribute__((ext_vector_type(2)));
+    auto min_halves = [&](const uint32_t x, const uint32_t y) __attribute__((always_inline)) {
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(half2, x), __builtin_bit_cast(half2, y)));
+    };
+
+    // lanes holding a bin of proposal qq (packed pp, ss) for another proposal of
+    // its batch (ops) or for the next batch (nps)
+    auto shared_bins = [&](const int qq, const uint32_t pp, const uint32_t ss) __attribute__((always_inline)) {
+        const uint32_t hc = min_halves(ops ^ pp, ops ^ ss), hn = min_halves(nps ^ pp, nps ^ ss);
+        return zero_half(min_halves(__builtin_amdgcn_inverse_ballot_w64(owner_lanes<G>(qq)) ? 0xffffffffu : hc, hn));
+    };
+    // the value lane lead + qq of the walker holds
+    auto of_owner = [&](const double x, const int qq) __attribute__((always_inline)) {
+        if constexpr (G == 4) {
+            switch (qq) {  // a compile-time proposal: one DPP move per half
+                case 0: return dpp_swap<0x00>(x);
+                case 1: return dpp_swap<0x55>(x);
+                case 2: return dpp_swap<0xAA>(x);
+                default: return dpp_swap<0xFF>(x);
+            }
+        } else {
+            return __shfl(x, (lane & ~(G - 1)) + qq, 64);
         }
-        // start values first: vector memory operations complete in issue
-        // order, so the next proposal's loop waits only for these, while the
-        // spectrum values (needed after its loop) keep almost two proposals
-        e0p_ = buffer_load_r<R>(e0_rs, (uint32_t)(p_ * L + c) * (uint32_t)sizeof(R));
-        e0s_ = buffer_load_r<R>(e0_rs, (uint32_t)(s_ * L + c) * (uint32_t)sizeof(R));
-        bp_ = buffer_load_f64(b_rs, brow + ((uint32_t)p_ << 3));
-        bs_ = buffer_load_f64(b_rs, brow + ((uint32_t)s_ << 3));
     };
 
-    // One proposal: qq indexes the staged batch; `more` says whether record
-    // qq + 1 exists (its data are prefetched while this proposal's residual
-    // loop runs).
-    auto body = [&](const int qq, const bool more) __attribute__((always_inline)) {
-        const double *rc = myrec + qq * kRecWords;
-        int np_ = 0, ns_ = 0;
-        double ndp = 0.0, nds = 0.0, nc0 = 0.0, nc1 = 0.0, nrinv = 1.0, nrm1 = 0.0, nr = 1.0, nzsum = 2.0,
-               nzprod = -1.0, nT = 0.0, nS1 = 0.0, nbp = 0.0, nbs = 0.0;
-        R nE0p = 0, nE0s = 0;
-        if (more)
-            fetch(qq + 1, np_, ns_, ndp, nds, nc0, nc1, nrinv, nrm1, nr, nzsum, nzprod, nT, nS1, nE0p, nE0s, nbp, nbs);
-        const double dp = cdp, ds = cds;
-        const double rm1d = crm1, thr = rc[kRecThr], tol = rc[kRecTol];
+    // One proposal: v is its record and columns, bp and bs the spectrum values
+    // of its bins: in every lane of the walker, or, with spectra in memory and
+    // uniform selection, in its owner lanes.
+    // hit: with staged masks (SPLIT), the lanes of walkers with a bin of this
+    // proposal elsewhere in the batch or in the next one.
+    auto body = [&](const int qq, const Rec &v, const double bp, const double bs, const uint64_t hit)
+                    __attribute__((always_inline)) {
+        constexpr bool OWNED = !WALK && !LDSB;
+        const double rm1d = v.rm1, r = v.rm1 + 1.0;
         // F' = r F + s with s_i = dp K_pi + ds K_si.  The residue change
         // sum_i w_i ((Phi'_i - Phit_i)^2 - (Phi_i - Phit_i)^2) expands into
         //   (r - 1) (r Q2 + chi^2 - C) + 2 r S2 + S1 + S3,
         // Q2 = sum_i w_i Phi_i^2 (the walker's, exact at each sweep's start and
-        // carried through the accepted moves), S2 = sum_i w_i Phi_i s_i (the only
-        // sum over tau that needs the walker), and S1 = sum_i w_i s_i^2,
-        // S3 = sum_i c_i s_i from tables (staged); chi^2 - Q2 - C = sum_i c_i Phi_i.
-        // Every term is bounded by the condition scale of the direct sum, so
-        // the expansion keeps its rounding error (with r^2 - 1 taken as
-        // (r - 1)(r + 1), r - 1 exact).
-        R acc = 0;
-        if constexpr (sizeof(R) == 8) {
-            // s_i is a sum of two geometric sequences, so it obeys
-            // s_{i+2} = (z_p + z_s) s_{i+1} - z_p z_s s_i: two operations per tau
-            // point instead of three (rounding error below 2 TPL^2 u relative
-            // to |dp K_p| + |ds K_s|, far inside the FP64 bar); s_0 and s_1
-            // from the start values and the staged dp z_p, ds z_s
-            const R zsum = (R)czsum, zprod = (R)czprod;
-            R s0 = fma(cE0p, (R)dp, cE0s * (R)ds), s1 = fma(cE0p, (R)cc0, cE0s * (R)cc1);
+        // carried through the accepted moves), S2 = sum_i w_i Phi_i s_i =
+        // phi . sigma (the only sum that needs the walker), and S1 =
+        // sum_i w_i s_i^2, S3 = sum_i c_i s_i from tables (staged);
+        // chi^2 - Q2 - C = sum_i c_i Phi_i.  Every term is bounded by the
+        // condition scale of the direct sum, so the expansion keeps its
+        // rounding error (with r^2 - 1 taken as (r - 1)(r + 1), r - 1 exact).
+        // The part of s outside the basis meets the part of Phi outside it
+        // only: the two residuals' product is what the basis leaves out.
+        R sv[MR], acc = 0;
+        const R dpr = (R)v.dp, dsr = (R)v.ds;
+        if constexpr (M > 0) {
 #pragma unroll
-            for (int t = 0; t < TPL; ++t) {
-                sv[t] = s0;
-                if (t + 2 < TPL) {
-                    const R s2 = fma(zsum, s1, zprod * s0);
-                    s0 = s1;
-                    s1 = s2;
-                } else {
-                    s0 = s1;
-                }
-                acc = fma(Phi[t], wh[t] * sv[t], acc);
+            for (int t = 0; t < MR; ++t) {
+                sv[t] = fma(dpr, v.rp[t], dsr * v.rs[t]);
+                acc = t == 0 ? phi[t] * sv[t] : fma(phi[t], sv[t], acc);
             }
         } else {
-            // FP32: two first-order recurrences (the two-term form would double
-            // the rounding error of the FP32 bar)
-            R ep = (R)dp * cE0p, es = (R)ds * cE0s;
-            const R zpr = (R)cc0, zsr = (R)cc1;
-#pragma unroll
-            for (int t = 0; t < TPL; ++t) {
-                sv[t] = ep + es;
-                acc = fma(Phi[t], wh[t] * sv[t], acc);
-                ep = ep * zpr;
-                es = es * zsr;
-            }
+            const R *cp = colg + (size_t)(v.p * 4 + ch) * ms, *cs = colg + (size_t)(v.s * 4 + ch) * ms;
+            for (int t = 0; t < ms; ++t) acc = fma(phig[t], fma(dpr, cp[t], dsr * cs[t]), acc);
         }
-        // the reduction, decision and commit are a serial chain: the wavefront
-        // runs it at raised issue priority so that it returns to the next
-        // proposal's loop sooner, while the other wavefront on the SIMD fills
-        // the dependency gaps
-        __builtin_amdgcn_s_setprio(1);
-        const double S2 = (double)group_sum<L>(acc);
-        const double r = cr, r2 = r + r;
-        const double dchi2 = fma(rm1d, fma(r, Q2, chi2 - cC), fma(r2, S2, cT));
+        const double S2 = (double)group_sum<4>(acc);
+        const double r2 = r + r;
+        const double dchi2 = fma(rm1d, fma(r, Q2, chi2 - cC), fma(r2, S2, v.t));
         // r g, exactly rounded (r - 1 is exact, so g (r - 1) + g is g r): the
         // scale after an accepted move and the factor of the positivity test
         const double rg = fma(rm1d, g, g);
-        const double ap = fma(rg, cbp, dp), as = fma(rg, cbs, ds);
-        const bool ok = (cp != cs) & (ap >= 0.0) & (as >= 0.0);
-        double thr_e = thr;
-        if (ok & (fabs(dchi2 - thr) <= tol)) {
-            // rare: the staged threshold cannot decide; take the exact -T ln u
-            uint32_t x0, x1, x2, x3;
-            philox10((uint32_t)(q0 + qq), (uint32_t)k, (uint32_t)lw, kStreamProposal, key0, key1, x0, x1, x2, x3);
-            thr_e = -Tabs * log(u01(x3));
+        const double ap = fma(rg, bp, v.dp), as = fma(rg, bs, v.ds);
+        const double diff = dchi2 - v.thr;
+        // (decisions are lane masks, combined by the scalar unit, which also
+        // spreads the owner lane's positivity over the walker's G lanes)
+        const uint64_t own = owner_lanes<G>(qq);
+        uint64_t pos = __builtin_amdgcn_ballot_w64(ap >= 0.0) & __builtin_amdgcn_ballot_w64(as >= 0.0);
+        if constexpr (OWNED) {
+            const uint64_t bit = (pos & own) >> qq;
+            pos = (bit << G) - bit;
         }
-        const bool accept = ok && dchi2 < thr_e;
-        // the pair's new spectrum values (scaled by the new 1/g); the two stores
-        // are issued for every proposal and dropped (offset past the buffer)
-        // unless it is accepted: with no memory operation under a branch, the
-        // waits for the prefetched loads count exactly the operations issued
-        // after them
-        const double gn = ginv * crinv;
-        const double bpn = ap * gn, bsn = as * gn;
-        {
-            const bool store = accept & valid;
-            buffer_store_f64(b_rs, store ? brow + ((uint32_t)cp << 3) : kDropStore, bpn);
-            buffer_store_f64(b_rs, store ? brow + ((uint32_t)cs << 3) : kDropStore, bsn);
+        if constexpr (WALK) pos &= __builtin_amdgcn_ballot_w64(v.p != v.s);
+        uint64_t am = pos & __builtin_amdgcn_ballot_w64(diff < 0.0);
+        // a decision within thr_tol (|thr| + T) of the staged threshold is
+        // retaken with the exact logarithm
+        const uint64_t near = pos & __builtin_amdgcn_ballot_w64(fabs(diff) <= fma(fabs(v.thr), thr_tol, thr_T));
+        if (near) {
+            bool take = false;
+            if (__builtin_amdgcn_inverse_ballot_w64(near)) {
+                uint32_t x0, x1, x2, x3;
+                philox10((uint32_t)(q0 + qq), (uint32_t)k, (uint32_t)lw, kStreamProposal, key0, key1, x0, x1, x2, x3);
+                take = v.thr > kNever && dchi2 < -Tabs * log(u01(x3));
+            }
+            am = (am & ~near) | (near & __builtin_amdgcn_ballot_w64(take));
         }
         if (TRACE) {
-            if (c == 0 && valid && k >= a.tk0 && k < a.tk1 && q0 + qq < No) {
+            if (c == qq && valid && k >= a.tk0 && k < a.tk1 && q0 + qq < No) {
                 const size_t o = ((size_t)l * (size_t)(a.tk1 - a.tk0) + (size_t)(k - a.tk0)) * No + q0 + qq;
                 a.tr_dchi2[o] = dchi2;
-                a.tr_flags[o] = (uint8_t)((accept ? 1 : 0) | (ok ? 2 : 0));
+                a.tr_flags[o] = (uint8_t)((__builtin_amdgcn_inverse_ballot_w64(am) ? 1 : 0) |
+                                          (__builtin_amdgcn_inverse_ballot_w64(pos) && v.p != v.s ? 2 : 0));
             }
         }
-        if (accept) {
-            if constexpr (sizeof(R) == 8) {
-                // the three-operand FMA writes Phi in place (the compiler's
-                // accumulating form lands in sv and needs a copy back per point)
+        if constexpr (OWNED) accm |= am & own;
+        if (__builtin_amdgcn_inverse_ballot_w64(am)) {
+            if constexpr (M == 0) {
+                const R *cp = colg + (size_t)(v.p * 4 + ch) * ms, *cs = colg + (size_t)(v.s * 4 + ch) * ms;
+                for (int t = 0; t < ms; ++t) {
+                    const R s = fma(dpr, cp[t], dsr * cs[t]);
+                    if constexpr (sizeof(R) == 8) phig[t] = fma((R)r, phig[t], s);
+                    else phig[t] = phig[t] + fma((R)rm1d, phig[t], s);
+                }
+            } else if constexpr (sizeof(R) == 8) {
+                // the three-operand FMA writes phi in place (the compiler's
+                // accumulating form lands in sv and needs a copy back each)
 #pragma unroll
-                for (int t = 0; t < TPL; ++t) asm("v_fma_f64 %0, %1, %0, %2" : "+v"(Phi[t]) : "v"(r), "v"(sv[t]));
+                for (int t = 0; t < MR; ++t) asm("v_fma_f64 %0, %1, %0, %2" : "+v"(phi[t]) : "v"(r), "v"(sv[t]));
             } else {
                 // FP32: r - 1 rounds to FP32 with a relative error far smaller
                 // than r would, so the change is formed first
                 const R rm1 = (R)rm1d;
 #pragma unroll
-                for (int t = 0; t < TPL; ++t) Phi[t] = Phi[t] + fma(rm1, Phi[t], sv[t]);
+                for (int t = 0; t < MR; ++t) phi[t] = phi[t] + fma(rm1, phi[t], sv[t]);
             }
-            Q2 = fma(r * r, Q2, fma(r2, S2, cS1));
+            Q2 = fma(r * r, Q2, fma(r2, S2, v.s1));
             chi2 = chi2 + dchi2;
             g = rg;
-            ginv = gn;
-            // the prefetched values of the next proposal may predate this move
-            // (rare: the two proposals share a bin)
-            const bool pp = np_ == cp, ps = np_ == cs, sp = ns_ == cp, ss = ns_ == cs;
-            if (pp | ps | sp | ss) {
-                asm volatile("");  // keeps this a branch: no lane of most wavefronts enters it
-                if (pp) nbp = bpn;
-                if (ps) nbp = bsn;
-                if (sp) nbs = bpn;
-                if (ss) nbs = bsn;
-            }
+            ginv = ginv * v.rinv;
             ++nacc;
-        }
-        __builtin_amdgcn_s_setprio(0);
-        cp = np_;
-        cs = ns_;
-        cdp = ndp;
-        cds = nds;
-        cc0 = nc0;
-        cc1 = nc1;
-        crinv = nrinv;
-        crm1 = nrm1;
-        cr = nr;
-        czsum = nzsum;
-        czprod = nzprod;
-        cT = nT;
-        cS1 = nS1;
-        cE0p = nE0p;
-        cE0s = nE0s;
-        cbp = nbp;
-        cbs = nbs;
-    };
-
-    // Sec. 2.3 index selection: from the uniform p, s of record qq, walk_len
-    // independence Metropolis steps on a_j / A with uniform proposals (step st
-    // draws Philox block (q, k, l, st): word 0 proposes p, word 1 accepts it,
-    // words 2 and 3 the same for s), then the move of the chosen pair.
-    auto walk_setup = [&](const int qq) __attribute__((always_inline)) {
-        const double *rc = myrec + qq * kRecWords;
-        const double w0 = rc[kRecPS];
-        int p = __double2loint(w0), s = __double2hiint(w0);
-        const int q = q0 + qq;
-        double bp = buffer_load_f64(b_rs, brow + ((uint32_t)p << 3));
-        double bs = buffer_load_f64(b_rs, brow + ((uint32_t)s << 3));
-        const double r = rc[kRecR];
-        crinv = rc[kRecRinv];
-        crm1 = rc[kRecRm1];
-        cr = r;
-        double dp = 0.0, ds = 0.0;
-        if (q < No) {
-            for (int st = 1; st <= walk_len; ++st) {
-                uint32_t y0, y1, y2, y3;
-                philox10((uint32_t)q, (uint32_t)k, (uint32_t)lw, (uint32_t)st, key0, key1, y0, y1, y2, y3);
-                const int pc = index_of(y0, No), sc = index_of(y2, No);
-                const double bpc = buffer_load_f64(b_rs, brow + ((uint32_t)pc << 3));
-                const double bsc = buffer_load_f64(b_rs, brow + ((uint32_t)sc << 3));
-                if (u01(y1) * (g * bp) < g * bpc) {
-                    p = pc;
-                    bp = bpc;
+            // the pair's new spectrum values, scaled by the new 1/g
+            const double bpn = ap * ginv, bsn = as * ginv;
+            if constexpr (LDSB) {
+                if (c == 0) {
+                    bsp[v.p] = bpn;
+                    bsp[v.s] = bsn;
                 }
-                if (u01(y3) * (g * bs) < g * bsc) {
-                    s = sc;
-                    bs = bsc;
+            } else if constexpr (WALK) {
+                // the next walk reads the spectrum: store at once
+                if (valid && c == 0) {
+                    buffer_store_f64(b_rs, brow + ((uint32_t)v.p << 3), bpn);
+                    buffer_store_f64(b_rs, brow + ((uint32_t)v.s << 3), bsn);
+                }
+            } else {
+                // they stay with their owner until the batch ends; any lane that
+                // holds one of the two bins, for this batch or the next, takes
+                // them over (few walkers per proposal: a branch on the whole
+                // wavefront; the next batch's values, still in flight, are not
+                // touched)
+                if (__builtin_amdgcn_inverse_ballot_w64(own)) {
+                    obp = bpn;
+                    obs = bsn;
+                }
+                if (am & (SPLIT ? hit : shared_bins(qq, v.pp, v.ss))) {
+                    const double vp = of_owner(bpn, qq), vs = of_owner(bsn, qq);
+                    if (__builtin_amdgcn_inverse_ballot_w64(~own)) {
+                        obp = op == v.p ? vp : op == v.s ? vs : obp;
+                        obs = os == v.p ? vp : os == v.s ? vs : obs;
+                    }
+                    fbp = np_ == v.p ? vp : np_ == v.s ? vs : fbp;
+                    fbs = ns_ == v.p ? vp : ns_ == v.s ? vs : fbs;
+                    fp = ((np_ == v.p) | (np_ == v.s)) ? 1u : fp;
+                    fs = ((ns_ == v.p) | (ns_ == v.s)) ? 1u : fs;
+                    asm volatile("" : "+v"(fp), "+v"(fs));
                 }
             }
-            if (p != s) move_deltas(Asum, Bsum, om_s[p], om_s[s], r, dp, ds);
         }
-        cp = p;
-        cs = s;
-        cdp = dp;
-        cds = ds;
-        // the chosen pair's walker-independent residue terms replace the staged ones
-        pair_terms(p, s, dp, ds, cS1, cT);
-        const double zp = z_s[p], zs = z_s[s];
-        if constexpr (sizeof(R) == 8) {
-            // the chosen pair's recurrence coefficients replace the staged ones
-            cc0 = dp * zp;
-            cc1 = ds * zs;
-            czsum = zp + zs;
-            czprod = -(zp * zs);
-        } else {
-            cc0 = zp;
-            cc1 = zs;
-        }
-        cE0p = buffer_load_r<R>(e0_rs, (uint32_t)(p * L + c) * (uint32_t)sizeof(R));
-        cE0s = buffer_load_r<R>(e0_rs, (uint32_t)(s * L + c) * (uint32_t)sizeof(R));
-        cbp = bp;
-        cbs = bs;
     };
 
-    for (k = a.k0; k < k1; ++k) {
+    // starts sweep k: temperature, amplitude (Eq. amplitude-acceptance-adjustment
+    // on the running acceptance rate) and the exact Q2
+    auto temperature = [&]() __attribute__((always_inline)) {
         Tabs = Tsched[k];
-        // Eq. (amplitude-acceptance-adjustment) on the running acceptance rate
+        thr_T = thr_tol * Tabs;
+    };
+    auto begin_sweep = [&]() __attribute__((always_inline)) {
+        temperature();
         double y = 1.0;
         if (rate < amp_p) {
             const double q = rate / amp_p;
             for (int m = 0; m < amp_m; ++m) y = y * q;
         }
-        const double yeps = y * eps0;
+        yeps = y * eps0;
         nacc = 0;
-        {
-            double q2 = 0.0;
+        double q2 = 0.0;
+        if constexpr (M > 0) {
 #pragma unroll
-            for (int t = 0; t < TPL; ++t) q2 = fma((double)wh[t] * (double)Phi[t], (double)Phi[t], q2);
-            Q2 = group_sum<L>(q2);
+            for (int t = 0; t < MR; ++t) q2 = fma((double)phi[t], (double)phi[t], q2);
+        } else {
+            for (int t = 0; t < ms; ++t) q2 = fma((double)phig[t], (double)phig[t], q2);
         }
-        for (q0 = 0; q0 < No; q0 += L) {
-            {
-                // lane c stages proposal q0 + c
-                const int q = q0 + c;
-                double *rcw = myrec + c * kRecWords;
-                if (q < No) {
-                    uint32_t x0, x1, x2, x3;
-                    philox10((uint32_t)q, (uint32_t)k, (uint32_t)lw, kStreamProposal, key0, key1, x0, x1, x2, x3);
-                    const int p = index_of(x0, No), s = index_of(x1, No);
-                    const double ur = u01(x2), ua = u01(x3);
-                    const double r = 1.0 - yeps * fma(2.0, ur, -1.0);  // 2u - 1 is exact either way
-                    double dp = 0.0, ds = 0.0;
-                    if (p != s) move_deltas(Asum, Bsum, om_s[p], om_s[s], r, dp, ds);
-                    const double zp = z_s[p], zs = z_s[s];
-                    rcw[kRecPS] = __hiloint2double(s, p);
-                    rcw[kRecDp] = dp;
-                    rcw[kRecDs] = ds;
-                    if constexpr (sizeof(R) == 8) {
-                        rcw[kRecC0] = dp * zp;
-                        rcw[kRecC1] = ds * zs;
-                        rcw[kRecZsum] = zp + zs;
-                        rcw[kRecZprod] = -(zp * zs);
-                    } else {
-                        rcw[kRecC0] = zp;
-                        rcw[kRecC1] = zs;
-                    }
-                    rcw[kRecRinv] = recip(r);
-                    rcw[kRecRm1] = r - 1.0;  // exact for r in [1/2, 2]
-                    rcw[kRecR] = r;
-                    double s1t, tt;
-                    pair_terms(p, s, dp, ds, s1t, tt);
-                    rcw[kRecS1] = s1t;
-                    rcw[kRecT] = tt;
-                    // u < e^{-dchi2/T}  <=>  dchi2 < -T ln u  (T > 0); a residue
-                    // change within tol of it is decided with the exact logarithm
-                    const double thr = staged_threshold(Tabs, ua);
-                    rcw[kRecThr] = thr;
-                    rcw[kRecTol] = thr_tol * (fabs(thr) + Tabs);
-                } else {
-                    // no-op record: p = s (inadmissible), r = 1, never accepted
-                    rcw[kRecPS] = __hiloint2double(0, 0);
-                    rcw[kRecDp] = 0.0;
-                    rcw[kRecDs] = 0.0;
-                    rcw[kRecC0] = sizeof(R) == 8 ? 0.0 : 1.0;
-                    rcw[kRecC1] = sizeof(R) == 8 ? 0.0 : 1.0;
-                    rcw[kRecRinv] = 1.0;
-                    rcw[kRecRm1] = 0.0;
-                    rcw[kRecR] = 1.0;
-                    rcw[kRecS1] = 0.0;
-                    rcw[kRecT] = 0.0;
-                    rcw[kRecZsum] = 2.0;
-                    rcw[kRecZprod] = -1.0;
-                    rcw[kRecThr] = -INFINITY;
-                    rcw[kRecTol] = 0.0;
-                }
+        Q2 = group_sum<4>(q2);
+    };
+    auto end_sweep = [&]() __attribute__((always_inline)) {
+        rate = (1.0 - amp_avg) * rate + amp_avg * ((double)nacc / (double)No);
+    };
+    // the records are private to this wavefront: a wavefront-level ordering
+    // point is enough (SAIL_SWEEP_SYNC=1 selects a workgroup barrier)
+    auto order = [&]() __attribute__((always_inline)) {
+        if (wg_sync) __syncthreads();
+        else wave_lds_sync();
+    };
+
+    if constexpr (SPLIT) {
+        // Both roles pass the same barriers: one to start, and in every sweep
+        // two for the first two batches' records and one per batch.  Records
+        // are staged two batches ahead of the chain (a ring of three) within a
+        // sweep, since their move width follows from the sweep before; bins are
+        // drawn one batch further ahead, across sweeps (a ring of four).
+        auto barrier = [&]() __attribute__((always_inline)) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        };
+        double *width = myrec + 3 * G * kRecWords + 4 * G;  // move width of the sweep
+        // masks of the proposals' shared bins, [slot][proposal], one set per pair of wavefronts
+        uint64_t *hits = (uint64_t *)(lds + wpb * RSTR) + (ws >> 4) * kSplitHits;
+        auto uniform = [](const uint64_t x) __attribute__((always_inline)) {
+            return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x) |
+                   (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32;
+        };
+        auto of_owner_word = [](const uint32_t x, const int t) __attribute__((always_inline)) {
+            switch (t) {
+                case 0: return (uint32_t)dpp_swap<0x00>((int)x);
+                case 1: return (uint32_t)dpp_swap<0x55>((int)x);
+                case 2: return (uint32_t)dpp_swap<0xAA>((int)x);
+                default: return (uint32_t)dpp_swap<0xFF>((int)x);
             }
-            // the records are private to this wavefront: a wavefront-level
-            // ordering point is enough (SAIL_SWEEP_SYNC=1 selects a workgroup barrier)
-            if (wg_sync) __syncthreads(); else wave_lds_sync();
-            if constexpr (WALK) {
-                // the walk reads the current spectrum, so each proposal is set
-                // up after the previous one committed (no prefetch)
-                for (int qq = 0; qq < L; ++qq) {
-                    walk_setup(qq);
-                    body(qq, false);
-                }
-            } else {
-                fetch(0, cp, cs, cdp, cds, cc0, cc1, crinv, crm1, cr, czsum, czprod, cT, cS1, cE0p, cE0s, cbp, cbs);
-                // a batch always holds L records; past N_omega they are rejected no-ops
+        };
+        int rs = 0, bsl = 0;                                 // slots of the next record and bins
+        if (stager) {
+            Pair pr, npr;
+            draw(c, k, np_, ns_, nx2, nx3);
+            load_pair(np_, ns_, npr);
+            stage_bins(0, c, np_, ns_);
+            bsl = 1;
+            barrier();
+            for (; k < k1; ++k) {
+                temperature();
+                yeps = *width;
+                for (q0 = 0; q0 < No; q0 += G) {
+                    op = np_;
+                    os = ns_;
+                    const uint32_t x2 = nx2, x3 = nx3;
+                    pr = npr;
+                    const bool ends = q0 + G >= No;
+                    const int q1 = ends ? 0 : q0 + G;
+                    draw(q1 + c, ends ? k + 1 : k, np_, ns_, nx2, nx3);
+                    load_pair(np_, ns_, npr);
+                    stage_bins(bsl, q1 + c, np_, ns_);
+                    bsl = (bsl + 1) & 3;
+                    // the walkers' lanes of this wavefront mirror the chain's
+                    ops = (uint32_t)op | (uint32_t)os << 16;
+                    nps = (uint32_t)np_ | (uint32_t)ns_ << 16;
 #pragma unroll
-                for (int qq = 0; qq < L; ++qq) {
-                    body(qq, qq + 1 < L);
+                    for (int t = 0; t < G; ++t) {
+                        const uint32_t w = of_owner_word(ops, t);
+                        const uint64_t h = shared_bins(t, (w & 0xffffu) * 0x10001u, (w >> 16) * 0x10001u);
+                        if (lane == 0) hits[rs * G + t] = h;
+                    }
+                    stage(rs, q0 + c, op, os, x2, x3, pr);
+                    rs = rs == 2 ? 0 : rs + 1;
+                    barrier();
+                }
+                barrier();
+                barrier();
+            }
+            return;
+        }
+        __builtin_amdgcn_s_setprio(2);
+        begin_sweep();
+        if (c == 0) *width = yeps;
+        barrier();
+        Rec v[2];
+        double next_bins;  // of the proposal after the next
+        {
+            // the first batch's bins and spectrum values
+            const double w0 = *bins_at(0, 0), own_bins = *bins_at(0, c);
+            next_bins = *bins_at(0, 1);
+            rows(__double2loint(w0), __double2hiint(w0), v[0]);
+            np_ = __double2loint(own_bins);
+            ns_ = __double2hiint(own_bins);
+            nbp = load_b(np_);
+            nbs = load_b(ns_);
+        }
+        for (;;) {
+            barrier();
+            barrier();
+            fetch(rec_at(rs, 0), v[0]);
+            bool last = false;
+            for (q0 = 0; q0 < No; q0 += G) {
+                const int bn = (bsl + 1) & 3, rn = rs == 2 ? 0 : rs + 1;  // the next batch's slots
+                const double own_bins = *bins_at(bn, c);
+                const bool ends = q0 + G >= No;
+                uint64_t hit[G];
+#pragma unroll
+                for (int t = 0; t < G; ++t) hit[t] = uniform(hits[rs * G + t]);
+                // this batch's spectrum values have arrived (waited for before
+                // the stores below are issued, so that nothing waits for those)
+                asm volatile("" : "+v"(nbp), "+v"(nbs));
+                if (__builtin_amdgcn_inverse_ballot_w64(accm & validm)) {
+                    buffer_store_f64(b_rs, brow + ((uint32_t)op << 3), obp);
+                    buffer_store_f64(b_rs, brow + ((uint32_t)os << 3), obs);
+                }
+                obp = fp ? fbp : nbp;
+                obs = fs ? fbs : nbs;
+                fp = fs = 0;
+                asm volatile("" : "+v"(fp), "+v"(fs));
+                accm = 0;
+                op = np_;
+                os = ns_;
+                np_ = __double2loint(own_bins);
+                ns_ = __double2hiint(own_bins);
+                ops = (uint32_t)op | (uint32_t)os << 16;
+                nps = (uint32_t)np_ | (uint32_t)ns_ << 16;
+                nbp = load_b(np_);
+                nbs = load_b(ns_);
+#pragma unroll
+                for (int t = 0; t < G; ++t) {
+                    // the next proposal's columns (its bins were read a proposal
+                    // ago), its record, and the bins of the one after it
+                    Rec &cur = v[t & 1], &nx = v[(t + 1) & 1];
+                    rows(__double2loint(next_bins), __double2hiint(next_bins), nx);
+                    fetch(t + 1 < G ? rec_at(rs, t + 1) : rec_at(rn, 0), nx);
+                    next_bins = t + 2 < G ? *bins_at(bsl, t + 2) : *bins_at(bn, t + 2 - G);
+                    body(t, cur, obp, obs, hit[t]);
                     // keep each proposal's code together (bounds register pressure)
                     __builtin_amdgcn_sched_barrier(0);
                 }
+                rs = rn;
+                bsl = bn;
+                if (ends) {
+                    end_sweep();
+                    last = k + 1 >= k1;
+                    if (!last) {
+                        ++k;
+                        begin_sweep();
+                        if (c == 0) *width = yeps;
+                    }
+                }
+                barrier();
             }
-            if (wg_sync) __syncthreads(); else wave_lds_sync();
+            if (last) break;
         }
-        rate = (1.0 - amp_avg) * rate + amp_avg * ((double)nacc / (double)No);
+        if (__builtin_amdgcn_inverse_ballot_w64(accm & validm)) {
+            buffer_store_f64(b_rs, brow + ((uint32_t)op << 3), obp);
+            buffer_store_f64(b_rs, brow + ((uint32_t)os << 3), obs);
+        }
+    } else if constexpr (WALK) {
+        // Sec. 2.3 index selection: from the uniform p, s of each proposal,
+        // walk_len independence Metropolis steps on a_j / A with uniform
+        // proposals (step st draws Philox block (q, k, l, st): word 0 proposes
+        // p, word 1 accepts it, words 2 and 3 the same for s), then the move of
+        // the chosen pair.  The steps' draws and spectrum values do not depend
+        // on one another: lane c takes step c + 1 (+ G, ...), and the lanes
+        // exchange them through LDS.
+        double *wk = myrec + G * (kRecWords + 1);
+        for (; k < k1; ++k) {
+            begin_sweep();
+            for (q0 = 0; q0 < No; q0 += G) {
+                Pair pr;
+                uint32_t x2, x3;
+                draw(q0 + c, k, op, os, x2, x3);
+                stage_bins(0, q0 + c, op, os);
+                stage(0, q0 + c, op, os, x2, x3, pr);
+                order();
+                const int nq = min(G, No - q0);
+                for (int qq = 0; qq < nq; ++qq) {
+                    Rec v;
+                    fetch(rec_at(0, qq), v);
+                    const double w0 = *bins_at(0, qq);
+                    int p = __double2loint(w0), s = __double2hiint(w0);
+                    double bp = load_b(p), bs = load_b(s);
+                    for (int st0 = 0; st0 < walk_len; st0 += G) {
+                        const int n = min(G, walk_len - st0);
+                        if (c < n) {
+                            uint32_t y0, y1, y2, y3;
+                            philox10((uint32_t)(q0 + qq), (uint32_t)k, (uint32_t)lw, (uint32_t)(st0 + c + 1), key0, key1,
+                                     y0, y1, y2, y3);
+                            const int pc = index_of(y0, No), sc = index_of(y2, No);
+                            double *w = wk + c * kWalkWords;
+                            w[0] = __hiloint2double(sc, pc);
+                            w[1] = load_b(pc);
+                            w[2] = load_b(sc);
+                            w[3] = u01(y1);
+                            w[4] = u01(y3);
+                        }
+                        order();
+                        for (int st = 0; st < n; ++st) {
+                            const double *w = wk + st * kWalkWords;
+                            const double bpc = w[1], bsc = w[2];
+                            if (w[3] * (g * bp) < g * bpc) {
+                                p = __double2loint(w[0]);
+                                bp = bpc;
+                            }
+                            if (w[4] * (g * bs) < g * bsc) {
+                                s = __double2hiint(w[0]);
+                                bs = bsc;
+                            }
+                        }
+                        order();
+                    }
+                    rows(p, s, v);
+                    load_pair(p, s, pr);
+                    pair_terms(p, s, pr, v.rm1 + 1.0, v.dp, v.ds, v.s1, v.t);
+                    body(qq, v, bp, bs, 0);
+                    order();
+                }
+            }
+            end_sweep();
+        }
+    } else {
+        // Three batches are under way: n runs, n + 1 has its bins, its spectrum
+        // values load (where spectra are in memory) and its records are staged,
+        // n + 2 is drawn and its table values load.  The work on the later two
+        // stands between the loads and the serial tails of batch n's proposals
+        // and fills their latencies.  After the last batch the draws are not
+        // used.
+        Pair npr, mpr;
+        int mp = 0, ms_ = 0;
+        uint32_t mx2 = 0, mx3 = 0;
+        begin_sweep();
+        draw(c, k, np_, ns_, nx2, nx3);
+        if constexpr (!LDSB) {
+            nbp = load_b(np_);
+            nbs = load_b(ns_);
+        }
+        load_pair(np_, ns_, npr);
+        int q1 = G < No ? G : 0, kn = G < No ? k : k + 1;  // the batch after the current one
+        draw(q1 + c, kn, mp, ms_, mx2, mx3);
+        load_pair(mp, ms_, mpr);
+        stage_bins(0, c, np_, ns_);
+        stage(0, c, np_, ns_, nx2, nx3, npr);
+        order();
+        Rec v[2];
+        double next_bins;  // of the proposal after the next
+        {
+            const double w0 = *bins_at(0, 0);
+            next_bins = *bins_at(0, 1);
+            rows(__double2loint(w0), __double2hiint(w0), v[0]);
+            fetch(rec_at(0, 0), v[0]);
+        }
+        for (;;) {
+            if constexpr (!LDSB) {
+                // this batch's spectrum values have arrived (waited for before
+                // the stores below are issued, so that nothing waits for those)
+                asm volatile("" : "+v"(nbp), "+v"(nbs));
+                if (__builtin_amdgcn_inverse_ballot_w64(accm & validm)) {
+                    buffer_store_f64(b_rs, brow + ((uint32_t)op << 3), obp);
+                    buffer_store_f64(b_rs, brow + ((uint32_t)os << 3), obs);
+                }
+                obp = fp ? fbp : nbp;
+                obs = fs ? fbs : nbs;
+                fp = fs = 0;
+                asm volatile("" : "+v"(fp), "+v"(fs));
+                accm = 0;
+            }
+            op = np_;
+            os = ns_;
+            np_ = mp;
+            ns_ = ms_;
+            nx2 = mx2;
+            nx3 = mx3;
+            npr = mpr;
+            if constexpr (!LDSB) {
+                ops = (uint32_t)op | (uint32_t)os << 16;
+                nps = (uint32_t)np_ | (uint32_t)ns_ << 16;
+                nbp = load_b(np_);
+                nbs = load_b(ns_);
+            }
+            const bool ends = q0 + G >= No;
+            const int q2 = q1 + G >= No ? 0 : q1 + G, k2 = q1 + G >= No ? kn + 1 : kn;
+#pragma unroll
+            for (int t = 0; t < G; ++t) {
+                // the next proposal's columns (its bins were read a proposal
+                // ago), its record, and the bins of the one after it
+                Rec &cur = v[t & 1], &nx = v[(t + 1) & 1];
+                rows(__double2loint(next_bins), __double2hiint(next_bins), nx);
+                fetch(t + 1 < G ? rec_at(buf, t + 1) : rec_at(buf ^ 1, 0), nx);
+                next_bins = t + 2 < G ? *bins_at(buf, t + 2) : *bins_at(buf ^ 1, t + 2 - G);
+                if (t == 0) {
+                    stage_bins(buf ^ 1, q1 + c, np_, ns_);
+                    stage(buf ^ 1, q1 + c, np_, ns_, nx2, nx3, npr);
+                }
+                if (t == 1) {
+                    draw(q2 + c, k2, mp, ms_, mx2, mx3);
+                    load_pair(mp, ms_, mpr);
+                }
+                if constexpr (LDSB) body(t, cur, bsp[cur.p], bsp[cur.s], 0);
+                else body(t, cur, obp, obs, 0);
+                if (t == 1) order();
+                else if constexpr (LDSB) wave_lds_sync();
+                // keep each proposal's code together (bounds register pressure)
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (ends) {
+                end_sweep();
+                if (kn >= k1) break;
+                // the next sweep's temperature and move width: stage again
+                k = kn;
+                begin_sweep();
+                stage(buf ^ 1, q1 + c, np_, ns_, nx2, nx3, npr);
+                order();
+                fetch(rec_at(buf ^ 1, 0), v[0]);
+            }
+            buf ^= 1;
+            q0 = q1;
+            q1 = q2;
+            kn = k2;
+        }
+        if constexpr (!LDSB) {
+            if (__builtin_amdgcn_inverse_ballot_w64(accm & validm)) {
+                buffer_store_f64(b_rs, brow + ((uint32_t)op << 3), obp);
+                buffer_store_f64(b_rs, brow + ((uint32_t)os << 3), obs);
+            }
+        }
     }
     if (valid) {
+        if constexpr (M > 0) {
+            if (c < 4) {
 #pragma unroll
-        for (int t = 0; t < TPL; ++t) {
-            Phig[sbase + t] = Phi[t];
+                for (int t = 0; t < MR; ++t) phig[t] = phi[t];
+            }
+        }
+        if constexpr (LDSB) {
+            wave_lds_sync();
+            double *bl = a.b + (size_t)l * No;
+            for (int j = c; j < No; j += G) bl[j] = bsp[j];
         }
         if (c == 0) {
             a.gsc[l] = g;
@@ -735,54 +1066,46 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
     }
 }
 
-template <typename R, int TPL, int L, bool TRACE, bool WALK>
-__global__ __launch_bounds__(kThreads) void k_sweep(SweepArgs a)
+// Workgroups of 64 to kSweepThreads threads (split sweeps: 128 to twice as
+// many), as the launch plan asks.
+constexpr int kSweepThreads = 256;
+
+template <typename R, int M, int G, bool LDSC, bool LDSB, int MODE>
+__global__ __launch_bounds__(kSweepThreads) void k_sweep(SweepArgs a)
 {
-    __shared__ double recs[kRecsMax];
-    extern __shared__ double dyn[];
-    sweep_block<R, TPL, L, TRACE, WALK>(a, blockIdx.x, recs, dyn);
+    extern __shared__ __align__(16) double lds[];
+    sweep_block<R, M, G, LDSC, LDSB, MODE, false>(a, blockIdx.x, lds);
 }
 
-// Many problems in one launch: workgroup b runs block work[b].y of problem
-// work[b].x (work items ordered longest first by the host); the lane layout
-// L and the index-selection walk (Sec. 2.3) are chosen per problem at run time.
-// The TRACE instantiation (uniform selection only) records the proposals of
-// the jobs whose trace window the round overlaps; it differs from the other
-// only by those stores.  Two wavefronts per SIMD are required: the switch
-// over layouts would otherwise take a few registers past the 256 that allow
-// them (FP64 at 16 and FP32 at 32 tau per lane), at the cost of a few spills.
-template <typename R, int TPL, bool TRACE>
-__global__ __launch_bounds__(kThreads, 2) void k_sweep_batched(const SweepArgs *__restrict__ jobs,
-                                                            const int *__restrict__ first, int n_jobs)
+template <typename R, int M, bool LDSC>
+__global__ __launch_bounds__(2 * kSweepThreads) void k_sweep_split(SweepArgs a)
 {
-    __shared__ double recs[kRecsMax];
-    extern __shared__ double dyn[];
+    extern __shared__ __align__(16) double lds[];
+    sweep_block<R, M, 4, LDSC, false, kSweepFast, true>(a, blockIdx.x, lds);
+}
+
+// Many problems in one launch: problem q owns workgroups [first[q], first[q + 1]);
+// where a problem's columns sit is its own (a uniform branch).
+template <typename R, int M, int MODE>
+__global__ __launch_bounds__(kSweepThreads, 2) void k_sweep_batched(const SweepArgs *__restrict__ jobs,
+                                                                   const int *__restrict__ first, int n_jobs)
+{
+    extern __shared__ __align__(16) double lds[];
+    const int q = owner_of(first, n_jobs, blockIdx.x);
+    constexpr int G = M > 0 && MODE == kSweepWalk ? 8 : 4;
+    sweep_block<R, M, G, false, false, MODE, false>(jobs[q], blockIdx.x - first[q], lds);
+}
+
+template <typename R, int M>
+__global__ __launch_bounds__(2 * kSweepThreads) void k_sweep_split_batched(const SweepArgs *__restrict__ jobs,
+                                                                          const int *__restrict__ first, int n_jobs)
+{
+    extern __shared__ __align__(16) double lds[];
     const int q = owner_of(first, n_jobs, blockIdx.x);
     const SweepArgs &a = jobs[q];
     const int block = blockIdx.x - first[q];
-    if constexpr (!TRACE) {
-        if (a.walk_len > 0) {
-            switch (a.lanes) {
-                case 1: sweep_block<R, TPL, 1, false, true>(a, block, recs, dyn); break;
-                case 2: sweep_block<R, TPL, 2, false, true>(a, block, recs, dyn); break;
-                case 4: sweep_block<R, TPL, 4, false, true>(a, block, recs, dyn); break;
-                case 8: sweep_block<R, TPL, 8, false, true>(a, block, recs, dyn); break;
-                case 16: sweep_block<R, TPL, 16, false, true>(a, block, recs, dyn); break;
-                case 32: sweep_block<R, TPL, 32, false, true>(a, block, recs, dyn); break;
-                default: sweep_block<R, TPL, 64, false, true>(a, block, recs, dyn); break;
-            }
-            return;
-        }
-    }
-    switch (a.lanes) {
-        case 1: sweep_block<R, TPL, 1, TRACE, false>(a, block, recs, dyn); break;
-        case 2: sweep_block<R, TPL, 2, TRACE, false>(a, block, recs, dyn); break;
-        case 4: sweep_block<R, TPL, 4, TRACE, false>(a, block, recs, dyn); break;
-        case 8: sweep_block<R, TPL, 8, TRACE, false>(a, block, recs, dyn); break;
-        case 16: sweep_block<R, TPL, 16, TRACE, false>(a, block, recs, dyn); break;
-        case 32: sweep_block<R, TPL, 32, TRACE, false>(a, block, recs, dyn); break;
-        default: sweep_block<R, TPL, 64, TRACE, false>(a, block, recs, dyn); break;
-    }
+    if (a.columns_lds) sweep_block<R, M, 4, true, false, kSweepFast, true>(a, block, lds);
+    else sweep_block<R, M, 4, false, false, kSweepFast, true>(a, block, lds);
 }
 
 // --------------------------------------------------------------------------
@@ -837,12 +1160,14 @@ __device__ __forceinline__ T wave_reduce(T v, Op op)
 // Phi = E b, G and chi^2 (one workgroup per walker).
 // --------------------------------------------------------------------------
 struct ResyncArgs {
-    int n_omega, n_tau, ntau_pad;
+    int n_omega, n_tau;
+    int cols;             // columns of E: n_tau, then 4 echunk
+    int echunk, chunk;    // basis dimensions per chunk as stored in E and in phi
     const double *omega;
-    const double *E;      // [N_omega][ntau_pad] e^{-omega_j tau_i}, 0 on padding
+    const double *E;      // [N_omega][cols] e^{-omega_j tau_i}, then the column in the basis
     const double *wh, *Phit;
     double *b, *gsc, *ginv, *chi2;
-    void *Phi;                   // in the loop precision
+    void *phi;                   // [N_w][4][chunk], in the loop precision
     double A, B;
     int renorm;
     const int32_t *list;        // optional walker list
@@ -865,15 +1190,15 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// kResyncWPB walkers per workgroup share every read of the E table:
-// thread i accumulates Phi_i of all of them in FP64, j ascending; Phi is
-// stored in the loop precision R.
+// kResyncWPB walkers per workgroup share every read of the E table: thread i
+// accumulates column i of all of them in FP64, j ascending: Phi_i, whose
+// residuals give chi^2, or a basis coordinate, stored in the loop precision R.
 template <typename R>
 __device__ __forceinline__ void resync_block(const ResyncArgs &a, const int block, double *sh)
 {
     // sh: [kResyncWPB][N_omega] spectra (room for at least [kResyncWPB][kThreads]
     // partial sums of Phi), then [4][kResyncWPB] partial residues
-    const int No = a.n_omega, ntp = a.ntau_pad;
+    const int No = a.n_omega, Nt = a.n_tau, cols = a.cols;
     double *sb = sh;
     double *red = sh + (size_t)kResyncWPB * (No > kThreads ? No : kThreads);
     const int count = a.list ? *a.list_count : a.n_items;
@@ -973,56 +1298,61 @@ __device__ __forceinline__ void resync_block(const ResyncArgs &a, const int bloc
     double part[kResyncWPB];
 #pragma unroll
     for (int w = 0; w < kResyncWPB; ++w) part[w] = 0.0;
-    if (ntp * 4 > (int)blockDim.x) {
-        for (int i = threadIdx.x; i < ntp; i += blockDim.x) {
+    // column i of walker slot w is v: a residual, or a basis coordinate
+    auto take = [&](const int i, const int w, const double v) __attribute__((always_inline)) {
+        if (i < Nt) {
+            const double rsd = v - a.Phit[i];
+            part[w] += a.wh[i] * rsd * rsd;
+        } else {
+            const int d = i - Nt, q = d / a.echunk, t = d % a.echunk;
+            if (t < a.chunk) ((R *)a.phi)[((size_t)wl[w] * 4 + q) * a.chunk + t] = (R)v;
+        }
+    };
+    if (cols * 3 > (int)blockDim.x) {
+        for (int i = threadIdx.x; i < cols; i += blockDim.x) {
             double f[kResyncWPB];
 #pragma unroll
             for (int w = 0; w < kResyncWPB; ++w) f[w] = 0.0;
             for (int j = 0; j < No; ++j) {
-                const double e = a.E[(size_t)j * ntp + i];
+                const double e = a.E[(size_t)j * cols + i];
 #pragma unroll
                 for (int w = 0; w < kResyncWPB; ++w) f[w] = fma(sb[w * No + j], e, f[w]);
             }
-            const double pt = a.Phit[i], wi = a.wh[i];
 #pragma unroll
-            for (int w = 0; w < kResyncWPB; ++w) {
-                if (wl[w] < 0) continue;
-                const double rsd = f[w] - pt;
-                ((R *)a.Phi)[(size_t)wl[w] * ntp + i] = (R)f[w];
-                part[w] += wi * rsd * rsd;
-            }
+            for (int w = 0; w < kResyncWPB; ++w)
+                if (wl[w] >= 0) take(i, w, f[w]);
         }
     } else {
-        // at most a quarter as many tau points as threads (ntp is a power of
-        // two; one wavefront or less would work): G groups of ntp threads split
-        // the bins, each group summing its range in bin order, and the partial
-        // sums are added in group order (measured: 1.7x faster batched resyncs;
-        // at half as many, the exchange costs more than it gains)
-        const int G = (int)blockDim.x / ntp, g = threadIdx.x / ntp, i = threadIdx.x % ntp;
-        const int j0 = (int)((int64_t)No * g / G), j1 = (int)((int64_t)No * (g + 1) / G);
+        // at most a third as many columns as threads: G groups of cols threads
+        // split the bins, each group summing its range in bin order, and the
+        // partial sums are added in group order (measured: 1.7x faster batched
+        // resyncs; with two groups the exchange costs more than it gains)
+        const int G = (int)blockDim.x / cols, g = threadIdx.x / cols, i = threadIdx.x % cols;
         double f[kResyncWPB];
 #pragma unroll
         for (int w = 0; w < kResyncWPB; ++w) f[w] = 0.0;
-        for (int j = j0; j < j1; ++j) {
-            const double e = a.E[(size_t)j * ntp + i];
+        if (g < G) {
+            const int j0 = (int)((int64_t)No * g / G), j1 = (int)((int64_t)No * (g + 1) / G);
+            for (int j = j0; j < j1; ++j) {
+                const double e = a.E[(size_t)j * cols + i];
 #pragma unroll
-            for (int w = 0; w < kResyncWPB; ++w) f[w] = fma(sb[w * No + j], e, f[w]);
+                for (int w = 0; w < kResyncWPB; ++w) f[w] = fma(sb[w * No + j], e, f[w]);
+            }
         }
         __syncthreads();  // the spectra in LDS are read for the last time
-        double *pf = sh;  // partial sums [walker][group][tau], over the spectra
+        double *pf = sh;  // partial sums [walker][group][column], over the spectra
+        if (g < G) {
 #pragma unroll
-        for (int w = 0; w < kResyncWPB; ++w) pf[(w * G + g) * ntp + i] = f[w];
+            for (int w = 0; w < kResyncWPB; ++w) pf[(w * G + g) * cols + i] = f[w];
+        }
         __syncthreads();
         if (g == 0) {
-            const double pt = a.Phit[i], wi = a.wh[i];
 #pragma unroll
             for (int w = 0; w < kResyncWPB; ++w) {
                 if (wl[w] < 0) continue;
-                double v = pf[(w * G) * ntp + i];
-                for (int gg = 1; gg < G; ++gg) v += pf[(w * G + gg) * ntp + i];
-                const double rsd = v - pt;
-                ((R *)a.Phi)[(size_t)wl[w] * ntp + i] = (R)v;
-                part[w] += wi * rsd * rsd;
+                double v = pf[(w * G) * cols + i];
+                for (int gg = 1; gg < G; ++gg) v += pf[(w * G + gg) * cols + i];
+                take(i, w, v);
             }
         }
     }
@@ -1054,6 +1384,21 @@ __global__ __launch_bounds__(kThreads) void k_resync_batched(const ResyncArgs *_
     extern __shared__ double sh[];
     const int q = owner_of(first, n_jobs, blockIdx.x);
     resync_block<R>(jobs[q], blockIdx.x - first[q], sh);
+}
+
+// Reconstructions of the walkers for read-out: Phi_i = g sum_j b_j E_ji, one
+// workgroup per walker, stored in the loop precision.
+template <typename R>
+__global__ __launch_bounds__(kThreads) void k_reconstruct(int n_omega, int n_tau, int cols, int stride, const double *E,
+                                                          const double *b, const double *gsc, R *Phi)
+{
+    const int l = blockIdx.x;
+    const double *bl = b + (size_t)l * n_omega;
+    for (int i = threadIdx.x; i < n_tau; i += blockDim.x) {
+        double f = 0.0;
+        for (int j = 0; j < n_omega; ++j) f = fma(bl[j], E[(size_t)j * cols + i], f);
+        Phi[(size_t)l * stride + i] = (R)(gsc[l] * f);
+    }
 }
 
 __global__ void k_init_walkers(int n_walkers, int n_omega, const double *a0, double *b, double *gsc, double *ginv,
@@ -2183,24 +2528,37 @@ struct sail_problem {
     int n_omega = 0, n_tau = 0, mode = 0;
     double dw = 0, tau0 = 0, dtau = 0, A = 0, B = 0, m0 = 0, m1 = 0;
     std::vector<double> omega, tau, F, w, cfac;
-    // sweep layout
-    int tpl = 16, lanes = 1, log2_lanes = 0, ntau_pad = 16;
+    // nominal lane layout (sail_layout)
+    int tpl = 16, lanes = 1, ntau_pad = 16;
     int tpl_hint = 0;  // requested tau points per lane (0: automatic)
-    // tables (device)
-    double *d_omega = nullptr, *d_z = nullptr, *d_E = nullptr;
-    double *d_wh = nullptr, *d_Phit = nullptr;
-    void *d_E0r = nullptr, *d_whr = nullptr;  // start values and wh in the loop precision
-    // walker-independent residue tables of the sweep (FP64): per bin D, V and
-    // the pair-sum table (G, H), with the constant C and the grid's omega_0, d_omega
-    double *d_Dg = nullptr, *d_Vg = nullptr, *d_GH = nullptr;
+    // tables (device); E holds the exact kernel columns and the columns in the basis
+    double *d_omega = nullptr, *d_E = nullptr, *d_wh = nullptr, *d_Phit = nullptr;
+    // walker-independent residue tables of the sweep (FP64): (omega, D, V, 0) per
+    // bin and the pair-sum table (G, H), with the constant C and the grid's omega_0, d_omega
+    double *d_bin = nullptr, *d_GH = nullptr;
     double tC = 0.0, tw0 = 0.0, tdW = 0.0;
+    // the basis: dimensions per chunk for either precision (dimension d lies in
+    // chunk d mod 4, so the FP32 loop's shorter basis is a prefix of every
+    // chunk), the columns in it [N_omega][4][echunk] and its vectors times
+    // sqrt(wh), [n_tau][4][echunk]
+    int dims64 = 1, dims32 = 1, echunk = 2;
+    std::vector<double> h_col, h_proj;
+    void *d_col = nullptr;  // columns in the loop precision, [N_omega][4][chunk()]
     int layout_precision = -1;
+    int dims(int precision_) const { return precision_ == SAIL_FP32 ? dims32 : dims64; }
+    int chunk(int precision_) const
+    {
+        return precision_ == SAIL_FP32 ? chunk_stride<float>(dims32) : chunk_stride<double>(dims64);
+    }
+    int cols() const { return n_tau + 4 * echunk; }
+    int phi_row() const { return 4 * chunk(precision); }  // stored coordinates per walker
     // walkers (device)
     int n_walkers = 0, precision = 0;
     uint64_t seed = 0;
     double chi2_unit = NAN;
     double *d_b = nullptr, *d_gsc = nullptr, *d_ginv = nullptr, *d_chi2 = nullptr, *d_rate = nullptr;
-    void *d_Phi = nullptr;  // in the loop precision
+    void *d_phi = nullptr;  // [N_w][4][chunk()] in the loop precision
+    void *d_Phi = nullptr;  // [N_w][ntau_pad], filled when reconstructions are read; absent beside a large basis
     double *d_a0 = nullptr, *d_tmp = nullptr, *d_teff = nullptr;  // d_teff: imprint strength of the last event
     double *d_part = nullptr;               // partial sums of the averaged spectrum
     unsigned long long *d_hist = nullptr;   // counts of the residue histogram, kept from its first call
@@ -2222,7 +2580,7 @@ struct sail_problem {
     bool watch_active = false;  // set while sail_run_schedule runs with the watchdog on
     unsigned int *d_watch = nullptr;
     double *sn_b = nullptr, *sn_gsc = nullptr, *sn_ginv = nullptr, *sn_chi2 = nullptr, *sn_rate = nullptr;
-    double *sn_Phi = nullptr;  // the loop-precision Phi as raw 8-byte words
+    double *sn_phi = nullptr;  // the loop-precision phi as raw 8-byte words
     int watch_tripped = -1, watch_restored = -1;
     // per-block log: a ring of records and the walkers' drift at the last resync
     sail_block_record *d_blog = nullptr;
@@ -2244,7 +2602,7 @@ struct sail_problem {
 
     void free_walkers()
     {
-        dfree(d_b); dfree(d_Phi); dfree(d_gsc); dfree(d_ginv); dfree(d_chi2); dfree(d_rate);
+        dfree(d_b); dfree(d_phi); dfree(d_Phi); dfree(d_gsc); dfree(d_ginv); dfree(d_chi2); dfree(d_rate);
         dfree(d_a0); dfree(d_tmp); dfree(d_teff); dfree(d_part); dfree(d_hist); dfree(d_m); dfree(d_targets); dfree(d_donors); dfree(d_npairs);
         dfree(d_tree);
         dfree(d_ev_delta); dfree(d_ev_pr); dfree(d_ev_z); dfree(d_ev_status); dfree(d_ev_m);
@@ -2263,15 +2621,15 @@ struct sail_problem {
     }
     void free_watch()
     {
-        dfree(d_watch); dfree(sn_b); dfree(sn_gsc); dfree(sn_ginv); dfree(sn_chi2); dfree(sn_rate); dfree(sn_Phi);
+        dfree(d_watch); dfree(sn_b); dfree(sn_gsc); dfree(sn_ginv); dfree(sn_chi2); dfree(sn_rate); dfree(sn_phi);
         watch_bound = 0.0;
     }
     ~sail_problem()
     {
         (void)hipSetDevice(device);
         free_walkers();
-        dfree(d_omega); dfree(d_z); dfree(d_E); dfree(d_wh); dfree(d_Phit); dfree(d_Tabs);
-        dfree(d_E0r); dfree(d_whr); dfree(d_Dg); dfree(d_Vg); dfree(d_GH);
+        dfree(d_omega); dfree(d_E); dfree(d_wh); dfree(d_Phit); dfree(d_Tabs);
+        dfree(d_col); dfree(d_bin); dfree(d_GH);
         for (auto e : ev_start) (void)hipEventDestroy(e);
         for (auto e : ev_stop) (void)hipEventDestroy(e);
         if (done_ev) (void)hipEventDestroy(done_ev);
@@ -2413,7 +2771,9 @@ ResyncArgs make_resync_args(const sail_problem *p, int renorm, const int32_t *li
     ResyncArgs r;
     r.n_omega = p->n_omega;
     r.n_tau = p->n_tau;
-    r.ntau_pad = p->ntau_pad;
+    r.cols = p->cols();
+    r.echunk = p->echunk;
+    r.chunk = p->chunk(p->precision);
     r.omega = p->d_omega;
     r.E = p->d_E;
     r.wh = p->d_wh;
@@ -2421,7 +2781,7 @@ ResyncArgs make_resync_args(const sail_problem *p, int renorm, const int32_t *li
     r.b = p->d_b;
     r.gsc = p->d_gsc;
     r.ginv = p->d_ginv;
-    r.Phi = p->d_Phi;
+    r.phi = p->d_phi;
     r.chi2 = p->d_chi2;
     r.A = p->A;
     r.B = p->B;
@@ -2453,17 +2813,15 @@ int resync_blocks(int n_items) { return (n_items + kResyncWPB - 1) / kResyncWPB;
 // LDS one workgroup may hold on gfx950 (the 160 KiB of a compute unit).
 constexpr size_t kLdsBytes = 160 * 1024;
 
-// The resync stages kResyncWPB spectra per workgroup and the sweep stages
-// its per-bin tables next to its records, so N_omega is bounded by the LDS
-// of one workgroup (N_omega <= 2556 on gfx950, the resync's bound).
+// The resync stages kResyncWPB spectra per workgroup, so N_omega is bounded by
+// the LDS of one workgroup (N_omega <= 2556 on gfx950); a sweep needs its
+// records only (its tables are read from memory where they do not fit).
 sail_status check_lds(int n_omega, size_t limit = kLdsBytes)
 {
     const size_t resync = resync_shmem(n_omega);
-    const size_t sweep = sizeof(double) * kRecsMax + sweep_shmem(n_omega);
-    if (resync > limit || sweep > limit)
-        return fail(SAIL_EINVAL, "n_omega = " + std::to_string(n_omega) + " needs " +
-                                     std::to_string(std::max(resync, sweep)) + " bytes of LDS per workgroup; " +
-                                     std::to_string(limit) + " are available");
+    if (resync > limit)
+        return fail(SAIL_EINVAL, "n_omega = " + std::to_string(n_omega) + " needs " + std::to_string(resync) +
+                                     " bytes of LDS per workgroup; " + std::to_string(limit) + " are available");
     return SAIL_OK;
 }
 
@@ -2544,21 +2902,6 @@ BranchArgs make_branch_args(const sail_problem *p, double fraction, int event, i
     return ba;
 }
 
-template <typename R, int TPL, int L>
-void launch_sweep_l(const SweepArgs &s, int grid, bool trace, hipStream_t stream)
-{
-    // LDS: bin centres, decay factors and the per-bin residue tables
-    const size_t shm = sweep_shmem(s.n_omega);
-    if (s.walk_len > 0) {
-        if (trace) hipLaunchKernelGGL((k_sweep<R, TPL, L, true, true>), dim3(grid), dim3(kThreads), shm, stream, s);
-        else hipLaunchKernelGGL((k_sweep<R, TPL, L, false, true>), dim3(grid), dim3(kThreads), shm, stream, s);
-    } else if (trace) {
-        hipLaunchKernelGGL((k_sweep<R, TPL, L, true, false>), dim3(grid), dim3(kThreads), shm, stream, s);
-    } else {
-        hipLaunchKernelGGL((k_sweep<R, TPL, L, false, false>), dim3(grid), dim3(kThreads), shm, stream, s);
-    }
-}
-
 struct SweepParams {
     double eps0, amp_p, amp_avg;
     int amp_m, walk_len;
@@ -2573,14 +2916,13 @@ int sweep_wg_sync()
     return v;
 }
 
-SweepArgs make_sweep_args(const sail_problem *p, int k0, int k1, const SweepParams &sp)
+SweepArgs make_sweep_args(const sail_problem *p, int k0, int k1, const SweepParams &sp, int columns_lds)
 {
     SweepArgs s;
     s.n_walkers = p->n_walkers;
     s.n_omega = p->n_omega;
-    s.lanes = p->lanes;
-    s.log2_lanes = p->log2_lanes;
-    s.ntau_pad = p->ntau_pad;
+    s.chunk = p->chunk(p->precision);
+    s.columns_lds = columns_lds;
     s.k0 = k0;
     s.k1 = k1;
     s.key0 = (uint32_t)p->seed;
@@ -2591,13 +2933,9 @@ SweepArgs make_sweep_args(const sail_problem *p, int k0, int k1, const SweepPara
     s.amp_p = sp.amp_p;
     s.amp_avg = sp.amp_avg;
     s.amp_m = sp.amp_m;
-    s.omega = p->d_omega;
-    s.z = p->d_z;
-    s.E0 = p->d_E0r;
-    s.wh = p->d_whr;
-    s.Phi = p->d_Phi;
-    s.D = p->d_Dg;
-    s.V = p->d_Vg;
+    s.col = p->d_col;
+    s.phi = p->d_phi;
+    s.bin = (const double4 *)p->d_bin;
     s.GH = (const double2 *)p->d_GH;
     s.C = p->tC;
     s.w0 = p->tw0;
@@ -2620,75 +2958,351 @@ SweepArgs make_sweep_args(const sail_problem *p, int k0, int k1, const SweepPara
     return s;
 }
 
-int sweep_blocks(const sail_problem *p) { return (int)(((size_t)p->n_walkers * p->lanes + kThreads - 1) / kThreads); }
+// How a sweep is launched: split or not, lanes per walker, threads and walkers
+// per workgroup, whether the columns and the walkers' spectra sit in LDS, and
+// the LDS they take with the records.  The results have the same bits for any
+// plan.
+struct SweepPlan {
+    bool split;
+    int lanes, threads, walkers;
+    int columns_lds, spectra_lds;
+    size_t shm;
+};
 
-template <typename R, int TPL>
+// The columns, then the spectra of the workgroup's walkers (if asked for), go
+// to LDS if they fit in `budget` bytes beside the records.
+SweepPlan plan_sweep(const sail_problem *p, bool split, int lanes, int threads, size_t budget, bool walk, bool spectra)
+{
+    const int walkers = (split ? threads / 2 : threads) / lanes;
+    SweepPlan s{split, lanes, threads, walkers, 0, 0,
+                sizeof(double) * (split ? (size_t)walkers * kSplitStride + (size_t)walkers / 16 * kSplitHits
+                                     : (size_t)walkers * rec_stride(lanes, walk))};
+    const size_t col = column_bytes(p->n_omega, p->chunk(p->precision),
+                                    p->precision == SAIL_FP32 ? sizeof(float) : sizeof(double));
+    if (basis_class(p->precision, p->dims(p->precision)) == 0) return s;
+    if (s.shm + col <= budget) {
+        s.shm += col;
+        s.columns_lds = 1;
+        const size_t spec = sizeof(double) * (size_t)walkers * p->n_omega;
+        if (spectra && s.shm + spec <= budget) {
+            s.shm += spec;
+            s.spectra_lds = 1;
+        }
+    }
+    return s;
+}
+
+int sweep_blocks(const sail_problem *p, const SweepPlan &s) { return (p->n_walkers + s.walkers - 1) / s.walkers; }
+
+bool sweep_traced(const sail_problem *p, int k0, int k1) { return p->tk1 > p->tk0 && k0 < p->tk1 && k1 > p->tk0; }
+
+constexpr int kCUs = 256;
+
+// The plan of a problem swept alone.  A population whose spectra fit in the
+// LDS of the chip beside the columns keeps them there, 16 lanes a walker
+// (@PLAN16@); a larger one keeps them in memory and splits its workgroups
+// into chains and stagers.  Workgroups are the smallest that leave at most one
+// per compute unit, so that a small population spreads over the chip, each
+// with as much LDS as its share of a compute unit.
+SweepPlan plan_alone(const sail_problem *p, int mode)
+{
+    const size_t n = (size_t)p->n_walkers;
+    const bool general = basis_class(p->precision, p->dims(p->precision)) == 0;
+    auto sized = [&](bool split, int lanes, bool spectra) {
+        const int most = split ? 2 * kSweepThreads : kSweepThreads, per = split ? 2 * lanes : lanes;
+        int threads = split ? 128 : 64;
+        while (threads < most && n * per > (size_t)threads * kCUs) threads *= 2;
+        const size_t blocks = (n * per + threads - 1) / threads;
+        const size_t per_cu = std::min<size_t>(std::max<size_t>((blocks + kCUs - 1) / kCUs, 1), 4);
+        return plan_sweep(p, split, lanes, threads, kLdsBytes / per_cu, mode == kSweepWalk, spectra);
+    };
+    if (mode == kSweepTraced || general) return sized(false, 4, false);
+    if (mode == kSweepWalk) return sized(false, 8, true);
+    const SweepPlan s = sized(false, 16, true);
+    return s.spectra_lds ? s : sized(true, 4, false);
+}
+
+template <typename R, int M, int G, bool LDSC, bool LDSB, int MODE>
+void launch_sweep_k(const SweepArgs &a, int blocks, const SweepPlan &s, hipStream_t stream)
+{
+    hipLaunchKernelGGL((k_sweep<R, M, G, LDSC, LDSB, MODE>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
+}
+
+template <typename R, int M>
+void launch_sweep_m(const SweepArgs &a, int blocks, const SweepPlan &s, int mode, hipStream_t stream)
+{
+    if (mode == kSweepTraced) return launch_sweep_k<R, M, 4, false, false, kSweepTraced>(a, blocks, s, stream);
+    if constexpr (M > 0) {
+        if (mode == kSweepWalk) {
+            if (s.spectra_lds) return launch_sweep_k<R, M, 8, true, true, kSweepWalk>(a, blocks, s, stream);
+            return launch_sweep_k<R, M, 8, false, false, kSweepWalk>(a, blocks, s, stream);
+        }
+        if (s.spectra_lds) return launch_sweep_k<R, M, 16, true, true, kSweepFast>(a, blocks, s, stream);
+        if (s.columns_lds)
+            hipLaunchKernelGGL((k_sweep_split<R, M, true>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
+        else
+            hipLaunchKernelGGL((k_sweep_split<R, M, false>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
+    } else {
+        // the general variant: four lanes, phi and columns in memory
+        if (mode == kSweepWalk) return launch_sweep_k<R, M, 4, false, false, kSweepWalk>(a, blocks, s, stream);
+        launch_sweep_k<R, M, 4, false, false, kSweepFast>(a, blocks, s, stream);
+    }
+}
+
+// Calls f(R{}, std::integral_constant<int, M>{}) for the kernel of a basis class.
+template <typename F>
+void with_basis_class(int precision, int cls, F &&f)
+{
+#define SAIL_CASE(R, M) case M: f(R{}, std::integral_constant<int, M>{}); break;
+    if (precision == SAIL_FP32) {
+        switch (cls) {
+            SAIL_CASE(float, 2) SAIL_CASE(float, 3) SAIL_CASE(float, 4) SAIL_CASE(float, 6)
+            default: f(float{}, std::integral_constant<int, 0>{});
+        }
+    } else {
+        switch (cls) {
+            SAIL_CASE(double, 2) SAIL_CASE(double, 4) SAIL_CASE(double, 6) SAIL_CASE(double, 8)
+            default: f(double{}, std::integral_constant<int, 0>{});
+        }
+    }
+#undef SAIL_CASE
+}
+
 sail_status launch_sweep(sail_problem *p, int k0, int k1, const SweepParams &sp, hipStream_t stream)
 {
-    const SweepArgs s = make_sweep_args(p, k0, k1, sp);
-    const int grid = sweep_blocks(p);
-    const bool trace = p->tk1 > p->tk0 && k0 < p->tk1 && k1 > p->tk0;
+    const int mode = sp.walk_len > 0 ? kSweepWalk : sweep_traced(p, k0, k1) ? kSweepTraced : kSweepFast;
+    const SweepPlan s = plan_alone(p, mode);
+    const SweepArgs a = make_sweep_args(p, k0, k1, sp, s.columns_lds);
+    const int blocks = sweep_blocks(p, s);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (p->timing) {
         if (p->ev_used == p->ev_start.size()) {
-            hipEvent_t a, b;
-            SAIL_HIP(hipEventCreate(&a));
-            SAIL_HIP(hipEventCreate(&b));
-            p->ev_start.push_back(a);
-            p->ev_stop.push_back(b);
+            hipEvent_t x, y;
+            SAIL_HIP(hipEventCreate(&x));
+            SAIL_HIP(hipEventCreate(&y));
+            p->ev_start.push_back(x);
+            p->ev_stop.push_back(y);
         }
         e0 = p->ev_start[p->ev_used];
         e1 = p->ev_stop[p->ev_used];
         p->ev_used++;
         SAIL_HIP(hipEventRecord(e0, stream));
     }
-    sail_status st = SAIL_OK;
-    switch (p->lanes) {
-        case 1: launch_sweep_l<R, TPL, 1>(s, grid, trace, stream); break;
-        case 2: launch_sweep_l<R, TPL, 2>(s, grid, trace, stream); break;
-        case 4: launch_sweep_l<R, TPL, 4>(s, grid, trace, stream); break;
-        case 8: launch_sweep_l<R, TPL, 8>(s, grid, trace, stream); break;
-        case 16: launch_sweep_l<R, TPL, 16>(s, grid, trace, stream); break;
-        case 32: launch_sweep_l<R, TPL, 32>(s, grid, trace, stream); break;
-        case 64: launch_sweep_l<R, TPL, 64>(s, grid, trace, stream); break;
-        default: st = fail(SAIL_EINVAL, "unsupported lanes per walker");
-    }
-    if (st) return st;
+    with_basis_class(p->precision, basis_class(p->precision, p->dims(p->precision)), [&](auto r, auto m) {
+        launch_sweep_m<decltype(r), decltype(m)::value>(a, blocks, s, mode, stream);
+    });
     SAIL_HIP(hipGetLastError());
     if (p->timing) SAIL_HIP(hipEventRecord(e1, stream));
     return SAIL_OK;
 }
 
-sail_status launch_sweep_any(sail_problem *p, int k0, int k1, const SweepParams &sp, hipStream_t stream)
+// The basis of the weighted columns and everything built from the kernel: the
+// exact columns E, the columns in the basis, and the sweep's residue tables.
+//
+// Basis: a greedy (pivoted, twice orthogonalised Gram-Schmidt) selection of
+// columns sqrt(wh_i) e^{-omega_j tau_i}, each taken relative to its own norm,
+// until what it leaves of any column is below kBasisTol64.  The sweep drops
+// the product of two such residuals, so the scalar products of the FP64 loop
+// are good to kBasisTol64^2 = 1e-14 of the norms at worst, and to their own
+// rounding in practice (measured over the benchmark's grids with annealed
+// spectra: 3e-17 of the condition scale rms with 16 dimensions, against 3e-16
+// of the two-term recurrence along tau that generated the columns before).  The
+// FP32 loop takes the first vectors, up to kBasisTol32 (squared 1e-8, below
+// its rounding).  The greedy choice runs on at most kBasisSample columns spread
+// over the grid and on any column found outside its span afterwards.
+constexpr double kBasisTol64 = 1e-7, kBasisTol32 = 1e-4;
+constexpr int kBasisSample = 64;
+
+struct Basis {
+    std::vector<double> q;  // [dims][n_tau], orthonormal
+    std::vector<double> c;  // [n_omega][dims], columns in the basis
+    int dims = 0, dims32 = 0;
+};
+
+double dot(const double *x, const double *y, int n)
 {
-    if (p->precision == SAIL_FP32) {
-        switch (p->tpl) {
-            case 8: return launch_sweep<float, 8>(p, k0, k1, sp, stream);
-            case 16: return launch_sweep<float, 16>(p, k0, k1, sp, stream);
-            case 32: return launch_sweep<float, 32>(p, k0, k1, sp, stream);
-            default: return fail(SAIL_EINVAL, "unsupported tau points per lane");
-        }
-    }
-    switch (p->tpl) {
-        case 4: return launch_sweep<double, 4>(p, k0, k1, sp, stream);
-        case 8: return launch_sweep<double, 8>(p, k0, k1, sp, stream);
-        case 16: return launch_sweep<double, 16>(p, k0, k1, sp, stream);
-        default: return fail(SAIL_EINVAL, "unsupported tau points per lane");
-    }
+    double s[8] = {};
+    int i = 0;
+    for (; i + 8 <= n; i += 8)
+        for (int t = 0; t < 8; ++t) s[t] += x[i + t] * y[i + t];
+    for (; i < n; ++i) s[0] += x[i] * y[i];
+    return ((s[0] + s[4]) + (s[2] + s[6])) + ((s[1] + s[5]) + (s[3] + s[7]));
 }
 
-// Lane layout and the tables that depend on it: TPL tau points per lane
-// (16 unless requested otherwise; more only when N_tau needs it), a
-// power-of-two number of lanes per walker,
-// tau padded to lanes * TPL with zero weight.
+// a: [n_omega][n_tau] weighted columns
+Basis make_basis(const std::vector<double> &a, int n_omega, int n_tau)
+{
+    Basis b;
+    const int most = std::min(n_omega, n_tau);
+    std::vector<double> norm(n_omega);
+    for (int j = 0; j < n_omega; ++j) {
+        const double v = std::sqrt(dot(&a[(size_t)j * n_tau], &a[(size_t)j * n_tau], n_tau));
+        norm[j] = std::isfinite(v) ? v : 0.0;  // a column that overflows or vanishes spans nothing
+    }
+    std::vector<std::vector<double>> q, work;  // basis vectors; residuals of the sampled columns
+    std::vector<std::vector<double>> c;        // [dims][n_omega]
+    auto sample = [&](int j) {
+        if (!(norm[j] > 0.0)) return;
+        std::vector<double> v(&a[(size_t)j * n_tau], &a[(size_t)j * n_tau] + n_tau);
+        for (auto &x : v) x /= norm[j];
+        for (const auto &u : q) {
+            const double s = dot(u.data(), v.data(), n_tau);
+            for (int i = 0; i < n_tau; ++i) v[i] -= s * u[i];
+        }
+        work.push_back(std::move(v));
+    };
+    const int ns = std::min(n_omega, kBasisSample);
+    for (int i = 0; i < ns; ++i) sample((int)((int64_t)i * (n_omega - 1) / std::max(1, ns - 1)));
+    std::vector<double> left(n_omega, 1.0);  // squared residual of each column relative to its norm
+    std::vector<double> worst;               // largest of them after each vector
+    while ((int)q.size() < most) {
+        int pick = -1;
+        double big = kBasisTol64;
+        for (size_t i = 0; i < work.size(); ++i) {
+            const double v = std::sqrt(dot(work[i].data(), work[i].data(), n_tau));
+            if (v > big) {
+                big = v;
+                pick = (int)i;
+            }
+        }
+        if (pick < 0) {
+            // the sample is spanned: is every column?
+            int j = (int)(std::max_element(left.begin(), left.end()) - left.begin());
+            if (q.empty() || !(left[j] > kBasisTol64 * kBasisTol64)) break;
+            const size_t had = work.size();
+            sample(j);
+            left[j] = 0.0;  // taken into the sample (its residual may be rounding only)
+            if (work.size() == had) break;
+            continue;
+        }
+        std::vector<double> u = work[pick];
+        for (int pass = 0; pass < 2; ++pass)
+            for (const auto &w : q) {
+                const double s = dot(w.data(), u.data(), n_tau);
+                for (int i = 0; i < n_tau; ++i) u[i] -= s * w[i];
+            }
+        const double un = std::sqrt(dot(u.data(), u.data(), n_tau));
+        if (!(un > 0.5 * big)) {  // nothing but rounding was left
+            work.erase(work.begin() + pick);
+            continue;
+        }
+        for (auto &x : u) x /= un;
+        for (auto &v : work) {
+            const double s = dot(u.data(), v.data(), n_tau);
+            for (int i = 0; i < n_tau; ++i) v[i] -= s * u[i];
+        }
+        std::vector<double> cd(n_omega);
+        double w = 0.0;
+        for (int j = 0; j < n_omega; ++j) {
+            cd[j] = dot(u.data(), &a[(size_t)j * n_tau], n_tau);
+            if (!(norm[j] > 0.0)) {
+                cd[j] = left[j] = 0.0;
+                continue;
+            }
+            left[j] -= (cd[j] / norm[j]) * (cd[j] / norm[j]);
+            w = std::max(w, left[j]);
+        }
+        worst.push_back(w);
+        q.push_back(std::move(u));
+        c.push_back(std::move(cd));
+    }
+    b.dims = (int)q.size();
+    b.dims32 = b.dims;
+    for (int d = b.dims; d >= 1 && worst[d - 1] <= kBasisTol32 * kBasisTol32; --d) b.dims32 = d;
+    b.q.reserve((size_t)b.dims * n_tau);
+    for (const auto &u : q) b.q.insert(b.q.end(), u.begin(), u.end());
+    b.c.assign((size_t)n_omega * b.dims, 0.0);
+    for (int d = 0; d < b.dims; ++d)
+        for (int j = 0; j < n_omega; ++j) b.c[(size_t)j * b.dims + d] = c[d][j];
+    return b;
+}
+
+// Host tables of the problem and their device copies; independent of the
+// precision and the lane layout.
+sail_status build_tables(sail_problem *p)
+{
+    const int n_omega = p->n_omega, n_tau = p->n_tau;
+    std::vector<double> wh(n_tau), cn(n_tau), Phit(n_tau), sw(n_tau);
+    double C = 0.0;
+    for (int i = 0; i < n_tau; ++i) {
+        wh[i] = p->w[i] * p->cfac[i] * p->cfac[i];
+        Phit[i] = p->F[i] / p->cfac[i];
+        cn[i] = -(2.0 * wh[i]) * Phit[i];
+        sw[i] = std::sqrt(wh[i]);
+        C += wh[i] * Phit[i] * Phit[i];
+    }
+    // E_ji, D_j = sum_i w_i K_ij^2, V_j = sum_i c_i K_ij
+    std::vector<double> k((size_t)n_omega * n_tau), a(k.size()), bin(4 * (size_t)n_omega, 0.0);
+    for (int j = 0; j < n_omega; ++j) {
+        double d = 0.0, v = 0.0;
+        for (int i = 0; i < n_tau; ++i) {
+            const double e = std::exp(-p->omega[j] * p->tau[i]);
+            k[(size_t)j * n_tau + i] = e;
+            a[(size_t)j * n_tau + i] = sw[i] * e;
+            d += wh[i] * e * e;
+            v += cn[i] * e;
+        }
+        bin[4 * (size_t)j] = p->omega[j];
+        bin[4 * (size_t)j + 1] = d;
+        bin[4 * (size_t)j + 2] = v;
+    }
+    // (G_k, H_k) = sum_i w_i (1, tau_i) e^{-wbar_k tau_i} with wbar_k = 2 omega_0 + k d_omega
+    const double w0 = p->omega[0], dW = (p->omega[n_omega - 1] - p->omega[0]) / (double)(n_omega - 1);
+    std::vector<double> GH(2 * (size_t)(2 * n_omega - 1));
+    for (int kk = 0; kk < 2 * n_omega - 1; ++kk) {
+        const double wbar = 2.0 * w0 + (double)kk * dW;
+        double g = 0.0, h = 0.0;
+        for (int i = 0; i < n_tau; ++i) {
+            const double e = wh[i] * std::exp(-wbar * p->tau[i]);
+            g += e;
+            h += e * p->tau[i];
+        }
+        GH[2 * (size_t)kk] = g;
+        GH[2 * (size_t)kk + 1] = h;
+    }
+    const Basis b = make_basis(a, n_omega, n_tau);
+    p->dims64 = round_dims(SAIL_FP64, b.dims);
+    p->dims32 = round_dims(SAIL_FP32, b.dims32);
+    const int ec = p->echunk = chunk_stride<double>(p->dims64), cols = p->cols();
+    p->h_col.assign((size_t)n_omega * 4 * ec, 0.0);
+    p->h_proj.assign((size_t)n_tau * 4 * ec, 0.0);
+    std::vector<double> E((size_t)n_omega * cols, 0.0);
+    for (int d = 0; d < b.dims; ++d) {
+        const int at = (d % 4) * ec + d / 4;
+        for (int j = 0; j < n_omega; ++j) p->h_col[(size_t)j * 4 * ec + at] = b.c[(size_t)j * b.dims + d];
+        for (int i = 0; i < n_tau; ++i) p->h_proj[(size_t)i * 4 * ec + at] = sw[i] * b.q[(size_t)d * n_tau + i];
+    }
+    for (int j = 0; j < n_omega; ++j) {
+        std::copy(&k[(size_t)j * n_tau], &k[(size_t)j * n_tau] + n_tau, &E[(size_t)j * cols]);
+        std::copy(&p->h_col[(size_t)j * 4 * ec], &p->h_col[(size_t)j * 4 * ec] + 4 * ec, &E[(size_t)j * cols + n_tau]);
+    }
+    sail_status st;
+    if ((st = dalloc(&p->d_E, E.size())) || (st = dalloc(&p->d_wh, n_tau)) || (st = dalloc(&p->d_Phit, n_tau)) ||
+        (st = dalloc(&p->d_bin, bin.size())) || (st = dalloc(&p->d_GH, GH.size())))
+        return st;
+    p->tC = C;
+    p->tw0 = w0;
+    p->tdW = dW;
+    auto up = [&](double *d, const std::vector<double> &h) {
+        return hipMemcpy(d, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice);
+    };
+    hipError_t e = up(p->d_E, E);
+    if (e == hipSuccess) e = up(p->d_wh, wh);
+    if (e == hipSuccess) e = up(p->d_Phit, Phit);
+    if (e == hipSuccess) e = up(p->d_bin, bin);
+    if (e == hipSuccess) e = up(p->d_GH, GH);
+    if (e != hipSuccess) return fail(SAIL_EDEVICE, std::string("table upload: ") + hipGetErrorString(e));
+    return SAIL_OK;
+}
+
+// The nominal lane layout: TPL tau points per lane (16 unless requested
+// otherwise; more only when N_tau needs it), a power-of-two number of lanes per
+// walker, tau padded to lanes * TPL; and the columns in the loop precision.
 sail_status build_layout(sail_problem *p, int precision)
 {
     const int n_omega = p->n_omega, n_tau = p->n_tau;
     const int tpl_max = precision == SAIL_FP32 ? 32 : 16;
-    int tpl = 16;  // measured fastest for both precisions at 512 bins x 128 times x 16384 walkers
-    // the smaller tiles give a walker more lanes: fewer tau points each
-    // (a shorter serial loop per proposal) for a longer reduction, which pays
-    // when there are too few walkers to fill the chip
+    int tpl = 16;
     auto tile_ok = [&](int v) { return v == tpl_max || v == tpl_max / 2 || v == tpl_max / 4; };
     if (tile_ok(p->tpl_hint)) {
         tpl = p->tpl_hint;
@@ -2702,90 +3316,28 @@ sail_status build_layout(sail_problem *p, int precision)
         lanes = next_pow2((n_tau + tpl - 1) / tpl);
     }
     if (lanes > 64) return fail(SAIL_EINVAL, "n_tau too large for the sweep layout");
-    if (p->layout_precision == precision && p->tpl == tpl) return SAIL_OK;
-    const int ntp = lanes * tpl;
-    const double dt = p->dtau, t0 = p->tau0;
-    std::vector<double> h_E0((size_t)n_omega * lanes), h_E((size_t)n_omega * ntp, 0.0);
-    std::vector<double> h_wh(ntp, 0.0), h_cn(ntp, 0.0), h_Phit(ntp, 0.0);
-    // the tables below describe the columns as the sweep generates them,
-    // e^{-omega_j (t0 + i d_tau)} on the padded grid (zero weight past n_tau)
-    for (int j = 0; j < n_omega; ++j) {
-        for (int c = 0; c < lanes; ++c)
-            h_E0[(size_t)j * lanes + c] = std::exp(-p->omega[j] * (t0 + dt * (double)(c * tpl)));
-        for (int i = 0; i < n_tau; ++i) h_E[(size_t)j * ntp + i] = std::exp(-p->omega[j] * p->tau[i]);
-    }
-    for (int i = 0; i < n_tau; ++i) {
-        h_wh[i] = p->w[i] * p->cfac[i] * p->cfac[i];
-        h_Phit[i] = p->F[i] / p->cfac[i];
-        h_cn[i] = -(2.0 * h_wh[i]) * h_Phit[i];
-    }
-    // D_j = sum_i w_i K_ij^2, V_j = sum_i c_i K_ij, (G_k, H_k) = sum_i w_i (1, tau_i)
-    // e^{-wbar_k tau_i} with wbar_k = 2 omega_0 + k d_omega, C = sum_i w_i Phit_i^2
-    const double w0 = p->omega[0], dW = (p->omega[n_omega - 1] - p->omega[0]) / (double)(n_omega - 1);
-    std::vector<double> h_D(n_omega, 0.0), h_V(n_omega, 0.0), h_GH(2 * (size_t)(2 * n_omega - 1), 0.0);
-    double C = 0.0;
-    for (int i = 0; i < n_tau; ++i) C += h_wh[i] * h_Phit[i] * h_Phit[i];
-    for (int j = 0; j < n_omega; ++j) {
-        double d = 0.0, v = 0.0;
-        for (int i = 0; i < n_tau; ++i) {
-            const double k = std::exp(-p->omega[j] * (t0 + dt * (double)i));
-            d += h_wh[i] * k * k;
-            v += h_cn[i] * k;
-        }
-        h_D[j] = d;
-        h_V[j] = v;
-    }
-    for (int kk = 0; kk < 2 * n_omega - 1; ++kk) {
-        const double wbar = 2.0 * w0 + (double)kk * dW;
-        double g = 0.0, h = 0.0;
-        for (int i = 0; i < n_tau; ++i) {
-            const double ti = t0 + dt * (double)i;
-            const double e = h_wh[i] * std::exp(-wbar * ti);
-            g += e;
-            h += e * ti;
-        }
-        h_GH[2 * (size_t)kk] = g;
-        h_GH[2 * (size_t)kk + 1] = h;
-    }
-    const size_t rsz = precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
-    dfree(p->d_E); dfree(p->d_wh); dfree(p->d_Phit); dfree(p->d_E0r); dfree(p->d_whr);
-    dfree(p->d_Dg); dfree(p->d_Vg); dfree(p->d_GH);
-    p->layout_precision = -1;
-    sail_status st;
-    char *e0r = nullptr, *whr = nullptr;
-    if ((st = dalloc(&p->d_E, (size_t)n_omega * ntp)) || (st = dalloc(&p->d_wh, ntp)) || (st = dalloc(&p->d_Phit, ntp)) ||
-        (st = dalloc(&e0r, rsz * (size_t)n_omega * lanes)) || (st = dalloc(&whr, rsz * ntp)) ||
-        (st = dalloc(&p->d_Dg, (size_t)n_omega)) || (st = dalloc(&p->d_Vg, (size_t)n_omega)) ||
-        (st = dalloc(&p->d_GH, h_GH.size()))) {
-        dfree(e0r); dfree(whr);
-        return st;
-    }
-    p->d_E0r = e0r;
-    p->d_whr = whr;
-    p->tC = C;
-    p->tw0 = w0;
-    p->tdW = dW;
-    auto up = [&](void *d, const void *h, size_t bytes) { return hipMemcpy(d, h, bytes, hipMemcpyHostToDevice); };
-    hipError_t e = up(p->d_E, h_E.data(), sizeof(double) * h_E.size());
-    if (e == hipSuccess) e = up(p->d_wh, h_wh.data(), sizeof(double) * ntp);
-    if (e == hipSuccess) e = up(p->d_Phit, h_Phit.data(), sizeof(double) * ntp);
-    if (e == hipSuccess) e = up(p->d_Dg, h_D.data(), sizeof(double) * h_D.size());
-    if (e == hipSuccess) e = up(p->d_Vg, h_V.data(), sizeof(double) * h_V.size());
-    if (e == hipSuccess) e = up(p->d_GH, h_GH.data(), sizeof(double) * h_GH.size());
-    if (precision == SAIL_FP32) {
-        std::vector<float> f0(h_E0.begin(), h_E0.end()), fw(h_wh.begin(), h_wh.end());
-        if (e == hipSuccess) e = up(e0r, f0.data(), sizeof(float) * f0.size());
-        if (e == hipSuccess) e = up(whr, fw.data(), sizeof(float) * fw.size());
-    } else {
-        if (e == hipSuccess) e = up(e0r, h_E0.data(), sizeof(double) * h_E0.size());
-        if (e == hipSuccess) e = up(whr, h_wh.data(), sizeof(double) * ntp);
-    }
-    if (e != hipSuccess) return fail(SAIL_EDEVICE, std::string("table upload: ") + hipGetErrorString(e));
     p->tpl = tpl;
     p->lanes = lanes;
-    p->log2_lanes = 0;
-    while ((1 << p->log2_lanes) < lanes) p->log2_lanes++;
-    p->ntau_pad = ntp;
+    p->ntau_pad = lanes * tpl;
+    if (p->layout_precision == precision) return SAIL_OK;
+    dfree(p->d_col);
+    p->layout_precision = -1;
+    const int ec = p->echunk, ck = p->chunk(precision);
+    const size_t n = (size_t)n_omega * 4 * ck, rsz = precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
+    char *col = nullptr;
+    const sail_status st = dalloc(&col, rsz * n);
+    if (st) return st;
+    p->d_col = col;
+    hipError_t e;
+    if (precision == SAIL_FP32) {
+        std::vector<float> f(n, 0.f);
+        for (size_t r = 0; r < (size_t)n_omega * 4; ++r)
+            for (int t = 0; t < std::min(ec, ck); ++t) f[r * ck + t] = (float)p->h_col[r * ec + t];
+        e = hipMemcpy(col, f.data(), rsz * n, hipMemcpyHostToDevice);
+    } else {
+        e = hipMemcpy(col, p->h_col.data(), rsz * n, hipMemcpyHostToDevice);
+    }
+    if (e != hipSuccess) return fail(SAIL_EDEVICE, std::string("table upload: ") + hipGetErrorString(e));
     p->layout_precision = precision;
     return SAIL_OK;
 }
@@ -2862,28 +3414,22 @@ sail_status prepare_schedule(sail_problem *p, const sail_schedule *sc, int last,
     return SAIL_OK;
 }
 
-// The largest tau padding and lane count any candidate layout of this
-// precision takes.
-void max_padding(int n_tau, int precision, size_t *ntp, size_t *lanes)
+// The largest padded time grid any candidate layout of this precision takes.
+size_t max_padding(int n_tau, int precision)
 {
     const int tmin = precision == SAIL_FP32 ? 16 : 8;
-    *ntp = *lanes = 0;
-    for (int t = tmin; t <= 2 * tmin; t *= 2) {
-        const size_t l = (size_t)next_pow2((n_tau + t - 1) / t);
-        *ntp = std::max(*ntp, l * t);
-        *lanes = std::max(*lanes, l);
-    }
+    size_t ntp = 0;
+    for (int t = tmin; t <= 2 * tmin; t *= 2) ntp = std::max(ntp, (size_t)next_pow2((n_tau + t - 1) / t) * t);
+    return ntp;
 }
 
-// Device bytes of a problem's tables (omega, z, one lane layout and the
-// sweep's residue tables), each rounded as the allocator rounds it.
+// Device bytes of a problem's tables, each rounded as the allocator rounds it;
+// the basis has at most min(n_tau, n_omega) dimensions.
 size_t table_bytes(int n_omega, int n_tau, int precision)
 {
     const size_t rsz = precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
-    size_t ntp, lanes;
-    max_padding(n_tau, precision, &ntp, &lanes);
-    const size_t No = (size_t)n_omega;
-    return sizeof(double) * (2 * No + No * ntp + 2 * ntp + 2 * No + 2 * (2 * No - 1)) + rsz * (No * lanes + ntp) +
+    const size_t No = (size_t)n_omega, dims = (size_t)std::min(n_tau, n_omega) + kBasisPad;
+    return sizeof(double) * (5 * No + No * (n_tau + dims) + 2 * (size_t)n_tau + 2 * (2 * No - 1)) + rsz * No * dims +
            12 * 256;
 }
 
@@ -2979,6 +3525,8 @@ struct BatchJob {
     int k = 0, last = 0;
 };
 
+constexpr int kSweepGroups = 2 * 5 * 3;  // precisions x basis classes of each x modes
+
 struct StageRing {
     static constexpr int kSlots = 4;
     char *h[kSlots] = {};
@@ -2992,10 +3540,10 @@ struct StageRing {
     // and one branching descriptor, plus one workgroup offset per launch
     // list the job joins (one sweep list, three resync passes).  Each put
     // starts on a 64-byte boundary and each launch list ends with one extra
-    // offset: at most kMaxPuts puts per round (4 sweep groups x 2, 2
+    // offset: at most kMaxPuts puts per round (kSweepGroups sweep groups x 2, 2
     // precisions x 3 resync passes x kResyncClasses LDS classes x 2, one
     // branching array, one block-log array).
-    static constexpr size_t kMaxPuts = 4 * 2 + 2 * 3 * kResyncClasses * 2 + 1 + 1;
+    static constexpr size_t kMaxPuts = kSweepGroups * 2 + 2 * 3 * kResyncClasses * 2 + 1 + 1;
     static size_t bytes_per_job()
     {
         return sizeof(SweepArgs) + 3 * sizeof(ResyncArgs) + sizeof(BranchArgs) + sizeof(BlockLogArgs) + 4 * sizeof(int);
@@ -3125,14 +3673,33 @@ struct SweepTimer {
     }
 };
 
-template <typename R, int TPL>
-void launch_sweep_batched(const SweepArgs *jobs, const int *first, int n_jobs, int blocks, size_t shm, bool trace,
-                          hipStream_t stream)
+struct Launch {
+    int kind, blocks, n;
+    const void *args;
+    const int *first;
+    size_t shm;
+    int cls = 0, mode = 0, threads = kThreads;  // sweeps only
+};
+
+template <typename R, int M>
+void launch_sweep_batched_m(const Launch &L, const SweepArgs *jobs, hipStream_t stream)
 {
-    if (trace)
-        hipLaunchKernelGGL((k_sweep_batched<R, TPL, true>), dim3(blocks), dim3(kThreads), shm, stream, jobs, first, n_jobs);
+    const dim3 grid(L.blocks), thr(L.threads);
+    if (L.mode == kSweepTraced)
+        hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepTraced>), grid, thr, L.shm, stream, jobs, L.first, L.n);
+    else if (L.mode == kSweepWalk)
+        hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepWalk>), grid, thr, L.shm, stream, jobs, L.first, L.n);
+    else if constexpr (M > 0)
+        hipLaunchKernelGGL((k_sweep_split_batched<R, M>), grid, thr, L.shm, stream, jobs, L.first, L.n);
     else
-        hipLaunchKernelGGL((k_sweep_batched<R, TPL, false>), dim3(blocks), dim3(kThreads), shm, stream, jobs, first, n_jobs);
+        hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepFast>), grid, thr, L.shm, stream, jobs, L.first, L.n);
+}
+
+void launch_sweep_batched(const Launch &L, const SweepArgs *jobs, hipStream_t stream)
+{
+    with_basis_class(L.kind, L.cls, [&](auto r, auto m) {
+        launch_sweep_batched_m<decltype(r), decltype(m)::value>(L, jobs, stream);
+    });
 }
 
 // Enqueues one round for the unfinished jobs in `jobs` (advancing their k).
@@ -3153,38 +3720,48 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
     for (size_t i = 0; i < act.size(); ++i) kend[i] = segment_end(&act[i]->sc, act[i]->k, act[i]->last);
 
     // sweep groups, heaviest workgroups first
-    struct Launch { int kind, blocks, n; const void *args; const int *first; size_t shm; bool trace; };
     std::vector<Launch> sweeps, resyncs, targets, smooths;
-    const int gkeys[6][2] = {{SAIL_FP64, 4}, {SAIL_FP64, 8}, {SAIL_FP64, 16},
-                             {SAIL_FP32, 8}, {SAIL_FP32, 16}, {SAIL_FP32, 32}};
-    for (int g = 0; g < 6; ++g) {
+    // one sweep launch per (precision, basis class, mode); jobs of one
+    // workload share theirs
+    std::vector<int> group(act.size());
+    for (size_t i = 0; i < act.size(); ++i) {
+        const sail_problem *p = act[i]->p;
+        const int mode = act[i]->sc.walk_len > 0 ? kSweepWalk : sweep_traced(p, act[i]->k, kend[i]) ? kSweepTraced : kSweepFast;
+        group[i] = (p->precision * kBasisClasses + basis_class(p->precision, p->dims(p->precision))) * 3 + mode;
+    }
+    for (int g = 0; g < 2 * kBasisClasses * 3; ++g) {
         std::vector<int> idx;
         for (size_t i = 0; i < act.size(); ++i)
-            if (act[i]->p->precision == gkeys[g][0] && act[i]->p->tpl == gkeys[g][1]) idx.push_back((int)i);
+            if (group[i] == g) idx.push_back((int)i);
         if (idx.empty()) continue;
         std::stable_sort(idx.begin(), idx.end(), [&](int x, int y) {
             const double cx = (double)act[x]->p->n_omega * (kend[x] - act[x]->k);
             const double cy = (double)act[y]->p->n_omega * (kend[y] - act[y]->k);
             return cx > cy;
         });
+        Launch L{};
+        L.mode = g % 3;
+        L.cls = (g / 3) % kBasisClasses;
+        L.kind = g / (3 * kBasisClasses);
+        const bool walk = L.mode == kSweepWalk, split = L.mode == kSweepFast && L.cls != 0;
+        L.threads = split ? 2 * kSweepThreads : kSweepThreads;
         std::vector<SweepArgs> sa;
         std::vector<int> first;
-        int blocks = 0;
-        size_t shm = 0;  // the largest any job of the launch takes (a job's LDS layout depends on its bins)
-        bool trace = false;
         for (int i : idx) {
             const sail_problem *p = act[i]->p;
-            trace = trace || (p->tk1 > p->tk0 && act[i]->k < p->tk1 && kend[i] > p->tk0);
             const sail_schedule &sc = act[i]->sc;
-            sa.push_back(make_sweep_args(act[i]->p, act[i]->k, kend[i], SweepParams{sc.eps0, sc.amp_p, sc.amp_avg, sc.amp_m, sc.walk_len}));
-            first.push_back(blocks);
-            blocks += sweep_blocks(act[i]->p);
-            shm = std::max(shm, sweep_shmem(act[i]->p->n_omega));
+            const SweepPlan s = plan_sweep(p, split, walk && L.cls != 0 ? 8 : 4, L.threads, split ? kLdsBytes : kLdsBytes / 2, walk, false);
+            sa.push_back(make_sweep_args(p, act[i]->k, kend[i],
+                                         SweepParams{sc.eps0, sc.amp_p, sc.amp_avg, sc.amp_m, sc.walk_len}, s.columns_lds));
+            first.push_back(L.blocks);
+            L.blocks += sweep_blocks(p, s);
+            L.shm = std::max(L.shm, s.shm);
         }
-        first.push_back(blocks);
-        const SweepArgs *dargs = sg.put(sa.data(), sa.size());
-        const int *dfirst = sg.put(first.data(), first.size());
-        sweeps.push_back({g, blocks, (int)idx.size(), dargs, dfirst, shm, trace});
+        first.push_back(L.blocks);
+        L.n = (int)idx.size();
+        L.args = sg.put(sa.data(), sa.size());
+        L.first = sg.put(first.data(), first.size());
+        sweeps.push_back(L);
     }
     // resyncs (renormalising) and imprint + target resyncs, by precision and
     // by the LDS their spectra need (one launch per class, so small problems
@@ -3226,7 +3803,7 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
             const ResyncArgs *dargs = sg.put(ra.data(), ra.size());
             const int *dfirst = sg.put(first.data(), first.size());
             (pass == 0 ? resyncs : pass == 1 ? targets : smooths)
-                .push_back({prec, blocks, (int)ra.size(), dargs, dfirst, resync_shmem(max_no), false});
+                .push_back({prec, blocks, (int)ra.size(), dargs, dfirst, resync_shmem(max_no)});
         }
     }
     const BranchArgs *dbranch = ba.empty() ? nullptr : sg.put(ba.data(), ba.size());
@@ -3259,15 +3836,7 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
     for (const Launch &L : sweeps) {
         hipEvent_t e1;
         if ((st = timer.begin(stream, &e1))) return st;
-        const SweepArgs *a = (const SweepArgs *)L.args;
-        switch (L.kind) {
-            case 0: launch_sweep_batched<double, 4>(a, L.first, L.n, L.blocks, L.shm, L.trace, stream); break;
-            case 1: launch_sweep_batched<double, 8>(a, L.first, L.n, L.blocks, L.shm, L.trace, stream); break;
-            case 2: launch_sweep_batched<double, 16>(a, L.first, L.n, L.blocks, L.shm, L.trace, stream); break;
-            case 3: launch_sweep_batched<float, 8>(a, L.first, L.n, L.blocks, L.shm, L.trace, stream); break;
-            case 4: launch_sweep_batched<float, 16>(a, L.first, L.n, L.blocks, L.shm, L.trace, stream); break;
-            default: launch_sweep_batched<float, 32>(a, L.first, L.n, L.blocks, L.shm, L.trace, stream); break;
-        }
+        launch_sweep_batched(L, (const SweepArgs *)L.args, stream);
         SAIL_HIP(hipGetLastError());
         if (e1) SAIL_HIP(hipEventRecord(e1, stream));
     }
@@ -3605,6 +4174,29 @@ void serve(sail_server *S)
 
 }  // namespace
 
+namespace {
+
+// phi_d = sum_i sqrt(wh_i) q_id Phi_i of every walker, in the layout of d_phi.
+template <typename R>
+std::vector<R> phi_from_rows(const sail_problem *p, const char *rows)
+{
+    const int Nt = p->n_tau, ec = p->echunk, ck = p->chunk(p->precision);
+    std::vector<R> out((size_t)p->n_walkers * 4 * ck, (R)0);
+    std::vector<R> row(p->ntau_pad);
+    std::vector<double> acc(4 * ec);
+    for (int l = 0; l < p->n_walkers; ++l) {
+        std::memcpy(row.data(), rows + sizeof(R) * (size_t)l * p->ntau_pad, sizeof(R) * p->ntau_pad);
+        std::fill(acc.begin(), acc.end(), 0.0);
+        for (int i = 0; i < Nt; ++i)
+            for (int d = 0; d < 4 * ec; ++d) acc[d] += p->h_proj[(size_t)i * 4 * ec + d] * (double)row[i];
+        for (int q = 0; q < 4; ++q)
+            for (int t = 0; t < std::min(ec, ck); ++t) out[((size_t)l * 4 + q) * ck + t] = (R)acc[q * ec + t];
+    }
+    return out;
+}
+
+}  // namespace
+
 struct sail_batch {
     int device = 0;
     std::vector<sail_problem *> probs;
@@ -3667,10 +4259,9 @@ size_t sail_footprint_bytes(int n_omega, int n_tau, int n_walkers, int precision
 {
     if (n_omega <= 0 || n_tau <= 0 || n_walkers < 0) return 0;
     const size_t rsz = precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
-    size_t ntp, lanes;
-    max_padding(n_tau, precision, &ntp, &lanes);
     const size_t No = (size_t)n_omega, Nw = (size_t)n_walkers;
-    const size_t walkers = sizeof(double) * Nw * (No + 4) + rsz * Nw * ntp + sizeof(int32_t) * (3 * Nw + 4) +
+    // a basis too large for kPhiRow coordinates per walker goes without the read-out's rows
+    const size_t walkers = sizeof(double) * Nw * (No + 4) + rsz * Nw * (max_padding(n_tau, precision) + kPhiRow) + sizeof(int32_t) * (3 * Nw + 4) +
                            sizeof(double) * (No + std::max<size_t>(No, 64) + No * (size_t)mean_spans(n_walkers)) + 64 * (4 * sizeof(double) + 2 * sizeof(int32_t)) +
                            sizeof(BranchTree);
     return table_bytes(n_omega, n_tau, precision) + walkers;
@@ -3735,16 +4326,17 @@ sail_status sail_problem_create(const double *omega, int n_omega, const double *
     if (kernel_mode == SAIL_K_BIN_EXACT)
         for (int i = 0; i < n_tau; ++i)
             if (tau[i] > 0.0) p->cfac[i] = (std::exp(0.5 * dw * tau[i]) - std::exp(-0.5 * dw * tau[i])) / (kTwoPi * tau[i]);
-    std::vector<double> h_z(n_omega);
-    for (int j = 0; j < n_omega; ++j) h_z[j] = std::exp(-omega[j] * dt);
-    if ((st = dalloc(&p->d_omega, n_omega)) || (st = dalloc(&p->d_z, n_omega))) {
+    if ((st = dalloc(&p->d_omega, n_omega))) {
         delete p;
         return st;
     }
-    if (hipMemcpy(p->d_omega, p->omega.data(), sizeof(double) * n_omega, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(p->d_z, h_z.data(), sizeof(double) * n_omega, hipMemcpyHostToDevice) != hipSuccess) {
+    if (hipMemcpy(p->d_omega, p->omega.data(), sizeof(double) * n_omega, hipMemcpyHostToDevice) != hipSuccess) {
         delete p;
         return fail(SAIL_EDEVICE, "table upload failed");
+    }
+    if ((st = build_tables(p))) {
+        delete p;
+        return st;
     }
     if ((st = build_layout(p, SAIL_FP64))) {
         delete p;
@@ -3815,11 +4407,11 @@ sail_status autotune_layout(sail_problem_t p, int n_walkers, int precision, int 
         if ((st = sail_walkers_init(p, n_walkers, 1, precision, stream_))) break;
         if (p->tpl != c) continue;  // the layout could not take this tile
         if ((st = prepare_schedule(p, &sc, 8, stream))) break;
-        if ((st = launch_sweep_any(p, 0, 1, sp, stream))) break;  // warm-up
+        if ((st = launch_sweep(p, 0, 1, sp, stream))) break;  // warm-up
         float ms = 1e30f;
         for (int rep = 0; rep < 3 && st == SAIL_OK; ++rep) {
             hipError_t e = hipEventRecord(e0, stream);
-            if (e == hipSuccess) st = launch_sweep_any(p, 1 + 2 * rep, 3 + 2 * rep, sp, stream);
+            if (e == hipSuccess) st = launch_sweep(p, 1 + 2 * rep, 3 + 2 * rep, sp, stream);
             if (e == hipSuccess && st == SAIL_OK) e = hipEventRecord(e1, stream);
             if (e == hipSuccess && st == SAIL_OK) e = hipEventSynchronize(e1);
             float x = 0.f;
@@ -3879,9 +4471,17 @@ sail_status sail_walkers_init(sail_problem_t p, int n_walkers, uint64_t seed, in
     if ((st = build_layout(p, precision))) return st;
     const int No = p->n_omega, ntp = p->ntau_pad;
     const size_t rsz = precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
-    char *phi = nullptr;
-    if ((st = dalloc(&phi, rsz * (size_t)n_walkers * ntp))) return st;
-    p->d_Phi = phi;
+    const size_t phi_bytes = rsz * (size_t)n_walkers * 4 * p->chunk(precision);
+    char *phi = nullptr, *Phi = nullptr;
+    if ((st = dalloc(&phi, phi_bytes))) return st;
+    p->d_phi = phi;
+    if (4 * p->chunk(precision) <= kPhiRow) {
+        if ((st = dalloc(&Phi, rsz * (size_t)n_walkers * ntp))) {
+            p->free_walkers();
+            return st;
+        }
+        p->d_Phi = Phi;
+    }
     if ((st = dalloc(&p->d_b, (size_t)n_walkers * No)) || (st = dalloc(&p->d_gsc, n_walkers)) || (st = dalloc(&p->d_ginv, n_walkers)) ||
         (st = dalloc(&p->d_chi2, n_walkers)) || (st = dalloc(&p->d_rate, n_walkers)) || (st = dalloc(&p->d_a0, No)) ||
         (st = dalloc(&p->d_tmp, std::max(No, 64))) || (st = dalloc(&p->d_teff, 1)) ||
@@ -3898,7 +4498,7 @@ sail_status sail_walkers_init(sail_problem_t p, int n_walkers, uint64_t seed, in
         return st;
     }
     SAIL_HIP(hipMemcpyAsync(p->d_a0, a0.data(), sizeof(double) * No, hipMemcpyHostToDevice, stream));
-    SAIL_HIP(hipMemsetAsync(p->d_Phi, 0, rsz * (size_t)n_walkers * ntp, stream));
+    SAIL_HIP(hipMemsetAsync(p->d_phi, 0, phi_bytes, stream));  // the padding of the chunks
     const size_t total = (size_t)n_walkers * No;
     hipLaunchKernelGGL(k_init_walkers, dim3((unsigned)((total + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream,
                        n_walkers, No, (const double *)p->d_a0, p->d_b, p->d_gsc, p->d_ginv, p->d_rate);
@@ -3981,9 +4581,9 @@ sail_status watch_copy(sail_problem *p, bool to_snapshot, hipStream_t stream)
 {
     const size_t n = (size_t)p->n_walkers;
     const size_t rsz = p->precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
-    const size_t phi_words = rsz * n * (size_t)p->ntau_pad / sizeof(double);
+    const size_t phi_words = rsz * n * (size_t)p->phi_row() / sizeof(double);
     struct { double *live, *snap; size_t words; } bufs[] = {
-        {p->d_b, p->sn_b, n * (size_t)p->n_omega}, {(double *)p->d_Phi, p->sn_Phi, phi_words},
+        {p->d_b, p->sn_b, n * (size_t)p->n_omega}, {(double *)p->d_phi, p->sn_phi, phi_words},
         {p->d_gsc, p->sn_gsc, n}, {p->d_ginv, p->sn_ginv, n}, {p->d_chi2, p->sn_chi2, n}, {p->d_rate, p->sn_rate, n}};
     for (auto &bf : bufs) {
         const unsigned grid = (unsigned)std::min<size_t>((bf.words + kThreads - 1) / kThreads, 2048);
@@ -4043,7 +4643,7 @@ sail_status run_schedule(sail_problem_t p, const sail_schedule *sc, int first_sw
             if (k < p->tk0 && kend > p->tk0) kend = p->tk0;
             else if (k < p->tk1 && kend > p->tk1) kend = p->tk1;
         }
-        if ((st = launch_sweep_any(p, k, kend, sp, stream))) return st;
+        if ((st = launch_sweep(p, k, kend, sp, stream))) return st;
         if (kend % sc->resync_every == 0)
             if ((st = launch_resync(p, 1, nullptr, nullptr, p->n_walkers, stream))) return st;
         if (kend % sc->branch_every == 0) {
@@ -4123,7 +4723,7 @@ sail_status sail_set_watchdog(sail_problem_t p, double drift_bound)
         const size_t rsz = p->precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
         sail_status st;
         if ((st = dalloc(&p->d_watch, 4)) || (st = dalloc(&p->sn_b, n * (size_t)p->n_omega)) ||
-            (st = dalloc(&p->sn_Phi, rsz * n * (size_t)p->ntau_pad / sizeof(double))) || (st = dalloc(&p->sn_gsc, n)) ||
+            (st = dalloc(&p->sn_phi, rsz * n * (size_t)p->phi_row() / sizeof(double))) || (st = dalloc(&p->sn_gsc, n)) ||
             (st = dalloc(&p->sn_ginv, n)) || (st = dalloc(&p->sn_chi2, n)) || (st = dalloc(&p->sn_rate, n))) {
             p->free_watch();
             return st;
@@ -4269,14 +4869,31 @@ sail_status sail_read_state(sail_problem_t p, double *a, double *F, double *rate
     if (a) SAIL_HIP(hipMemcpyAsync(a, p->d_b, sizeof(double) * (size_t)n * No, hipMemcpyDeviceToHost, stream));
     std::vector<double> phi;
     std::vector<float> phif;
+    struct Scratch {
+        void *p = nullptr;
+        ~Scratch() { dfree(p); }
+    } tmp;  // the rows where the walkers hold none
     if (F) {
-        phi.resize((size_t)n * ntp);
-        if (p->precision == SAIL_FP32) {
-            phif.resize((size_t)n * ntp);
-            SAIL_HIP(hipMemcpyAsync(phif.data(), p->d_Phi, sizeof(float) * (size_t)n * ntp, hipMemcpyDeviceToHost, stream));
-        } else {
-            SAIL_HIP(hipMemcpyAsync(phi.data(), p->d_Phi, sizeof(double) * (size_t)n * ntp, hipMemcpyDeviceToHost, stream));
+        const bool f32 = p->precision == SAIL_FP32;
+        const size_t rows = (size_t)n * ntp * (f32 ? sizeof(float) : sizeof(double));
+        void *dst = p->d_Phi;
+        if (!dst) {
+            char *q = nullptr;
+            const sail_status st = dalloc(&q, rows);
+            if (st) return st;
+            dst = tmp.p = q;
         }
+        if (f32) {
+            phif.resize((size_t)n * ntp);
+            hipLaunchKernelGGL(k_reconstruct<float>, dim3(n), dim3(kThreads), 0, stream, No, Nt, p->cols(), ntp,
+                               (const double *)p->d_E, (const double *)p->d_b, (const double *)p->d_gsc, (float *)dst);
+        } else {
+            hipLaunchKernelGGL(k_reconstruct<double>, dim3(n), dim3(kThreads), 0, stream, No, Nt, p->cols(), ntp,
+                               (const double *)p->d_E, (const double *)p->d_b, (const double *)p->d_gsc, (double *)dst);
+        }
+        SAIL_HIP(hipGetLastError());
+        phi.resize((size_t)n * ntp);
+        SAIL_HIP(hipMemcpyAsync(f32 ? (void *)phif.data() : (void *)phi.data(), dst, rows, hipMemcpyDeviceToHost, stream));
     }
     if (rate) SAIL_HIP(hipMemcpyAsync(rate, p->d_rate, sizeof(double) * n, hipMemcpyDeviceToHost, stream));
     SAIL_HIP(hipStreamSynchronize(stream));
@@ -4331,27 +4948,29 @@ sail_status sail_read_event_margins(sail_problem_t p, int n_events, double *gap,
     return SAIL_OK;
 }
 
-// Checkpoint layout: header, then b [N_w][N_omega], Phi [N_w][ntau_pad] in
-// the loop precision, g, 1/g, chi^2, rate [N_w], all little-endian as in memory.
+// Checkpoint layout: header, then b [N_w][N_omega], phi [N_w][phi_row] in the
+// loop precision, g, 1/g, chi^2, rate [N_w], all little-endian as in memory.
+// Version 3 held the reconstructions Phi [N_w][ntau_pad] in place of phi
+// (phi_row 0); the import takes them to the basis.
 struct StateHeader {
-    uint64_t magic;  // "SAILSTv3"
-    int32_t n_walkers, n_omega, n_tau, ntau_pad, precision, reserved;
+    uint64_t magic;  // "SAILSTv4"
+    int32_t n_walkers, n_omega, n_tau, ntau_pad, precision, phi_row;
     uint64_t seed;
     double chi2_unit;
 };
-constexpr uint64_t kStateMagic = 0x33767453494c4153ull;
+constexpr uint64_t kStateMagic = 0x34767453494c4153ull, kStateMagicV3 = 0x33767453494c4153ull;
 
-size_t state_bytes(const sail_problem *p)
+size_t state_bytes(const sail_problem *p, int row)
 {
     const size_t n = (size_t)p->n_walkers, rsz = p->precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
-    return sizeof(StateHeader) + sizeof(double) * n * p->n_omega + rsz * n * p->ntau_pad + 4 * sizeof(double) * n;
+    return sizeof(StateHeader) + sizeof(double) * n * p->n_omega + rsz * n * row + 4 * sizeof(double) * n;
 }
 
 sail_status sail_state_export(sail_problem_t p, void *buf, size_t *bytes, void *stream_)
 {
     if (!p || !bytes) return fail(SAIL_EINVAL, "NULL argument");
     if (p->n_walkers == 0) return fail(SAIL_ESTATE, "initialise walkers first");
-    const size_t need = state_bytes(p);
+    const size_t need = state_bytes(p, p->phi_row());
     if (!buf) {
         *bytes = need;
         return SAIL_OK;
@@ -4359,15 +4978,15 @@ sail_status sail_state_export(sail_problem_t p, void *buf, size_t *bytes, void *
     if (*bytes < need) return fail(SAIL_EINVAL, "buffer too small");
     hipStream_t stream = (hipStream_t)stream_;
     SAIL_HIP(hipSetDevice(p->device));
-    StateHeader h{kStateMagic, p->n_walkers, p->n_omega, p->n_tau, p->ntau_pad, p->precision, 0, p->seed, p->chi2_unit};
+    StateHeader h{kStateMagic, p->n_walkers, p->n_omega, p->n_tau, p->ntau_pad, p->precision, p->phi_row(), p->seed, p->chi2_unit};
     char *o = (char *)buf;
     std::memcpy(o, &h, sizeof h);
     o += sizeof h;
     const size_t n = (size_t)p->n_walkers, rsz = p->precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
-    const size_t sb = sizeof(double) * n * p->n_omega, sp = rsz * n * p->ntau_pad, sv = sizeof(double) * n;
+    const size_t sb = sizeof(double) * n * p->n_omega, sp = rsz * n * p->phi_row(), sv = sizeof(double) * n;
     SAIL_HIP(hipMemcpyAsync(o, p->d_b, sb, hipMemcpyDeviceToHost, stream));
     o += sb;
-    SAIL_HIP(hipMemcpyAsync(o, p->d_Phi, sp, hipMemcpyDeviceToHost, stream));
+    SAIL_HIP(hipMemcpyAsync(o, p->d_phi, sp, hipMemcpyDeviceToHost, stream));
     o += sp;
     SAIL_HIP(hipMemcpyAsync(o, p->d_gsc, sv, hipMemcpyDeviceToHost, stream));
     o += sv;
@@ -4388,20 +5007,32 @@ sail_status sail_state_import(sail_problem_t p, const void *buf, size_t bytes, v
     StateHeader h;
     if (bytes < sizeof h) return fail(SAIL_EINVAL, "checkpoint truncated");
     std::memcpy(&h, buf, sizeof h);
-    if (h.magic != kStateMagic) return fail(SAIL_EINVAL, "not a checkpoint");
+    if (h.magic != kStateMagic && h.magic != kStateMagicV3) return fail(SAIL_EINVAL, "not a checkpoint");
+    const bool v3 = h.magic == kStateMagicV3;
+    const int row = v3 ? p->ntau_pad : p->phi_row();
     if (h.n_walkers != p->n_walkers || h.n_omega != p->n_omega || h.n_tau != p->n_tau || h.ntau_pad != p->ntau_pad ||
-        h.precision != p->precision)
+        h.precision != p->precision || (!v3 && h.phi_row != row))
         return fail(SAIL_EINVAL, "checkpoint does not match this problem's shape, layout or precision");
-    if (bytes < state_bytes(p)) return fail(SAIL_EINVAL, "checkpoint truncated");
+    if (bytes < state_bytes(p, row)) return fail(SAIL_EINVAL, "checkpoint truncated");
     p->self_T_end = 0;
     hipStream_t stream = (hipStream_t)stream_;
     SAIL_HIP(hipSetDevice(p->device));
     const char *o = (const char *)buf + sizeof h;
     const size_t n = (size_t)p->n_walkers, rsz = p->precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
-    const size_t sb = sizeof(double) * n * p->n_omega, sp = rsz * n * p->ntau_pad, sv = sizeof(double) * n;
+    const size_t sb = sizeof(double) * n * p->n_omega, sp = rsz * n * row, sv = sizeof(double) * n;
     SAIL_HIP(hipMemcpyAsync(p->d_b, o, sb, hipMemcpyHostToDevice, stream));
     o += sb;
-    SAIL_HIP(hipMemcpyAsync(p->d_Phi, o, sp, hipMemcpyHostToDevice, stream));
+    std::vector<double> phi64;
+    std::vector<float> phi32;
+    if (!v3) {
+        SAIL_HIP(hipMemcpyAsync(p->d_phi, o, sp, hipMemcpyHostToDevice, stream));
+    } else if (p->precision == SAIL_FP32) {
+        phi32 = phi_from_rows<float>(p, o);
+        SAIL_HIP(hipMemcpyAsync(p->d_phi, phi32.data(), sizeof(float) * phi32.size(), hipMemcpyHostToDevice, stream));
+    } else {
+        phi64 = phi_from_rows<double>(p, o);
+        SAIL_HIP(hipMemcpyAsync(p->d_phi, phi64.data(), sizeof(double) * phi64.size(), hipMemcpyHostToDevice, stream));
+    }
     o += sp;
     SAIL_HIP(hipMemcpyAsync(p->d_gsc, o, sv, hipMemcpyHostToDevice, stream));
     o += sv;
