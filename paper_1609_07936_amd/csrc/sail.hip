@@ -1619,7 +1619,7 @@ __global__ void k_watch_copy(const unsigned int *w, double *dst, const double *s
 // sum m = N_w for P_r between the N_w-th and (N_w+1)-th smallest threshold
 // (taken at their midpoint).  Delta: the smallest value of a fixed doubling +
 // bisection search whose zero count reaches round(fraction N_w).
-// One workgroup; walker l = thread * kBranchWPT + q.
+// One workgroup; walker l = thread * WPT + q.
 // --------------------------------------------------------------------------
 struct BranchArgs {
     int n;
@@ -1647,17 +1647,36 @@ __device__ __forceinline__ int branch_m(double xi, double w, double y, int n)
     return (int)v;
 }
 
-// Walker l = threadIdx.x * kBranchWPT + q.  The weights w_l of the current
-// Delta live in LDS (padded rows against bank conflicts), the branching
-// words xi in registers, the residues in global memory.
-constexpr int kBranchRow = kBranchWPT + 1;
+// Shapes of a branching workgroup, by the number of walkers.  An evaluation is
+// a chain of counts, each a handful of instructions per walker and a
+// reduction over the workgroup, so a small population takes few wavefronts
+// (their barrier is what a count waits for; one wavefront needs none) and few
+// walkers per thread (64 walkers, one event: 1250 us with 1024 threads of 16,
+// 261 us with one wavefront; the parallel search's evaluations: 38 to 17 us at
+// 1024 walkers, 43 to 29 us at 3001; a batch of 64 mixed events: 1290 to 769 us).  The shape follows from
+// the population alone, so an event has the same bits however it is run.
+struct BranchShape {
+    int wpt, threads;
+};
+constexpr BranchShape kBranchShapes[] = {{1, 64}, {1, 256}, {4, 256}, {4, 1024}, {kBranchWPT, kBranchThreads}};
+constexpr int kBranchShapeCount = 5;
+__host__ __device__ constexpr int branch_shape(int n)
+{
+    int i = 0;
+    while (i < kBranchShapeCount - 1 && n > kBranchShapes[i].wpt * kBranchShapes[i].threads) ++i;
+    return i;
+}
 
+// Walker l = threadIdx.x * WPT + q.  The weights w_l of the current
+// Delta live in LDS (padded rows against bank conflicts), the branching
+// words xi in registers, the residues too unless a thread has many walkers.
+template <int WPT, int THREADS>
 struct BranchShared {
-    double dred[2][kBranchThreads / 64];
-    int ired[2][kBranchThreads / 64];
-    int scan[kBranchThreads];
-    int scan2[kBranchThreads];
-    double sw[kBranchThreads * kBranchRow];
+    double dred[2][THREADS / 64];
+    int ired[2][THREADS / 64];
+    int scan[THREADS];
+    int scan2[THREADS];
+    double sw[THREADS * (WPT + 1)];
 };
 
 // Reduction over the branching workgroup with one barrier: each wavefront
@@ -1665,17 +1684,18 @@ struct BranchShared {
 // the partials.  Consecutive reductions alternate between two slot sets (par),
 // so a reduction never overwrites partials that the previous one may still be
 // reading; min, max and integer sums are exact in any order.
-template <typename T, typename Op>
-__device__ __forceinline__ T branch_reduce(T v, T (*slots)[kBranchThreads / 64], int &par, Op op)
+template <int WAVES, typename T, typename Op>
+__device__ __forceinline__ T branch_reduce(T v, T (*slots)[WAVES], int &par, Op op)
 {
     v = wave_reduce(v, op);
+    if constexpr (WAVES == 1) return v;
     T *sl = slots[par];
     par ^= 1;
     if ((threadIdx.x & 63) == 0) sl[threadIdx.x >> 6] = v;
     __syncthreads();
     T r = sl[0];
 #pragma unroll
-    for (int w = 1; w < kBranchThreads / 64; ++w) r = op(r, sl[w]);
+    for (int w = 1; w < WAVES; ++w) r = op(r, sl[w]);
     return r;
 }
 
@@ -1719,10 +1739,15 @@ __device__ __forceinline__ double tree_node_delta(double lo, double hi, int node
     return sqrt(lo * hi);
 }
 
-template <int MODE>
-__device__ __forceinline__ void branch_block(const BranchArgs &a, BranchShared &sm, BranchTree *tree = nullptr,
+// The workgroup's first THREADS threads solve the event (a launch for several
+// shapes has more: their wavefronts leave at once).
+template <int MODE, int WPT, int THREADS>
+__device__ __forceinline__ void branch_block(const BranchArgs &a, BranchShared<WPT, THREADS> &sm, BranchTree *tree = nullptr,
                                              int round = 0)
 {
+    constexpr int ROW = WPT + 1;
+    constexpr bool KEEP = WPT <= 4;  // residues in registers
+    if ((int)threadIdx.x >= THREADS) return;
     auto dred = sm.dred;
     auto ired = sm.ired;
     int par = 0;
@@ -1730,18 +1755,27 @@ __device__ __forceinline__ void branch_block(const BranchArgs &a, BranchShared &
     int *scan2 = sm.scan2;
     double *sw = sm.sw;
     const int n = a.n;
-    const int l0 = threadIdx.x * kBranchWPT;
-    const int nown = max(0, min(kBranchWPT, n - l0));
-    double *myw = sw + threadIdx.x * kBranchRow;
-    uint32_t xw[kBranchWPT];
-    int m[kBranchWPT];
-    auto chi2_of = [&](int q) -> double {
+    const int l0 = threadIdx.x * WPT;
+    const int nown = max(0, min(WPT, n - l0));
+    double *myw = sw + threadIdx.x * ROW;
+    uint32_t xw[WPT];
+    int m[WPT];
+    double kept[KEEP ? WPT : 1];
+    auto read_chi2 = [&](int q) -> double {
         const double v = a.chi2[min(l0 + q, n - 1)];
         return (v == v) ? v : INFINITY;
     };
+    if constexpr (KEEP) {
+#pragma unroll
+        for (int q = 0; q < WPT; ++q) kept[q] = read_chi2(q);
+    }
+    auto chi2_of = [&](int q) -> double {
+        if constexpr (KEEP) return kept[q];
+        else return read_chi2(q);
+    };
     double cmin = INFINITY, cmax = -INFINITY;
 #pragma unroll
-    for (int q = 0; q < kBranchWPT; ++q) {
+    for (int q = 0; q < WPT; ++q) {
         uint32_t x0, x1, x2, x3;
         philox10((uint32_t)min(l0 + q, n - 1), a.event, 0u, kStreamBranch, a.key0, a.key1, x0, x1, x2, x3);
         xw[q] = x0;
@@ -1765,9 +1799,10 @@ __device__ __forceinline__ void branch_block(const BranchArgs &a, BranchShared &
     // search then starts from [guess / 2, 2 guess] inside the full range.
     auto eval = [&](double delta, double guess, double *yout, int *found) __attribute__((always_inline)) -> int {
         double lo = INFINITY, hi = 0.0;
-        for (int q = 0; q < kBranchWPT; ++q) myw[q] = (q < nown) ? exp(-(chi2_of(q) - cmin) * delta) : 0.0;
+#pragma unroll KEEP ? WPT : 1
+        for (int q = 0; q < WPT; ++q) myw[q] = (q < nown) ? exp(-(chi2_of(q) - cmin) * delta) : 0.0;
 #pragma unroll
-        for (int q = 0; q < kBranchWPT; ++q) {
+        for (int q = 0; q < WPT; ++q) {
             const double w = myw[q];
             if (q < nown && w > 0.0) {
                 // walker q reaches m = 1 at y = (1 - xi) / w
@@ -1793,7 +1828,7 @@ __device__ __forceinline__ void branch_block(const BranchArgs &a, BranchShared &
         for (;;) {
             int cnt = 0, zz = 0;
 #pragma unroll
-            for (int q = 0; q < kBranchWPT; ++q) {
+            for (int q = 0; q < WPT; ++q) {
                 const int mq = (q < nown) ? branch_m(XI(q), myw[q], y, n) : 1;
                 cnt += (q < nown) ? mq : 0;
                 zz += (mq == 0);
@@ -2005,12 +2040,12 @@ __device__ __forceinline__ void branch_block(const BranchArgs &a, BranchShared &
         if (ok) {
             delta = hi;
 #pragma unroll
-            for (int q = 0; q < kBranchWPT; ++q) m[q] = (q < nown) ? branch_m(XI(q), myw[q], Y, n) : 0;
+            for (int q = 0; q < WPT; ++q) m[q] = (q < nown) ? branch_m(XI(q), myw[q], Y, n) : 0;
             // P_r: midpoint of the n-th and (n+1)-th smallest thresholds,
             // max_l theta_{l, m_l} and min_l theta_{l, m_l + 1}
             double thn = -INFINITY, thn1 = INFINITY;
 #pragma unroll
-            for (int q = 0; q < kBranchWPT; ++q) {
+            for (int q = 0; q < WPT; ++q) {
                 if (q < nown) {
                     const double c = chi2_of(q);
                     if (m[q] >= 1) thn = fmax(thn, c + log((double)m[q] - XI(q)) / delta);
@@ -2034,14 +2069,14 @@ __device__ __forceinline__ void branch_block(const BranchArgs &a, BranchShared &
         }
         if (status != 0) {
 #pragma unroll
-            for (int q = 0; q < kBranchWPT; ++q) m[q] = 1;
+            for (int q = 0; q < WPT; ++q) m[q] = 1;
         }
     }
     // pairing: zero-multiplier walkers in ascending order against donors in
     // ascending order, donor l repeated m_l - 1 times
     int nz = 0, nd = 0;
 #pragma unroll
-    for (int q = 0; q < kBranchWPT; ++q) {
+    for (int q = 0; q < WPT; ++q) {
         if (q < nown) {
             nz += (m[q] == 0);
             nd += max(m[q] - 1, 0);
@@ -2050,7 +2085,7 @@ __device__ __forceinline__ void branch_block(const BranchArgs &a, BranchShared &
     scan[threadIdx.x] = nz;
     scan2[threadIdx.x] = nd;
     __syncthreads();
-    for (int off = 1; off < kBranchThreads; off <<= 1) {
+    for (int off = 1; off < THREADS; off <<= 1) {
         const int v1 = (int)threadIdx.x >= off ? scan[threadIdx.x - off] : 0;
         const int v2 = (int)threadIdx.x >= off ? scan2[threadIdx.x - off] : 0;
         __syncthreads();
@@ -2059,10 +2094,10 @@ __device__ __forceinline__ void branch_block(const BranchArgs &a, BranchShared &
         __syncthreads();
     }
     int zpos = scan[threadIdx.x] - nz, dpos = scan2[threadIdx.x] - nd;
-    const int total_z = scan[kBranchThreads - 1], total_d = scan2[kBranchThreads - 1];
+    const int total_z = scan[THREADS - 1], total_d = scan2[THREADS - 1];
     const bool consistent = total_z == total_d;
 #pragma unroll
-    for (int q = 0; q < kBranchWPT; ++q) {
+    for (int q = 0; q < WPT; ++q) {
         if (q >= nown) continue;
         const int l = l0 + q;
         const int mq = consistent ? m[q] : 1;
@@ -2084,28 +2119,42 @@ __device__ __forceinline__ void branch_block(const BranchArgs &a, BranchShared &
 #undef XI
 }
 
-__global__ __launch_bounds__(kBranchThreads) void k_branch_solve(BranchArgs a)
+template <int SHAPE>
+__global__ __launch_bounds__(kBranchShapes[SHAPE].threads) void k_branch_solve(BranchArgs a)
 {
-    __shared__ BranchShared sm;
-    branch_block<kBranchSearch>(a, sm);
+    constexpr BranchShape S = kBranchShapes[SHAPE];
+    __shared__ BranchShared<S.wpt, S.threads> sm;
+    branch_block<kBranchSearch, S.wpt, S.threads>(a, sm);
 }
 
 // many problems: workgroup b solves the branching event of problem b
 __global__ __launch_bounds__(kBranchThreads) void k_branch_batched(const BranchArgs *__restrict__ jobs)
 {
-    __shared__ BranchShared sm;
+    __shared__ BranchShared<kBranchWPT, kBranchThreads> sm;  // the largest shape's
     const BranchArgs a = jobs[blockIdx.x];
-    branch_block<kBranchSearch>(a, sm);
+    auto solve = [&](auto shape) __attribute__((always_inline)) {
+        constexpr BranchShape S = kBranchShapes[decltype(shape)::value];
+        branch_block<kBranchSearch, S.wpt, S.threads>(a, reinterpret_cast<BranchShared<S.wpt, S.threads> &>(sm));
+    };
+    switch (branch_shape(a.n)) {
+        case 0: solve(std::integral_constant<int, 0>{}); break;
+        case 1: solve(std::integral_constant<int, 1>{}); break;
+        case 2: solve(std::integral_constant<int, 2>{}); break;
+        case 3: solve(std::integral_constant<int, 3>{}); break;
+        default: solve(std::integral_constant<int, 4>{});
+    }
 }
 
 // One round of the parallel Delta search: workgroup b evaluates the zero
 // count at the round's b-th Delta.
-__global__ __launch_bounds__(kBranchThreads) void k_branch_tree(BranchArgs a, BranchTree *t, int round)
+template <int SHAPE>
+__global__ __launch_bounds__(kBranchShapes[SHAPE].threads) void k_branch_tree(BranchArgs a, BranchTree *t, int round)
 {
     if (round == kRoundFar && (t->degenerate || t->dir == 0)) return;
     if (round >= kRoundBisect && (t->degenerate || !t->ok)) return;
-    __shared__ BranchShared sm;
-    branch_block<kBranchTreeEval>(a, sm, t, round);
+    constexpr BranchShape S = kBranchShapes[SHAPE];
+    __shared__ BranchShared<S.wpt, S.threads> sm;
+    branch_block<kBranchTreeEval, S.wpt, S.threads>(a, sm, t, round);
 }
 
 // The search's decisions over one round's results (one thread).
@@ -2194,10 +2243,12 @@ __global__ void k_branch_walk(BranchTree *t, int round, int levels)
 
 // The event itself at the tree's final Delta: multipliers, P_r, margins,
 // pairing and the event log, as the one-workgroup kernel ends.
-__global__ __launch_bounds__(kBranchThreads) void k_branch_final(BranchArgs a, BranchTree *t)
+template <int SHAPE>
+__global__ __launch_bounds__(kBranchShapes[SHAPE].threads) void k_branch_final(BranchArgs a, BranchTree *t)
 {
-    __shared__ BranchShared sm;
-    branch_block<kBranchTreeFinal>(a, sm, t);
+    constexpr BranchShape S = kBranchShapes[SHAPE];
+    __shared__ BranchShared<S.wpt, S.threads> sm;
+    branch_block<kBranchTreeFinal, S.wpt, S.threads>(a, sm, t);
 }
 
 // --------------------------------------------------------------------------
@@ -2852,25 +2903,38 @@ sail_status launch_resync(sail_problem *p, int renorm, const int32_t *list, cons
 // One branching event of a single problem: the parallel search for large
 // populations (a few rounds over many workgroups), the one-workgroup kernel
 // for small ones.
-sail_status launch_branch(sail_problem *p, const BranchArgs &ba, hipStream_t stream)
+template <int SHAPE>
+void launch_branch_tree(const BranchArgs &ba, BranchTree *t, hipStream_t stream)
 {
-    if (p->n_walkers < kTreeMinWalkers) {
-        hipLaunchKernelGGL(k_branch_solve, dim3(1), dim3(kBranchThreads), 0, stream, ba);
-        SAIL_HIP(hipGetLastError());
-        return SAIL_OK;
-    }
-    BranchTree *t = p->d_tree;
-    hipLaunchKernelGGL(k_branch_tree, dim3(2 * kTreeNear + 1), dim3(kBranchThreads), 0, stream, ba, t, (int)kRoundNear);
+    constexpr int T = kBranchShapes[SHAPE].threads;
+    hipLaunchKernelGGL(k_branch_tree<SHAPE>, dim3(2 * kTreeNear + 1), dim3(T), 0, stream, ba, t, (int)kRoundNear);
     hipLaunchKernelGGL(k_branch_walk, dim3(1), dim3(1), 0, stream, t, (int)kRoundNear, 0);
-    hipLaunchKernelGGL(k_branch_tree, dim3(kTreeFar - kTreeNear), dim3(kBranchThreads), 0, stream, ba, t, (int)kRoundFar);
+    hipLaunchKernelGGL(k_branch_tree<SHAPE>, dim3(kTreeFar - kTreeNear), dim3(T), 0, stream, ba, t, (int)kRoundFar);
     hipLaunchKernelGGL(k_branch_walk, dim3(1), dim3(1), 0, stream, t, (int)kRoundFar, 0);
     for (int r = 0, done = 0; done < kBisections; ++r) {
         const int lv = std::min(kTreeLevels, kBisections - done);
-        hipLaunchKernelGGL(k_branch_tree, dim3((1 << lv) - 1), dim3(kBranchThreads), 0, stream, ba, t, kRoundBisect + r);
+        hipLaunchKernelGGL(k_branch_tree<SHAPE>, dim3((1 << lv) - 1), dim3(T), 0, stream, ba, t, kRoundBisect + r);
         hipLaunchKernelGGL(k_branch_walk, dim3(1), dim3(1), 0, stream, t, kRoundBisect + r, lv);
         done += lv;
     }
-    hipLaunchKernelGGL(k_branch_final, dim3(1), dim3(kBranchThreads), 0, stream, ba, t);
+    hipLaunchKernelGGL(k_branch_final<SHAPE>, dim3(1), dim3(T), 0, stream, ba, t);
+}
+
+sail_status launch_branch(sail_problem *p, const BranchArgs &ba, hipStream_t stream)
+{
+    const int shape = branch_shape(p->n_walkers);
+    static_assert(kTreeMinWalkers > kBranchShapes[0].threads && kTreeMinWalkers <= kBranchShapes[1].threads, "shapes of either search");
+    if (p->n_walkers < kTreeMinWalkers) {
+        if (shape == 0) hipLaunchKernelGGL(k_branch_solve<0>, dim3(1), dim3(kBranchShapes[0].threads), 0, stream, ba);
+        else hipLaunchKernelGGL(k_branch_solve<1>, dim3(1), dim3(kBranchShapes[1].threads), 0, stream, ba);
+    } else {
+        switch (shape) {
+            case 1: launch_branch_tree<1>(ba, p->d_tree, stream); break;
+            case 2: launch_branch_tree<2>(ba, p->d_tree, stream); break;
+            case 3: launch_branch_tree<3>(ba, p->d_tree, stream); break;
+            default: launch_branch_tree<4>(ba, p->d_tree, stream);
+        }
+    }
     SAIL_HIP(hipGetLastError());
     return SAIL_OK;
 }
