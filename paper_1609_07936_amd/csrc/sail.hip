@@ -153,6 +153,7 @@ struct SweepArgs {
     int amp_m;
     int chunk;            // basis dimensions per chunk as stored (a multiple of 16 bytes)
     int columns_lds;      // 1: the workgroup copies the columns to LDS
+    int pairs;            // split sweeps: chain and stager wavefronts at work in a workgroup (any others leave)
     const void *col;      // [N_omega][4][chunk] columns in the basis, loop precision
     void *phi;            // [N_w][4][chunk] walkers in the basis, loop precision
     // the parts of the residue change that do not depend on the walker (FP64):
@@ -354,7 +355,8 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
     constexpr int RSTR = SPLIT ? kSplitStride : rec_stride(G, WALK);
     static_assert(M > 0 || !LDSC, "the general variant reads its columns from memory");
     static_assert(!SPLIT || (G == 4 && !LDSB && MODE == kSweepFast), "split sweeps: four lanes, spectra in memory");
-    const int nthr = blockDim.x;
+    const int nthr = SPLIT ? 128 * a.pairs : (int)blockDim.x;
+    if (SPLIT && (int)threadIdx.x >= nthr) return;
     const int lane = threadIdx.x & 63;
     const int c = lane & (G - 1), ch = lane & 3;
     // walkers of the workgroup, and this lane's among them
@@ -2980,13 +2982,14 @@ int sweep_wg_sync()
     return v;
 }
 
-SweepArgs make_sweep_args(const sail_problem *p, int k0, int k1, const SweepParams &sp, int columns_lds)
+SweepArgs make_sweep_args(const sail_problem *p, int k0, int k1, const SweepParams &sp, int columns_lds, int pairs)
 {
     SweepArgs s;
     s.n_walkers = p->n_walkers;
     s.n_omega = p->n_omega;
     s.chunk = p->chunk(p->precision);
     s.columns_lds = columns_lds;
+    s.pairs = pairs;
     s.k0 = k0;
     s.k1 = k1;
     s.key0 = (uint32_t)p->seed;
@@ -3136,7 +3139,7 @@ sail_status launch_sweep(sail_problem *p, int k0, int k1, const SweepParams &sp,
 {
     const int mode = sp.walk_len > 0 ? kSweepWalk : sweep_traced(p, k0, k1) ? kSweepTraced : kSweepFast;
     const SweepPlan s = plan_alone(p, mode);
-    const SweepArgs a = make_sweep_args(p, k0, k1, sp, s.columns_lds);
+    const SweepArgs a = make_sweep_args(p, k0, k1, sp, s.columns_lds, s.threads / 128);
     const int blocks = sweep_blocks(p, s);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (p->timing) {
@@ -3165,22 +3168,25 @@ sail_status launch_sweep(sail_problem *p, int k0, int k1, const SweepParams &sp,
 //
 // Basis: a greedy (pivoted, twice orthogonalised Gram-Schmidt) selection of
 // columns sqrt(wh_i) e^{-omega_j tau_i}, each taken relative to its own norm,
-// until what it leaves of any column is below kBasisTol64.  The sweep drops
+// then rotated to the principal directions of the selection's sample (one-sided
+// Jacobi), of which the first are kept, as many as leave less than kBasisTol64
+// of any column, filled up to the whole chunks they are stored in.  The sweep drops
 // the product of two such residuals, so the scalar products of the FP64 loop
 // are good to kBasisTol64^2 = 1e-14 of the norms at worst, and to their own
-// rounding in practice (measured over the benchmark's grids with annealed
-// spectra: 3e-17 of the condition scale rms with 16 dimensions, against 3e-16
-// of the two-term recurrence along tau that generated the columns before).  The
-// FP32 loop takes the first vectors, up to kBasisTol32 (squared 1e-8, below
-// its rounding).  The greedy choice runs on at most kBasisSample columns spread
-// over the grid and on any column found outside its span afterwards.
-constexpr double kBasisTol64 = 1e-7, kBasisTol32 = 1e-4;
+// rounding in practice (over the benchmark's and the batch's grids, in units of
+// the condition scale and on spectra of two bins, which resolve the columns
+// best: 2e-17 to 9e-17 rms, at most 2e-15, against 1e-16 to 4e-16 and 4e-15 of the
+// recurrence along tau that generated the columns before).  The FP32 loop takes
+// the first vectors, up to kBasisTol32 (squared 1e-8, below its rounding).  The
+// selection runs on at most kBasisSample columns spread over the grid and on
+// any column found outside their span.
+constexpr double kBasisTol64 = 1e-7, kBasisTol32 = 1e-4, kBasisGreedy = 1e-8;
 constexpr int kBasisSample = 64;
 
 struct Basis {
     std::vector<double> q;  // [dims][n_tau], orthonormal
     std::vector<double> c;  // [n_omega][dims], columns in the basis
-    int dims = 0, dims32 = 0;
+    int dims = 0, dims64 = 0, dims32 = 0;  // vectors held; vectors each precision needs
 };
 
 double dot(const double *x, const double *y, int n)
@@ -3191,6 +3197,52 @@ double dot(const double *x, const double *y, int n)
         for (int t = 0; t < 8; ++t) s[t] += x[i + t] * y[i + t];
     for (; i < n; ++i) s[0] += x[i] * y[i];
     return ((s[0] + s[4]) + (s[2] + s[6])) + ((s[1] + s[5]) + (s[3] + s[7]));
+}
+
+// Rotates the rows of b (n rows of m) to mutually orthogonal ones, largest
+// first, by one-sided Jacobi; r (n x n) receives the rotation.
+void principal_rows(std::vector<std::vector<double>> &b, std::vector<std::vector<double>> &r)
+{
+    const int n = (int)b.size(), m = n ? (int)b[0].size() : 0;
+    r.assign(n, std::vector<double>(n, 0.0));
+    for (int i = 0; i < n; ++i) r[i][i] = 1.0;
+    for (int sweep = 0; sweep < 12; ++sweep) {
+        bool moved = false;
+        for (int i = 0; i < n; ++i)
+            for (int j = i + 1; j < n; ++j) {
+                const double a = dot(b[i].data(), b[i].data(), m), d = dot(b[j].data(), b[j].data(), m);
+                const double g = dot(b[i].data(), b[j].data(), m);
+                if (!(std::fabs(g) > 1e-10 * std::sqrt(a * d)) || !(a * d > 0.0)) continue;
+                moved = true;
+                const double z = (d - a) / (2.0 * g);
+                const double t = (z >= 0.0 ? 1.0 : -1.0) / (std::fabs(z) + std::sqrt(1.0 + z * z));
+                const double cs = 1.0 / std::sqrt(1.0 + t * t), sn = cs * t;
+                auto turn = [&](std::vector<double> &x, std::vector<double> &y) {
+                    for (size_t k = 0; k < x.size(); ++k) {
+                        const double u = x[k], v = y[k];
+                        x[k] = cs * u - sn * v;
+                        y[k] = sn * u + cs * v;
+                    }
+                };
+                turn(b[i], b[j]);
+                turn(r[i], r[j]);
+            }
+        if (!moved) break;
+    }
+    std::vector<int> by(n);
+    std::vector<double> size(n);
+    for (int i = 0; i < n; ++i) {
+        by[i] = i;
+        size[i] = dot(b[i].data(), b[i].data(), m);
+    }
+    std::stable_sort(by.begin(), by.end(), [&](int x, int y) { return size[x] > size[y]; });
+    std::vector<std::vector<double>> br(n), rr(n);
+    for (int i = 0; i < n; ++i) {
+        br[i] = std::move(b[by[i]]);
+        rr[i] = std::move(r[by[i]]);
+    }
+    b = std::move(br);
+    r = std::move(rr);
 }
 
 // a: [n_omega][n_tau] weighted columns
@@ -3204,6 +3256,7 @@ Basis make_basis(const std::vector<double> &a, int n_omega, int n_tau)
         norm[j] = std::isfinite(v) ? v : 0.0;  // a column that overflows or vanishes spans nothing
     }
     std::vector<std::vector<double>> q, work;  // basis vectors; residuals of the sampled columns
+    std::vector<int> sampled;                  // which columns those are
     std::vector<std::vector<double>> c;        // [dims][n_omega]
     auto sample = [&](int j) {
         if (!(norm[j] > 0.0)) return;
@@ -3214,14 +3267,14 @@ Basis make_basis(const std::vector<double> &a, int n_omega, int n_tau)
             for (int i = 0; i < n_tau; ++i) v[i] -= s * u[i];
         }
         work.push_back(std::move(v));
+        sampled.push_back(j);
     };
     const int ns = std::min(n_omega, kBasisSample);
     for (int i = 0; i < ns; ++i) sample((int)((int64_t)i * (n_omega - 1) / std::max(1, ns - 1)));
     std::vector<double> left(n_omega, 1.0);  // squared residual of each column relative to its norm
-    std::vector<double> worst;               // largest of them after each vector
     while ((int)q.size() < most) {
         int pick = -1;
-        double big = kBasisTol64;
+        double big = kBasisGreedy;
         for (size_t i = 0; i < work.size(); ++i) {
             const double v = std::sqrt(dot(work[i].data(), work[i].data(), n_tau));
             if (v > big) {
@@ -3232,7 +3285,7 @@ Basis make_basis(const std::vector<double> &a, int n_omega, int n_tau)
         if (pick < 0) {
             // the sample is spanned: is every column?
             int j = (int)(std::max_element(left.begin(), left.end()) - left.begin());
-            if (q.empty() || !(left[j] > kBasisTol64 * kBasisTol64)) break;
+            if (q.empty() || !(left[j] > 0.25 * kBasisTol64 * kBasisTol64)) break;
             const size_t had = work.size();
             sample(j);
             left[j] = 0.0;  // taken into the sample (its residual may be rounding only)
@@ -3247,7 +3300,7 @@ Basis make_basis(const std::vector<double> &a, int n_omega, int n_tau)
             }
         const double un = std::sqrt(dot(u.data(), u.data(), n_tau));
         if (!(un > 0.5 * big)) {  // nothing but rounding was left
-            work.erase(work.begin() + pick);
+            std::fill(work[pick].begin(), work[pick].end(), 0.0);
             continue;
         }
         for (auto &x : u) x /= un;
@@ -3256,23 +3309,59 @@ Basis make_basis(const std::vector<double> &a, int n_omega, int n_tau)
             for (int i = 0; i < n_tau; ++i) v[i] -= s * u[i];
         }
         std::vector<double> cd(n_omega);
-        double w = 0.0;
         for (int j = 0; j < n_omega; ++j) {
             cd[j] = dot(u.data(), &a[(size_t)j * n_tau], n_tau);
-            if (!(norm[j] > 0.0)) {
-                cd[j] = left[j] = 0.0;
-                continue;
-            }
-            left[j] -= (cd[j] / norm[j]) * (cd[j] / norm[j]);
-            w = std::max(w, left[j]);
+            if (!(norm[j] > 0.0)) cd[j] = left[j] = 0.0;
+            else left[j] -= (cd[j] / norm[j]) * (cd[j] / norm[j]);
         }
-        worst.push_back(w);
         q.push_back(std::move(u));
         c.push_back(std::move(cd));
     }
     b.dims = (int)q.size();
-    b.dims32 = b.dims;
-    for (int d = b.dims; d >= 1 && worst[d - 1] <= kBasisTol32 * kBasisTol32; --d) b.dims32 = d;
+    // principal directions of the sampled columns (a basis of more vectors than
+    // the sweep takes in registers in any precision stays as it is)
+    if (b.dims <= kBasisSample) {
+        std::vector<std::vector<double>> rows(b.dims), r;
+        for (int d = 0; d < b.dims; ++d)
+            for (int j : sampled) rows[d].push_back(c[d][j] / norm[j]);
+        principal_rows(rows, r);
+        std::vector<std::vector<double>> y(b.dims, std::vector<double>(n_tau, 0.0));
+        for (int d = 0; d < b.dims; ++d)
+            for (int e = 0; e < b.dims; ++e)
+                for (int i = 0; i < n_tau; ++i) y[d][i] += r[d][e] * q[e][i];
+        q = std::move(y);
+    }
+    // the rotations leave q orthonormal to some 1e-15 only, which S2 would
+    // show: once more, in 80 bits
+    for (int d = 0; d < b.dims; ++d) {
+        std::vector<long double> u(q[d].begin(), q[d].end());
+        auto with = [&](const double *w) {
+            long double t = 0.0L;
+            for (int i = 0; i < n_tau; ++i) t += (w ? (long double)w[i] : u[i]) * u[i];
+            return t;
+        };
+        for (int e = 0; e < d; ++e) {
+            const long double t = with(q[e].data());
+            for (int i = 0; i < n_tau; ++i) u[i] -= t * q[e][i];
+        }
+        const long double un = std::sqrt(with(nullptr));
+        for (int i = 0; i < n_tau; ++i) q[d][i] = (double)(u[i] / un);
+        for (int j = 0; j < n_omega; ++j) c[d][j] = norm[j] > 0.0 ? dot(q[d].data(), &a[(size_t)j * n_tau], n_tau) : 0.0;
+    }
+    // the vectors each precision needs: what the others hold of any column
+    // stays below its tolerance
+    std::vector<double> tail(n_omega, 0.0);
+    b.dims64 = b.dims32 = b.dims;
+    for (int d = b.dims - 1; d >= 1; --d) {
+        double w = 0.0;
+        for (int j = 0; j < n_omega; ++j) {
+            if (norm[j] > 0.0) tail[j] += (c[d][j] / norm[j]) * (c[d][j] / norm[j]);
+            w = std::max(w, tail[j]);
+        }
+        if (w <= kBasisTol64 * kBasisTol64) b.dims64 = d;
+        if (w <= kBasisTol32 * kBasisTol32) b.dims32 = d;
+        else break;
+    }
     b.q.reserve((size_t)b.dims * n_tau);
     for (const auto &u : q) b.q.insert(b.q.end(), u.begin(), u.end());
     b.c.assign((size_t)n_omega * b.dims, 0.0);
@@ -3325,13 +3414,13 @@ sail_status build_tables(sail_problem *p)
         GH[2 * (size_t)kk + 1] = h;
     }
     const Basis b = make_basis(a, n_omega, n_tau);
-    p->dims64 = round_dims(SAIL_FP64, b.dims);
+    p->dims64 = round_dims(SAIL_FP64, b.dims64);
     p->dims32 = round_dims(SAIL_FP32, b.dims32);
     const int ec = p->echunk = chunk_stride<double>(p->dims64), cols = p->cols();
     p->h_col.assign((size_t)n_omega * 4 * ec, 0.0);
     p->h_proj.assign((size_t)n_tau * 4 * ec, 0.0);
     std::vector<double> E((size_t)n_omega * cols, 0.0);
-    for (int d = 0; d < b.dims; ++d) {
+    for (int d = 0; d < std::min(b.dims, 4 * p->dims64); ++d) {
         const int at = (d % 4) * ec + d / 4;
         for (int j = 0; j < n_omega; ++j) p->h_col[(size_t)j * 4 * ec + at] = b.c[(size_t)j * b.dims + d];
         for (int i = 0; i < n_tau; ++i) p->h_proj[(size_t)i * 4 * ec + at] = sw[i] * b.q[(size_t)d * n_tau + i];
@@ -3785,6 +3874,17 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
 
     // sweep groups, heaviest workgroups first
     std::vector<Launch> sweeps, resyncs, targets, smooths;
+    // pairs of wavefronts per split workgroup: four share a compute unit's LDS
+    // copy of the columns when workgroups abound; fewer when that would leave
+    // compute units idle (up to half as many workgroups again as compute units
+    // still pack well, longest first)
+    int pairs = 1;
+    auto groups_of = [&](int n) {
+        size_t b = 0;
+        for (const auto *j : act) b += ((size_t)j->p->n_walkers + 16 * n - 1) / (16 * n);
+        return b;
+    };
+    while (pairs < 4 && groups_of(pairs) > (size_t)kCUs * 3 / 2) pairs *= 2;
     // one sweep launch per (precision, basis class, mode); jobs of one
     // workload share theirs
     std::vector<int> group(act.size());
@@ -3814,9 +3914,17 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
         for (int i : idx) {
             const sail_problem *p = act[i]->p;
             const sail_schedule &sc = act[i]->sc;
-            const SweepPlan s = plan_sweep(p, split, walk && L.cls != 0 ? 8 : 4, L.threads, split ? kLdsBytes : kLdsBytes / 2, walk, false);
+            // a split job whose columns would not fit takes fewer pairs of
+            // wavefronts, hence fewer records (1024 FP64 bins: two)
+            SweepPlan s = plan_sweep(p, split, walk && L.cls != 0 ? 8 : 4, split ? 128 * pairs : L.threads,
+                                     split ? kLdsBytes : kLdsBytes / 2, walk, false);
+            for (int t = 64 * pairs; split && !s.columns_lds && t >= 128; t /= 2) {
+                const SweepPlan q = plan_sweep(p, true, 4, t, kLdsBytes, false, false);
+                if (q.columns_lds) s = q;
+            }
             sa.push_back(make_sweep_args(p, act[i]->k, kend[i],
-                                         SweepParams{sc.eps0, sc.amp_p, sc.amp_avg, sc.amp_m, sc.walk_len}, s.columns_lds));
+                                         SweepParams{sc.eps0, sc.amp_p, sc.amp_avg, sc.amp_m, sc.walk_len},
+                                         s.columns_lds, s.threads / 128));
             first.push_back(L.blocks);
             L.blocks += sweep_blocks(p, s);
             L.shm = std::max(L.shm, s.shm);
