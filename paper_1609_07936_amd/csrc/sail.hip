@@ -153,6 +153,7 @@ struct SweepArgs {
     int amp_m;
     int chunk;            // basis dimensions per chunk as stored (a multiple of 16 bytes)
     int columns_lds;      // 1: the workgroup copies the columns to LDS
+    int resident;         // split sweeps: bins of every spectrum, the first ones, that the workgroup keeps in LDS
     int pairs;            // split sweeps: chain and stager wavefronts at work in a workgroup (any others leave)
     const void *col;      // [N_omega][4][chunk] columns in the basis, loop precision
     void *phi;            // [N_w][4][chunk] walkers in the basis, loop precision
@@ -354,7 +355,8 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
     constexpr int MR = M > 0 ? M : 1;
     constexpr int RSTR = SPLIT ? kSplitStride : rec_stride(G, WALK);
     static_assert(M > 0 || !LDSC, "the general variant reads its columns from memory");
-    static_assert(!SPLIT || (G == 4 && !LDSB && MODE == kSweepFast), "split sweeps: four lanes, spectra in memory");
+    static_assert(!SPLIT || (G == 4 && MODE == kSweepFast), "split sweeps: four lanes");
+    constexpr bool ALLB = LDSB && !SPLIT;  // whole spectra in LDS; split sweeps keep the first bins there
     const int nthr = SPLIT ? 128 * a.pairs : (int)blockDim.x;
     if (SPLIT && (int)threadIdx.x >= nthr) return;
     const int lane = threadIdx.x & 63;
@@ -389,10 +391,12 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         for (size_t i = threadIdx.x; i < n16; i += nthr) ((float4 *)col_s)[i] = ((const float4 *)colg)[i];
     }
     double *spec = (double *)(col_s + (LDSC ? (size_t)No * 4 * ms : 0));
-    double *bsp = spec + ws * No;  // the walker's spectrum
+    // the walker's spectrum, or its first bins and a slot for the others' stores
+    const int nres = SPLIT ? a.resident : No;
+    double *bsp = spec + (size_t)ws * (SPLIT ? nres + 1 : No);
     if constexpr (LDSB) {
         const double *bl = a.b + (size_t)lw * No;
-        for (int j = c; j < No; j += G) bsp[j] = bl[j];
+        for (int j = c; j < nres && !stager; j += G) bsp[j] = bl[j];
     }
     __syncthreads();
 
@@ -401,7 +405,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
     const __amdgpu_buffer_rsrc_t b_rs = buffer_of(a.b, (uint32_t)((size_t)a.n_walkers * No * sizeof(double)));
     const uint32_t brow = (uint32_t)((size_t)lw * No * sizeof(double));  // byte offset of the walker's spectrum
     auto load_b = [&](const int j) __attribute__((always_inline)) {
-        if constexpr (LDSB) return bsp[j];
+        if constexpr (ALLB) return bsp[j];
         else return buffer_load_f64(b_rs, brow + ((uint32_t)j << 3));
     };
 
@@ -570,7 +574,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
     // proposal elsewhere in the batch or in the next one.
     auto body = [&](const int qq, const Rec &v, const double bp, const double bs, const uint64_t hit)
                     __attribute__((always_inline)) {
-        constexpr bool OWNED = !WALK && !LDSB;
+        constexpr bool OWNED = !WALK && !ALLB;
         const double rm1d = v.rm1, r = v.rm1 + 1.0;
         // F' = r F + s with s_i = dp K_pi + ds K_si.  The residue change
         // sum_i w_i ((Phi'_i - Phit_i)^2 - (Phi_i - Phit_i)^2) expands into
@@ -662,7 +666,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
             ++nacc;
             // the pair's new spectrum values, scaled by the new 1/g
             const double bpn = ap * ginv, bsn = as * ginv;
-            if constexpr (LDSB) {
+            if constexpr (ALLB) {
                 if (c == 0) {
                     bsp[v.p] = bpn;
                     bsp[v.s] = bsn;
@@ -800,6 +804,35 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
             return;
         }
         __builtin_amdgcn_s_setprio(2);
+        // A bin's places: a resident one is read and stored in LDS, and its
+        // memory offset is past the buffer, which costs no memory access;
+        // another one's LDS slot is the one nothing reads.
+        struct Place {
+            uint32_t mem;
+            double *lds;
+        };
+        auto place_of = [&](const int j) __attribute__((always_inline)) {
+            if constexpr (!LDSB) return Place{brow + ((uint32_t)j << 3), nullptr};
+            else return Place{j < nres ? kDropStore : brow + ((uint32_t)j << 3), bsp + min(j, nres)};
+        };
+        auto put = [&](const Place &o, const double x) __attribute__((always_inline)) {
+            buffer_store_f64(b_rs, o.mem, x);
+            if constexpr (LDSB) *o.lds = x;
+        };
+        Place opl, osl, npl, nsl;  // of op, os, np_ and ns_
+        double lbp = 0.0, lbs = 0.0;
+        auto load_next = [&](const double own_bins) __attribute__((always_inline)) {
+            np_ = __double2loint(own_bins);
+            ns_ = __double2hiint(own_bins);
+            npl = place_of(np_);
+            nsl = place_of(ns_);
+            nbp = buffer_load_f64(b_rs, npl.mem);
+            nbs = buffer_load_f64(b_rs, nsl.mem);
+            if constexpr (LDSB) {
+                lbp = *npl.lds;
+                lbs = *nsl.lds;
+            }
+        };
         begin_sweep();
         if (c == 0) *width = yeps;
         barrier();
@@ -810,10 +843,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
             const double w0 = *bins_at(0, 0), own_bins = *bins_at(0, c);
             next_bins = *bins_at(0, 1);
             rows(__double2loint(w0), __double2hiint(w0), v[0]);
-            np_ = __double2loint(own_bins);
-            ns_ = __double2hiint(own_bins);
-            nbp = load_b(np_);
-            nbs = load_b(ns_);
+            load_next(own_bins);
         }
         for (;;) {
             barrier();
@@ -831,8 +861,12 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
                 // the stores below are issued, so that nothing waits for those)
                 asm volatile("" : "+v"(nbp), "+v"(nbs));
                 if (__builtin_amdgcn_inverse_ballot_w64(accm & validm)) {
-                    buffer_store_f64(b_rs, brow + ((uint32_t)op << 3), obp);
-                    buffer_store_f64(b_rs, brow + ((uint32_t)os << 3), obs);
+                    put(opl, obp);
+                    put(osl, obs);
+                }
+                if constexpr (LDSB) {
+                    nbp = npl.mem == kDropStore ? lbp : nbp;
+                    nbs = nsl.mem == kDropStore ? lbs : nbs;
                 }
                 obp = fp ? fbp : nbp;
                 obs = fs ? fbs : nbs;
@@ -841,12 +875,11 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
                 accm = 0;
                 op = np_;
                 os = ns_;
-                np_ = __double2loint(own_bins);
-                ns_ = __double2hiint(own_bins);
+                opl = npl;
+                osl = nsl;
+                load_next(own_bins);
                 ops = (uint32_t)op | (uint32_t)os << 16;
                 nps = (uint32_t)np_ | (uint32_t)ns_ << 16;
-                nbp = load_b(np_);
-                nbs = load_b(ns_);
 #pragma unroll
                 for (int t = 0; t < G; ++t) {
                     // the next proposal's columns (its bins were read a proposal
@@ -875,8 +908,8 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
             if (last) break;
         }
         if (__builtin_amdgcn_inverse_ballot_w64(accm & validm)) {
-            buffer_store_f64(b_rs, brow + ((uint32_t)op << 3), obp);
-            buffer_store_f64(b_rs, brow + ((uint32_t)os << 3), obs);
+            put(opl, obp);
+            put(osl, obs);
         }
     } else if constexpr (WALK) {
         // Sec. 2.3 index selection: from the uniform p, s of each proposal,
@@ -1057,7 +1090,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         if constexpr (LDSB) {
             wave_lds_sync();
             double *bl = a.b + (size_t)l * No;
-            for (int j = c; j < No; j += G) bl[j] = bsp[j];
+            for (int j = c; j < nres; j += G) bl[j] = bsp[j];
         }
         if (c == 0) {
             a.gsc[l] = g;
@@ -1079,11 +1112,11 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep(SweepArgs a)
     sweep_block<R, M, G, LDSC, LDSB, MODE, false>(a, blockIdx.x, lds);
 }
 
-template <typename R, int M, bool LDSC>
+template <typename R, int M, bool LDSC, bool LDSB>
 __global__ __launch_bounds__(2 * kSweepThreads) void k_sweep_split(SweepArgs a)
 {
     extern __shared__ __align__(16) double lds[];
-    sweep_block<R, M, 4, LDSC, false, kSweepFast, true>(a, blockIdx.x, lds);
+    sweep_block<R, M, 4, LDSC, LDSB, kSweepFast, true>(a, blockIdx.x, lds);
 }
 
 // Many problems in one launch: problem q owns workgroups [first[q], first[q + 1]);
@@ -1106,7 +1139,8 @@ __global__ __launch_bounds__(2 * kSweepThreads) void k_sweep_split_batched(const
     const int q = owner_of(first, n_jobs, blockIdx.x);
     const SweepArgs &a = jobs[q];
     const int block = blockIdx.x - first[q];
-    if (a.columns_lds) sweep_block<R, M, 4, true, false, kSweepFast, true>(a, block, lds);
+    if (a.resident) sweep_block<R, M, 4, true, true, kSweepFast, true>(a, block, lds);
+    else if (a.columns_lds) sweep_block<R, M, 4, true, false, kSweepFast, true>(a, block, lds);
     else sweep_block<R, M, 4, false, false, kSweepFast, true>(a, block, lds);
 }
 
@@ -2982,14 +3016,27 @@ int sweep_wg_sync()
     return v;
 }
 
-SweepArgs make_sweep_args(const sail_problem *p, int k0, int k1, const SweepParams &sp, int columns_lds, int pairs)
+// How a sweep is launched: split or not, lanes per walker, threads and walkers
+// per workgroup, whether the columns and the walkers' spectra sit in LDS, and
+// the LDS they take with the records.  The results have the same bits for any
+// plan.
+struct SweepPlan {
+    bool split;
+    int lanes, threads, walkers;
+    int columns_lds, spectra_lds;
+    int resident;  // split: bins of every spectrum in LDS
+    size_t shm;
+};
+
+SweepArgs make_sweep_args(const sail_problem *p, int k0, int k1, const SweepParams &sp, const SweepPlan &plan)
 {
     SweepArgs s;
     s.n_walkers = p->n_walkers;
     s.n_omega = p->n_omega;
     s.chunk = p->chunk(p->precision);
-    s.columns_lds = columns_lds;
-    s.pairs = pairs;
+    s.columns_lds = plan.columns_lds;
+    s.resident = plan.resident;
+    s.pairs = plan.threads / 128;
     s.k0 = k0;
     s.k1 = k1;
     s.key0 = (uint32_t)p->seed;
@@ -3025,23 +3072,12 @@ SweepArgs make_sweep_args(const sail_problem *p, int k0, int k1, const SweepPara
     return s;
 }
 
-// How a sweep is launched: split or not, lanes per walker, threads and walkers
-// per workgroup, whether the columns and the walkers' spectra sit in LDS, and
-// the LDS they take with the records.  The results have the same bits for any
-// plan.
-struct SweepPlan {
-    bool split;
-    int lanes, threads, walkers;
-    int columns_lds, spectra_lds;
-    size_t shm;
-};
-
 // The columns, then the spectra of the workgroup's walkers (if asked for), go
 // to LDS if they fit in `budget` bytes beside the records.
 SweepPlan plan_sweep(const sail_problem *p, bool split, int lanes, int threads, size_t budget, bool walk, bool spectra)
 {
     const int walkers = (split ? threads / 2 : threads) / lanes;
-    SweepPlan s{split, lanes, threads, walkers, 0, 0,
+    SweepPlan s{split, lanes, threads, walkers, 0, 0, 0,
                 sizeof(double) * (split ? (size_t)walkers * kSplitStride + (size_t)walkers / 16 * kSplitHits
                                      : (size_t)walkers * rec_stride(lanes, walk))};
     const size_t col = column_bytes(p->n_omega, p->chunk(p->precision),
@@ -3051,9 +3087,21 @@ SweepPlan plan_sweep(const sail_problem *p, bool split, int lanes, int threads, 
         s.shm += col;
         s.columns_lds = 1;
         const size_t spec = sizeof(double) * (size_t)walkers * p->n_omega;
-        if (spectra && s.shm + spec <= budget) {
+        if (!split && spectra && s.shm + spec <= budget) {
             s.shm += spec;
             s.spectra_lds = 1;
+        }
+        // Many walkers per compute unit: the spectra in flight outgrow the L2
+        // caches (8 MB per 4 MB cache at 512 bins), and the sweep waits for the
+        // memory behind them.  What LDS is left keeps the first bins of each
+        // (512 bins, 16384 walkers: 14 % of them in FP64, 27 % in FP32; block
+        // 22.9 to 20.6 ms and 22.9 to 18.7 ms).  Smaller workgroups mean
+        // spectra that the caches hold, where the extra instructions lose 2 %
+        // (24 FP64 jobs: 27.2 to 27.8 ms; band: 26.0 to 26.6 ms).
+        if (split && threads == 2 * kSweepThreads) {
+            const int slots = (int)((budget - s.shm) / (sizeof(double) * (size_t)walkers));
+            s.resident = std::min(std::max(slots - 1, 0), p->n_omega);
+            if (s.resident) s.shm += sizeof(double) * (size_t)walkers * (s.resident + 1);
         }
     }
     return s;
@@ -3105,10 +3153,12 @@ void launch_sweep_m(const SweepArgs &a, int blocks, const SweepPlan &s, int mode
             return launch_sweep_k<R, M, 8, false, false, kSweepWalk>(a, blocks, s, stream);
         }
         if (s.spectra_lds) return launch_sweep_k<R, M, 16, true, true, kSweepFast>(a, blocks, s, stream);
-        if (s.columns_lds)
-            hipLaunchKernelGGL((k_sweep_split<R, M, true>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
+        if (s.resident)
+            hipLaunchKernelGGL((k_sweep_split<R, M, true, true>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
+        else if (s.columns_lds)
+            hipLaunchKernelGGL((k_sweep_split<R, M, true, false>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
         else
-            hipLaunchKernelGGL((k_sweep_split<R, M, false>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
+            hipLaunchKernelGGL((k_sweep_split<R, M, false, false>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
     } else {
         // the general variant: four lanes, phi and columns in memory
         if (mode == kSweepWalk) return launch_sweep_k<R, M, 4, false, false, kSweepWalk>(a, blocks, s, stream);
@@ -3139,7 +3189,7 @@ sail_status launch_sweep(sail_problem *p, int k0, int k1, const SweepParams &sp,
 {
     const int mode = sp.walk_len > 0 ? kSweepWalk : sweep_traced(p, k0, k1) ? kSweepTraced : kSweepFast;
     const SweepPlan s = plan_alone(p, mode);
-    const SweepArgs a = make_sweep_args(p, k0, k1, sp, s.columns_lds, s.threads / 128);
+    const SweepArgs a = make_sweep_args(p, k0, k1, sp, s);
     const int blocks = sweep_blocks(p, s);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (p->timing) {
@@ -3923,8 +3973,7 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
                 if (q.columns_lds) s = q;
             }
             sa.push_back(make_sweep_args(p, act[i]->k, kend[i],
-                                         SweepParams{sc.eps0, sc.amp_p, sc.amp_avg, sc.amp_m, sc.walk_len},
-                                         s.columns_lds, s.threads / 128));
+                                         SweepParams{sc.eps0, sc.amp_p, sc.amp_avg, sc.amp_m, sc.walk_len}, s));
             first.push_back(L.blocks);
             L.blocks += sweep_blocks(p, s);
             L.shm = std::max(L.shm, s.shm);
