@@ -244,6 +244,12 @@ constexpr int rec_stride(int G, bool walk) { return (walk ? G * (kRecWords + 1 +
 constexpr int kSplitHits = 3 * 4;
 constexpr int kSplitStride = 3 * 4 * kRecWords + 4 * 4 + 2;
 
+// A split walk's walker: of two batches of 16 proposals, the records (r - 1 or
+// its draw, 1/r, the threshold and the uniform bins) and the walk's steps (two
+// words a side: the candidate bin and its draw); the move width.
+constexpr int kWalkRec = 4;
+constexpr int64_t walk_split_stride(int walk_len) { return (int64_t)2 * 16 * (kWalkRec + (int64_t)2 * walk_len) + 2; }
+
 // Basis dimensions per chunk as stored: whole 16-byte words.
 template <typename R>
 constexpr int chunk_stride(int m) { return sizeof(R) == 8 ? (m + 1) & ~1 : (m + 3) & ~3; }
@@ -353,10 +359,10 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
 {
     constexpr bool WALK = MODE == kSweepWalk, TRACE = MODE != kSweepFast;
     constexpr int MR = M > 0 ? M : 1;
-    constexpr int RSTR = SPLIT ? kSplitStride : rec_stride(G, WALK);
+    const int RSTR = !SPLIT ? rec_stride(G, WALK) : WALK ? (int)walk_split_stride(a.walk_len) : kSplitStride;
     static_assert(M > 0 || !LDSC, "the general variant reads its columns from memory");
-    static_assert(!SPLIT || (G == 4 && MODE == kSweepFast), "split sweeps: four lanes");
-    constexpr bool ALLB = LDSB && !SPLIT;  // whole spectra in LDS; split sweeps keep the first bins there
+    static_assert(!SPLIT || (WALK ? G == 16 && LDSC && LDSB : G == 4 && MODE == kSweepFast), "split sweeps");
+    constexpr bool ALLB = LDSB && (!SPLIT || WALK);  // whole spectra in LDS; split sweeps keep the first bins there
     const int nthr = SPLIT ? 128 * a.pairs : (int)blockDim.x;
     if (SPLIT && (int)threadIdx.x >= nthr) return;
     const int lane = threadIdx.x & 63;
@@ -385,18 +391,25 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
     // records, columns and spectra in LDS
     double *myrec = lds + ws * RSTR;
     const R *colg = (const R *)a.col;
-    R *col_s = (R *)(lds + wpb * RSTR + (SPLIT ? (wpb >> 4) * kSplitHits : 0));
+    R *col_s = (R *)(lds + wpb * RSTR + (SPLIT && !WALK ? (wpb >> 4) * kSplitHits : 0));
     if constexpr (LDSC) {
         const size_t n16 = (size_t)No * 4 * ms * sizeof(R) / 16;
         for (size_t i = threadIdx.x; i < n16; i += nthr) ((float4 *)col_s)[i] = ((const float4 *)colg)[i];
     }
     double *spec = (double *)(col_s + (LDSC ? (size_t)No * 4 * ms : 0));
     // the walker's spectrum, or its first bins and a slot for the others' stores
-    const int nres = SPLIT ? a.resident : No;
-    double *bsp = spec + (size_t)ws * (SPLIT ? nres + 1 : No);
+    const int nres = ALLB ? No : a.resident;
+    double *bsp = spec + (size_t)ws * (ALLB ? No : nres + 1);
     if constexpr (LDSB) {
         const double *bl = a.b + (size_t)lw * No;
         for (int j = c; j < nres && !stager; j += G) bsp[j] = bl[j];
+    }
+    // a split walk's bins are known late: their table values sit in LDS too
+    double4 *bin_s = (double4 *)(spec + (((size_t)wpb * No + 1) & ~(size_t)1));
+    double2 *GH_s = (double2 *)(bin_s + No);
+    if constexpr (SPLIT && WALK) {
+        for (int i = threadIdx.x; i < No; i += nthr) bin_s[i] = bin[i];
+        for (int i = threadIdx.x; i < 2 * No - 1; i += nthr) GH_s[i] = GH[i];
     }
     __syncthreads();
 
@@ -630,8 +643,8 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
             }
             am = (am & ~near) | (near & __builtin_amdgcn_ballot_w64(take));
         }
-        if (TRACE) {
-            if (c == qq && valid && k >= a.tk0 && k < a.tk1 && q0 + qq < No) {
+        if (TRACE && k >= a.tk0 && k < a.tk1) {
+            if (c == qq && valid && q0 + qq < No) {
                 const size_t o = ((size_t)l * (size_t)(a.tk1 - a.tk0) + (size_t)(k - a.tk0)) * No + q0 + qq;
                 a.tr_dchi2[o] = dchi2;
                 a.tr_flags[o] = (uint8_t)((__builtin_amdgcn_inverse_ballot_w64(am) ? 1 : 0) |
@@ -642,7 +655,8 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         if (__builtin_amdgcn_inverse_ballot_w64(am)) {
             if constexpr (M == 0) {
                 const R *cp = colg + (size_t)(v.p * 4 + ch) * ms, *cs = colg + (size_t)(v.s * 4 + ch) * ms;
-                for (int t = 0; t < ms; ++t) {
+                // (lanes without a walker compute on another's coordinates)
+                for (int t = 0; t < ms && valid; ++t) {
                     const R s = fma(dpr, cp[t], dsr * cs[t]);
                     if constexpr (sizeof(R) == 8) phig[t] = fma((R)r, phig[t], s);
                     else phig[t] = phig[t] + fma((R)rm1d, phig[t], s);
@@ -737,7 +751,139 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         else wave_lds_sync();
     };
 
-    if constexpr (SPLIT) {
+    if constexpr (SPLIT && WALK) {
+        // Sec. 2.3 index selection (see below), split: what a walk draws does
+        // not depend on the walker, so the stagers draw a batch of 16 proposals
+        // with all their steps ahead.  The chain's lanes take one of a pair's
+        // walks each, p's the even ones, s's the odd: the candidates' values are
+        // read together, the steps decided one after another, and the pair's
+        // table values read at its end.  A sweep's first batch is staged before
+        // its move width is known: the chain completes those records.
+        auto barrier = [&]() __attribute__((always_inline)) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        };
+        double *width = myrec + 2 * G * (kWalkRec + 2 * walk_len);
+        auto wrec = [&](const int h, const int qq) __attribute__((always_inline)) { return myrec + (h * G + qq) * kWalkRec; };
+        auto steps = [&](const int h, const int qq) __attribute__((always_inline)) {
+            return (uint2 *)(myrec + 2 * G * kWalkRec) + (h * G + qq) * 2 * walk_len;
+        };
+        auto complete = [&](double *rc, const double ur) __attribute__((always_inline)) {
+            const double rm1 = (1.0 - yeps * fma(2.0, ur, -1.0)) - 1.0;
+            rc[0] = rm1;
+            rc[1] = recip(rm1 + 1.0);
+        };
+        if (stager) {
+            auto stage_walk = [&](const int h, const int q, const bool first) __attribute__((always_inline)) {
+                uint32_t x2, x3, y0, y1, y2, y3;
+                draw(q + c, k, op, os, x2, x3);
+                double *rc = wrec(h, c);
+                rc[0] = u01(x2);
+                if (!first) complete(rc, u01(x2));
+                rc[2] = staged_threshold(Tabs, u01(x3));
+                rc[3] = __hiloint2double(os, op);
+                uint2 *w = steps(h, c);
+                for (int st = 0; st < walk_len; ++st) {
+                    philox10((uint32_t)(q + c), (uint32_t)k, (uint32_t)lw, (uint32_t)(st + 1), key0, key1, y0, y1, y2, y3);
+                    w[2 * st] = make_uint2((uint32_t)index_of(y0, No), y1);
+                    w[2 * st + 1] = make_uint2((uint32_t)index_of(y2, No), y3);
+                }
+            };
+            int h = 0;
+            for (; k < k1; ++k) {
+                temperature();
+                for (q0 = 0; q0 < No; q0 += G) {
+                    if (q0 > 0) yeps = *width;
+                    stage_walk(h, q0, q0 == 0);
+                    h ^= 1;
+                    barrier();
+                }
+            }
+            barrier();
+            return;
+        }
+        __builtin_amdgcn_s_setprio(2);
+        auto enter = [&]() __attribute__((always_inline)) {
+            begin_sweep();
+            if (c == 0) *width = yeps;
+        };
+        constexpr int W = 4;  // steps whose candidates are read together
+        const int side = c & 1;
+        auto step_words = [&](const int h, const int qq, const int st0, uint2 (&w)[W]) __attribute__((always_inline)) {
+            const uint2 *p = steps(h, qq) + side;
+#pragma unroll
+            for (int t = 0; t < W; ++t) w[t] = p[2 * min(st0 + t, walk_len - 1)];
+        };
+        int h = 0;
+        enter();
+        barrier();
+        for (;;) {
+            if (q0 == 0) {
+                double *rc = wrec(h, c);
+                complete(rc, rc[0]);
+                wave_lds_sync();
+            }
+            const int nq = min(G, No - q0);
+            uint2 w[W];
+            double rcv[kWalkRec];
+            step_words(h, 0, 0, w);
+#pragma unroll
+            for (int t = 0; t < kWalkRec; ++t) rcv[t] = wrec(h, 0)[t];
+            for (int qq = 0; qq < nq; ++qq) {
+                Rec v;
+                v.rm1 = rcv[0];
+                v.rinv = rcv[1];
+                v.thr = rcv[2];
+                int x = side ? __double2hiint(rcv[3]) : __double2loint(rcv[3]);
+                double gx = g * bsp[x];
+                for (int st0 = 0;;) {
+                    double cand[W];
+#pragma unroll
+                    for (int t = 0; t < W; ++t) cand[t] = bsp[w[t].x];
+#pragma unroll
+                    for (int t = 0; t < W; ++t) {
+                        const double gc = g * cand[t];
+                        const bool take = (u01(w[t].y) * gx < gc) & (st0 + t < walk_len);
+                        gx = take ? gc : gx;
+                        x = take ? (int)w[t].x : x;
+                    }
+                    st0 += W;
+                    if (st0 >= walk_len) break;
+                    step_words(h, qq, st0, w);
+                }
+                const int p = dpp_swap<0xA0>(x), s = dpp_swap<0xF5>(x);  // quad_perm 0, 0, 2, 2 and 1, 1, 3, 3
+                rows(p, s, v);
+                Pair pr;
+                pr.p = bin_s[p];
+                pr.s = bin_s[s];
+                pr.gh = GH_s[p + s];
+                const double bp = bsp[p], bs = bsp[s];
+                // the next proposal's words arrive meanwhile
+                const int qn = min(qq + 1, nq - 1);
+                step_words(h, qn, 0, w);
+#pragma unroll
+                for (int t = 0; t < kWalkRec; ++t) rcv[t] = wrec(h, qn)[t];
+                pair_terms(p, s, pr, v.rm1 + 1.0, v.dp, v.ds, v.s1, v.t);
+                body(qq, v, bp, bs, 0);
+                wave_lds_sync();
+            }
+            h ^= 1;
+            q0 += G;
+            bool last = false;
+            if (q0 >= No) {
+                end_sweep();
+                last = k + 1 >= k1;
+                if (!last) {
+                    ++k;
+                    q0 = 0;
+                    enter();
+                }
+            }
+            barrier();
+            if (last) break;
+        }
+    } else if constexpr (SPLIT) {
         // Both roles pass the same barriers: one to start, and in every sweep
         // two for the first two batches' records and one per batch.  Records
         // are staged two batches ahead of the chain (a ring of three) within a
@@ -1117,6 +1263,13 @@ __global__ __launch_bounds__(2 * kSweepThreads) void k_sweep_split(SweepArgs a)
 {
     extern __shared__ __align__(16) double lds[];
     sweep_block<R, M, 4, LDSC, LDSB, kSweepFast, true>(a, blockIdx.x, lds);
+}
+
+template <typename R, int M>
+__global__ __launch_bounds__(2 * kSweepThreads) void k_sweep_walk(SweepArgs a)
+{
+    extern __shared__ __align__(16) double lds[];
+    sweep_block<R, M, 16, true, true, kSweepWalk, true>(a, blockIdx.x, lds);
 }
 
 // Many problems in one launch: problem q owns workgroups [first[q], first[q + 1]);
@@ -3074,12 +3227,14 @@ SweepArgs make_sweep_args(const sail_problem *p, int k0, int k1, const SweepPara
 
 // The columns, then the spectra of the workgroup's walkers (if asked for), go
 // to LDS if they fit in `budget` bytes beside the records.
-SweepPlan plan_sweep(const sail_problem *p, bool split, int lanes, int threads, size_t budget, bool walk, bool spectra)
+SweepPlan plan_sweep(const sail_problem *p, bool split, int lanes, int threads, size_t budget, bool walk, bool spectra,
+                     int walk_len)
 {
     const int walkers = (split ? threads / 2 : threads) / lanes;
     SweepPlan s{split, lanes, threads, walkers, 0, 0, 0,
-                sizeof(double) * (split ? (size_t)walkers * kSplitStride + (size_t)walkers / 16 * kSplitHits
-                                     : (size_t)walkers * rec_stride(lanes, walk))};
+                sizeof(double) * (!split ? (size_t)walkers * rec_stride(lanes, walk)
+                                  : walk ? (size_t)walkers * walk_split_stride(walk_len)
+                                         : (size_t)walkers * kSplitStride + (size_t)walkers / 16 * kSplitHits)};
     const size_t col = column_bytes(p->n_omega, p->chunk(p->precision),
                                     p->precision == SAIL_FP32 ? sizeof(float) : sizeof(double));
     if (basis_class(p->precision, p->dims(p->precision)) == 0) return s;
@@ -3087,8 +3242,12 @@ SweepPlan plan_sweep(const sail_problem *p, bool split, int lanes, int threads, 
         s.shm += col;
         s.columns_lds = 1;
         const size_t spec = sizeof(double) * (size_t)walkers * p->n_omega;
-        if (!split && spectra && s.shm + spec <= budget) {
-            s.shm += spec;
+        // (a split walk: and the tables of the bins and their pairs)
+        const size_t all = !split || !walk ? spec
+                                           : ((spec + 15) & ~(size_t)15) + (size_t)p->n_omega * sizeof(double4) +
+                                                 (size_t)(2 * p->n_omega - 1) * sizeof(double2);
+        if ((!split || walk) && spectra && s.shm + all <= budget) {
+            s.shm += all;
             s.spectra_lds = 1;
         }
         // Many walkers per compute unit: the spectra in flight outgrow the L2
@@ -3098,7 +3257,7 @@ SweepPlan plan_sweep(const sail_problem *p, bool split, int lanes, int threads, 
         // 22.9 to 20.6 ms and 22.9 to 18.7 ms).  Smaller workgroups mean
         // spectra that the caches hold, where the extra instructions lose 2 %
         // (24 FP64 jobs: 27.2 to 27.8 ms; band: 26.0 to 26.6 ms).
-        if (split && threads == 2 * kSweepThreads) {
+        if (split && !walk && threads == 2 * kSweepThreads) {
             const int slots = (int)((budget - s.shm) / (sizeof(double) * (size_t)walkers));
             s.resident = std::min(std::max(slots - 1, 0), p->n_omega);
             if (s.resident) s.shm += sizeof(double) * (size_t)walkers * (s.resident + 1);
@@ -3119,7 +3278,7 @@ constexpr int kCUs = 256;
 // into chains and stagers.  Workgroups are the smallest that leave at most one
 // per compute unit, so that a small population spreads over the chip, each
 // with as much LDS as its share of a compute unit.
-SweepPlan plan_alone(const sail_problem *p, int mode)
+SweepPlan plan_alone(const sail_problem *p, int mode, int walk_len)
 {
     const size_t n = (size_t)p->n_walkers;
     const bool general = basis_class(p->precision, p->dims(p->precision)) == 0;
@@ -3129,10 +3288,16 @@ SweepPlan plan_alone(const sail_problem *p, int mode)
         while (threads < most && n * per > (size_t)threads * kCUs) threads *= 2;
         const size_t blocks = (n * per + threads - 1) / threads;
         const size_t per_cu = std::min<size_t>(std::max<size_t>((blocks + kCUs - 1) / kCUs, 1), 4);
-        return plan_sweep(p, split, lanes, threads, kLdsBytes / per_cu, mode == kSweepWalk, spectra);
+        return plan_sweep(p, split, lanes, threads, kLdsBytes / per_cu, mode == kSweepWalk, spectra, walk_len);
     };
     if (mode == kSweepTraced || general) return sized(false, 4, false);
-    if (mode == kSweepWalk) return sized(false, 8, true);
+    // Walks: split, 16 lanes a walker, everything in LDS, if it fits; else all in
+    // one wavefront, 8 lanes a walker (256 bins, 1024 walkers, 4 steps: a block
+    // 3.5 ms against 6.4 ms, and 9.3 ms with the tables in memory).
+    if (mode == kSweepWalk) {
+        const SweepPlan w = sized(true, 16, true);
+        return w.spectra_lds ? w : sized(false, 8, true);
+    }
     const SweepPlan s = sized(false, 16, true);
     return s.spectra_lds ? s : sized(true, 4, false);
 }
@@ -3149,6 +3314,10 @@ void launch_sweep_m(const SweepArgs &a, int blocks, const SweepPlan &s, int mode
     if (mode == kSweepTraced) return launch_sweep_k<R, M, 4, false, false, kSweepTraced>(a, blocks, s, stream);
     if constexpr (M > 0) {
         if (mode == kSweepWalk) {
+            if (s.split) {
+                hipLaunchKernelGGL((k_sweep_walk<R, M>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
+                return;
+            }
             if (s.spectra_lds) return launch_sweep_k<R, M, 8, true, true, kSweepWalk>(a, blocks, s, stream);
             return launch_sweep_k<R, M, 8, false, false, kSweepWalk>(a, blocks, s, stream);
         }
@@ -3188,7 +3357,7 @@ void with_basis_class(int precision, int cls, F &&f)
 sail_status launch_sweep(sail_problem *p, int k0, int k1, const SweepParams &sp, hipStream_t stream)
 {
     const int mode = sp.walk_len > 0 ? kSweepWalk : sweep_traced(p, k0, k1) ? kSweepTraced : kSweepFast;
-    const SweepPlan s = plan_alone(p, mode);
+    const SweepPlan s = plan_alone(p, mode, sp.walk_len);
     const SweepArgs a = make_sweep_args(p, k0, k1, sp, s);
     const int blocks = sweep_blocks(p, s);
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -3967,9 +4136,9 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
             // a split job whose columns would not fit takes fewer pairs of
             // wavefronts, hence fewer records (1024 FP64 bins: two)
             SweepPlan s = plan_sweep(p, split, walk && L.cls != 0 ? 8 : 4, split ? 128 * pairs : L.threads,
-                                     split ? kLdsBytes : kLdsBytes / 2, walk, false);
+                                     split ? kLdsBytes : kLdsBytes / 2, walk, false, sc.walk_len);
             for (int t = 64 * pairs; split && !s.columns_lds && t >= 128; t /= 2) {
-                const SweepPlan q = plan_sweep(p, true, 4, t, kLdsBytes, false, false);
+                const SweepPlan q = plan_sweep(p, true, 4, t, kLdsBytes, false, false, 0);
                 if (q.columns_lds) s = q;
             }
             sa.push_back(make_sweep_args(p, act[i]->k, kend[i],

@@ -1,0 +1,95 @@
+"""GPU: the sweep's launch plans and basis classes at their edges.
+
+A problem swept alone (its own plan), under a trace window (plain four-lane
+plan) and in a batch (split or walk plan of the shared launch) has the same
+bits, whatever the plan: compared with array_equal.  Problems whose weights
+spread the columns over more dimensions (the wider classes, and the general
+one of any number) are compared with the oracle, to the parity tests' bars.
+"""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_1609_07936_amd import workloads as W
+from test_gpu_parity import S, _anneal_lockstep  # noqa: F401 (the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def _workload(n_omega, n_tau, n_walkers, n_sweeps, spread=0.0):
+    """A two-peak target; spread > 0 weights the times so that the columns
+    sqrt(w_i) e^{-omega_j tau_i} become Gaussians along tau, whose rank grows
+    with it."""
+    w_max = 10.0 if spread == 0.0 else spread / 4.0
+    tau = W.uniform_tau(0.05, 1.6, n_tau) if spread == 0.0 else np.linspace(0.0, 4.0, n_tau)
+    tgt = W.Target([0.15 * w_max, 0.4 * w_max], [0.04 * w_max, 0.08 * w_max], [0.6, 0.4], w_max)
+    wl = W.make(f"sweep-{n_omega}x{n_tau}x{n_walkers}", w_max, n_omega, tau, tgt, 1e-3, 3, n_walkers, n_sweeps, 1e2,
+                1.0, n_sweeps, n_sweeps, 5, n_quad=4000)
+    if spread > 0.0:
+        v = w_max * (tau - tau * tau / 8.0)
+        sigma = np.exp(-(v - 0.5 * v.max()))
+        wl = dataclasses.replace(wl, sigma=sigma)
+    return wl
+
+
+# bins, times, walkers, precision, walk steps, column spread: which plan of its own it takes
+PLANS = [
+    (3, 5, 2, 0, 0, 0.0),        # spectra in LDS, fewer bins than a batch of proposals
+    (33, 9, 5, 1, 0, 0.0),       # the same in FP32
+    (130, 40, 1025, 0, 0, 0.0),  # more than one walker group per compute unit
+    (601, 33, 1100, 0, 0, 0.0),  # split, one pair of wavefronts
+    (601, 33, 2500, 1, 0, 0.0),  # split, FP32
+    (1300, 17, 70, 0, 0, 0.0),   # columns larger than LDS
+    (130, 40, 8197, 0, 0, 0.0),  # four pairs, whole spectra resident beside them
+    (515, 40, 8197, 0, 0, 0.0),  # four pairs, the first bins resident
+    (515, 40, 8197, 1, 0, 0.0),  # the same in FP32
+    (1023, 20, 8193, 0, 0, 0.0),  # four pairs, no room for columns
+    (96, 80, 37, 0, 0, 400.0),   # any number of dimensions
+    (96, 80, 37, 1, 0, 400.0),
+    (35, 12, 5, 0, 1, 0.0),      # split walk: one step, a remainder of proposals and of walkers
+    (35, 12, 1025, 0, 4, 0.0),
+    (160, 24, 130, 1, 5, 0.0),   # more steps than are read together
+    (3, 5, 2, 0, 9, 0.0),
+    (200, 24, 65, 0, 64, 0.0),   # more steps than fit: the walk in its own wavefront
+    (700, 24, 4100, 0, 2, 0.0),  # spectra in memory
+    (96, 80, 37, 0, 3, 400.0),
+]
+
+
+@pytest.mark.parametrize("n_omega,n_tau,n_walkers,prec,walk,spread", PLANS)
+def test_same_bits_for_every_plan(S, n_omega, n_tau, n_walkers, prec, walk, spread):  # noqa: F811
+    import torch
+    n = 2 if walk > 10 else 7
+    wl = _workload(n_omega, n_tau, n_walkers, n, spread)
+    side = _workload(40, 11, 19, n)
+    sched = S.Schedule(np.geomspace(100.0, 1.0, n), branch_every=n, resync_every=n, walk_len=walk)
+
+    def problem(w, precision):
+        gp = S.Problem(w.omega, w.tau, w.Ft, w.sigma, w.m0, w.m1)
+        gp.init_walkers(w.n_walkers, 11, precision=precision)
+        return gp
+
+    alone, traced, batched = (problem(wl, prec) for _ in range(3))
+    alone.run(sched, 0, n)
+    flags = torch.zeros((n_walkers, 1, n_omega), dtype=torch.uint8, device="cuda")
+    d = torch.zeros((n_walkers, 1, n_omega), dtype=torch.float64, device="cuda")
+    traced.set_trace(n - 1, n, d.data_ptr(), flags.data_ptr())
+    traced.run(sched, 0, n)
+    other = problem(side, 0)
+    S.Batch([batched, other]).run([sched, sched], [0, 0], [n, n])
+    torch.cuda.synchronize()
+    a = alone.read_state()
+    assert np.isfinite(a["a"]).all()
+    for name, gp in (("traced", traced), ("batch", batched)):
+        b = gp.read_state()
+        for k in ("a", "F", "rate"):
+            np.testing.assert_array_equal(a[k], b[k], err_msg=f"{name}: {k}")
+        np.testing.assert_array_equal(alone.read_chi2(), gp.read_chi2(), err_msg=f"{name}: chi2")
+
+
+@pytest.mark.parametrize("n_omega,n_tau,spread", [(60, 7, 0.0), (96, 80, 60.0), (96, 80, 150.0), (96, 80, 250.0),
+                                                  (96, 80, 400.0)])
+def test_basis_classes_against_oracle(S, n_omega, n_tau, spread):  # noqa: F811
+    wl = _workload(n_omega, n_tau, 18, 20, spread)
+    _anneal_lockstep(S, wl, 18, 11, 20, dict(branch_every=20, resync_every=10), T=np.geomspace(100.0, 1.0, 20))
