@@ -1590,6 +1590,107 @@ __global__ __launch_bounds__(kThreads) void k_reconstruct(int n_omega, int n_tau
     }
 }
 
+// --------------------------------------------------------------------------
+// Tables of a problem, one workgroup per bin: the exact column E_j, its terms
+// D_j = sum_i w_i K_ij^2 and V_j = sum_i c_i K_ij, and its coordinates along up
+// to kBasisPass basis vectors (`proj`, times sqrt(wh)).  Latency and the FP64
+// exponentials bound it: creating a problem of 512 bins and 128 times takes 0.33 ms,
+// of 1024 and 256 0.52 ms (1.34 and 4.3 ms with the exponentials on the host).
+// --------------------------------------------------------------------------
+constexpr int kBasisPass = 32;
+struct TableArgs {
+    int n_omega, n_tau;
+    int d0, nd;           // first basis vector of the pass, and how many
+    const double *omega, *tau, *wh, *cn;
+    const double *proj;   // [nd][n_tau]
+    double *tail;         // [n_omega] squared coordinates of a column from vector d0 on, relative to its norm
+    double *worst;        // [nd] the largest tail from each of the vectors on
+    double *E;            // written if not NULL: [n_omega][cols], and bin
+    double4 *bin;
+    int cols, echunk;
+};
+
+__global__ __launch_bounds__(kThreads) void k_tables(TableArgs a)
+{
+    extern __shared__ __align__(16) double lds[];
+    __shared__ double part[2][kThreads / 64], cs[kBasisPass];
+    const int j = blockIdx.x, Nt = a.n_tau;
+    const double w = a.omega[j];
+    double D = 0.0, V = 0.0;
+    for (int i = threadIdx.x; i < Nt; i += kThreads) {
+        const double e = exp(-w * a.tau[i]);
+        lds[i] = e;
+        D += a.wh[i] * e * e;
+        V += a.cn[i] * e;
+    }
+    D = wave_sum(D);
+    V = wave_sum(V);
+    if ((threadIdx.x & 63) == 0) {
+        part[0][threadIdx.x >> 6] = D;
+        part[1][threadIdx.x >> 6] = V;
+    }
+    __syncthreads();
+    D = V = 0.0;
+    for (int t = 0; t < kThreads / 64; ++t) {
+        D += part[0][t];
+        V += part[1][t];
+    }
+    const bool spans = D > 0.0 && isfinite(D);  // a column that overflows or vanishes spans nothing
+    const int c = threadIdx.x & 15;
+    for (int d = threadIdx.x >> 4; d < a.nd; d += kThreads / 16) {
+        const double *q = a.proj + (size_t)d * Nt;
+        double v = 0.0;
+        for (int i = c; i < Nt; i += 16) v = fma(lds[i], q[i], v);
+        v = group_sum<16>(v);
+        if (c == 0) cs[d] = spans ? v : 0.0;
+    }
+    __syncthreads();
+    if (a.E) {
+        double *row = a.E + (size_t)j * a.cols;
+        if (a.d0 == 0) {
+            for (int i = threadIdx.x; i < a.cols; i += kThreads) row[i] = i < Nt ? lds[i] : 0.0;
+            if (threadIdx.x == 0) a.bin[j] = make_double4(w, D, V, 0.0);
+        }
+        __syncthreads();
+        for (int d = threadIdx.x; d < a.nd; d += kThreads)
+            row[Nt + ((a.d0 + d) & 3) * a.echunk + ((a.d0 + d) >> 2)] = cs[d];
+    } else if (threadIdx.x == 0) {
+        // (an earlier pass's maxima may stay: tails only grow towards the first vector)
+        double t = a.tail[j];
+        for (int d = a.nd - 1; d >= 0 && spans; --d) {
+            t += cs[d] * cs[d] / D;
+            atomicMax((unsigned long long *)&a.worst[d], (unsigned long long)__double_as_longlong(t));
+        }
+        a.tail[j] = spans ? t : 1.0;
+    }
+}
+
+// (G_k, H_k) = sum_i w_i (1, tau_i) e^{-wbar_k tau_i}, a wavefront per pair sum.
+__global__ __launch_bounds__(64) void k_pair_sums(int n_tau, double w0x2, double dW, const double *tau, const double *wh,
+                                                  double2 *GH)
+{
+    const double wbar = fma((double)blockIdx.x, dW, w0x2);
+    double g = 0.0, h = 0.0;
+    for (int i = threadIdx.x; i < n_tau; i += 64) {
+        const double e = wh[i] * exp(-wbar * tau[i]);
+        g += e;
+        h += e * tau[i];
+    }
+    g = wave_sum(g);
+    h = wave_sum(h);
+    if (threadIdx.x == 0) GH[blockIdx.x] = make_double2(g, h);
+}
+
+// The basis columns of E in the loop precision, [N_omega][4][chunk].
+template <typename R>
+__global__ __launch_bounds__(kThreads) void k_columns(int n, int n_tau, int cols, int echunk, int chunk, const double *E, R *col)
+{
+    const int x = blockIdx.x * kThreads + threadIdx.x;
+    if (x >= n) return;
+    const int t = x % chunk, q = x / chunk & 3, j = x / (4 * chunk);
+    col[x] = t < echunk ? (R)E[(size_t)j * cols + n_tau + q * echunk + t] : (R)0;
+}
+
 __global__ void k_init_walkers(int n_walkers, int n_omega, const double *a0, double *b, double *gsc, double *ginv,
                                double *rate)
 {
@@ -2772,17 +2873,17 @@ struct sail_problem {
     int tpl = 16, lanes = 1, ntau_pad = 16;
     int tpl_hint = 0;  // requested tau points per lane (0: automatic)
     // tables (device); E holds the exact kernel columns and the columns in the basis
-    double *d_omega = nullptr, *d_E = nullptr, *d_wh = nullptr, *d_Phit = nullptr;
+    double *d_tab = nullptr, *d_E = nullptr;  // d_tab holds the other tables
+    double *d_omega = nullptr, *d_wh = nullptr, *d_Phit = nullptr;
     // walker-independent residue tables of the sweep (FP64): (omega, D, V, 0) per
     // bin and the pair-sum table (G, H), with the constant C and the grid's omega_0, d_omega
     double *d_bin = nullptr, *d_GH = nullptr;
     double tC = 0.0, tw0 = 0.0, tdW = 0.0;
     // the basis: dimensions per chunk for either precision (dimension d lies in
     // chunk d mod 4, so the FP32 loop's shorter basis is a prefix of every
-    // chunk), the columns in it [N_omega][4][echunk] and its vectors times
-    // sqrt(wh), [n_tau][4][echunk]
+    // chunk), and its vectors times sqrt(wh), [n_tau][4][echunk]
     int dims64 = 1, dims32 = 1, echunk = 2;
-    std::vector<double> h_col, h_proj;
+    std::vector<double> h_proj;
     void *d_col = nullptr;  // columns in the loop precision, [N_omega][4][chunk()]
     int layout_precision = -1;
     int dims(int precision_) const { return precision_ == SAIL_FP32 ? dims32 : dims64; }
@@ -2868,8 +2969,7 @@ struct sail_problem {
     {
         (void)hipSetDevice(device);
         free_walkers();
-        dfree(d_omega); dfree(d_E); dfree(d_wh); dfree(d_Phit); dfree(d_Tabs);
-        dfree(d_col); dfree(d_bin); dfree(d_GH);
+        dfree(d_tab); dfree(d_E); dfree(d_Tabs); dfree(d_col);
         for (auto e : ev_start) (void)hipEventDestroy(e);
         for (auto e : ev_stop) (void)hipEventDestroy(e);
         if (done_ev) (void)hipEventDestroy(done_ev);
@@ -3397,16 +3497,11 @@ sail_status launch_sweep(sail_problem *p, int k0, int k1, const SweepParams &sp,
 // best: 2e-17 to 9e-17 rms, at most 2e-15, against 1e-16 to 4e-16 and 4e-15 of the
 // recurrence along tau that generated the columns before).  The FP32 loop takes
 // the first vectors, up to kBasisTol32 (squared 1e-8, below its rounding).  The
-// selection runs on at most kBasisSample columns spread over the grid and on
-// any column found outside their span.
+// selection runs on the host on kBasisSample columns spread over the grid; the
+// device projects every column on it, and those found outside their span join
+// the sample.
 constexpr double kBasisTol64 = 1e-7, kBasisTol32 = 1e-4, kBasisGreedy = 1e-8;
 constexpr int kBasisSample = 64;
-
-struct Basis {
-    std::vector<double> q;  // [dims][n_tau], orthonormal
-    std::vector<double> c;  // [n_omega][dims], columns in the basis
-    int dims = 0, dims64 = 0, dims32 = 0;  // vectors held; vectors each precision needs
-};
 
 double dot(const double *x, const double *y, int n)
 {
@@ -3464,213 +3559,222 @@ void principal_rows(std::vector<std::vector<double>> &b, std::vector<std::vector
     r = std::move(rr);
 }
 
-// a: [n_omega][n_tau] weighted columns
-Basis make_basis(const std::vector<double> &a, int n_omega, int n_tau)
-{
-    Basis b;
-    const int most = std::min(n_omega, n_tau);
-    std::vector<double> norm(n_omega);
-    for (int j = 0; j < n_omega; ++j) {
-        const double v = std::sqrt(dot(&a[(size_t)j * n_tau], &a[(size_t)j * n_tau], n_tau));
-        norm[j] = std::isfinite(v) ? v : 0.0;  // a column that overflows or vanishes spans nothing
-    }
-    std::vector<std::vector<double>> q, work;  // basis vectors; residuals of the sampled columns
-    std::vector<int> sampled;                  // which columns those are
-    std::vector<std::vector<double>> c;        // [dims][n_omega]
-    auto sample = [&](int j) {
-        if (!(norm[j] > 0.0)) return;
-        std::vector<double> v(&a[(size_t)j * n_tau], &a[(size_t)j * n_tau] + n_tau);
-        for (auto &x : v) x /= norm[j];
-        for (const auto &u : q) {
-            const double s = dot(u.data(), v.data(), n_tau);
-            for (int i = 0; i < n_tau; ++i) v[i] -= s * u[i];
-        }
-        work.push_back(std::move(v));
-        sampled.push_back(j);
-    };
-    const int ns = std::min(n_omega, kBasisSample);
-    for (int i = 0; i < ns; ++i) sample((int)((int64_t)i * (n_omega - 1) / std::max(1, ns - 1)));
-    std::vector<double> left(n_omega, 1.0);  // squared residual of each column relative to its norm
-    while ((int)q.size() < most) {
-        int pick = -1;
-        double big = kBasisGreedy;
-        for (size_t i = 0; i < work.size(); ++i) {
-            const double v = std::sqrt(dot(work[i].data(), work[i].data(), n_tau));
-            if (v > big) {
-                big = v;
-                pick = (int)i;
-            }
-        }
-        if (pick < 0) {
-            // the sample is spanned: is every column?
-            int j = (int)(std::max_element(left.begin(), left.end()) - left.begin());
-            if (q.empty() || !(left[j] > 0.25 * kBasisTol64 * kBasisTol64)) break;
-            const size_t had = work.size();
-            sample(j);
-            left[j] = 0.0;  // taken into the sample (its residual may be rounding only)
-            if (work.size() == had) break;
-            continue;
-        }
-        std::vector<double> u = work[pick];
-        for (int pass = 0; pass < 2; ++pass)
-            for (const auto &w : q) {
-                const double s = dot(w.data(), u.data(), n_tau);
-                for (int i = 0; i < n_tau; ++i) u[i] -= s * w[i];
-            }
-        const double un = std::sqrt(dot(u.data(), u.data(), n_tau));
-        if (!(un > 0.5 * big)) {  // nothing but rounding was left
-            std::fill(work[pick].begin(), work[pick].end(), 0.0);
-            continue;
-        }
-        for (auto &x : u) x /= un;
-        for (auto &v : work) {
-            const double s = dot(u.data(), v.data(), n_tau);
-            for (int i = 0; i < n_tau; ++i) v[i] -= s * u[i];
-        }
-        std::vector<double> cd(n_omega);
-        for (int j = 0; j < n_omega; ++j) {
-            cd[j] = dot(u.data(), &a[(size_t)j * n_tau], n_tau);
-            if (!(norm[j] > 0.0)) cd[j] = left[j] = 0.0;
-            else left[j] -= (cd[j] / norm[j]) * (cd[j] / norm[j]);
-        }
-        q.push_back(std::move(u));
-        c.push_back(std::move(cd));
-    }
-    b.dims = (int)q.size();
-    // principal directions of the sampled columns (a basis of more vectors than
-    // the sweep takes in registers in any precision stays as it is)
-    if (b.dims <= kBasisSample) {
-        std::vector<std::vector<double>> rows(b.dims), r;
-        for (int d = 0; d < b.dims; ++d)
-            for (int j : sampled) rows[d].push_back(c[d][j] / norm[j]);
-        principal_rows(rows, r);
-        std::vector<std::vector<double>> y(b.dims, std::vector<double>(n_tau, 0.0));
-        for (int d = 0; d < b.dims; ++d)
-            for (int e = 0; e < b.dims; ++e)
-                for (int i = 0; i < n_tau; ++i) y[d][i] += r[d][e] * q[e][i];
-        q = std::move(y);
-    }
-    // the rotations leave q orthonormal to some 1e-15 only, which S2 would
-    // show: once more, in 80 bits
-    for (int d = 0; d < b.dims; ++d) {
-        std::vector<long double> u(q[d].begin(), q[d].end());
-        auto with = [&](const double *w) {
-            long double t = 0.0L;
-            for (int i = 0; i < n_tau; ++i) t += (w ? (long double)w[i] : u[i]) * u[i];
-            return t;
-        };
-        for (int e = 0; e < d; ++e) {
-            const long double t = with(q[e].data());
-            for (int i = 0; i < n_tau; ++i) u[i] -= t * q[e][i];
-        }
-        const long double un = std::sqrt(with(nullptr));
-        for (int i = 0; i < n_tau; ++i) q[d][i] = (double)(u[i] / un);
-        for (int j = 0; j < n_omega; ++j) c[d][j] = norm[j] > 0.0 ? dot(q[d].data(), &a[(size_t)j * n_tau], n_tau) : 0.0;
-    }
-    // the vectors each precision needs: what the others hold of any column
-    // stays below its tolerance
-    std::vector<double> tail(n_omega, 0.0);
-    b.dims64 = b.dims32 = b.dims;
-    for (int d = b.dims - 1; d >= 1; --d) {
-        double w = 0.0;
-        for (int j = 0; j < n_omega; ++j) {
-            if (norm[j] > 0.0) tail[j] += (c[d][j] / norm[j]) * (c[d][j] / norm[j]);
-            w = std::max(w, tail[j]);
-        }
-        if (w <= kBasisTol64 * kBasisTol64) b.dims64 = d;
-        if (w <= kBasisTol32 * kBasisTol32) b.dims32 = d;
-        else break;
-    }
-    b.q.reserve((size_t)b.dims * n_tau);
-    for (const auto &u : q) b.q.insert(b.q.end(), u.begin(), u.end());
-    b.c.assign((size_t)n_omega * b.dims, 0.0);
-    for (int d = 0; d < b.dims; ++d)
-        for (int j = 0; j < n_omega; ++j) b.c[(size_t)j * b.dims + d] = c[d][j];
-    return b;
-}
+class BasisSample {
+public:
+    BasisSample(const sail_problem *p, const std::vector<double> &sw) : p_(p), sw_(sw) {}
 
-// Host tables of the problem and their device copies; independent of the
-// precision and the lane layout.
+    // takes column j into the sample; false if it was there or spans nothing
+    bool take(int j)
+    {
+        if (std::find(bins_.begin(), bins_.end(), j) != bins_.end()) return false;
+        const int n = p_->n_tau;
+        std::vector<double> v(n);
+        for (int i = 0; i < n; ++i) v[i] = sw_[i] * std::exp(-p_->omega[j] * p_->tau[i]);
+        const double norm = std::sqrt(dot(v.data(), v.data(), n));
+        if (!(norm > 0.0) || !std::isfinite(norm)) return false;
+        for (auto &x : v) x /= norm;
+        column_.push_back(v);
+        for (const auto &u : q_) {
+            const double s = dot(u.data(), v.data(), n);
+            for (int i = 0; i < n; ++i) v[i] -= s * u[i];
+        }
+        rest_.push_back(std::move(v));
+        bins_.push_back(j);
+        return true;
+    }
+
+    // extends the selection until it spans the sample to kBasisGreedy, and
+    // returns it rotated: [vectors][n_tau], orthonormal
+    std::vector<std::vector<double>> vectors()
+    {
+        const int n = p_->n_tau, most = std::min(p_->n_omega, n);
+        while ((int)q_.size() < most) {
+            int pick = -1;
+            double big = kBasisGreedy;
+            for (size_t i = 0; i < rest_.size(); ++i) {
+                const double v = std::sqrt(dot(rest_[i].data(), rest_[i].data(), n));
+                if (v > big) {
+                    big = v;
+                    pick = (int)i;
+                }
+            }
+            if (pick < 0) break;
+            std::vector<double> u = rest_[pick];
+            for (int pass = 0; pass < 2; ++pass)
+                for (const auto &w : q_) {
+                    const double s = dot(w.data(), u.data(), n);
+                    for (int i = 0; i < n; ++i) u[i] -= s * w[i];
+                }
+            const double un = std::sqrt(dot(u.data(), u.data(), n));
+            if (!(un > 0.5 * big)) {  // nothing but rounding was left
+                std::fill(rest_[pick].begin(), rest_[pick].end(), 0.0);
+                continue;
+            }
+            for (auto &x : u) x /= un;
+            for (auto &v : rest_) {
+                const double s = dot(u.data(), v.data(), n);
+                for (int i = 0; i < n; ++i) v[i] -= s * u[i];
+            }
+            q_.push_back(std::move(u));
+        }
+        std::vector<std::vector<double>> q = q_;
+        const int dims = (int)q.size();
+        // principal directions of the sampled columns (a basis of more vectors
+        // than the sweep takes in registers in any precision stays as it is)
+        if (dims <= kBasisSample) {
+            std::vector<std::vector<double>> rows(dims), r;
+            for (int d = 0; d < dims; ++d)
+                for (const auto &v : column_) rows[d].push_back(dot(q_[d].data(), v.data(), n));
+            principal_rows(rows, r);
+            for (int d = 0; d < dims; ++d) {
+                std::fill(q[d].begin(), q[d].end(), 0.0);
+                for (int e = 0; e < dims; ++e)
+                    for (int i = 0; i < n; ++i) q[d][i] += r[d][e] * q_[e][i];
+            }
+        }
+        // the rotations leave q orthonormal to some 1e-15 only, which S2 would
+        // show: once more, in 80 bits
+        for (int d = 0; d < dims; ++d) {
+            std::vector<long double> u(q[d].begin(), q[d].end());
+            for (int e = 0; e < d; ++e) {
+                long double t = 0.0L;
+                for (int i = 0; i < n; ++i) t += q[e][i] * u[i];
+                for (int i = 0; i < n; ++i) u[i] -= t * q[e][i];
+            }
+            long double t = 0.0L;
+            for (int i = 0; i < n; ++i) t += u[i] * u[i];
+            t = std::sqrt(t);
+            for (int i = 0; i < n; ++i) q[d][i] = (double)(u[i] / t);
+        }
+        return q;
+    }
+
+private:
+    const sail_problem *p_;
+    const std::vector<double> &sw_;
+    std::vector<int> bins_;                             // the sampled columns
+    std::vector<std::vector<double>> column_, rest_, q_;  // they, relative to their norms; what q_ leaves of them
+};
+
 sail_status build_tables(sail_problem *p)
 {
-    const int n_omega = p->n_omega, n_tau = p->n_tau;
-    std::vector<double> wh(n_tau), cn(n_tau), Phit(n_tau), sw(n_tau);
-    double C = 0.0;
-    for (int i = 0; i < n_tau; ++i) {
-        wh[i] = p->w[i] * p->cfac[i] * p->cfac[i];
-        Phit[i] = p->F[i] / p->cfac[i];
-        cn[i] = -(2.0 * wh[i]) * Phit[i];
-        sw[i] = std::sqrt(wh[i]);
-        C += wh[i] * Phit[i] * Phit[i];
-    }
-    // E_ji, D_j = sum_i w_i K_ij^2, V_j = sum_i c_i K_ij
-    std::vector<double> k((size_t)n_omega * n_tau), a(k.size()), bin(4 * (size_t)n_omega, 0.0);
-    for (int j = 0; j < n_omega; ++j) {
-        double d = 0.0, v = 0.0;
-        for (int i = 0; i < n_tau; ++i) {
-            const double e = std::exp(-p->omega[j] * p->tau[i]);
-            k[(size_t)j * n_tau + i] = e;
-            a[(size_t)j * n_tau + i] = sw[i] * e;
-            d += wh[i] * e * e;
-            v += cn[i] * e;
-        }
-        bin[4 * (size_t)j] = p->omega[j];
-        bin[4 * (size_t)j + 1] = d;
-        bin[4 * (size_t)j + 2] = v;
-    }
-    // (G_k, H_k) = sum_i w_i (1, tau_i) e^{-wbar_k tau_i} with wbar_k = 2 omega_0 + k d_omega
-    const double w0 = p->omega[0], dW = (p->omega[n_omega - 1] - p->omega[0]) / (double)(n_omega - 1);
-    std::vector<double> GH(2 * (size_t)(2 * n_omega - 1));
-    for (int kk = 0; kk < 2 * n_omega - 1; ++kk) {
-        const double wbar = 2.0 * w0 + (double)kk * dW;
-        double g = 0.0, h = 0.0;
-        for (int i = 0; i < n_tau; ++i) {
-            const double e = wh[i] * std::exp(-wbar * p->tau[i]);
-            g += e;
-            h += e * p->tau[i];
-        }
-        GH[2 * (size_t)kk] = g;
-        GH[2 * (size_t)kk + 1] = h;
-    }
-    const Basis b = make_basis(a, n_omega, n_tau);
-    p->dims64 = round_dims(SAIL_FP64, b.dims64);
-    p->dims32 = round_dims(SAIL_FP32, b.dims32);
-    const int ec = p->echunk = chunk_stride<double>(p->dims64), cols = p->cols();
-    p->h_col.assign((size_t)n_omega * 4 * ec, 0.0);
-    p->h_proj.assign((size_t)n_tau * 4 * ec, 0.0);
-    std::vector<double> E((size_t)n_omega * cols, 0.0);
-    for (int d = 0; d < std::min(b.dims, 4 * p->dims64); ++d) {
-        const int at = (d % 4) * ec + d / 4;
-        for (int j = 0; j < n_omega; ++j) p->h_col[(size_t)j * 4 * ec + at] = b.c[(size_t)j * b.dims + d];
-        for (int i = 0; i < n_tau; ++i) p->h_proj[(size_t)i * 4 * ec + at] = sw[i] * b.q[(size_t)d * n_tau + i];
-    }
-    for (int j = 0; j < n_omega; ++j) {
-        std::copy(&k[(size_t)j * n_tau], &k[(size_t)j * n_tau] + n_tau, &E[(size_t)j * cols]);
-        std::copy(&p->h_col[(size_t)j * 4 * ec], &p->h_col[(size_t)j * 4 * ec] + 4 * ec, &E[(size_t)j * cols + n_tau]);
-    }
+    const int No = p->n_omega, Nt = p->n_tau;
+    const size_t pairs = 2 * (size_t)No - 1;
+    // one array: what the host makes (omega, tau, wh, Phit, cn), then the
+    // pass's vectors and results, then the tables of bins and pair sums
+    auto whole = [](size_t n) { return (n + 31) & ~(size_t)31; };
+    const size_t o_tau = whole(No), o_wh = o_tau + whole(Nt), o_Phit = o_wh + whole(Nt), o_cn = o_Phit + whole(Nt),
+                 o_proj = o_cn + whole(Nt), o_worst = o_proj + (size_t)kBasisPass * Nt, o_tail = o_worst + kBasisPass,
+                 o_bin = o_tail + whole(No), o_GH = o_bin + 4 * whole(No), size = o_GH + 2 * pairs;
     sail_status st;
-    if ((st = dalloc(&p->d_E, E.size())) || (st = dalloc(&p->d_wh, n_tau)) || (st = dalloc(&p->d_Phit, n_tau)) ||
-        (st = dalloc(&p->d_bin, bin.size())) || (st = dalloc(&p->d_GH, GH.size())))
-        return st;
+    if ((st = dalloc(&p->d_tab, size))) return st;
+    double *tab = p->d_tab;
+    p->d_omega = tab;
+    p->d_wh = tab + o_wh;
+    p->d_Phit = tab + o_Phit;
+    p->d_bin = tab + o_bin;
+    p->d_GH = tab + o_GH;
+    std::vector<double> h(o_proj, 0.0), sw(Nt);
+    std::copy(p->omega.begin(), p->omega.end(), h.begin());
+    std::copy(p->tau.begin(), p->tau.end(), h.begin() + o_tau);
+    double C = 0.0;
+    for (int i = 0; i < Nt; ++i) {
+        const double wh = p->w[i] * p->cfac[i] * p->cfac[i], Phit = p->F[i] / p->cfac[i];
+        h[o_wh + i] = wh;
+        h[o_Phit + i] = Phit;
+        h[o_cn + i] = -(2.0 * wh) * Phit;
+        sw[i] = std::sqrt(wh);
+        C += wh * Phit * Phit;
+    }
     p->tC = C;
-    p->tw0 = w0;
-    p->tdW = dW;
-    auto up = [&](double *d, const std::vector<double> &h) {
-        return hipMemcpy(d, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice);
+    p->tw0 = p->omega[0];
+    p->tdW = (p->omega[No - 1] - p->omega[0]) / (double)(No - 1);
+    SAIL_HIP(hipMemcpy(tab, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice));
+    hipLaunchKernelGGL(k_pair_sums, dim3((unsigned)pairs), dim3(64), 0, nullptr, Nt, 2.0 * p->tw0, p->tdW,
+                       (const double *)(tab + o_tau), (const double *)p->d_wh, (double2 *)p->d_GH);
+    SAIL_HIP(hipGetLastError());
+    TableArgs a{};
+    a.n_omega = No;
+    a.n_tau = Nt;
+    a.omega = tab;
+    a.tau = tab + o_tau;
+    a.wh = p->d_wh;
+    a.cn = tab + o_cn;
+    a.proj = tab + o_proj;
+    a.worst = tab + o_worst;
+    a.tail = tab + o_tail;
+    a.bin = (double4 *)p->d_bin;
+    std::vector<std::vector<double>> q;
+    std::vector<double> up((size_t)kBasisPass * Nt);
+    int loaded = -1;  // first vector of the pass on the device
+    auto pass = [&](int d0, int nd) -> sail_status {
+        a.d0 = d0;
+        a.nd = nd;
+        if (loaded != d0) {
+            for (int d = 0; d < nd; ++d)
+                for (int i = 0; i < Nt; ++i) up[(size_t)d * Nt + i] = sw[i] * q[d0 + d][i];
+            SAIL_HIP(hipMemcpy(tab + o_proj, up.data(), sizeof(double) * (size_t)nd * Nt, hipMemcpyHostToDevice));
+            loaded = d0;
+        }
+        hipLaunchKernelGGL(k_tables, dim3(No), dim3(kThreads), sizeof(double) * Nt, nullptr, a);
+        SAIL_HIP(hipGetLastError());
+        return SAIL_OK;
     };
-    hipError_t e = up(p->d_E, E);
-    if (e == hipSuccess) e = up(p->d_wh, wh);
-    if (e == hipSuccess) e = up(p->d_Phit, Phit);
-    if (e == hipSuccess) e = up(p->d_bin, bin);
-    if (e == hipSuccess) e = up(p->d_GH, GH);
-    if (e != hipSuccess) return fail(SAIL_EDEVICE, std::string("table upload: ") + hipGetErrorString(e));
+    BasisSample sample(p, sw);
+    const int ns = std::min(No, kBasisSample);
+    for (int i = 0; i < ns; ++i) sample.take((int)((int64_t)i * (No - 1) / std::max(1, ns - 1)));
+    std::vector<double> got(kBasisPass + No), worst;
+    for (;;) {
+        q = sample.vectors();
+        loaded = -1;
+        // what every column holds from each vector on, last vectors first
+        const int dims = (int)q.size();
+        worst.assign(dims, 0.0);
+        std::fill(got.begin(), got.end(), 0.0);
+        SAIL_HIP(hipMemcpy(tab + o_worst, got.data(), sizeof(double) * got.size(), hipMemcpyHostToDevice));
+        for (int d0 = (dims - 1) / kBasisPass * kBasisPass; dims > 0 && d0 >= 0; d0 -= kBasisPass) {
+            const int nd = std::min(kBasisPass, dims - d0);
+            if ((st = pass(d0, nd))) return st;
+            SAIL_HIP(hipMemcpy(got.data(), tab + o_worst, sizeof(double) * got.size(), hipMemcpyDeviceToHost));
+            std::copy(got.begin(), got.begin() + nd, worst.begin() + d0);
+        }
+        // columns outside the span: take some and select on
+        std::vector<int> out;
+        for (int j = 0; dims > 0 && j < No; ++j)
+            if (1.0 - got[kBasisPass + j] > 0.25 * kBasisTol64 * kBasisTol64) out.push_back(j);
+        bool more = false;
+        const int want = std::min<int>((int)out.size(), 16);
+        for (int i = 0; i < want; ++i) more |= sample.take(out[(size_t)i * out.size() / want]);
+        if (!more) break;
+    }
+    const int dims = (int)q.size();
+    int dims64 = dims, dims32 = dims;
+    for (int d = dims - 1; d >= 1; --d) {
+        if (worst[d] <= kBasisTol64 * kBasisTol64) dims64 = d;
+        if (worst[d] <= kBasisTol32 * kBasisTol32) dims32 = d;
+    }
+    p->dims64 = round_dims(SAIL_FP64, dims64);
+    p->dims32 = round_dims(SAIL_FP32, dims32);
+    const int ec = p->echunk = chunk_stride<double>(p->dims64), kept = std::min(dims, 4 * p->dims64);
+    p->h_proj.assign((size_t)Nt * 4 * ec, 0.0);
+    for (int d = 0; d < kept; ++d)
+        for (int i = 0; i < Nt; ++i) p->h_proj[(size_t)i * 4 * ec + (d % 4) * ec + d / 4] = sw[i] * q[d][i];
+    if ((st = dalloc(&p->d_E, (size_t)No * p->cols()))) return st;
+    a.E = p->d_E;
+    a.cols = p->cols();
+    a.echunk = ec;
+    int d0 = 0;
+    do {
+        if ((st = pass(d0, std::min(kBasisPass, kept - d0)))) return st;
+        d0 += kBasisPass;
+    } while (d0 < kept);
     return SAIL_OK;
 }
 
 // The nominal lane layout: TPL tau points per lane (16 unless requested
 // otherwise; more only when N_tau needs it), a power-of-two number of lanes per
 // walker, tau padded to lanes * TPL; and the columns in the loop precision.
-sail_status build_layout(sail_problem *p, int precision)
+sail_status build_layout(sail_problem *p, int precision, hipStream_t stream)
 {
     const int n_omega = p->n_omega, n_tau = p->n_tau;
     const int tpl_max = precision == SAIL_FP32 ? 32 : 16;
@@ -3700,16 +3804,13 @@ sail_status build_layout(sail_problem *p, int precision)
     const sail_status st = dalloc(&col, rsz * n);
     if (st) return st;
     p->d_col = col;
-    hipError_t e;
-    if (precision == SAIL_FP32) {
-        std::vector<float> f(n, 0.f);
-        for (size_t r = 0; r < (size_t)n_omega * 4; ++r)
-            for (int t = 0; t < std::min(ec, ck); ++t) f[r * ck + t] = (float)p->h_col[r * ec + t];
-        e = hipMemcpy(col, f.data(), rsz * n, hipMemcpyHostToDevice);
-    } else {
-        e = hipMemcpy(col, p->h_col.data(), rsz * n, hipMemcpyHostToDevice);
-    }
-    if (e != hipSuccess) return fail(SAIL_EDEVICE, std::string("table upload: ") + hipGetErrorString(e));
+    auto columns = [&](auto *to) {
+        hipLaunchKernelGGL(k_columns, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream, (int)n, n_tau,
+                           p->cols(), ec, ck, (const double *)p->d_E, to);
+    };
+    if (precision == SAIL_FP32) columns((float *)col);
+    else columns((double *)col);
+    SAIL_HIP(hipGetLastError());
     p->layout_precision = precision;
     return SAIL_OK;
 }
@@ -3801,7 +3902,8 @@ size_t table_bytes(int n_omega, int n_tau, int precision)
 {
     const size_t rsz = precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
     const size_t No = (size_t)n_omega, dims = (size_t)std::min(n_tau, n_omega) + kBasisPad;
-    return sizeof(double) * (5 * No + No * (n_tau + dims) + 2 * (size_t)n_tau + 2 * (2 * No - 1)) + rsz * No * dims +
+    return sizeof(double) * (6 * No + No * (n_tau + dims) + (4 + kBasisPass) * (size_t)n_tau + kBasisPass + 2 * (2 * No - 1)) +
+           rsz * No * dims +
            12 * 256;
 }
 
@@ -4716,21 +4818,17 @@ sail_status sail_problem_create(const double *omega, int n_omega, const double *
     if (kernel_mode == SAIL_K_BIN_EXACT)
         for (int i = 0; i < n_tau; ++i)
             if (tau[i] > 0.0) p->cfac[i] = (std::exp(0.5 * dw * tau[i]) - std::exp(-0.5 * dw * tau[i])) / (kTwoPi * tau[i]);
-    if ((st = dalloc(&p->d_omega, n_omega))) {
-        delete p;
-        return st;
-    }
-    if (hipMemcpy(p->d_omega, p->omega.data(), sizeof(double) * n_omega, hipMemcpyHostToDevice) != hipSuccess) {
-        delete p;
-        return fail(SAIL_EDEVICE, "table upload failed");
-    }
     if ((st = build_tables(p))) {
         delete p;
         return st;
     }
-    if ((st = build_layout(p, SAIL_FP64))) {
+    if ((st = build_layout(p, SAIL_FP64, nullptr))) {
         delete p;
         return st;
+    }
+    if (hipStreamSynchronize(nullptr) != hipSuccess) {  // other streams use them
+        delete p;
+        return fail(SAIL_EDEVICE, "table kernels failed");
     }
     *out = p;
     return SAIL_OK;
@@ -4858,7 +4956,7 @@ sail_status sail_walkers_init(sail_problem_t p, int n_walkers, uint64_t seed, in
     if (st) return st;
     SAIL_HIP(hipStreamSynchronize(stream));
     p->free_walkers();
-    if ((st = build_layout(p, precision))) return st;
+    if ((st = build_layout(p, precision, stream))) return st;
     const int No = p->n_omega, ntp = p->ntau_pad;
     const size_t rsz = precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
     const size_t phi_bytes = rsz * (size_t)n_walkers * 4 * p->chunk(precision);
