@@ -242,7 +242,7 @@ constexpr int rec_stride(int G, bool walk) { return (walk ? G * (kRecWords + 1 +
 // A split sweep's walker: records of three batches, bins of four, the move
 // width; and a wavefront's masks of shared bins of three batches.
 constexpr int kSplitHits = 3 * 4;
-constexpr int kSplitStride = 3 * 4 * kRecWords + 4 * 4 + 2;
+constexpr int split_stride(int G) { return 3 * G * kRecWords + 4 * G + 2; }
 
 // A split walk's walker: of two batches of 16 proposals, the records (r - 1 or
 // its draw, 1/r, the threshold and the uniform bins) and the walk's steps (two
@@ -258,8 +258,7 @@ constexpr int chunk_stride(int m) { return sizeof(R) == 8 ? (m + 1) & ~1 : (m + 
 // larger basis runs the general variant (class 0).
 constexpr int kDims64[4] = {2, 4, 6, 8}, kDims32[4] = {2, 3, 4, 6};
 constexpr int kBasisClasses = 9;
-constexpr int kBasisPad = 12;  // dimensions a basis may be padded by
-constexpr int kPhiRow = 72;    // coordinates per walker up to which the read-out keeps its own rows
+constexpr int kReadRows = 16;  // walkers whose reconstructions are read at once, at least
 // Dimensions per chunk for a basis of n dimensions.
 int round_dims(int precision, int n)
 {
@@ -359,10 +358,10 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
 {
     constexpr bool WALK = MODE == kSweepWalk, TRACE = MODE != kSweepFast;
     constexpr int MR = M > 0 ? M : 1;
-    const int RSTR = !SPLIT ? rec_stride(G, WALK) : WALK ? (int)walk_split_stride(a.walk_len) : kSplitStride;
+    const int RSTR = !SPLIT ? rec_stride(G, WALK) : WALK ? (int)walk_split_stride(a.walk_len) : split_stride(G);
     static_assert(M > 0 || !LDSC, "the general variant reads its columns from memory");
-    static_assert(!SPLIT || (WALK ? G == 16 && LDSC && LDSB : G == 4 && MODE == kSweepFast), "split sweeps");
-    constexpr bool ALLB = LDSB && (!SPLIT || WALK);  // whole spectra in LDS; split sweeps keep the first bins there
+    static_assert(!SPLIT || (G == 16 ? LDSC && LDSB : G == 4 && MODE == kSweepFast), "split sweeps");
+    constexpr bool ALLB = LDSB && (!SPLIT || G == 16);  // whole spectra in LDS; split sweeps keep the first bins there
     const int nthr = SPLIT ? 128 * a.pairs : (int)blockDim.x;
     if (SPLIT && (int)threadIdx.x >= nthr) return;
     const int lane = threadIdx.x & 63;
@@ -391,7 +390,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
     // records, columns and spectra in LDS
     double *myrec = lds + ws * RSTR;
     const R *colg = (const R *)a.col;
-    R *col_s = (R *)(lds + wpb * RSTR + (SPLIT && !WALK ? (wpb >> 4) * kSplitHits : 0));
+    R *col_s = (R *)(lds + wpb * RSTR + (SPLIT && G == 4 ? (wpb >> 4) * kSplitHits : 0));
     if constexpr (LDSC) {
         const size_t n16 = (size_t)No * 4 * ms * sizeof(R) / 16;
         for (size_t i = threadIdx.x; i < n16; i += nthr) ((float4 *)col_s)[i] = ((const float4 *)colg)[i];
@@ -931,14 +930,16 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
                     load_pair(np_, ns_, npr);
                     stage_bins(bsl, q1 + c, np_, ns_);
                     bsl = (bsl + 1) & 3;
-                    // the walkers' lanes of this wavefront mirror the chain's
-                    ops = (uint32_t)op | (uint32_t)os << 16;
-                    nps = (uint32_t)np_ | (uint32_t)ns_ << 16;
+                    if constexpr (!ALLB) {
+                        // the walkers' lanes of this wavefront mirror the chain's
+                        ops = (uint32_t)op | (uint32_t)os << 16;
+                        nps = (uint32_t)np_ | (uint32_t)ns_ << 16;
 #pragma unroll
-                    for (int t = 0; t < G; ++t) {
-                        const uint32_t w = of_owner_word(ops, t);
-                        const uint64_t h = shared_bins(t, (w & 0xffffu) * 0x10001u, (w >> 16) * 0x10001u);
-                        if (lane == 0) hits[rs * G + t] = h;
+                        for (int t = 0; t < G; ++t) {
+                            const uint32_t w = of_owner_word(ops, t);
+                            const uint64_t h = shared_bins(t, (w & 0xffffu) * 0x10001u, (w >> 16) * 0x10001u);
+                            if (lane == 0) hits[rs * G + t] = h;
+                        }
                     }
                     stage(rs, q0 + c, op, os, x2, x3, pr);
                     rs = rs == 2 ? 0 : rs + 1;
@@ -968,6 +969,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         Place opl, osl, npl, nsl;  // of op, os, np_ and ns_
         double lbp = 0.0, lbs = 0.0;
         auto load_next = [&](const double own_bins) __attribute__((always_inline)) {
+            if constexpr (ALLB) return;
             np_ = __double2loint(own_bins);
             ns_ = __double2hiint(own_bins);
             npl = place_of(np_);
@@ -998,34 +1000,36 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
             bool last = false;
             for (q0 = 0; q0 < No; q0 += G) {
                 const int bn = (bsl + 1) & 3, rn = rs == 2 ? 0 : rs + 1;  // the next batch's slots
-                const double own_bins = *bins_at(bn, c);
                 const bool ends = q0 + G >= No;
-                uint64_t hit[G];
+                uint64_t hit[G] = {};
+                if constexpr (!ALLB) {
+                    const double own_bins = *bins_at(bn, c);
 #pragma unroll
-                for (int t = 0; t < G; ++t) hit[t] = uniform(hits[rs * G + t]);
-                // this batch's spectrum values have arrived (waited for before
-                // the stores below are issued, so that nothing waits for those)
-                asm volatile("" : "+v"(nbp), "+v"(nbs));
-                if (__builtin_amdgcn_inverse_ballot_w64(accm & validm)) {
-                    put(opl, obp);
-                    put(osl, obs);
+                    for (int t = 0; t < G; ++t) hit[t] = uniform(hits[rs * G + t]);
+                    // this batch's spectrum values have arrived (waited for before
+                    // the stores below are issued, so that nothing waits for those)
+                    asm volatile("" : "+v"(nbp), "+v"(nbs));
+                    if (__builtin_amdgcn_inverse_ballot_w64(accm & validm)) {
+                        put(opl, obp);
+                        put(osl, obs);
+                    }
+                    if constexpr (LDSB) {
+                        nbp = npl.mem == kDropStore ? lbp : nbp;
+                        nbs = nsl.mem == kDropStore ? lbs : nbs;
+                    }
+                    obp = fp ? fbp : nbp;
+                    obs = fs ? fbs : nbs;
+                    fp = fs = 0;
+                    asm volatile("" : "+v"(fp), "+v"(fs));
+                    accm = 0;
+                    op = np_;
+                    os = ns_;
+                    opl = npl;
+                    osl = nsl;
+                    load_next(own_bins);
+                    ops = (uint32_t)op | (uint32_t)os << 16;
+                    nps = (uint32_t)np_ | (uint32_t)ns_ << 16;
                 }
-                if constexpr (LDSB) {
-                    nbp = npl.mem == kDropStore ? lbp : nbp;
-                    nbs = nsl.mem == kDropStore ? lbs : nbs;
-                }
-                obp = fp ? fbp : nbp;
-                obs = fs ? fbs : nbs;
-                fp = fs = 0;
-                asm volatile("" : "+v"(fp), "+v"(fs));
-                accm = 0;
-                op = np_;
-                os = ns_;
-                opl = npl;
-                osl = nsl;
-                load_next(own_bins);
-                ops = (uint32_t)op | (uint32_t)os << 16;
-                nps = (uint32_t)np_ | (uint32_t)ns_ << 16;
 #pragma unroll
                 for (int t = 0; t < G; ++t) {
                     // the next proposal's columns (its bins were read a proposal
@@ -1034,7 +1038,12 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
                     rows(__double2loint(next_bins), __double2hiint(next_bins), nx);
                     fetch(t + 1 < G ? rec_at(rs, t + 1) : rec_at(rn, 0), nx);
                     next_bins = t + 2 < G ? *bins_at(bsl, t + 2) : *bins_at(bn, t + 2 - G);
-                    body(t, cur, obp, obs, hit[t]);
+                    if constexpr (ALLB) {
+                        body(t, cur, bsp[cur.p], bsp[cur.s], 0);
+                        wave_lds_sync();
+                    } else {
+                        body(t, cur, obp, obs, hit[t]);
+                    }
                     // keep each proposal's code together (bounds register pressure)
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -1053,9 +1062,11 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
             }
             if (last) break;
         }
-        if (__builtin_amdgcn_inverse_ballot_w64(accm & validm)) {
-            put(opl, obp);
-            put(osl, obs);
+        if constexpr (!ALLB) {
+            if (__builtin_amdgcn_inverse_ballot_w64(accm & validm)) {
+                put(opl, obp);
+                put(osl, obs);
+            }
         }
     } else if constexpr (WALK) {
         // Sec. 2.3 index selection: from the uniform p, s of each proposal,
@@ -1265,11 +1276,11 @@ __global__ __launch_bounds__(2 * kSweepThreads) void k_sweep_split(SweepArgs a)
     sweep_block<R, M, 4, LDSC, LDSB, kSweepFast, true>(a, blockIdx.x, lds);
 }
 
-template <typename R, int M>
-__global__ __launch_bounds__(2 * kSweepThreads) void k_sweep_walk(SweepArgs a)
+template <typename R, int M, int MODE>
+__global__ __launch_bounds__(2 * kSweepThreads) void k_sweep_split16(SweepArgs a)
 {
     extern __shared__ __align__(16) double lds[];
-    sweep_block<R, M, 16, true, true, kSweepWalk, true>(a, blockIdx.x, lds);
+    sweep_block<R, M, 16, true, true, MODE, true>(a, blockIdx.x, lds);
 }
 
 // Many problems in one launch: problem q owns workgroups [first[q], first[q + 1]);
@@ -2899,7 +2910,8 @@ struct sail_problem {
     double chi2_unit = NAN;
     double *d_b = nullptr, *d_gsc = nullptr, *d_ginv = nullptr, *d_chi2 = nullptr, *d_rate = nullptr;
     void *d_phi = nullptr;  // [N_w][4][chunk()] in the loop precision
-    void *d_Phi = nullptr;  // [N_w][ntau_pad], filled when reconstructions are read; absent beside a large basis
+    void *d_Phi = nullptr;  // [read_rows][ntau_pad], filled when reconstructions are read
+    int read_rows = 0;
     double *d_a0 = nullptr, *d_tmp = nullptr, *d_teff = nullptr;  // d_teff: imprint strength of the last event
     double *d_part = nullptr;               // partial sums of the averaged spectrum
     unsigned long long *d_hist = nullptr;   // counts of the residue histogram, kept from its first call
@@ -3334,7 +3346,7 @@ SweepPlan plan_sweep(const sail_problem *p, bool split, int lanes, int threads, 
     SweepPlan s{split, lanes, threads, walkers, 0, 0, 0,
                 sizeof(double) * (!split ? (size_t)walkers * rec_stride(lanes, walk)
                                   : walk ? (size_t)walkers * walk_split_stride(walk_len)
-                                         : (size_t)walkers * kSplitStride + (size_t)walkers / 16 * kSplitHits)};
+                                         : (size_t)walkers * split_stride(lanes) + (lanes == 4 ? (size_t)walkers / 16 * kSplitHits : 0))};
     const size_t col = column_bytes(p->n_omega, p->chunk(p->precision),
                                     p->precision == SAIL_FP32 ? sizeof(float) : sizeof(double));
     if (basis_class(p->precision, p->dims(p->precision)) == 0) return s;
@@ -3346,7 +3358,7 @@ SweepPlan plan_sweep(const sail_problem *p, bool split, int lanes, int threads, 
         const size_t all = !split || !walk ? spec
                                            : ((spec + 15) & ~(size_t)15) + (size_t)p->n_omega * sizeof(double4) +
                                                  (size_t)(2 * p->n_omega - 1) * sizeof(double2);
-        if ((!split || walk) && spectra && s.shm + all <= budget) {
+        if (!(split && lanes == 4) && spectra && s.shm + all <= budget) {
             s.shm += all;
             s.spectra_lds = 1;
         }
@@ -3357,7 +3369,7 @@ SweepPlan plan_sweep(const sail_problem *p, bool split, int lanes, int threads, 
         // 22.9 to 20.6 ms and 22.9 to 18.7 ms).  Smaller workgroups mean
         // spectra that the caches hold, where the extra instructions lose 2 %
         // (24 FP64 jobs: 27.2 to 27.8 ms; band: 26.0 to 26.6 ms).
-        if (split && !walk && threads == 2 * kSweepThreads) {
+        if (split && lanes == 4 && threads == 2 * kSweepThreads) {
             const int slots = (int)((budget - s.shm) / (sizeof(double) * (size_t)walkers));
             s.resident = std::min(std::max(slots - 1, 0), p->n_omega);
             if (s.resident) s.shm += sizeof(double) * (size_t)walkers * (s.resident + 1);
@@ -3398,6 +3410,10 @@ SweepPlan plan_alone(const sail_problem *p, int mode, int walk_len)
         const SweepPlan w = sized(true, 16, true);
         return w.spectra_lds ? w : sized(false, 8, true);
     }
+    if (n * 16 <= (size_t)kSweepThreads * kCUs) {
+        const SweepPlan t = sized(true, 16, true);
+        if (t.spectra_lds) return t;
+    }
     const SweepPlan s = sized(false, 16, true);
     return s.spectra_lds ? s : sized(true, 4, false);
 }
@@ -3415,11 +3431,15 @@ void launch_sweep_m(const SweepArgs &a, int blocks, const SweepPlan &s, int mode
     if constexpr (M > 0) {
         if (mode == kSweepWalk) {
             if (s.split) {
-                hipLaunchKernelGGL((k_sweep_walk<R, M>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
+                hipLaunchKernelGGL((k_sweep_split16<R, M, kSweepWalk>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
                 return;
             }
             if (s.spectra_lds) return launch_sweep_k<R, M, 8, true, true, kSweepWalk>(a, blocks, s, stream);
             return launch_sweep_k<R, M, 8, false, false, kSweepWalk>(a, blocks, s, stream);
+        }
+        if (s.split && s.lanes == 16) {
+            hipLaunchKernelGGL((k_sweep_split16<R, M, kSweepFast>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
+            return;
         }
         if (s.spectra_lds) return launch_sweep_k<R, M, 16, true, true, kSweepFast>(a, blocks, s, stream);
         if (s.resident)
@@ -3502,6 +3522,10 @@ sail_status launch_sweep(sail_problem *p, int k0, int k1, const SweepParams &sp,
 // the sample.
 constexpr double kBasisTol64 = 1e-7, kBasisTol32 = 1e-4, kBasisGreedy = 1e-8;
 constexpr int kBasisSample = 64;
+// Vectors a footprint reckons with.  Decaying kernels give 5 to 25; weights that
+// turn the columns into separate Gaussians reach 67 when they span the whole
+// range of a double.
+constexpr int kBasisMost = 96;
 
 double dot(const double *x, const double *y, int n)
 {
@@ -3774,9 +3798,9 @@ sail_status build_tables(sail_problem *p)
 // The nominal lane layout: TPL tau points per lane (16 unless requested
 // otherwise; more only when N_tau needs it), a power-of-two number of lanes per
 // walker, tau padded to lanes * TPL; and the columns in the loop precision.
-sail_status build_layout(sail_problem *p, int precision, hipStream_t stream)
+sail_status build_layout(sail_problem *p, int precision)
 {
-    const int n_omega = p->n_omega, n_tau = p->n_tau;
+    const int n_tau = p->n_tau;
     const int tpl_max = precision == SAIL_FP32 ? 32 : 16;
     int tpl = 16;
     auto tile_ok = [&](int v) { return v == tpl_max || v == tpl_max / 2 || v == tpl_max / 4; };
@@ -3795,6 +3819,13 @@ sail_status build_layout(sail_problem *p, int precision, hipStream_t stream)
     p->tpl = tpl;
     p->lanes = lanes;
     p->ntau_pad = lanes * tpl;
+    return SAIL_OK;
+}
+
+// The sweep's columns in the loop precision.
+sail_status build_columns(sail_problem *p, int precision, hipStream_t stream)
+{
+    const int n_omega = p->n_omega, n_tau = p->n_tau;
     if (p->layout_precision == precision) return SAIL_OK;
     dfree(p->d_col);
     p->layout_precision = -1;
@@ -3897,13 +3928,16 @@ size_t max_padding(int n_tau, int precision)
 }
 
 // Device bytes of a problem's tables, each rounded as the allocator rounds it;
-// the basis has at most min(n_tau, n_omega) dimensions.
+// the basis has at most min(n_tau, n_omega, kBasisMost) dimensions.
 size_t table_bytes(int n_omega, int n_tau, int precision)
 {
     const size_t rsz = precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
-    const size_t No = (size_t)n_omega, dims = (size_t)std::min(n_tau, n_omega) + kBasisPad;
-    return sizeof(double) * (6 * No + No * (n_tau + dims) + (4 + kBasisPass) * (size_t)n_tau + kBasisPass + 2 * (2 * No - 1)) +
-           rsz * No * dims +
+    const size_t No = (size_t)n_omega;
+    const int most = std::min(std::min(n_tau, n_omega), kBasisMost);
+    const size_t d64 = 4 * (size_t)chunk_stride<double>(round_dims(SAIL_FP64, most));
+    const size_t d32 = 4 * (size_t)chunk_stride<float>(round_dims(SAIL_FP32, most));
+    return sizeof(double) * (6 * No + No * (n_tau + d64) + (4 + kBasisPass) * (size_t)n_tau + kBasisPass + 2 * (2 * No - 1)) +
+           rsz * No * (precision == SAIL_FP32 ? d32 : d64) +
            12 * 256;
 }
 
@@ -4397,11 +4431,11 @@ struct ServedJob {
 };
 
 // Device bytes a served job takes from the arena: the problem at its
-// precision, the FP64 tables sail_problem_create builds first, the schedule,
-// a larger event log if needed, the mean-spectrum output and alignment.
+// precision, the schedule, a larger event log if needed, the mean-spectrum
+// output and alignment.
 size_t served_job_bytes(int n_omega, int n_tau, int n_walkers, int precision, int n_T, int branch_every)
 {
-    size_t b = sail_footprint_bytes(n_omega, n_tau, n_walkers, precision) + table_bytes(n_omega, n_tau, SAIL_FP64);
+    size_t b = sail_footprint_bytes(n_omega, n_tau, n_walkers, precision);
     b += sizeof(double) * ((size_t)n_T + (size_t)n_omega);
     const int events = n_T / branch_every + 1;
     if (events > 64) b += (size_t)std::max(events, 128) * (4 * sizeof(double) + 2 * sizeof(int32_t));
@@ -4752,8 +4786,8 @@ size_t sail_footprint_bytes(int n_omega, int n_tau, int n_walkers, int precision
     if (n_omega <= 0 || n_tau <= 0 || n_walkers < 0) return 0;
     const size_t rsz = precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
     const size_t No = (size_t)n_omega, Nw = (size_t)n_walkers;
-    // a basis too large for kPhiRow coordinates per walker goes without the read-out's rows
-    const size_t walkers = sizeof(double) * Nw * (No + 4) + rsz * Nw * (max_padding(n_tau, precision) + kPhiRow) + sizeof(int32_t) * (3 * Nw + 4) +
+    // (a walker's coordinates and its share of the read-out's rows: a padded row)
+    const size_t walkers = sizeof(double) * Nw * (No + 4) + rsz * (Nw + kReadRows) * max_padding(n_tau, precision) + sizeof(int32_t) * (3 * Nw + 4) +
                            sizeof(double) * (No + std::max<size_t>(No, 64) + No * (size_t)mean_spans(n_walkers)) + 64 * (4 * sizeof(double) + 2 * sizeof(int32_t)) +
                            sizeof(BranchTree);
     return table_bytes(n_omega, n_tau, precision) + walkers;
@@ -4822,7 +4856,7 @@ sail_status sail_problem_create(const double *omega, int n_omega, const double *
         delete p;
         return st;
     }
-    if ((st = build_layout(p, SAIL_FP64, nullptr))) {
+    if ((st = build_layout(p, SAIL_FP64))) {
         delete p;
         return st;
     }
@@ -4956,20 +4990,21 @@ sail_status sail_walkers_init(sail_problem_t p, int n_walkers, uint64_t seed, in
     if (st) return st;
     SAIL_HIP(hipStreamSynchronize(stream));
     p->free_walkers();
-    if ((st = build_layout(p, precision, stream))) return st;
+    if ((st = build_layout(p, precision)) || (st = build_columns(p, precision, stream))) return st;
     const int No = p->n_omega, ntp = p->ntau_pad;
     const size_t rsz = precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
     const size_t phi_bytes = rsz * (size_t)n_walkers * 4 * p->chunk(precision);
     char *phi = nullptr, *Phi = nullptr;
     if ((st = dalloc(&phi, phi_bytes))) return st;
     p->d_phi = phi;
-    if (4 * p->chunk(precision) <= kPhiRow) {
-        if ((st = dalloc(&Phi, rsz * (size_t)n_walkers * ntp))) {
-            p->free_walkers();
-            return st;
-        }
-        p->d_Phi = Phi;
+    // rows of the read-out of reconstructions: what the walkers' coordinates
+    // leave of a row per walker
+    p->read_rows = std::max((int)((int64_t)n_walkers * (ntp - 4 * p->chunk(precision)) / ntp), std::min(n_walkers, kReadRows));
+    if ((st = dalloc(&Phi, rsz * (size_t)p->read_rows * ntp))) {
+        p->free_walkers();
+        return st;
     }
+    p->d_Phi = Phi;
     if ((st = dalloc(&p->d_b, (size_t)n_walkers * No)) || (st = dalloc(&p->d_gsc, n_walkers)) || (st = dalloc(&p->d_ginv, n_walkers)) ||
         (st = dalloc(&p->d_chi2, n_walkers)) || (st = dalloc(&p->d_rate, n_walkers)) || (st = dalloc(&p->d_a0, No)) ||
         (st = dalloc(&p->d_tmp, std::max(No, 64))) || (st = dalloc(&p->d_teff, 1)) ||
@@ -5357,31 +5392,22 @@ sail_status sail_read_state(sail_problem_t p, double *a, double *F, double *rate
     if (a) SAIL_HIP(hipMemcpyAsync(a, p->d_b, sizeof(double) * (size_t)n * No, hipMemcpyDeviceToHost, stream));
     std::vector<double> phi;
     std::vector<float> phif;
-    struct Scratch {
-        void *p = nullptr;
-        ~Scratch() { dfree(p); }
-    } tmp;  // the rows where the walkers hold none
     if (F) {
         const bool f32 = p->precision == SAIL_FP32;
-        const size_t rows = (size_t)n * ntp * (f32 ? sizeof(float) : sizeof(double));
-        void *dst = p->d_Phi;
-        if (!dst) {
-            char *q = nullptr;
-            const sail_status st = dalloc(&q, rows);
-            if (st) return st;
-            dst = tmp.p = q;
-        }
-        if (f32) {
-            phif.resize((size_t)n * ntp);
-            hipLaunchKernelGGL(k_reconstruct<float>, dim3(n), dim3(kThreads), 0, stream, No, Nt, p->cols(), ntp,
-                               (const double *)p->d_E, (const double *)p->d_b, (const double *)p->d_gsc, (float *)dst);
-        } else {
-            hipLaunchKernelGGL(k_reconstruct<double>, dim3(n), dim3(kThreads), 0, stream, No, Nt, p->cols(), ntp,
-                               (const double *)p->d_E, (const double *)p->d_b, (const double *)p->d_gsc, (double *)dst);
-        }
-        SAIL_HIP(hipGetLastError());
+        if (f32) phif.resize((size_t)n * ntp);
         phi.resize((size_t)n * ntp);
-        SAIL_HIP(hipMemcpyAsync(f32 ? (void *)phif.data() : (void *)phi.data(), dst, rows, hipMemcpyDeviceToHost, stream));
+        for (int l = 0; l < n; l += p->read_rows) {
+            const int rows = std::min(p->read_rows, n - l);
+            auto read = [&](auto *dst, auto *host) {
+                typedef std::remove_reference_t<decltype(*dst)> R;
+                hipLaunchKernelGGL(k_reconstruct<R>, dim3(rows), dim3(kThreads), 0, stream, No, Nt, p->cols(), ntp,
+                                   (const double *)p->d_E, (const double *)p->d_b + (size_t)l * No,
+                                   (const double *)p->d_gsc + l, dst);
+                const hipError_t e = hipGetLastError();
+                return e != hipSuccess ? e : hipMemcpyAsync(host + (size_t)l * ntp, dst, sizeof(R) * (size_t)rows * ntp, hipMemcpyDeviceToHost, stream);
+            };
+            SAIL_HIP(f32 ? read((float *)p->d_Phi, phif.data()) : read((double *)p->d_Phi, phi.data()));
+        }
     }
     if (rate) SAIL_HIP(hipMemcpyAsync(rate, p->d_rate, sizeof(double) * n, hipMemcpyDeviceToHost, stream));
     SAIL_HIP(hipStreamSynchronize(stream));
