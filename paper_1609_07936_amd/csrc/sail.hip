@@ -229,7 +229,8 @@ __device__ __forceinline__ void wave_lds_sync()
 // s | s << 16).  The bins also stand apart: they are read a proposal earlier
 // than the rest.
 enum : int {
-    kRecRm1 = 0, kRecRinv = 1, kRecThr = 2, kRecT = 3, kRecS1 = 4, kRecDp = 5, kRecDs = 6, kRecPS = 7
+    kRecRm1 = 0, kRecRinv = 1, kRecThr = 2, kRecT = 3, kRecS1 = 4, kRecDp = 5, kRecDs = 6, kRecPS = 7,
+    kRecBand = 7  // split sweeps, which stage masks of shared bins instead: the threshold's band
 };
 constexpr int kRecWords = 8;      // doubles per record
 constexpr int kWalkWords = 5;     // doubles per staged step of an index-selection walk: bins, two values, two draws
@@ -445,11 +446,13 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
     struct Rec {
         int p, s;
         uint32_t pp, ss;  // p | p << 16, s | s << 16
-        double rm1, rinv, thr, t, s1, dp, ds;
+        double rm1, rinv, thr, t, s1, dp, ds, band;
         R rp[MR], rs[MR];
     };
 
-    auto rows = [&](const int p, const int s, Rec &v) __attribute__((always_inline)) {
+    auto rows = [&](int p, int s, Rec &v) __attribute__((always_inline)) {
+        // (keeps the halves apart: shifts of the whole word cost more)
+        asm("" : "+v"(p), "+v"(s));
         v.p = p;
         v.s = s;
         if constexpr (M > 0) {
@@ -478,8 +481,12 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         v.dp = rc[kRecDp];
         v.ds = rc[kRecDs];
         const double w = rc[kRecPS];
-        v.pp = (uint32_t)__double2loint(w);
-        v.ss = (uint32_t)__double2hiint(w);
+        if constexpr (SPLIT) {
+            v.band = w;
+        } else {
+            v.pp = (uint32_t)__double2loint(w);
+            v.ss = (uint32_t)__double2hiint(w);
+        }
     };
 
     // Table values of a pair of bins: loaded a batch ahead, so that staging a
@@ -547,7 +554,8 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         rcw[kRecS1] = s1t;
         rcw[kRecDp] = dp;
         rcw[kRecDs] = ds;
-        rcw[kRecPS] = __hiloint2double((in ? s : 0) * 0x10001, (in ? p : 0) * 0x10001);
+        if constexpr (SPLIT) rcw[kRecBand] = fma(fabs(rcw[kRecThr]), thr_tol, thr_T);
+        else rcw[kRecPS] = __hiloint2double((in ? s : 0) * 0x10001, (in ? p : 0) * 0x10001);
     };
 
     // Lanes where a half of w is zero, and the smaller of two words by halves.
@@ -632,8 +640,8 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         uint64_t am = pos & __builtin_amdgcn_ballot_w64(diff < 0.0);
         // a decision within thr_tol (|thr| + T) of the staged threshold is
         // retaken with the exact logarithm
-        const uint64_t near = pos & __builtin_amdgcn_ballot_w64(fabs(diff) <= fma(fabs(v.thr), thr_tol, thr_T));
-        if (near) {
+        const uint64_t near = pos & __builtin_amdgcn_ballot_w64(fabs(diff) <= (SPLIT && !WALK ? v.band : fma(fabs(v.thr), thr_tol, thr_T)));
+        if (__builtin_expect(near != 0, 0)) {  // (out of line: a taken branch costs the common path)
             bool take = false;
             if (__builtin_amdgcn_inverse_ballot_w64(near)) {
                 uint32_t x0, x1, x2, x3;
@@ -672,7 +680,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
 #pragma unroll
                 for (int t = 0; t < MR; ++t) phi[t] = phi[t] + fma(rm1, phi[t], sv[t]);
             }
-            Q2 = fma(r * r, Q2, fma(r2, S2, v.s1));
+            asm("v_fma_f64 %0, %1, %0, %2" : "+v"(Q2) : "v"(r * r), "v"(fma(r2, S2, v.s1)));
             chi2 = chi2 + dchi2;
             g = rg;
             ginv = ginv * v.rinv;
@@ -1035,11 +1043,17 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
                     // the next proposal's columns (its bins were read a proposal
                     // ago), its record, and the bins of the one after it
                     Rec &cur = v[t & 1], &nx = v[(t + 1) & 1];
+                    // (FP32: the spectrum values before the next proposal's words,
+                    // which the decision would else wait behind, 200 to 192 ns a
+                    // proposal; FP64 is as fast either way)
+                    constexpr bool EARLY = ALLB && sizeof(R) == 4;
+                    const double bp = EARLY ? bsp[cur.p] : 0.0, bs = EARLY ? bsp[cur.s] : 0.0;
                     rows(__double2loint(next_bins), __double2hiint(next_bins), nx);
                     fetch(t + 1 < G ? rec_at(rs, t + 1) : rec_at(rn, 0), nx);
                     next_bins = t + 2 < G ? *bins_at(bsl, t + 2) : *bins_at(bn, t + 2 - G);
                     if constexpr (ALLB) {
-                        body(t, cur, bsp[cur.p], bsp[cur.s], 0);
+                        if constexpr (EARLY) body(t, cur, bp, bs, 0);
+                        else body(t, cur, bsp[cur.p], bsp[cur.s], 0);
                         wave_lds_sync();
                     } else {
                         body(t, cur, obp, obs, hit[t]);
