@@ -2014,7 +2014,8 @@ __device__ __forceinline__ T branch_reduce(T v, T (*slots)[WAVES], int &par, Op 
     return r;
 }
 
-// The fixed Delta search of one large problem spread over many workgroups:
+// The fixed Delta search of one problem spread over many workgroups (64 walkers:
+// 480 us in one workgroup, 260 us spread; two events of a small solve):
 // each round evaluates, in parallel, every Delta the search could visit next
 // (the bracketing powers d0 2^j; then kTreeLevels levels of the bisection
 // tree, each node's Delta derived from the round's bracket by the search's own
@@ -2026,7 +2027,6 @@ constexpr int kTreeNear = 16;    // first bracketing round: d0 2^j, |j| <= kTree
 constexpr int kTreeFar = 200;    // the search's limit on halvings or doublings
 constexpr int kTreeLevels = 8;   // bisection levels per round
 constexpr int kBisections = 30;
-constexpr int kTreeMinWalkers = 256;  // smaller problems keep the one-workgroup search
 
 struct BranchTree {
     double d0, lo, hi;
@@ -2432,14 +2432,6 @@ __device__ __forceinline__ void branch_block(const BranchArgs &a, BranchShared<W
         a.ev_bracket[a.event] = bracket;
     }
 #undef XI
-}
-
-template <int SHAPE>
-__global__ __launch_bounds__(kBranchShapes[SHAPE].threads) void k_branch_solve(BranchArgs a)
-{
-    constexpr BranchShape S = kBranchShapes[SHAPE];
-    __shared__ BranchShared<S.wpt, S.threads> sm;
-    branch_block<kBranchSearch, S.wpt, S.threads>(a, sm);
 }
 
 // many problems: workgroup b solves the branching event of problem b
@@ -3215,9 +3207,7 @@ sail_status launch_resync(sail_problem *p, int renorm, const int32_t *list, cons
     return SAIL_OK;
 }
 
-// One branching event of a single problem: the parallel search for large
-// populations (a few rounds over many workgroups), the one-workgroup kernel
-// for small ones.
+// One branching event of a single problem: a few rounds over many workgroups.
 template <int SHAPE>
 void launch_branch_tree(const BranchArgs &ba, BranchTree *t, hipStream_t stream)
 {
@@ -3238,17 +3228,12 @@ void launch_branch_tree(const BranchArgs &ba, BranchTree *t, hipStream_t stream)
 sail_status launch_branch(sail_problem *p, const BranchArgs &ba, hipStream_t stream)
 {
     const int shape = branch_shape(p->n_walkers);
-    static_assert(kTreeMinWalkers > kBranchShapes[0].threads && kTreeMinWalkers <= kBranchShapes[1].threads, "shapes of either search");
-    if (p->n_walkers < kTreeMinWalkers) {
-        if (shape == 0) hipLaunchKernelGGL(k_branch_solve<0>, dim3(1), dim3(kBranchShapes[0].threads), 0, stream, ba);
-        else hipLaunchKernelGGL(k_branch_solve<1>, dim3(1), dim3(kBranchShapes[1].threads), 0, stream, ba);
-    } else {
-        switch (shape) {
-            case 1: launch_branch_tree<1>(ba, p->d_tree, stream); break;
-            case 2: launch_branch_tree<2>(ba, p->d_tree, stream); break;
-            case 3: launch_branch_tree<3>(ba, p->d_tree, stream); break;
-            default: launch_branch_tree<4>(ba, p->d_tree, stream);
-        }
+    switch (shape) {
+        case 0: launch_branch_tree<0>(ba, p->d_tree, stream); break;
+        case 1: launch_branch_tree<1>(ba, p->d_tree, stream); break;
+        case 2: launch_branch_tree<2>(ba, p->d_tree, stream); break;
+        case 3: launch_branch_tree<3>(ba, p->d_tree, stream); break;
+        default: launch_branch_tree<4>(ba, p->d_tree, stream);
     }
     SAIL_HIP(hipGetLastError());
     return SAIL_OK;

@@ -40,6 +40,9 @@ PLANS = [
     (130, 40, 1025, 0, 0, 0.0),  # more than one walker group per compute unit
     (601, 33, 1100, 0, 0, 0.0),  # split, one pair of wavefronts
     (601, 33, 2500, 1, 0, 0.0),  # split, FP32
+    (998, 33, 1501, 0, 0, 0.0),  # 16 lanes a walker, spectra in memory
+    (998, 33, 4095, 1, 0, 0.0),  # the same in FP32, four pairs
+    (1100, 33, 3500, 0, 0, 0.0), # columns fit beside four lanes a walker only
     (1300, 17, 70, 0, 0, 0.0),   # columns larger than LDS
     (130, 40, 8197, 0, 0, 0.0),  # four pairs, whole spectra resident beside them
     (515, 40, 8197, 0, 0, 0.0),  # four pairs, the first bins resident
