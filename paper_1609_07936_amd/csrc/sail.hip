@@ -186,6 +186,29 @@ __device__ __forceinline__ double dpp_swap(double v)
     return __hiloint2double(hi, lo);
 }
 
+// Lane t (a compile-time number) of the walker's G = 4 or 16 lanes, by DPP
+// (quad_perm, row_newbcast).
+template <int G>
+__device__ __forceinline__ int lane_of(const int x, const int t)
+{
+#define SAIL_LANE(n, ctrl) case n: return __builtin_amdgcn_mov_dpp(x, ctrl, 0xF, 0xF, true);
+    if constexpr (G == 4) {
+        switch (t) {
+            SAIL_LANE(0, 0x00) SAIL_LANE(1, 0x55) SAIL_LANE(2, 0xAA)
+            default: return __builtin_amdgcn_mov_dpp(x, 0xFF, 0xF, 0xF, true);
+        }
+    } else {
+        static_assert(G == 16, "a quad or a row");
+        switch (t) {
+            SAIL_LANE(0, 0x150) SAIL_LANE(1, 0x151) SAIL_LANE(2, 0x152) SAIL_LANE(3, 0x153) SAIL_LANE(4, 0x154)
+            SAIL_LANE(5, 0x155) SAIL_LANE(6, 0x156) SAIL_LANE(7, 0x157) SAIL_LANE(8, 0x158) SAIL_LANE(9, 0x159)
+            SAIL_LANE(10, 0x15A) SAIL_LANE(11, 0x15B) SAIL_LANE(12, 0x15C) SAIL_LANE(13, 0x15D) SAIL_LANE(14, 0x15E)
+            default: return __builtin_amdgcn_mov_dpp(x, 0x15F, 0xF, 0xF, true);
+        }
+    }
+#undef SAIL_LANE
+}
+
 template <int CTRL>
 __device__ __forceinline__ float dpp_swap(float v)
 {
@@ -242,7 +265,7 @@ constexpr int rec_stride(int G, bool walk) { return (walk ? G * (kRecWords + 1 +
 
 // A split sweep's walker: records of three batches, bins of four, the move
 // width; and a wavefront's masks of shared bins of three batches.
-constexpr int kSplitHits = 3 * 4;
+constexpr int split_hits(int G) { return 3 * G; }
 constexpr int split_stride(int G) { return 3 * G * kRecWords + 4 * G + 2; }
 
 // A split walk's walker: of two batches of 16 proposals, the records (r - 1 or
@@ -352,8 +375,9 @@ enum : int { kSweepFast = 0, kSweepTraced = 1, kSweepWalk = 2 };
 // a walker; the other half, one beside each on the same SIMD, draw and stage
 // the proposals for them.  A chain's proposal is a serial sequence of some
 // hundred instructions, mostly waiting on its own results, so the staging's
-// instructions cost little beside it and a lot within it (512 bins, 16384
-// walkers: @SPLIT@).
+// instructions cost little beside it and a lot within it (512 bins, four lanes,
+// spectra in memory: 1024 walkers 378 ns a proposal in one wavefront and 250 ns
+// split, 16384 walkers 441 and 393 ns).
 template <typename R, int M, int G, bool LDSC, bool LDSB, int MODE, bool SPLIT>
 __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block, double *lds)
 {
@@ -361,7 +385,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
     constexpr int MR = M > 0 ? M : 1;
     const int RSTR = !SPLIT ? rec_stride(G, WALK) : WALK ? (int)walk_split_stride(a.walk_len) : split_stride(G);
     static_assert(M > 0 || !LDSC, "the general variant reads its columns from memory");
-    static_assert(!SPLIT || (G == 16 ? LDSC && LDSB : G == 4 && MODE == kSweepFast), "split sweeps");
+    static_assert(!SPLIT || (WALK ? G == 16 && LDSB : G == 16 || G == 4), "split sweeps");
     constexpr bool ALLB = LDSB && (!SPLIT || G == 16);  // whole spectra in LDS; split sweeps keep the first bins there
     const int nthr = SPLIT ? 128 * a.pairs : (int)blockDim.x;
     if (SPLIT && (int)threadIdx.x >= nthr) return;
@@ -391,7 +415,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
     // records, columns and spectra in LDS
     double *myrec = lds + ws * RSTR;
     const R *colg = (const R *)a.col;
-    R *col_s = (R *)(lds + wpb * RSTR + (SPLIT && G == 4 ? (wpb >> 4) * kSplitHits : 0));
+    R *col_s = (R *)(lds + wpb * RSTR + (SPLIT && !ALLB ? wpb / (64 / G) * split_hits(G) : 0));
     if constexpr (LDSC) {
         const size_t n16 = (size_t)No * 4 * ms * sizeof(R) / 16;
         for (size_t i = threadIdx.x; i < n16; i += nthr) ((float4 *)col_s)[i] = ((const float4 *)colg)[i];
@@ -575,16 +599,8 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
     };
     // the value lane lead + qq of the walker holds
     auto of_owner = [&](const double x, const int qq) __attribute__((always_inline)) {
-        if constexpr (G == 4) {
-            switch (qq) {  // a compile-time proposal: one DPP move per half
-                case 0: return dpp_swap<0x00>(x);
-                case 1: return dpp_swap<0x55>(x);
-                case 2: return dpp_swap<0xAA>(x);
-                default: return dpp_swap<0xFF>(x);
-            }
-        } else {
-            return __shfl(x, (lane & ~(G - 1)) + qq, 64);
-        }
+        if constexpr (SPLIT || G == 4) return __hiloint2double(lane_of<G>(__double2hiint(x), qq), lane_of<G>(__double2loint(x), qq));
+        else return __shfl(x, (lane & ~(G - 1)) + qq, 64);
     };
 
     // One proposal: v is its record and columns, bp and bs the spectrum values
@@ -903,18 +919,13 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         };
         double *width = myrec + 3 * G * kRecWords + 4 * G;  // move width of the sweep
         // masks of the proposals' shared bins, [slot][proposal], one set per pair of wavefronts
-        uint64_t *hits = (uint64_t *)(lds + wpb * RSTR) + (ws >> 4) * kSplitHits;
+        uint64_t *hits = (uint64_t *)(lds + wpb * RSTR) + ws / (64 / G) * split_hits(G);
         auto uniform = [](const uint64_t x) __attribute__((always_inline)) {
             return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x) |
                    (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32;
         };
         auto of_owner_word = [](const uint32_t x, const int t) __attribute__((always_inline)) {
-            switch (t) {
-                case 0: return (uint32_t)dpp_swap<0x00>((int)x);
-                case 1: return (uint32_t)dpp_swap<0x55>((int)x);
-                case 2: return (uint32_t)dpp_swap<0xAA>((int)x);
-                default: return (uint32_t)dpp_swap<0xFF>((int)x);
-            }
+            return (uint32_t)lane_of<G>((int)x, t);
         };
         int rs = 0, bsl = 0;                                 // slots of the next record and bins
         if (stager) {
@@ -1009,11 +1020,16 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
             for (q0 = 0; q0 < No; q0 += G) {
                 const int bn = (bsl + 1) & 3, rn = rs == 2 ? 0 : rs + 1;  // the next batch's slots
                 const bool ends = q0 + G >= No;
+                // the batch's masks, read at its start, or at use (FP32, 16 lanes:
+                // 221 against 231 ns a proposal; FP64: 220 against 215)
+                constexpr bool AHEAD = G == 4 || sizeof(R) == 8;
                 uint64_t hit[G] = {};
                 if constexpr (!ALLB) {
                     const double own_bins = *bins_at(bn, c);
+                    if constexpr (AHEAD) {
 #pragma unroll
-                    for (int t = 0; t < G; ++t) hit[t] = uniform(hits[rs * G + t]);
+                        for (int t = 0; t < G; ++t) hit[t] = uniform(hits[rs * G + t]);
+                    }
                     // this batch's spectrum values have arrived (waited for before
                     // the stores below are issued, so that nothing waits for those)
                     asm volatile("" : "+v"(nbp), "+v"(nbs));
@@ -1056,6 +1072,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
                         else body(t, cur, bsp[cur.p], bsp[cur.s], 0);
                         wave_lds_sync();
                     } else {
+                        if constexpr (!AHEAD) hit[t] = uniform(hits[rs * G + t]);
                         body(t, cur, obp, obs, hit[t]);
                     }
                     // keep each proposal's code together (bounds register pressure)
@@ -1290,11 +1307,11 @@ __global__ __launch_bounds__(2 * kSweepThreads) void k_sweep_split(SweepArgs a)
     sweep_block<R, M, 4, LDSC, LDSB, kSweepFast, true>(a, blockIdx.x, lds);
 }
 
-template <typename R, int M, int MODE>
+template <typename R, int M, bool LDSC, bool LDSB, int MODE>
 __global__ __launch_bounds__(2 * kSweepThreads) void k_sweep_split16(SweepArgs a)
 {
     extern __shared__ __align__(16) double lds[];
-    sweep_block<R, M, 16, true, true, MODE, true>(a, blockIdx.x, lds);
+    sweep_block<R, M, 16, LDSC, LDSB, MODE, true>(a, blockIdx.x, lds);
 }
 
 // Many problems in one launch: problem q owns workgroups [first[q], first[q + 1]);
@@ -3345,7 +3362,7 @@ SweepPlan plan_sweep(const sail_problem *p, bool split, int lanes, int threads, 
     SweepPlan s{split, lanes, threads, walkers, 0, 0, 0,
                 sizeof(double) * (!split ? (size_t)walkers * rec_stride(lanes, walk)
                                   : walk ? (size_t)walkers * walk_split_stride(walk_len)
-                                         : (size_t)walkers * split_stride(lanes) + (lanes == 4 ? (size_t)walkers / 16 * kSplitHits : 0))};
+                                         : (size_t)walkers * split_stride(lanes) + (size_t)walkers / (64 / lanes) * split_hits(lanes))};
     const size_t col = column_bytes(p->n_omega, p->chunk(p->precision),
                                     p->precision == SAIL_FP32 ? sizeof(float) : sizeof(double));
     if (basis_class(p->precision, p->dims(p->precision)) == 0) return s;
@@ -3383,12 +3400,21 @@ bool sweep_traced(const sail_problem *p, int k0, int k1) { return p->tk1 > p->tk
 
 constexpr int kCUs = 256;
 
-// The plan of a problem swept alone.  A population whose spectra fit in the
-// LDS of the chip beside the columns keeps them there, 16 lanes a walker
-// (@PLAN16@); a larger one keeps them in memory and splits its workgroups
-// into chains and stagers.  Workgroups are the smallest that leave at most one
-// per compute unit, so that a small population spreads over the chip, each
-// with as much LDS as its share of a compute unit.
+// The plan of a problem swept alone.  Workgroups are the smallest that leave at
+// most one per compute unit, so that a small population spreads over the chip,
+// each with as much LDS as its share of a compute unit.  In order of
+// preference (times of one proposal of every walker):
+//   split, 16 lanes a walker, spectra in LDS beside the columns, for up to 16
+//     walkers per compute unit: 196 ns (64 bins, 64 walkers) and 215 ns (300
+//     bins, 3000 walkers), against 207 and 220 ns in one wavefront (the next);
+//   16 lanes in one wavefront, which stages its own proposals: its records take
+//     two thirds of the LDS, so that larger spectra fit;
+//   split, 16 lanes, spectra in memory: a batch's loads, stores and masks of
+//     shared bins are paid once in 16 proposals: 215 ns (1000 bins, 1500
+//     walkers), against 244 ns for four lanes;
+//   split, four lanes a walker: 64 walkers per compute unit at a time, 360 ns
+//     (512 bins, 16384 walkers); also where the columns fit beside these smaller
+//     records only (900 bins, 3500 walkers: 246 against 253 ns).
 SweepPlan plan_alone(const sail_problem *p, int mode, int walk_len)
 {
     const size_t n = (size_t)p->n_walkers;
@@ -3412,6 +3438,9 @@ SweepPlan plan_alone(const sail_problem *p, int mode, int walk_len)
     if (n * 16 <= (size_t)kSweepThreads * kCUs) {
         const SweepPlan t = sized(true, 16, true);
         if (t.spectra_lds) return t;
+        const SweepPlan u = sized(false, 16, true);
+        if (u.spectra_lds) return u;
+        if (t.columns_lds) return t;
     }
     const SweepPlan s = sized(false, 16, true);
     return s.spectra_lds ? s : sized(true, 4, false);
@@ -3430,14 +3459,19 @@ void launch_sweep_m(const SweepArgs &a, int blocks, const SweepPlan &s, int mode
     if constexpr (M > 0) {
         if (mode == kSweepWalk) {
             if (s.split) {
-                hipLaunchKernelGGL((k_sweep_split16<R, M, kSweepWalk>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
+                hipLaunchKernelGGL((k_sweep_split16<R, M, true, true, kSweepWalk>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
                 return;
             }
             if (s.spectra_lds) return launch_sweep_k<R, M, 8, true, true, kSweepWalk>(a, blocks, s, stream);
             return launch_sweep_k<R, M, 8, false, false, kSweepWalk>(a, blocks, s, stream);
         }
         if (s.split && s.lanes == 16) {
-            hipLaunchKernelGGL((k_sweep_split16<R, M, kSweepFast>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
+            if (s.spectra_lds)
+                hipLaunchKernelGGL((k_sweep_split16<R, M, true, true, kSweepFast>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
+            else if (s.columns_lds)
+                hipLaunchKernelGGL((k_sweep_split16<R, M, true, false, kSweepFast>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
+            else
+                hipLaunchKernelGGL((k_sweep_split16<R, M, false, false, kSweepFast>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
             return;
         }
         if (s.spectra_lds) return launch_sweep_k<R, M, 16, true, true, kSweepFast>(a, blocks, s, stream);
