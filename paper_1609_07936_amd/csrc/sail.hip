@@ -1413,7 +1413,12 @@ struct ResyncArgs {
     double *drift;              // optional [N_w]: each walker's relative sum-rule drift before the renormalisation
 };
 
-constexpr int kResyncWPB = 8;  // walkers per workgroup in the resync
+// Doubles between two walkers' spectra in the resync's LDS: odd, so that the 16
+// rows a matrix instruction reads lie in different banks (but for the largest
+// N_omega that fits, which needs every word).
+constexpr int kResyncMost = 2556;
+__host__ __device__ constexpr int resync_stride(int n_omega) { return n_omega < kResyncMost ? n_omega | 1 : n_omega; }
+
 
 __device__ __forceinline__ double wave_sum(double v)
 {
@@ -1421,39 +1426,44 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// kResyncWPB walkers per workgroup share every read of the E table: thread i
-// accumulates column i of all of them in FP64, j ascending: Phi_i, whose
-// residuals give chi^2, or a basis coordinate, stored in the loop precision R.
-template <typename R>
+// WPB (8 or 16) walkers per workgroup.  The columns, and the basis coordinates
+// beside them, are a product [walkers x N_omega] [N_omega x cols] in FP64 on the
+// matrix cores: a wavefront takes up to three tiles of 16 columns at a time, the
+// walkers' spectra come from LDS and E from the caches.  Phi_i's residuals give
+// chi^2; the basis coordinates are stored in the loop precision R.  A walker's
+// sums are taken in the same order for either WPB.  8 walkers leave half of a
+// tile's rows idle but twice the workgroups.  512 bins, 144 columns, 16384 walkers:
+// 96 us, 25 TFLOP/s (165 us on the vector units, which an LDS read per FMA held
+// back); 64 walkers of 64 bins 11 us (19), mostly latency.
+template <typename R, int WPB>
 __device__ __forceinline__ void resync_block(const ResyncArgs &a, const int block, double *sh)
 {
-    // sh: [kResyncWPB][N_omega] spectra (room for at least [kResyncWPB][kThreads]
-    // partial sums of Phi), then [4][kResyncWPB] partial residues
-    const int No = a.n_omega, Nt = a.n_tau, cols = a.cols;
+    // sh: [WPB][stride] spectra, then [4][WPB] partial residues
+    const int No = a.n_omega, Nt = a.n_tau, cols = a.cols, ld = resync_stride(No);
     double *sb = sh;
-    double *red = sh + (size_t)kResyncWPB * (No > kThreads ? No : kThreads);
+    double *red = sh + (size_t)WPB * ld;
     const int count = a.list ? *a.list_count : a.n_items;
-    const int base = block * kResyncWPB;
+    const int base = block * WPB;
     if (base >= count) return;
-    int wl[kResyncWPB];
+    int wl[WPB];
 #pragma unroll
-    for (int w = 0; w < kResyncWPB; ++w) {
+    for (int w = 0; w < WPB; ++w) {
         const int idx = base + w;
         wl[w] = idx < count ? (a.list ? a.list[idx] : idx) : -1;
     }
     // imprint (Sec. 2.5; donors are never targets, so their spectra are
     // read-only here), then fold the lazy scale
 #pragma unroll
-    for (int w = 0; w < kResyncWPB; ++w) {
+    for (int w = 0; w < WPB; ++w) {
         if (wl[w] < 0) continue;
         const double g = a.gsc[wl[w]];
         const double *bl = a.b + (size_t)wl[w] * No;
         if (a.donors) {
             const double t = a.imprint_t_dev ? *a.imprint_t_dev : a.imprint_t, t1 = 1.0 - t;
             const double *bd = a.b + (size_t)a.donors[base + w] * No;
-            for (int j = threadIdx.x; j < No; j += blockDim.x) sb[w * No + j] = g * (t * bd[j] + t1 * bl[j]);
+            for (int j = threadIdx.x; j < No; j += blockDim.x) sb[w * ld + j] = g * (t * bd[j] + t1 * bl[j]);
         } else {
-            for (int j = threadIdx.x; j < No; j += blockDim.x) sb[w * No + j] = g * bl[j];
+            for (int j = threadIdx.x; j < No; j += blockDim.x) sb[w * ld + j] = g * bl[j];
         }
     }
     __syncthreads();
@@ -1464,9 +1474,9 @@ __device__ __forceinline__ void resync_block(const ResyncArgs &a, const int bloc
         // value left of the chunk in a register (the wavefront's LDS reads of
         // a chunk precede its writes, and the next chunk's reads lie beyond)
         const double sm = a.smooth, cm = 1.0 - 2.0 * sm, em = 1.0 - sm;
-        for (int w = wave; w < kResyncWPB; w += kThreads / 64) {
+        for (int w = wave; w < WPB; w += kThreads / 64) {
             if (wl[w] < 0) continue;
-            double *row = sb + w * No;
+            double *row = sb + w * ld;
             double left = 0.0;
             for (int j0 = 0; j0 < No; j0 += 64) {
                 const int j = j0 + lane;
@@ -1487,134 +1497,145 @@ __device__ __forceinline__ void resync_block(const ResyncArgs &a, const int bloc
     }
     if (a.renorm) {
         // Reading of Sec. 2.6: a_j <- a_j (1 + d0 + d1 omega_j) restores both sums
-        for (int w = wave; w < kResyncWPB; w += kThreads / 64) {
-            if (wl[w] < 0) continue;
+        // 16 lanes a walker, every walker at once
+        const int w = threadIdx.x >> 4, c = threadIdx.x & 15;
+        int walker = -1;
+#pragma unroll
+        for (int t = 0; t < WPB; ++t) walker = w == t ? wl[t] : walker;
+        if (walker >= 0) {
+            double *row = sb + w * ld;
             double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-            for (int j = lane; j < No; j += 64) {
-                const double v = sb[w * No + j], x = a.omega[j];
+            for (int j = c; j < No; j += 16) {
+                const double v = row[j], x = a.omega[j];
                 s0 += v;
                 s1 += v * x;
                 s2 += v * x * x;
             }
-            s0 = wave_sum(s0);
-            s1 = wave_sum(s1);
-            s2 = wave_sum(s2);
-            if ((a.watch || a.drift) && lane == 0) {
+            s0 = group_sum<16>(s0);
+            s1 = group_sum<16>(s1);
+            s2 = group_sum<16>(s2);
+            if ((a.watch || a.drift) && c == 0) {
                 // both sums are invariants of every move (Sec. 2.2): their drift
                 // since the last renormalisation measures accumulated error
                 const double drift = fmax(fabs(s0 - a.A) / a.A, fabs(s1 - a.B) / fabs(a.B));
                 if (a.watch && !(drift <= a.watch_bound)) atomicOr(a.watch, 1u);
-                if (a.drift) a.drift[wl[w]] = drift;
+                if (a.drift) a.drift[walker] = drift;
             }
             const double e0 = a.A - s0, e1 = a.B - s1;
             const double det = s0 * s2 - s1 * s1;
             if (det > 0.0 && isfinite(det)) {
                 const double d0 = (e0 * s2 - e1 * s1) / det;
                 const double d1 = (e1 * s0 - e0 * s1) / det;
-                for (int j = lane; j < No; j += 64) sb[w * No + j] = sb[w * No + j] + sb[w * No + j] * (d0 + d1 * a.omega[j]);
+                for (int j = c; j < No; j += 16) row[j] = row[j] + row[j] * (d0 + d1 * a.omega[j]);
             }
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int w = 0; w < kResyncWPB; ++w) {
+    for (int w = 0; w < WPB; ++w) {
         if (wl[w] < 0) continue;
         double *bl = a.b + (size_t)wl[w] * No;
-        for (int j = threadIdx.x; j < No; j += blockDim.x) bl[j] = sb[w * No + j];
+        for (int j = threadIdx.x; j < No; j += blockDim.x) bl[j] = sb[w * ld + j];
         if (threadIdx.x == 0) {
             a.gsc[wl[w]] = 1.0;
             a.ginv[wl[w]] = 1.0;
         }
     }
-    double part[kResyncWPB];
+    // lane: column lane % 16 of a tile; rows (walkers) and bins by lane / 16
+    constexpr int T = 3;  // tiles at a time
+    typedef double v4 __attribute__((ext_vector_type(4)));
+    const int lc = lane & 15, lk = lane >> 4;
+    const double *arow = sb + (lc % WPB) * ld;
+    double part[WPB / 4] = {};
+    int mine[WPB / 4];  // the walkers of this lane's results
 #pragma unroll
-    for (int w = 0; w < kResyncWPB; ++w) part[w] = 0.0;
-    // column i of walker slot w is v: a residual, or a basis coordinate
-    auto take = [&](const int i, const int w, const double v) __attribute__((always_inline)) {
-        if (i < Nt) {
-            const double rsd = v - a.Phit[i];
-            part[w] += a.wh[i] * rsd * rsd;
-        } else {
-            const int d = i - Nt, q = d / a.echunk, t = d % a.echunk;
-            if (t < a.chunk) ((R *)a.phi)[((size_t)wl[w] * 4 + q) * a.chunk + t] = (R)v;
-        }
-    };
-    if (cols * 3 > (int)blockDim.x) {
-        for (int i = threadIdx.x; i < cols; i += blockDim.x) {
-            double f[kResyncWPB];
+    for (int r = 0; r < WPB / 4; ++r) {
+        mine[r] = -1;
 #pragma unroll
-            for (int w = 0; w < kResyncWPB; ++w) f[w] = 0.0;
-            for (int j = 0; j < No; ++j) {
-                const double e = a.E[(size_t)j * cols + i];
+        for (int w = 0; w < WPB; ++w) mine[r] = lk + 4 * r == w ? wl[w] : mine[r];
+    }
+    const int tiles = (cols + 15) / 16;
+    for (int t0 = wave; t0 < tiles; t0 += 4 * T) {
+        v4 acc[T] = {};
+        int col[T];
 #pragma unroll
-                for (int w = 0; w < kResyncWPB; ++w) f[w] = fma(sb[w * No + j], e, f[w]);
+        for (int t = 0; t < T; ++t) col[t] = min((t0 + 4 * t) * 16 + lc, cols - 1);  // past the last: not used
+        int k = lk;
+        for (; k - lk + 16 <= No; k += 16) {
+            double av[4], e[4][T];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                av[u] = arow[k + 4 * u];
+                const double *Er = a.E + (size_t)(k + 4 * u) * cols;
+#pragma unroll
+                for (int t = 0; t < T; ++t) e[u][t] = Er[col[t]];
             }
 #pragma unroll
-            for (int w = 0; w < kResyncWPB; ++w)
-                if (wl[w] >= 0) take(i, w, f[w]);
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int t = 0; t < T; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], e[u][t], acc[t], 0, 0, 0);
         }
-    } else {
-        // at most a third as many columns as threads: G groups of cols threads
-        // split the bins, each group summing its range in bin order, and the
-        // partial sums are added in group order (measured: 1.7x faster batched
-        // resyncs; with two groups the exchange costs more than it gains)
-        const int G = (int)blockDim.x / cols, g = threadIdx.x / cols, i = threadIdx.x % cols;
-        double f[kResyncWPB];
+        for (; k - lk < No; k += 4) {
+            const bool in = k < No;
+            const double av = in ? arow[k] : 0.0;
 #pragma unroll
-        for (int w = 0; w < kResyncWPB; ++w) f[w] = 0.0;
-        if (g < G) {
-            const int j0 = (int)((int64_t)No * g / G), j1 = (int)((int64_t)No * (g + 1) / G);
-            for (int j = j0; j < j1; ++j) {
-                const double e = a.E[(size_t)j * cols + i];
-#pragma unroll
-                for (int w = 0; w < kResyncWPB; ++w) f[w] = fma(sb[w * No + j], e, f[w]);
+            for (int t = 0; t < T; ++t) {
+                const double e = in ? a.E[(size_t)k * cols + col[t]] : 0.0;
+                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, e, acc[t], 0, 0, 0);
             }
         }
-        __syncthreads();  // the spectra in LDS are read for the last time
-        double *pf = sh;  // partial sums [walker][group][column], over the spectra
-        if (g < G) {
+        // acc[t][r]: walker slot lk + 4 r, column i
 #pragma unroll
-            for (int w = 0; w < kResyncWPB; ++w) pf[(w * G + g) * cols + i] = f[w];
-        }
-        __syncthreads();
-        if (g == 0) {
+        for (int t = 0; t < T; ++t) {
+            const int i = (t0 + 4 * t) * 16 + lc;
+            if (i >= cols) continue;
 #pragma unroll
-            for (int w = 0; w < kResyncWPB; ++w) {
-                if (wl[w] < 0) continue;
-                double v = pf[(w * G) * cols + i];
-                for (int gg = 1; gg < G; ++gg) v += pf[(w * G + gg) * cols + i];
-                take(i, w, v);
+            for (int r = 0; r < WPB / 4; ++r) {
+                const int walker = mine[r];
+                if (walker < 0) continue;
+                if (i < Nt) {
+                    const double rsd = acc[t][r] - a.Phit[i];
+                    part[r] += a.wh[i] * rsd * rsd;
+                } else {
+                    const int d = i - Nt, q = d / a.echunk, x = d % a.echunk;
+                    if (x < a.chunk) ((R *)a.phi)[((size_t)walker * 4 + q) * a.chunk + x] = (R)acc[t][r];
+                }
             }
         }
     }
 #pragma unroll
-    for (int w = 0; w < kResyncWPB; ++w) {
-        const double v = wave_sum(part[w]);
-        if (lane == 0) red[wave * kResyncWPB + w] = v;
+    for (int r = 0; r < WPB / 4; ++r) {
+        const double v = group_sum<16>(part[r]);
+        if (lc == 0) red[wave * WPB + lk + 4 * r] = v;
     }
     __syncthreads();
-    if (threadIdx.x < kResyncWPB && wl[threadIdx.x] >= 0) {
-        double v = 0.0;
-        for (int wv = 0; wv < kThreads / 64; ++wv) v += red[wv * kResyncWPB + threadIdx.x];
-        a.chi2[wl[threadIdx.x]] = v;
-        if (a.watch && !isfinite(v)) atomicOr(a.watch, 2u);
+    if (threadIdx.x < WPB) {
+        int walker = -1;
+#pragma unroll
+        for (int w = 0; w < WPB; ++w) walker = (int)threadIdx.x == w ? wl[w] : walker;
+        if (walker >= 0) {
+            double v = 0.0;
+            for (int wv = 0; wv < kThreads / 64; ++wv) v += red[wv * WPB + threadIdx.x];
+            a.chi2[walker] = v;
+            if (a.watch && !isfinite(v)) atomicOr(a.watch, 2u);
+        }
     }
 }
 
-template <typename R>
+template <typename R, int WPB>
 __global__ __launch_bounds__(kThreads) void k_resync(ResyncArgs a)
 {
     extern __shared__ double sh[];
-    resync_block<R>(a, blockIdx.x, sh);
+    resync_block<R, WPB>(a, blockIdx.x, sh);
 }
 
-template <typename R>
+template <typename R, int WPB>
 __global__ __launch_bounds__(kThreads) void k_resync_batched(const ResyncArgs *__restrict__ jobs,
                                                              const int *__restrict__ first, int n_jobs)
 {
     extern __shared__ double sh[];
     const int q = owner_of(first, n_jobs, blockIdx.x);
-    resync_block<R>(jobs[q], blockIdx.x - first[q], sh);
+    resync_block<R, WPB>(jobs[q], blockIdx.x - first[q], sh);
 }
 
 // Reconstructions of the walkers for read-out: Phi_i = g sum_j b_j E_ji, one
@@ -1696,14 +1717,16 @@ __global__ __launch_bounds__(kThreads) void k_tables(TableArgs a)
         __syncthreads();
         for (int d = threadIdx.x; d < a.nd; d += kThreads)
             row[Nt + ((a.d0 + d) & 3) * a.echunk + ((a.d0 + d) >> 2)] = cs[d];
-    } else if (threadIdx.x == 0) {
-        // (an earlier pass's maxima may stay: tails only grow towards the first vector)
+    } else if ((int)threadIdx.x < a.nd) {
+        // (an earlier pass's maxima may stay: tails only grow towards the first
+        // vector; a read first spares most of the atomics)
+        const int d = threadIdx.x;
         double t = a.tail[j];
-        for (int d = a.nd - 1; d >= 0 && spans; --d) {
-            t += cs[d] * cs[d] / D;
+        for (int e = a.nd - 1; e >= d && spans; --e) t += cs[e] * cs[e] / D;
+        if (spans && t > a.worst[d])
             atomicMax((unsigned long long *)&a.worst[d], (unsigned long long)__double_as_longlong(t));
-        }
-        a.tail[j] = spans ? t : 1.0;
+        wave_lds_sync();  // (nd <= 64: one wavefront has read the tail)
+        if (d == 0) a.tail[j] = spans ? t : 1.0;
     }
 }
 
@@ -3174,26 +3197,39 @@ ResyncArgs make_resync_args(const sail_problem *p, int renorm, const int32_t *li
     return r;
 }
 
-// LDS of a resync workgroup: the walkers' spectra (later the partial sums
-// of Phi, kResyncWPB x kThreads), then the per-wavefront residue partials.
-size_t resync_region(int n_omega) { return (size_t)kResyncWPB * (size_t)std::max(n_omega, kThreads); }
-
 // Batched resyncs are launched per class of that LDS size: N_omega up to
 // 256, 512, 1024, and beyond.
 constexpr int kResyncClasses = 4;
 int resync_class(int n_omega) { return n_omega <= 256 ? 0 : n_omega <= 512 ? 1 : n_omega <= 1024 ? 2 : 3; }
-size_t resync_shmem(int n_omega) { return sizeof(double) * (resync_region(n_omega) + 4 * kResyncWPB); }
-int resync_blocks(int n_items) { return (n_items + kResyncWPB - 1) / kResyncWPB; }
+// Walkers per resync workgroup: 16 fill the matrix instructions' rows, where two
+// such workgroups fit a compute unit and there are more than 8 per compute unit;
+// else 8.
+int resync_wpb(int n_omega, size_t n_items) { return n_omega <= 512 && n_items > 8 * 256 ? 16 : 8; }
+// its LDS: the walkers' spectra, then the per-wavefront residue partials
+size_t resync_shmem(int n_omega, int wpb) { return sizeof(double) * wpb * (resync_stride(n_omega) + 4); }
+int resync_blocks(int n_items, int wpb) { return (n_items + wpb - 1) / wpb; }
+template <typename R>
+void launch_resync_k(int wpb, int blocks, size_t shm, hipStream_t stream, const ResyncArgs &r)
+{
+    if (wpb == 16) hipLaunchKernelGGL((k_resync<R, 16>), dim3(blocks), dim3(kThreads), shm, stream, r);
+    else hipLaunchKernelGGL((k_resync<R, 8>), dim3(blocks), dim3(kThreads), shm, stream, r);
+}
+template <typename R>
+void launch_resync_k(int wpb, int blocks, size_t shm, hipStream_t stream, const ResyncArgs *r, const int *first, int n)
+{
+    if (wpb == 16) hipLaunchKernelGGL((k_resync_batched<R, 16>), dim3(blocks), dim3(kThreads), shm, stream, r, first, n);
+    else hipLaunchKernelGGL((k_resync_batched<R, 8>), dim3(blocks), dim3(kThreads), shm, stream, r, first, n);
+}
 
 // LDS one workgroup may hold on gfx950 (the 160 KiB of a compute unit).
 constexpr size_t kLdsBytes = 160 * 1024;
 
-// The resync stages kResyncWPB spectra per workgroup, so N_omega is bounded by
+// The resync stages 8 spectra per workgroup at least, so N_omega is bounded by
 // the LDS of one workgroup (N_omega <= 2556 on gfx950); a sweep needs its
 // records only (its tables are read from memory where they do not fit).
 sail_status check_lds(int n_omega, size_t limit = kLdsBytes)
 {
-    const size_t resync = resync_shmem(n_omega);
+    const size_t resync = resync_shmem(n_omega, 8);
     if (resync > limit)
         return fail(SAIL_EINVAL, "n_omega = " + std::to_string(n_omega) + " needs " + std::to_string(resync) +
                                      " bytes of LDS per workgroup; " + std::to_string(limit) + " are available");
@@ -3214,12 +3250,10 @@ sail_status launch_resync(sail_problem *p, int renorm, const int32_t *list, cons
         r.watch_bound = (renorm && !donors && !(smooth > 0.0)) ? p->watch_bound : INFINITY;
     }
     if (p->d_drift && renorm && !list && !donors && !(smooth > 0.0)) r.drift = p->d_drift;
-    const size_t shmem = resync_shmem(p->n_omega);
-    const int blocks = resync_blocks(n_items);
-    if (p->precision == SAIL_FP32)
-        hipLaunchKernelGGL(k_resync<float>, dim3(blocks), dim3(kThreads), shmem, stream, r);
-    else
-        hipLaunchKernelGGL(k_resync<double>, dim3(blocks), dim3(kThreads), shmem, stream, r);
+    const int wpb = resync_wpb(p->n_omega, n_items), blocks = resync_blocks(n_items, wpb);
+    const size_t shmem = resync_shmem(p->n_omega, wpb);
+    if (p->precision == SAIL_FP32) launch_resync_k<float>(wpb, blocks, shmem, stream, r);
+    else launch_resync_k<double>(wpb, blocks, shmem, stream, r);
     SAIL_HIP(hipGetLastError());
     return SAIL_OK;
 }
@@ -4220,6 +4254,7 @@ struct Launch {
     const int *first;
     size_t shm;
     int cls = 0, mode = 0, threads = kThreads;  // sweeps only
+    int wpb = 8;  // resyncs only
 };
 
 template <typename R, int M>
@@ -4333,6 +4368,13 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
             std::vector<ResyncArgs> ra;
             std::vector<int> first;
             int blocks = 0, max_no = 0;
+            size_t items = 0;
+            for (const auto *j : act)
+                if (j->p->precision == prec && resync_class(j->p->n_omega) == cls) {
+                    items += (size_t)j->p->n_walkers;
+                    max_no = std::max(max_no, j->p->n_omega);
+                }
+            const int wpb = resync_wpb(max_no, items);
             for (size_t i = 0; i < act.size(); ++i) {
                 sail_problem *p = act[i]->p;
                 const sail_schedule &sc = act[i]->sc;
@@ -4354,15 +4396,14 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
                     ba.push_back(make_branch_args(p, sc.branch_fraction, kend[i] / sc.branch_every - 1, sc.adaptive,
                                                   sc.imprint_t));
                 first.push_back(blocks);
-                blocks += resync_blocks(p->n_walkers);
-                max_no = std::max(max_no, p->n_omega);
+                blocks += resync_blocks(p->n_walkers, wpb);
             }
             if (ra.empty()) continue;
             first.push_back(blocks);
             const ResyncArgs *dargs = sg.put(ra.data(), ra.size());
             const int *dfirst = sg.put(first.data(), first.size());
             (pass == 0 ? resyncs : pass == 1 ? targets : smooths)
-                .push_back({prec, blocks, (int)ra.size(), dargs, dfirst, resync_shmem(max_no)});
+                .push_back({prec, blocks, (int)ra.size(), dargs, dfirst, resync_shmem(max_no, wpb), 0, 0, kThreads, wpb});
         }
     }
     const BranchArgs *dbranch = ba.empty() ? nullptr : sg.put(ba.data(), ba.size());
@@ -4401,10 +4442,8 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
     }
     auto resync_launch = [&](const Launch &L) -> sail_status {
         const ResyncArgs *a = (const ResyncArgs *)L.args;
-        if (L.kind == SAIL_FP32)
-            hipLaunchKernelGGL(k_resync_batched<float>, dim3(L.blocks), dim3(kThreads), L.shm, stream, a, L.first, L.n);
-        else
-            hipLaunchKernelGGL(k_resync_batched<double>, dim3(L.blocks), dim3(kThreads), L.shm, stream, a, L.first, L.n);
+        if (L.kind == SAIL_FP32) launch_resync_k<float>(L.wpb, L.blocks, L.shm, stream, a, L.first, L.n);
+        else launch_resync_k<double>(L.wpb, L.blocks, L.shm, stream, a, L.first, L.n);
         SAIL_HIP(hipGetLastError());
         return SAIL_OK;
     };
