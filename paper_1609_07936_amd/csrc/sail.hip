@@ -2059,8 +2059,8 @@ __device__ __forceinline__ T branch_reduce(T v, T (*slots)[WAVES], int &par, Op 
 // each round evaluates, in parallel, every Delta the search could visit next
 // (the bracketing powers d0 2^j; then kTreeLevels levels of the bisection
 // tree, each node's Delta derived from the round's bracket by the search's own
-// sequence of square roots, so bit for bit the same values), and a one-thread
-// walk applies the search's decisions to the results.  Zero counts do not
+// sequence of square roots, so bit for bit the same values), and the last
+// workgroup's walk applies the search's decisions to the results.  Zero counts do not
 // depend on where inside the count-n interval of y an evaluation lands, so the
 // walk takes exactly the decisions of the one-workgroup search.
 constexpr int kTreeNear = 16;    // first bracketing round: d0 2^j, |j| <= kTreeNear
@@ -2074,6 +2074,7 @@ struct BranchTree {
     int zt, degenerate;
     int ok;           // the bracket was found
     int dir;          // after the first round: 0 bracket found, -1 keep halving, +1 keep doubling
+    unsigned int done;  // workgroups of the round that have finished (0 between rounds)
     int z[kTreeFar + (1 << kTreeLevels)];     // zero counts of the round's evaluations
     double y[kTreeFar + (1 << kTreeLevels)];  // their y (0 where none was found)
 };
@@ -2492,20 +2493,8 @@ __global__ __launch_bounds__(kBranchThreads) void k_branch_batched(const BranchA
     }
 }
 
-// One round of the parallel Delta search: workgroup b evaluates the zero
-// count at the round's b-th Delta.
-template <int SHAPE>
-__global__ __launch_bounds__(kBranchShapes[SHAPE].threads) void k_branch_tree(BranchArgs a, BranchTree *t, int round)
-{
-    if (round == kRoundFar && (t->degenerate || t->dir == 0)) return;
-    if (round >= kRoundBisect && (t->degenerate || !t->ok)) return;
-    constexpr BranchShape S = kBranchShapes[SHAPE];
-    __shared__ BranchShared<S.wpt, S.threads> sm;
-    branch_block<kBranchTreeEval, S.wpt, S.threads>(a, sm, t, round);
-}
-
 // The search's decisions over one round's results (one thread).
-__global__ void k_branch_walk(BranchTree *t, int round, int levels)
+__device__ __forceinline__ void branch_walk(BranchTree *t, int round, int levels)
 {
     if (t->degenerate) return;
     const int zt = t->zt;
@@ -2586,6 +2575,29 @@ __global__ void k_branch_walk(BranchTree *t, int round, int levels)
     }
     t->lo = lo;
     t->hi = hi;
+}
+
+// One round of the parallel Delta search: workgroup b evaluates the zero
+// count at the round's b-th Delta.
+template <int SHAPE>
+__global__ __launch_bounds__(kBranchShapes[SHAPE].threads) void k_branch_tree(BranchArgs a, BranchTree *t, int round, int levels)
+{
+    if (round == kRoundFar && (t->degenerate || t->dir == 0)) return;
+    if (round >= kRoundBisect && (t->degenerate || !t->ok)) return;
+    constexpr BranchShape S = kBranchShapes[SHAPE];
+    __shared__ BranchShared<S.wpt, S.threads> sm;
+    branch_block<kBranchTreeEval, S.wpt, S.threads>(a, sm, t, round);
+    // the last workgroup to finish applies the search's decisions (a launch of
+    // its own took 5 us and a gap, six times an event)
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        if (atomicAdd(&t->done, 1u) == gridDim.x - 1) {
+            __threadfence();
+            branch_walk(t, round, levels);
+            t->done = 0;
+        }
+    }
 }
 
 // The event itself at the tree's final Delta: multipliers, P_r, margins,
@@ -3263,14 +3275,11 @@ template <int SHAPE>
 void launch_branch_tree(const BranchArgs &ba, BranchTree *t, hipStream_t stream)
 {
     constexpr int T = kBranchShapes[SHAPE].threads;
-    hipLaunchKernelGGL(k_branch_tree<SHAPE>, dim3(2 * kTreeNear + 1), dim3(T), 0, stream, ba, t, (int)kRoundNear);
-    hipLaunchKernelGGL(k_branch_walk, dim3(1), dim3(1), 0, stream, t, (int)kRoundNear, 0);
-    hipLaunchKernelGGL(k_branch_tree<SHAPE>, dim3(kTreeFar - kTreeNear), dim3(T), 0, stream, ba, t, (int)kRoundFar);
-    hipLaunchKernelGGL(k_branch_walk, dim3(1), dim3(1), 0, stream, t, (int)kRoundFar, 0);
+    hipLaunchKernelGGL(k_branch_tree<SHAPE>, dim3(2 * kTreeNear + 1), dim3(T), 0, stream, ba, t, (int)kRoundNear, 0);
+    hipLaunchKernelGGL(k_branch_tree<SHAPE>, dim3(kTreeFar - kTreeNear), dim3(T), 0, stream, ba, t, (int)kRoundFar, 0);
     for (int r = 0, done = 0; done < kBisections; ++r) {
         const int lv = std::min(kTreeLevels, kBisections - done);
-        hipLaunchKernelGGL(k_branch_tree<SHAPE>, dim3((1 << lv) - 1), dim3(T), 0, stream, ba, t, kRoundBisect + r);
-        hipLaunchKernelGGL(k_branch_walk, dim3(1), dim3(1), 0, stream, t, kRoundBisect + r, lv);
+        hipLaunchKernelGGL(k_branch_tree<SHAPE>, dim3((1 << lv) - 1), dim3(T), 0, stream, ba, t, kRoundBisect + r, lv);
         done += lv;
     }
     hipLaunchKernelGGL(k_branch_final<SHAPE>, dim3(1), dim3(T), 0, stream, ba, t);
@@ -5094,6 +5103,7 @@ sail_status sail_walkers_init(sail_problem_t p, int n_walkers, uint64_t seed, in
     }
     SAIL_HIP(hipMemcpyAsync(p->d_a0, a0.data(), sizeof(double) * No, hipMemcpyHostToDevice, stream));
     SAIL_HIP(hipMemsetAsync(p->d_phi, 0, phi_bytes, stream));  // the padding of the chunks
+    SAIL_HIP(hipMemsetAsync(p->d_tree, 0, sizeof(BranchTree), stream));
     const size_t total = (size_t)n_walkers * No;
     hipLaunchKernelGGL(k_init_walkers, dim3((unsigned)((total + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream,
                        n_walkers, No, (const double *)p->d_a0, p->d_b, p->d_gsc, p->d_ginv, p->d_rate);
