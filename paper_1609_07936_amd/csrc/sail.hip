@@ -10,7 +10,8 @@
 //   * The weighted columns sqrt(wh_i) e^{-omega_j tau_i} of all bins lie, to
 //     rounding, in a space of few dimensions (16 for the benchmark's 512 bins
 //     and 128 times): a Laplace kernel's singular values fall geometrically.
-//     The host builds an orthonormal basis of it, the sweep carries each
+//     The host builds an orthonormal basis of it from a sample of columns, the
+//     device projects all of them, the sweep carries each
 //     walker's coordinates phi of sqrt(wh) Phi in that basis, and sums over
 //     tau become sums over the basis.
 //   * A walker occupies G lanes of a wavefront; lane c holds chunk c mod 4 of
@@ -21,9 +22,9 @@
 //     same accept decision, whatever G is); the walker-independent sums come
 //     from per-bin and pair-sum tables, and a commit is phi = r phi + sigma.
 //   * Spectra live in HBM as b_j with a_j = g b_j (a lazy scale g per walker),
-//     so a move touches two coefficients instead of N_omega.  Lane c of a
-//     walker owns the spectrum accesses of the proposals it staged; the scale
-//     is folded back at resync.
+//     so a move touches two coefficients instead of N_omega; the scale is folded
+//     back at resync.  While a sweep runs they sit in LDS where they fit; else
+//     lane c of a walker owns the spectrum accesses of a batch's proposal c.
 //
 // All code is compiled with -ffp-contract=off; fused multiply-adds are
 // written explicitly where wanted, and the scalar move arithmetic keeps the
@@ -154,6 +155,7 @@ struct SweepArgs {
     int chunk;            // basis dimensions per chunk as stored (a multiple of 16 bytes)
     int columns_lds;      // 1: the workgroup copies the columns to LDS
     int resident;         // split sweeps: bins of every spectrum, the first ones, that the workgroup keeps in LDS
+    int lanes;            // lanes a walker takes (a batch's split sweeps: 4 or 16)
     int pairs;            // split sweeps: chain and stager wavefronts at work in a workgroup (any others leave)
     const void *col;      // [N_omega][4][chunk] columns in the basis, loop precision
     void *phi;            // [N_w][4][chunk] walkers in the basis, loop precision
@@ -249,8 +251,8 @@ __device__ __forceinline__ void wave_lds_sync()
 // threshold, the walker-independent parts of the residue change, S1 =
 // sum_i w_i s_i^2 and S1 + S3 with S3 = sum_i c_i s_i (s_i = dp K_pi + ds K_si),
 // the deltas dp and ds, and the bins, each twice in one word (p | p << 16,
-// s | s << 16).  The bins also stand apart: they are read a proposal earlier
-// than the rest.
+// s | s << 16), or the threshold's band.  The bins also stand apart: they are
+// read a proposal earlier than the rest.
 enum : int {
     kRecRm1 = 0, kRecRinv = 1, kRecThr = 2, kRecT = 3, kRecS1 = 4, kRecDp = 5, kRecDs = 6, kRecPS = 7,
     kRecBand = 7  // split sweeps, which stage masks of shared bins instead: the threshold's band
@@ -1334,7 +1336,11 @@ __global__ __launch_bounds__(2 * kSweepThreads) void k_sweep_split_batched(const
     const int q = owner_of(first, n_jobs, blockIdx.x);
     const SweepArgs &a = jobs[q];
     const int block = blockIdx.x - first[q];
-    if (a.resident) sweep_block<R, M, 4, true, true, kSweepFast, true>(a, block, lds);
+    if (a.lanes == 16) {
+        if (a.columns_lds) sweep_block<R, M, 16, true, false, kSweepFast, true>(a, block, lds);
+        else sweep_block<R, M, 16, false, false, kSweepFast, true>(a, block, lds);
+    }
+    else if (a.resident) sweep_block<R, M, 4, true, true, kSweepFast, true>(a, block, lds);
     else if (a.columns_lds) sweep_block<R, M, 4, true, false, kSweepFast, true>(a, block, lds);
     else sweep_block<R, M, 4, false, false, kSweepFast, true>(a, block, lds);
 }
@@ -1734,7 +1740,7 @@ __global__ __launch_bounds__(kThreads) void k_tables(TableArgs a)
 __global__ __launch_bounds__(64) void k_pair_sums(int n_tau, double w0x2, double dW, const double *tau, const double *wh,
                                                   double2 *GH)
 {
-    const double wbar = fma((double)blockIdx.x, dW, w0x2);
+    const double wbar = w0x2 + (double)blockIdx.x * dW;
     double g = 0.0, h = 0.0;
     for (int i = threadIdx.x; i < n_tau; i += 64) {
         const double e = wh[i] * exp(-wbar * tau[i]);
@@ -3360,6 +3366,7 @@ SweepArgs make_sweep_args(const sail_problem *p, int k0, int k1, const SweepPara
     s.chunk = p->chunk(p->precision);
     s.columns_lds = plan.columns_lds;
     s.resident = plan.resident;
+    s.lanes = plan.lanes;
     s.pairs = plan.threads / 128;
     s.k0 = k0;
     s.k1 = k1;
@@ -4317,6 +4324,28 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
         return b;
     };
     while (pairs < 4 && groups_of(pairs) > (size_t)kCUs * 3 / 2) pairs *= 2;
+    // A round ends with its longest jobs.  While SIMDs would be left without a
+    // chain, those take 16 lanes a walker (1024 bins: 283 to 220 ns a proposal),
+    // longest first, where their columns fit in LDS beside the larger records
+    // (16 FP32 jobs of 9472 walkers, one round: 14.5 to 11.6 ms).
+    std::vector<char> wide(act.size(), 0);
+    {
+        int64_t simds = 4 * kCUs;
+        std::vector<int> by(act.size());
+        for (size_t i = 0; i < act.size(); ++i) {
+            by[i] = (int)i;
+            simds -= (act[i]->p->n_walkers + 15) / 16;
+        }
+        std::stable_sort(by.begin(), by.end(), [&](int x, int y) {
+            return (int64_t)act[x]->p->n_omega * (kend[x] - act[x]->k) > (int64_t)act[y]->p->n_omega * (kend[y] - act[y]->k);
+        });
+        for (int i : by) {
+            const int more = (act[i]->p->n_walkers + 3) / 4 - (act[i]->p->n_walkers + 15) / 16;
+            if (more > simds) break;
+            simds -= more;
+            wide[i] = 1;
+        }
+    }
     // one sweep launch per (precision, basis class, mode); jobs of one
     // workload share theirs
     std::vector<int> group(act.size());
@@ -4353,6 +4382,12 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
             for (int t = 64 * pairs; split && !s.columns_lds && t >= 128; t /= 2) {
                 const SweepPlan q = plan_sweep(p, true, 4, t, kLdsBytes, false, false, 0);
                 if (q.columns_lds) s = q;
+            }
+            for (int t = 4 * 128; split && wide[i] && t >= 128; t /= 2) {
+                const SweepPlan q = plan_sweep(p, true, 16, t, kLdsBytes, false, false, 0);
+                if (!q.columns_lds) continue;
+                s = q;
+                break;
             }
             sa.push_back(make_sweep_args(p, act[i]->k, kend[i],
                                          SweepParams{sc.eps0, sc.amp_p, sc.amp_avg, sc.amp_m, sc.walk_len}, s));
