@@ -410,16 +410,19 @@ void sail_server_destroy(sail_server_t s);
  * temperature schedule (8 bytes per sweep) and event logs beyond 64 events. */
 size_t sail_footprint_bytes(int n_omega, int n_tau, int n_walkers, int precision);
 
-/* Lanes per walker and tau points per lane the sweep kernel uses. */
+/* The nominal layout: tau points per lane as requested (16 if not), and lanes
+ * per walker, next_pow2(ceil(n_tau / tau_per_lane)).  The sweep carries a
+ * walker's coordinates in a basis of the kernel's columns and takes its lanes
+ * per walker (4, 8 or 16) from the population and the LDS; results do not
+ * depend on either. */
 sail_status sail_layout(sail_problem_t p, int *lanes_per_walker, int *tau_per_lane);
 
 /* Requests tau points per lane for the next sail_walkers_init: 4, 8 or 16
  * for FP64, 8, 16 or 32 for FP32, 0 for the library's choice (16).  A
- * request the precision does not take falls back to the choice.  The walkers
- * per wavefront follow as 64 / next_pow2(ceil(n_tau / tau_per_lane)); the
- * smaller tiles give each walker more lanes, which pays when too few walkers
- * fill the device.  The layout changes only the summation order of the
- * residue change.  Any other value: SAIL_EINVAL. */
+ * request the precision does not take falls back to the choice.  It sets the
+ * nominal layout (sail_layout), hence the padding of the reconstructions'
+ * rows in device memory; results and speed do not depend on it.  Any other
+ * value: SAIL_EINVAL. */
 sail_status sail_set_tau_per_lane(sail_problem_t p, int tau_per_lane);
 
 /* Chooses the tau points per lane for this problem at n_walkers walkers and
@@ -439,11 +442,8 @@ sail_status sail_autotune_layout(sail_problem_t p, int n_walkers, int precision,
 
 /* As sail_autotune_layout, for a problem that will have the device to
  * itself: the smallest tile (4 tau points per lane for FP64, 8 for FP32) is
- * a candidate too.  More lanes per walker shorten each proposal's serial
- * chain for more total work, which wins when the walkers alone leave the
- * device underfilled and loses once other jobs fill it.  Its choices are
- * cached apart from sail_autotune_layout's (a SAIL_TUNE_CACHE line tagged
- * sail-tune-alone-v1). */
+ * a candidate too.  Its choices are cached apart from sail_autotune_layout's
+ * (a SAIL_TUNE_CACHE line tagged sail-tune-alone-v1). */
 sail_status sail_autotune_layout_alone(sail_problem_t p, int n_walkers, int precision, int *tau_per_lane,
                                        void *stream);
 
