@@ -3220,8 +3220,10 @@ ResyncArgs make_resync_args(const sail_problem *p, int renorm, const int32_t *li
 constexpr int kResyncClasses = 4;
 int resync_class(int n_omega) { return n_omega <= 256 ? 0 : n_omega <= 512 ? 1 : n_omega <= 1024 ? 2 : 3; }
 // Walkers per resync workgroup: 16 fill the matrix instructions' rows, where two
-// such workgroups fit a compute unit and there are more than 8 per compute unit;
-// else 8.
+// such workgroups fit a compute unit and there are more than 8 walkers per compute
+// unit (a resync with its launch, 16 against 8 walkers: 512 bins, 16384 walkers
+// 133 and 168 us, 3000 walkers 48 and 62 us); else 8 (256 bins, 2048 walkers 38
+// and 27 us; 1000 bins, 8000 walkers 210 and 212 us, and 8 take half the LDS).
 int resync_wpb(int n_omega, size_t n_items) { return n_omega <= 512 && n_items > 8 * 256 ? 16 : 8; }
 // its LDS: the walkers' spectra, then the per-wavefront residue partials
 size_t resync_shmem(int n_omega, int wpb) { return sizeof(double) * wpb * (resync_stride(n_omega) + 4); }
@@ -4316,7 +4318,9 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
     // pairs of wavefronts per split workgroup: four share a compute unit's LDS
     // copy of the columns when workgroups abound; fewer when that would leave
     // compute units idle (up to half as many workgroups again as compute units
-    // still pack well, longest first)
+    // still pack well, longest first; 24 FP64 jobs of 20736 walkers, with the
+    // columns of 1024 bins in LDS beside two pairs: a round 27 ms, with four pairs
+    // for all 46 ms)
     int pairs = 1;
     auto groups_of = [&](int n) {
         size_t b = 0;
