@@ -2976,6 +2976,7 @@ struct sail_problem {
     void *d_phi = nullptr;  // [N_w][4][chunk()] in the loop precision
     void *d_Phi = nullptr;  // [read_rows][ntau_pad], filled when reconstructions are read
     int read_rows = 0;
+    std::mutex read_mu;  // one read-out of reconstructions at a time uses them
     double *d_a0 = nullptr, *d_tmp = nullptr, *d_teff = nullptr;  // d_teff: imprint strength of the last event
     double *d_part = nullptr;               // partial sums of the averaged spectrum
     unsigned long long *d_hist = nullptr;   // counts of the residue histogram, kept from its first call
@@ -5513,7 +5514,9 @@ sail_status sail_read_state(sail_problem_t p, double *a, double *F, double *rate
     if (a) SAIL_HIP(hipMemcpyAsync(a, p->d_b, sizeof(double) * (size_t)n * No, hipMemcpyDeviceToHost, stream));
     std::vector<double> phi;
     std::vector<float> phif;
+    std::unique_lock<std::mutex> rows_lock(p->read_mu, std::defer_lock);
     if (F) {
+        rows_lock.lock();
         const bool f32 = p->precision == SAIL_FP32;
         if (f32) phif.resize((size_t)n * ntp);
         phi.resize((size_t)n * ntp);
