@@ -259,7 +259,9 @@ enum : int {
 };
 constexpr int kRecWords = 8;      // doubles per record
 constexpr int kWalkWords = 5;     // doubles per staged step of an index-selection walk: bins, two values, two draws
-constexpr double kNever = -1.7976931348623157e308;  // threshold of a proposal that is never accepted
+// Threshold of a proposal that is never accepted: nothing compares below it, a
+// residue change of -infinity (an infinite residue's) included, or near it.
+constexpr double kNever = __builtin_nan("");
 // Doubles of LDS per walker, padded against bank conflicts: the records and
 // bins of two batches (one runs while the next is staged), or of one batch and
 // its walk steps.
@@ -664,7 +666,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
             if (__builtin_amdgcn_inverse_ballot_w64(near)) {
                 uint32_t x0, x1, x2, x3;
                 philox10((uint32_t)(q0 + qq), (uint32_t)k, (uint32_t)lw, kStreamProposal, key0, key1, x0, x1, x2, x3);
-                take = v.thr > kNever && dchi2 < -Tabs * log(u01(x3));
+                take = dchi2 < -Tabs * log(u01(x3));
             }
             am = (am & ~near) | (near & __builtin_amdgcn_ballot_w64(take));
         }
