@@ -280,14 +280,17 @@ sail_status sail_set_trace(sail_problem_t p, int k0, int k1, double *dchi2, uint
 sail_status sail_set_timing(sail_problem_t p, int enable);
 sail_status sail_sweep_timing(sail_problem_t p, double *total_ms, int64_t *launches, int reset);
 
-/* Checkpoint of the walker population (spectra, reconstructions, scales,
- * residues, acceptance rates, seed and residue unit); with the counter-based
- * random stream, export -> import -> continue is bit-identical to an
- * uninterrupted run.  Export: buf host; with buf == NULL only *bytes is set
- * to the size needed; otherwise *bytes is the capacity of buf on entry and
- * the size written on return.  Import: buf host, bytes its size; the problem
- * must already hold walkers of the same count, layout and precision
- * (sail_walkers_init). */
+/* Checkpoint of the walker population (spectra, coordinates of the
+ * reconstructions in the problem's basis, scales, residues, acceptance rates,
+ * seed and residue unit); with the counter-based random stream, export ->
+ * import -> continue is bit-identical to an uninterrupted run.  Export: buf
+ * host; with buf == NULL only *bytes is set to the size needed; otherwise
+ * *bytes is the capacity of buf on entry and the size written on return.
+ * Import: buf host, bytes its size; the problem must already hold walkers of
+ * the same count and precision (sail_walkers_init).  A checkpoint of another
+ * basis (a problem of the same sizes with other errors, or a format before the
+ * current one, 3 or 4) is taken by its spectra: coordinates and residues are
+ * recomputed from them. */
 sail_status sail_state_export(sail_problem_t p, void *buf, size_t *bytes, void *stream);
 sail_status sail_state_import(sail_problem_t p, const void *buf, size_t bytes, void *stream);
 

@@ -2958,9 +2958,9 @@ struct sail_problem {
     double tC = 0.0, tw0 = 0.0, tdW = 0.0;
     // the basis: dimensions per chunk for either precision (dimension d lies in
     // chunk d mod 4, so the FP32 loop's shorter basis is a prefix of every
-    // chunk), and its vectors times sqrt(wh), [n_tau][4][echunk]
+    // chunk), and a digest of its vectors, which checkpoints carry
     int dims64 = 1, dims32 = 1, echunk = 2;
-    std::vector<double> h_proj;
+    uint64_t basis_id = 0;
     void *d_col = nullptr;  // columns in the loop precision, [N_omega][4][chunk()]
     int layout_precision = -1;
     int dims(int precision_) const { return precision_ == SAIL_FP32 ? dims32 : dims64; }
@@ -3868,9 +3868,15 @@ sail_status build_tables(sail_problem *p)
     p->dims64 = round_dims(SAIL_FP64, dims64);
     p->dims32 = round_dims(SAIL_FP32, dims32);
     const int ec = p->echunk = chunk_stride<double>(p->dims64), kept = std::min(dims, 4 * p->dims64);
-    p->h_proj.assign((size_t)Nt * 4 * ec, 0.0);
+    uint64_t id = 0xcbf29ce484222325ull;  // FNV-1a, word by word
     for (int d = 0; d < kept; ++d)
-        for (int i = 0; i < Nt; ++i) p->h_proj[(size_t)i * 4 * ec + (d % 4) * ec + d / 4] = sw[i] * q[d][i];
+        for (int i = 0; i < Nt; ++i) {
+            const double v = sw[i] * q[d][i];
+            uint64_t x;
+            std::memcpy(&x, &v, sizeof x);
+            id = (id ^ x) * 0x100000001b3ull;
+        }
+    p->basis_id = id;
     if ((st = dalloc(&p->d_E, (size_t)No * p->cols()))) return st;
     a.E = p->d_E;
     a.cols = p->cols();
@@ -4823,29 +4829,6 @@ void serve(sail_server *S)
 
 }  // namespace
 
-namespace {
-
-// phi_d = sum_i sqrt(wh_i) q_id Phi_i of every walker, in the layout of d_phi.
-template <typename R>
-std::vector<R> phi_from_rows(const sail_problem *p, const char *rows)
-{
-    const int Nt = p->n_tau, ec = p->echunk, ck = p->chunk(p->precision);
-    std::vector<R> out((size_t)p->n_walkers * 4 * ck, (R)0);
-    std::vector<R> row(p->ntau_pad);
-    std::vector<double> acc(4 * ec);
-    for (int l = 0; l < p->n_walkers; ++l) {
-        std::memcpy(row.data(), rows + sizeof(R) * (size_t)l * p->ntau_pad, sizeof(R) * p->ntau_pad);
-        std::fill(acc.begin(), acc.end(), 0.0);
-        for (int i = 0; i < Nt; ++i)
-            for (int d = 0; d < 4 * ec; ++d) acc[d] += p->h_proj[(size_t)i * 4 * ec + d] * (double)row[i];
-        for (int q = 0; q < 4; ++q)
-            for (int t = 0; t < std::min(ec, ck); ++t) out[((size_t)l * 4 + q) * ck + t] = (R)acc[q * ec + t];
-    }
-    return out;
-}
-
-}  // namespace
-
 struct sail_batch {
     int device = 0;
     std::vector<sail_problem *> probs;
@@ -5589,21 +5572,28 @@ sail_status sail_read_event_margins(sail_problem_t p, int n_events, double *gap,
 }
 
 // Checkpoint layout: header, then b [N_w][N_omega], phi [N_w][phi_row] in the
-// loop precision, g, 1/g, chi^2, rate [N_w], all little-endian as in memory.
-// Version 3 held the reconstructions Phi [N_w][ntau_pad] in place of phi
-// (phi_row 0); the import takes them to the basis.
+// loop precision, g, 1/g, chi^2, rate [N_w], and the digest of the basis that
+// phi is in, all little-endian as in memory.  phi means something in that basis
+// alone, which follows from the weights and the times (and the selection's
+// rounding): coordinates in another one, as of a problem with other errors, are
+// not read, and those of version 4, which had no digest, neither.  Version 3 held
+// the reconstructions Phi [N_w][ntau_pad] in place of phi (phi_row 0).  Where phi
+// is not read it is taken from the spectra, with the residues.
 struct StateHeader {
-    uint64_t magic;  // "SAILSTv4"
+    uint64_t magic;  // "SALIStv5"
     int32_t n_walkers, n_omega, n_tau, ntau_pad, precision, phi_row;
     uint64_t seed;
     double chi2_unit;
 };
-constexpr uint64_t kStateMagic = 0x34767453494c4153ull, kStateMagicV3 = 0x33767453494c4153ull;
+constexpr uint64_t kStateMagic = 0x35767453494c4153ull, kStateMagicV4 = 0x34767453494c4153ull,
+                   kStateMagicV3 = 0x33767453494c4153ull;
 
-size_t state_bytes(const sail_problem *p, int row)
+// (version 3 and 4 files end before the digest)
+size_t state_bytes(const sail_problem *p, int row, bool digest = true)
 {
     const size_t n = (size_t)p->n_walkers, rsz = p->precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
-    return sizeof(StateHeader) + sizeof(double) * n * p->n_omega + rsz * n * row + 4 * sizeof(double) * n;
+    return sizeof(StateHeader) + sizeof(double) * n * p->n_omega + rsz * n * row + 4 * sizeof(double) * n +
+           (digest ? sizeof(uint64_t) : 0);
 }
 
 sail_status sail_state_export(sail_problem_t p, void *buf, size_t *bytes, void *stream_)
@@ -5635,6 +5625,8 @@ sail_status sail_state_export(sail_problem_t p, void *buf, size_t *bytes, void *
     SAIL_HIP(hipMemcpyAsync(o, p->d_chi2, sv, hipMemcpyDeviceToHost, stream));
     o += sv;
     SAIL_HIP(hipMemcpyAsync(o, p->d_rate, sv, hipMemcpyDeviceToHost, stream));
+    o += sv;
+    std::memcpy(o, &p->basis_id, sizeof p->basis_id);
     SAIL_HIP(hipStreamSynchronize(stream));
     *bytes = need;
     return SAIL_OK;
@@ -5647,13 +5639,18 @@ sail_status sail_state_import(sail_problem_t p, const void *buf, size_t bytes, v
     StateHeader h;
     if (bytes < sizeof h) return fail(SAIL_EINVAL, "checkpoint truncated");
     std::memcpy(&h, buf, sizeof h);
-    if (h.magic != kStateMagic && h.magic != kStateMagicV3) return fail(SAIL_EINVAL, "not a checkpoint");
-    const bool v3 = h.magic == kStateMagicV3;
-    const int row = v3 ? p->ntau_pad : p->phi_row();
-    if (h.n_walkers != p->n_walkers || h.n_omega != p->n_omega || h.n_tau != p->n_tau || h.ntau_pad != p->ntau_pad ||
-        h.precision != p->precision || (!v3 && h.phi_row != row))
+    const bool v3 = h.magic == kStateMagicV3, digest = h.magic == kStateMagic;
+    if (!digest && !v3 && h.magic != kStateMagicV4) return fail(SAIL_EINVAL, "not a checkpoint");
+    // (phi does not depend on the padding of the times: only version 3's rows do)
+    const int row = v3 ? h.ntau_pad : h.phi_row;
+    if (h.n_walkers != p->n_walkers || h.n_omega != p->n_omega || h.n_tau != p->n_tau || (v3 && h.ntau_pad != p->ntau_pad) ||
+        h.precision != p->precision || row <= 0)
         return fail(SAIL_EINVAL, "checkpoint does not match this problem's shape, layout or precision");
-    if (bytes < state_bytes(p, row)) return fail(SAIL_EINVAL, "checkpoint truncated");
+    const size_t need = state_bytes(p, row, digest);
+    if (bytes < need) return fail(SAIL_EINVAL, "checkpoint truncated");
+    uint64_t id = 0;
+    if (digest) std::memcpy(&id, (const char *)buf + need - sizeof id, sizeof id);
+    const bool same_basis = digest && id == p->basis_id && row == p->phi_row();
     p->self_T_end = 0;
     hipStream_t stream = (hipStream_t)stream_;
     SAIL_HIP(hipSetDevice(p->device));
@@ -5662,17 +5659,7 @@ sail_status sail_state_import(sail_problem_t p, const void *buf, size_t bytes, v
     const size_t sb = sizeof(double) * n * p->n_omega, sp = rsz * n * row, sv = sizeof(double) * n;
     SAIL_HIP(hipMemcpyAsync(p->d_b, o, sb, hipMemcpyHostToDevice, stream));
     o += sb;
-    std::vector<double> phi64;
-    std::vector<float> phi32;
-    if (!v3) {
-        SAIL_HIP(hipMemcpyAsync(p->d_phi, o, sp, hipMemcpyHostToDevice, stream));
-    } else if (p->precision == SAIL_FP32) {
-        phi32 = phi_from_rows<float>(p, o);
-        SAIL_HIP(hipMemcpyAsync(p->d_phi, phi32.data(), sizeof(float) * phi32.size(), hipMemcpyHostToDevice, stream));
-    } else {
-        phi64 = phi_from_rows<double>(p, o);
-        SAIL_HIP(hipMemcpyAsync(p->d_phi, phi64.data(), sizeof(double) * phi64.size(), hipMemcpyHostToDevice, stream));
-    }
+    if (same_basis) SAIL_HIP(hipMemcpyAsync(p->d_phi, o, sp, hipMemcpyHostToDevice, stream));
     o += sp;
     SAIL_HIP(hipMemcpyAsync(p->d_gsc, o, sv, hipMemcpyHostToDevice, stream));
     o += sv;
@@ -5681,6 +5668,10 @@ sail_status sail_state_import(sail_problem_t p, const void *buf, size_t bytes, v
     SAIL_HIP(hipMemcpyAsync(p->d_chi2, o, sv, hipMemcpyHostToDevice, stream));
     o += sv;
     SAIL_HIP(hipMemcpyAsync(p->d_rate, o, sv, hipMemcpyHostToDevice, stream));
+    if (!same_basis) {
+        const sail_status st = launch_resync(p, 0, nullptr, nullptr, p->n_walkers, stream);
+        if (st) return st;
+    }
     SAIL_HIP(hipStreamSynchronize(stream));
     p->seed = h.seed;
     p->chi2_unit = h.chi2_unit;

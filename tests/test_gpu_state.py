@@ -18,10 +18,10 @@ def S():
     return sail
 
 
-def _workload(n_omega, n_tau, n_walkers):
-    tau = W.uniform_tau(0.05, 1.6, n_tau)
-    tgt = W.Target([1.5, 4.0], [0.4, 0.8], [0.6, 0.4], 10.0)
-    return W.make("state", 10.0, n_omega, tau, tgt, 1e-3, 3, n_walkers, 8, 1e2, 1.0, 100, 100, 5, n_quad=2000)
+def _workload(n_omega, n_tau, n_walkers, w_max=10.0, tau_hi=1.6):
+    tau = W.uniform_tau(0.05, tau_hi, n_tau)
+    tgt = W.Target([1.5, 4.0], [0.4, 0.8], [0.6, 0.4], w_max)
+    return W.make("state", w_max, n_omega, tau, tgt, 1e-3, 3, n_walkers, 8, 1e2, 1.0, 100, 100, 5, n_quad=2000)
 
 
 def _problem(S, wl, precision=0, seed=11, sigma=None):
@@ -70,3 +70,86 @@ def test_infinite_residue_keeps_the_sum_rules(S, how, precision):
     # at most three moves of three bins each, a few roundings a term
     np.testing.assert_allclose(a.sum(axis=1) * dw, wl.m0, rtol=64 * 2.0 ** -53)
     assert not np.isfinite(gp.read_chi2()).any()
+
+
+def _coordinates(blob):
+    at, (n, n_omega, n_tau, ntau_pad, precision, row) = _sections(blob)
+    return np.frombuffer(blob[at[1]:at[2]], dtype=np.float32 if precision else np.float64).reshape(n, row).astype(np.float64)
+
+
+def _assert_coordinates(gp, wl, sigma, precision):
+    """|phi|^2 = sum_i w_i F_i^2 whatever the basis (to what the basis leaves out
+    of it, squared, and the loop precision's rounding), and the residues are the
+    spectra's."""
+    st = gp.read_state()
+    dw = wl.omega[1] - wl.omega[0]
+    F = st["a"] @ (np.exp(-np.outer(wl.omega, wl.tau)) * (dw / (2.0 * np.pi)))
+    w = 1.0 / sigma ** 2
+    phi = _coordinates(gp.state_export())
+    np.testing.assert_allclose((phi ** 2).sum(axis=1), (w * F * F).sum(axis=1), rtol=1e-5 if precision else 1e-11)
+    np.testing.assert_allclose(gp.read_chi2(), (w * (F - wl.Ft) ** 2).sum(axis=1), rtol=1e-6)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("other", ["errors", "dimensions", "format 3", "format 4"])
+def test_checkpoint_of_another_basis_is_taken_by_its_spectra(S, other, precision):
+    """Coordinates in a basis that is not the problem's, or not known to be, are
+    not taken as its own: other errors (also such that the basis has another
+    number of dimensions), and the formats without a digest."""
+    wl = _workload(40, 24, 33, 25.0, 4.0) if other == "dimensions" else _workload(40, 24, 33)
+    n, n_tau = wl.n_walkers, wl.tau.size
+    sched = S.Schedule(np.full(100, 1e-3))
+    a = _problem(S, wl, precision)
+    a.run(sched, 0, 3)  # between resyncs
+    blob, st = a.state_export(), a.read_state()
+    sigma = wl.sigma
+    if other == "errors":
+        sigma = wl.sigma * (1.0 + 0.5 * np.cos(np.arange(n_tau)))
+    elif other == "dimensions":
+        v = 25.0 * (wl.tau - wl.tau ** 2 / 8.0)  # columns like Gaussians along the times: more of them count
+        sigma = np.exp(0.5 * v.max() - v)
+    else:
+        at, (_, _, _, ntau_pad, _, _) = _sections(blob)
+        phi = blob[at[1]:at[2]]
+        if other == "format 3":
+            dw = wl.omega[1] - wl.omega[0]
+            rows = np.zeros((n, ntau_pad), dtype=np.float32 if precision else np.float64)
+            rows[:, :n_tau] = st["F"] / (dw / (2.0 * np.pi))
+            phi = rows.tobytes()
+        head = bytearray(blob[:48])
+        head[7:8] = other[-1:].encode()
+        if other == "format 3":
+            head[28:32] = struct.pack("<i", 0)
+        blob = bytes(head) + blob[48:at[1]] + phi + blob[at[2]:at[6]]
+    b = _problem(S, wl, precision, seed=999, sigma=sigma)
+    if precision == 0:
+        assert (_sections(b.state_export())[1][5] != _sections(a.state_export())[1][5]) == (other == "dimensions")
+    b.state_import(blob)
+    np.testing.assert_array_equal(b.read_state()["rate"], st["rate"])
+    np.testing.assert_allclose(b.read_state()["a"], st["a"], rtol=1e-15)
+    _assert_coordinates(b, wl, sigma, precision)
+    if other.startswith("format") and precision == 0:
+        # the same decisions, for a few sweeps, and so the same spectra
+        a.run(sched, 3, 3)
+        b.run(sched, 3, 3)
+        np.testing.assert_allclose(b.read_state()["a"], a.read_state()["a"], rtol=1e-9)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_checkpoint_of_the_same_basis_keeps_its_bits(S, precision):
+    """Import and export give the same file, also with another padding of the
+    times (which no section of it depends on)."""
+    wl = _workload(40, 24, 33)
+    a = _problem(S, wl, precision)
+    a.run(S.Schedule(np.full(100, 1e-3)), 0, 3)
+    blob = a.state_export()
+    b = S.Problem(wl.omega, wl.tau, wl.Ft, wl.sigma, wl.m0, wl.m1)
+    b.set_tau_per_lane(8)
+    b.init_walkers(wl.n_walkers, 999, precision=precision)
+    assert a.layout() != b.layout()
+    b.state_import(blob)
+    again = b.state_export()
+    assert blob[:20] + blob[24:] == again[:20] + again[24:]  # (bytes 20 to 23 hold the padding)
+    b.state_import(blob + b"\0" * 16)  # a buffer larger than the checkpoint
+    with pytest.raises(S.SailError):
+        b.state_import(blob[:-1])
