@@ -429,24 +429,20 @@ sail_status sail_layout(sail_problem_t p, int *lanes_per_walker, int *tau_per_la
 sail_status sail_set_tau_per_lane(sail_problem_t p, int tau_per_lane);
 
 /* Chooses the tau points per lane for this problem at n_walkers walkers and
- * `precision` by timing a few sweeps of each candidate layout on `stream`
- * (the two larger tiles of the precision: 8 and 16 for FP64, 16 and 32 for
- * FP32, the right candidates when the job will share the device with
- * others, as in a batch or the served loop), and requests it as
- * sail_set_tau_per_lane does (*tau_per_lane receives it, may be NULL).  The served loop tunes each new shape after the rounds
- * already enqueued have drained, so the candidates run on an otherwise idle
- * device.  Results are cached per (device architecture,
- * n_omega, n_tau, n_walkers, precision) for the life of the process, and
- * across processes when the environment variable SAIL_TUNE_CACHE names a
- * file (read at the first lookup; each new choice is appended as one text
- * line).  Leaves the problem without walkers: call it before
- * sail_walkers_init. */
+ * `precision` and requests it as sail_set_tau_per_lane does (*tau_per_lane
+ * receives it, may be NULL).  Nothing is timed, since the nominal layout has
+ * no bearing on speed: the choice is 16, or the one remembered for (device
+ * architecture, n_omega, n_tau, n_walkers, precision).  Choices are remembered
+ * for the life of the process, and across processes when the environment
+ * variable SAIL_TUNE_CACHE names a file (read at the first lookup; each new
+ * choice is appended as one text line).  May leave the problem without
+ * walkers: call it before sail_walkers_init. */
 sail_status sail_autotune_layout(sail_problem_t p, int n_walkers, int precision, int *tau_per_lane, void *stream);
 
 /* As sail_autotune_layout, for a problem that will have the device to
- * itself: the smallest tile (4 tau points per lane for FP64, 8 for FP32) is
- * a candidate too.  Its choices are cached apart from sail_autotune_layout's
- * (a SAIL_TUNE_CACHE line tagged sail-tune-alone-v1). */
+ * itself.  Its choices are remembered apart from sail_autotune_layout's (a
+ * SAIL_TUNE_CACHE line tagged sail-tune-alone-v1), and a remembered one may be
+ * the smallest tile too (4 tau points per lane for FP64, 8 for FP32). */
 sail_status sail_autotune_layout_alone(sail_problem_t p, int n_walkers, int precision, int *tau_per_lane,
                                        void *stream);
 

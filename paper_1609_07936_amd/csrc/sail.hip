@@ -3889,6 +3889,8 @@ sail_status build_tables(sail_problem *p)
     return SAIL_OK;
 }
 
+constexpr int kDefaultTile = 16;
+
 // The nominal lane layout: TPL tau points per lane (16 unless requested
 // otherwise; more only when N_tau needs it), a power-of-two number of lanes per
 // walker, tau padded to lanes * TPL; and the columns in the loop precision.
@@ -3896,7 +3898,7 @@ sail_status build_layout(sail_problem *p, int precision)
 {
     const int n_tau = p->n_tau;
     const int tpl_max = precision == SAIL_FP32 ? 32 : 16;
-    int tpl = 16;
+    int tpl = kDefaultTile;
     auto tile_ok = [&](int v) { return v == tpl_max || v == tpl_max / 2 || v == tpl_max / 4; };
     if (tile_ok(p->tpl_hint)) {
         tpl = p->tpl_hint;
@@ -4627,18 +4629,9 @@ sail_status setup_job(sail_server *S, ServedJob *j)
 {
     sail_status st;
     int tpl = j->tpl;
-    if (tpl < 0 && !tuned_layout(S->device, (int)j->omega.size(), (int)j->tau.size(), j->n_walkers, j->precision, &tpl)) {
-        // first job of this shape: tune on a scratch problem outside the
-        // arena, after the rounds already enqueued have drained, so that the
-        // candidates are timed on an otherwise idle device (once per shape)
-        (void)hipStreamSynchronize(S->stream);
-        sail_problem *scratch = nullptr;
-        st = sail_problem_create(j->omega.data(), (int)j->omega.size(), j->tau.data(), (int)j->tau.size(), j->F.data(),
-                                 j->has_sigma ? j->sigma.data() : nullptr, j->m0, j->m1, j->mode, S->device, &scratch);
-        if (!st) st = sail_autotune_layout(scratch, j->n_walkers, j->precision, &tpl, S->setup);
-        sail_problem_destroy(scratch);
-        if (st) return st;
-    }
+    const int No = (int)j->omega.size(), Nt = (int)j->tau.size();
+    if (tpl < 0 && !tuned_layout(S->device, No, Nt, j->n_walkers, j->precision, &tpl))
+        remember_layout(S->device, No, Nt, j->n_walkers, j->precision, tpl = kDefaultTile, false);
     RegionScope rs(&j->region);
     if ((st = sail_problem_create(j->omega.data(), (int)j->omega.size(), j->tau.data(), (int)j->tau.size(), j->F.data(),
                                   j->has_sigma ? j->sigma.data() : nullptr, j->m0, j->m1, j->mode, S->device, &j->p)))
@@ -4993,80 +4986,25 @@ sail_status sail_set_tau_per_lane(sail_problem_t p, int tau_per_lane)
     return SAIL_OK;
 }
 
-// Times a few sweeps of each candidate tile and requests the fastest.  The
-// smallest tile (more lanes per walker: a shorter serial chain per proposal
-// for more total work) is a candidate only for a problem that has the device
-// to itself: timed alone it wins whenever the walkers leave the device
-// underfilled, but jobs that share the device pay for its extra work.
-sail_status autotune_layout(sail_problem_t p, int n_walkers, int precision, int *tau_per_lane, void *stream_,
-                            bool alone)
+// The sweep has one speed and one result whatever the nominal layout, so there is
+// nothing to time: the choice is the remembered one (a cache file may hold
+// another) or the default tile.
+sail_status autotune_layout(sail_problem_t p, int n_walkers, int precision, int *tau_per_lane, void *stream, bool alone)
 {
     if (!p) return fail(SAIL_EINVAL, "NULL problem");
     if (precision != SAIL_FP64 && precision != SAIL_FP32) return fail(SAIL_EINVAL, "bad precision");
     if (n_walkers < 2 || n_walkers > kBranchMaxWalkers) return fail(SAIL_EINVAL, "bad walker count");
-    int cached = 0;
-    if (tuned_layout(p->device, p->n_omega, p->n_tau, n_walkers, precision, &cached, alone)) {
-        p->tpl_hint = cached;
-        if (tau_per_lane) *tau_per_lane = cached;
-        return SAIL_OK;
+    int tpl = 0;
+    if (!tuned_layout(p->device, p->n_omega, p->n_tau, n_walkers, precision, &tpl, alone)) {
+        SAIL_HIP(hipSetDevice(p->device));
+        SAIL_HIP(hipStreamSynchronize((hipStream_t)stream));
+        p->free_walkers();
+        p->chi2_unit = NAN;
+        tpl = kDefaultTile;
+        remember_layout(p->device, p->n_omega, p->n_tau, n_walkers, precision, tpl, alone);
     }
-    hipStream_t stream = (hipStream_t)stream_;
-    SAIL_HIP(hipSetDevice(p->device));
-    const int tpl_max = precision == SAIL_FP32 ? 32 : 16;
-    const int cands[3] = {tpl_max / 2, tpl_max, alone ? tpl_max / 4 : 0};
-    std::vector<double> T(8, 1.0);
-    sail_schedule sc;
-    sail_schedule_defaults(&sc);
-    sc.T = T.data();
-    sc.n_T = (int)T.size();
-    sc.branch_every = sc.resync_every = 1000;
-    const SweepParams sp{sc.eps0, sc.amp_p, sc.amp_avg, sc.amp_m, sc.walk_len};
-    hipEvent_t e0, e1;
-    SAIL_HIP(hipEventCreate(&e0));
-    SAIL_HIP(hipEventCreate(&e1));
-    int best = 0;
-    float best_ms = 0.f;
-    sail_status st = SAIL_OK;
-    const int saved_timing = p->timing;
-    p->timing = 0;
-    for (int c : cands) {
-        if (c == 0) continue;
-        p->tpl_hint = c;
-        if ((st = sail_walkers_init(p, n_walkers, 1, precision, stream_))) break;
-        if (p->tpl != c) continue;  // the layout could not take this tile
-        if ((st = prepare_schedule(p, &sc, 8, stream))) break;
-        if ((st = launch_sweep(p, 0, 1, sp, stream))) break;  // warm-up
-        float ms = 1e30f;
-        for (int rep = 0; rep < 3 && st == SAIL_OK; ++rep) {
-            hipError_t e = hipEventRecord(e0, stream);
-            if (e == hipSuccess) st = launch_sweep(p, 1 + 2 * rep, 3 + 2 * rep, sp, stream);
-            if (e == hipSuccess && st == SAIL_OK) e = hipEventRecord(e1, stream);
-            if (e == hipSuccess && st == SAIL_OK) e = hipEventSynchronize(e1);
-            float x = 0.f;
-            if (e == hipSuccess && st == SAIL_OK) e = hipEventElapsedTime(&x, e0, e1);
-            if (e != hipSuccess) st = fail(SAIL_EDEVICE, std::string("autotune timing: ") + hipGetErrorString(e));
-            ms = std::min(ms, x);
-        }
-        if (st) break;
-        if (best == 0 || ms < best_ms) {
-            best = c;
-            best_ms = ms;
-        }
-    }
-    p->timing = saved_timing;
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
-    (void)hipStreamSynchronize(stream);
-    p->free_walkers();
-    p->chi2_unit = NAN;
-    if (st) {
-        p->tpl_hint = 0;
-        return st;
-    }
-    if (best == 0) best = tpl_max;
-    p->tpl_hint = best;
-    remember_layout(p->device, p->n_omega, p->n_tau, n_walkers, precision, best, alone);
-    if (tau_per_lane) *tau_per_lane = best;
+    p->tpl_hint = tpl;
+    if (tau_per_lane) *tau_per_lane = tpl;
     return SAIL_OK;
 }
 

@@ -458,10 +458,10 @@ class Problem:
         _check(lib().sail_set_tau_per_lane(self._h, int(tpl)), "sail_set_tau_per_lane")
 
     def autotune_layout(self, n_walkers: int, precision: int = SAIL_FP64, stream=None, alone: bool = False) -> int:
-        """Times the candidate lane layouts and requests the fastest for the
+        """Requests the remembered nominal layout, or the default one, for the
         next init_walkers (this leaves the problem without walkers); alone:
-        the problem has the device to itself, so the smallest tile is a
-        candidate too."""
+        the layouts remembered for problems with the device to themselves.
+        The layout has no bearing on speed or results: nothing is timed."""
         v = ctypes.c_int()
         fn, name = ((lib().sail_autotune_layout_alone, "sail_autotune_layout_alone") if alone
                     else (lib().sail_autotune_layout, "sail_autotune_layout"))

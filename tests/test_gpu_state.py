@@ -153,3 +153,16 @@ def test_checkpoint_of_the_same_basis_keeps_its_bits(S, precision):
     b.state_import(blob + b"\0" * 16)  # a buffer larger than the checkpoint
     with pytest.raises(S.SailError):
         b.state_import(blob[:-1])
+
+
+def test_autotuned_layouts_do_not_vary(S):
+    """Speed does not depend on the nominal layout: the autotuners choose the
+    default, not what a timing of equal launches happens to favour."""
+    for n_omega in (33, 48, 65, 90, 127, 160):
+        wl = _workload(n_omega, 40, 64)
+        for precision in (0, 1):
+            for alone in (False, True):
+                gp = S.Problem(wl.omega, wl.tau, wl.Ft, wl.sigma, wl.m0, wl.m1)
+                assert gp.autotune_layout(wl.n_walkers, precision, alone=alone) == 16
+                gp.init_walkers(wl.n_walkers, 1, precision=precision)
+                assert gp.layout() == (4, 16)
