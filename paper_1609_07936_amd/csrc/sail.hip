@@ -3599,16 +3599,20 @@ sail_status launch_sweep(sail_problem *p, int k0, int k1, const SweepParams &sp,
 // Jacobi), of which the first are kept, as many as leave less than kBasisTol64
 // of any column, filled up to the whole chunks they are stored in.  The sweep drops
 // the product of two such residuals, so the scalar products of the FP64 loop
-// are good to kBasisTol64^2 = 1e-14 of the norms at worst, and to their own
-// rounding in practice (over the benchmark's and the batch's grids, in units of
-// the condition scale and on spectra of two bins, which resolve the columns
-// best: 2e-17 to 9e-17 rms, at most 2e-15, against 1e-16 to 4e-16 and 4e-15 of the
-// recurrence along tau that generated the columns before).  The FP32 loop takes
+// are good to kBasisTol64^2 = 1e-14 of the norms at worst.  That must not exceed
+// what summing over columns from a recurrence along tau in doubles left (in units of
+// the condition scale, spectra of two bins, which resolve the columns best, 600
+// grids of 32 to 900 bins and 16 to 256 times): 16 dimensions and more leave 2e-17 to
+// 9e-17 rms and at most 2.0e-15, the recurrence 8e-17 to 6e-16 and 5e-16 to 6e-15, the
+// larger its grids; at most 0.56 times the recurrence's maximum on any grid.  The
+// small grids that 8 dimensions hold to 1e-7 had a recurrence as short as
+// they (1.0e-15 to 2.1e-15) against up to 7e-15 left out, so these must hold to
+// kBasisTolLeast (else 16: 1.2e-16).  The FP32 loop takes
 // the first vectors, up to kBasisTol32 (squared 1e-8, below its rounding).  The
 // selection runs on the host on kBasisSample columns spread over the grid; the
 // device projects every column on it, and those found outside their span join
 // the sample.
-constexpr double kBasisTol64 = 1e-7, kBasisTol32 = 1e-4, kBasisGreedy = 1e-8;
+constexpr double kBasisTol64 = 1e-7, kBasisTolLeast = 2e-8, kBasisTol32 = 1e-4, kBasisGreedy = 1e-8;
 constexpr int kBasisSample = 64;
 // Vectors a footprint reckons with.  Decaying kernels give 5 to 25; weights that
 // turn the columns into separate Gaussians reach 67 when they span the whole
@@ -3862,7 +3866,8 @@ sail_status build_tables(sail_problem *p)
     const int dims = (int)q.size();
     int dims64 = dims, dims32 = dims;
     for (int d = dims - 1; d >= 1; --d) {
-        if (worst[d] <= kBasisTol64 * kBasisTol64) dims64 = d;
+        const double tol = d <= 4 * kDims64[0] ? kBasisTolLeast : kBasisTol64;
+        if (worst[d] <= tol * tol) dims64 = d;
         if (worst[d] <= kBasisTol32 * kBasisTol32) dims32 = d;
     }
     p->dims64 = round_dims(SAIL_FP64, dims64);
