@@ -2978,7 +2978,10 @@ struct sail_problem {
     void *d_phi = nullptr;  // [N_w][4][chunk()] in the loop precision
     void *d_Phi = nullptr;  // [read_rows][ntau_pad], filled when reconstructions are read
     int read_rows = 0;
-    std::mutex read_mu;  // one read-out of reconstructions at a time uses them
+    // One read-out at a time uses the buffers kept for them (d_Phi, d_tmp, d_part,
+    // d_hist): read-outs by several threads, which buffers of their own let run
+    // side by side, take turns.
+    std::mutex read_mu;
     double *d_a0 = nullptr, *d_tmp = nullptr, *d_teff = nullptr;  // d_teff: imprint strength of the last event
     double *d_part = nullptr;               // partial sums of the averaged spectrum
     unsigned long long *d_hist = nullptr;   // counts of the residue histogram, kept from its first call
@@ -5381,6 +5384,7 @@ sail_status sail_read_spectrum(sail_problem_t p, double *out, void *stream_)
     if (p->n_walkers == 0) return fail(SAIL_ESTATE, "initialise walkers first");
     hipStream_t stream = (hipStream_t)stream_;
     SAIL_HIP(hipSetDevice(p->device));
+    std::lock_guard<std::mutex> lock(p->read_mu);
     // d_tmp holds max(64, n_omega) doubles (allocated with the walkers)
     launch_mean_spectrum(p->n_walkers, p->n_omega, p->d_b, p->d_gsc, p->d_part, p->d_tmp, stream);
     SAIL_HIP(hipGetLastError());
@@ -5416,6 +5420,7 @@ sail_status sail_read_chi2_hist(sail_problem_t p, int n_bins, double lo, double 
     if (p->n_walkers == 0) return fail(SAIL_ESTATE, "initialise walkers first");
     hipStream_t stream = (hipStream_t)stream_;
     SAIL_HIP(hipSetDevice(p->device));
+    std::lock_guard<std::mutex> lock(p->read_mu);
     if (n_bins > p->cap_hist) {
         unsigned long long *d = nullptr;
         const sail_status st = dalloc(&d, n_bins);

@@ -32,3 +32,31 @@ def test_averaged_spectrum_and_histogram(n_omega, n_walkers):
         below = np.cumsum(counts)[:-1]
         assert np.all(below >= (v[None, :] < edges[:, None] - 1e-9).sum(axis=1))
         assert np.all(below <= (v[None, :] < edges[:, None] + 1e-9).sum(axis=1))
+
+
+def test_read_outs_by_several_threads():
+    """Histograms (of growing sizes, so that the kept buffer is replaced),
+    averaged spectra and states read by several threads at once equal those
+    read one after another."""
+    from concurrent.futures import ThreadPoolExecutor
+
+    from paper_1609_07936_amd import sail as S
+    n = 600
+    tgt = W.Target([1.5, 4.0], [0.4, 0.8], [0.6, 0.4], 10.0)
+    wl = W.make("ro", 10.0, 70, W.uniform_tau(0.05, 1.6, 12), tgt, 1e-3, 3, n, 4, 1e2, 1.0, 100, 100, 5, n_quad=2000)
+    gp = S.Problem(wl.omega, wl.tau, wl.Ft, wl.sigma, wl.m0, wl.m1)
+    gp.init_walkers(n, 7)
+    gp.run(S.Schedule(np.full(4, 50.0)), 0, 3)
+    v = np.log10(gp.read_chi2())
+
+    def read(i):
+        if i % 3 == 0:
+            return gp.read_spectrum()
+        if i % 3 == 1:
+            return gp.read_chi2_hist(1 + 7 * i, v.min() + 0.01 * i, v.max())
+        return gp.read_state()["F"]
+
+    with ThreadPoolExecutor(4) as pool:
+        together = list(pool.map(read, range(60)))
+    for i, got in enumerate(together):
+        np.testing.assert_array_equal(got, read(i), err_msg=str(i))
