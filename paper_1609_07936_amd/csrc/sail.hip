@@ -154,6 +154,7 @@ struct SweepArgs {
     int amp_m;
     int chunk;            // basis dimensions per chunk as stored (a multiple of 16 bytes)
     int columns_lds;      // 1: the workgroup copies the columns to LDS
+    int tables_lds;       // walks of one wavefront, columns in memory: 1: it copies the bins' and pairs' table values
     int resident;         // split sweeps: bins of every spectrum, the first ones, that the workgroup keeps in LDS
     int lanes;            // lanes a walker takes (a batch's split sweeps: 4 or 16)
     int pairs;            // split sweeps: chain and stager wavefronts at work in a workgroup (any others leave)
@@ -304,6 +305,19 @@ int basis_class(int precision, int m)
 
 size_t column_bytes(int n_omega, int chunk, size_t rsz) { return (size_t)n_omega * 4 * chunk * rsz; }
 
+// Workgroups go to the XCDs in turn; within a window of kXcdWindow of them (one a
+// compute unit), give each XCD neighbouring ones, so that the tables of few
+// problems share its L2 cache: for launches that read columns from memory (32 jobs of
+// 2000 bins, 2000 walkers: 16.5 to 10.4 ms).  Where the columns are in LDS the caches
+// hold spectra, and the largest jobs' would all meet in one (16 served FP32 jobs:
+// 20.8 to 24.4 ms).
+constexpr int kXcds = 8, kXcdWindow = 256;
+__device__ __forceinline__ int xcd_block(const int b, const int n)
+{
+    const int base = b / kXcdWindow * kXcdWindow, m = min(n - base, kXcdWindow), x = (b - base) % kXcds, i = (b - base) / kXcds;
+    return base + x * (m / kXcds) + min(x, m % kXcds) + i;
+}
+
 // Many problems in one launch: problem q owns workgroups [first[q], first[q + 1]).
 __device__ __forceinline__ int owner_of(const int *first, const int n_jobs, const int b)
 {
@@ -432,10 +446,11 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         const double *bl = a.b + (size_t)lw * No;
         for (int j = c; j < nres && !stager; j += G) bsp[j] = bl[j];
     }
-    // a split walk's bins are known late: their table values sit in LDS too
-    double4 *bin_s = (double4 *)(spec + (((size_t)wpb * No + 1) & ~(size_t)1));
+    // a walk's bins are known late: their table values sit in LDS too
+    const bool tables = WALK && (SPLIT || (!LDSC && a.tables_lds));
+    double4 *bin_s = (double4 *)(LDSC ? spec + (((size_t)wpb * No + 1) & ~(size_t)1) : lds + wpb * RSTR);
     double2 *GH_s = (double2 *)(bin_s + No);
-    if constexpr (SPLIT && WALK) {
+    if (tables) {
         for (int i = threadIdx.x; i < No; i += nthr) bin_s[i] = bin[i];
         for (int i = threadIdx.x; i < 2 * No - 1; i += nthr) GH_s[i] = GH[i];
     }
@@ -1158,7 +1173,13 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
                         order();
                     }
                     rows(p, s, v);
-                    load_pair(p, s, pr);
+                    if (tables) {
+                        pr.p = bin_s[p];
+                        pr.s = bin_s[s];
+                        pr.gh = GH_s[p + s];
+                    } else {
+                        load_pair(p, s, pr);
+                    }
                     pair_terms(p, s, pr, v.rm1 + 1.0, v.dp, v.ds, v.s1, v.t);
                     body(qq, v, bp, bs, 0);
                     order();
@@ -1318,26 +1339,28 @@ __global__ __launch_bounds__(2 * kSweepThreads) void k_sweep_split16(SweepArgs a
     sweep_block<R, M, 16, LDSC, LDSB, MODE, true>(a, blockIdx.x, lds);
 }
 
-// Many problems in one launch: problem q owns workgroups [first[q], first[q + 1]);
-// where a problem's columns sit is its own (a uniform branch).
-template <typename R, int M, int MODE>
+// Many problems in one launch: problem q owns workgroups [first[q], first[q + 1]).
+// Traces (4 lanes a walker) and walks (8, or 4 in a large batch), columns and
+// spectra in memory.
+template <typename R, int M, int MODE, int G>
 __global__ __launch_bounds__(kSweepThreads, 2) void k_sweep_batched(const SweepArgs *__restrict__ jobs,
                                                                    const int *__restrict__ first, int n_jobs)
 {
     extern __shared__ __align__(16) double lds[];
-    const int q = owner_of(first, n_jobs, blockIdx.x);
-    constexpr int G = M > 0 && MODE == kSweepWalk ? 8 : 4;
-    sweep_block<R, M, G, false, false, MODE, false>(jobs[q], blockIdx.x - first[q], lds);
+    const int b = xcd_block(blockIdx.x, gridDim.x);
+    const int q = owner_of(first, n_jobs, b);
+    sweep_block<R, M, G, false, false, MODE, false>(jobs[q], b - first[q], lds);
 }
 
 template <typename R, int M>
 __global__ __launch_bounds__(2 * kSweepThreads) void k_sweep_split_batched(const SweepArgs *__restrict__ jobs,
-                                                                          const int *__restrict__ first, int n_jobs)
+                                                                          const int *__restrict__ first, int n_jobs, int near)
 {
     extern __shared__ __align__(16) double lds[];
-    const int q = owner_of(first, n_jobs, blockIdx.x);
+    const int b = near ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
+    const int q = owner_of(first, n_jobs, b);
     const SweepArgs &a = jobs[q];
-    const int block = blockIdx.x - first[q];
+    const int block = b - first[q];
     if (a.lanes == 16) {
         if (a.columns_lds) sweep_block<R, M, 16, true, false, kSweepFast, true>(a, block, lds);
         else sweep_block<R, M, 16, false, false, kSweepFast, true>(a, block, lds);
@@ -3361,7 +3384,7 @@ int sweep_wg_sync()
 struct SweepPlan {
     bool split;
     int lanes, threads, walkers;
-    int columns_lds, spectra_lds;
+    int columns_lds, spectra_lds, tables_lds;
     int resident;  // split: bins of every spectrum in LDS
     size_t shm;
 };
@@ -3373,6 +3396,7 @@ SweepArgs make_sweep_args(const sail_problem *p, int k0, int k1, const SweepPara
     s.n_omega = p->n_omega;
     s.chunk = p->chunk(p->precision);
     s.columns_lds = plan.columns_lds;
+    s.tables_lds = plan.tables_lds;
     s.resident = plan.resident;
     s.lanes = plan.lanes;
     s.pairs = plan.threads / 128;
@@ -3412,27 +3436,35 @@ SweepArgs make_sweep_args(const sail_problem *p, int k0, int k1, const SweepPara
 }
 
 // The columns, then the spectra of the workgroup's walkers (if asked for), go
-// to LDS if they fit in `budget` bytes beside the records.
+// to LDS if they fit in `budget` bytes beside the records.  A walk's kernels, and
+// those of one wavefront, take both or neither.
 SweepPlan plan_sweep(const sail_problem *p, bool split, int lanes, int threads, size_t budget, bool walk, bool spectra,
                      int walk_len)
 {
     const int walkers = (split ? threads / 2 : threads) / lanes;
-    SweepPlan s{split, lanes, threads, walkers, 0, 0, 0,
+    SweepPlan s{split, lanes, threads, walkers, 0, 0, 0, 0,
                 sizeof(double) * (!split ? (size_t)walkers * rec_stride(lanes, walk)
                                   : walk ? (size_t)walkers * walk_split_stride(walk_len)
                                          : (size_t)walkers * split_stride(lanes) + (size_t)walkers / (64 / lanes) * split_hits(lanes))};
     const size_t col = column_bytes(p->n_omega, p->chunk(p->precision),
                                     p->precision == SAIL_FP32 ? sizeof(float) : sizeof(double));
     if (basis_class(p->precision, p->dims(p->precision)) == 0) return s;
+    const size_t spec = sizeof(double) * (size_t)walkers * p->n_omega;
+    // (a split walk: and the tables of the bins and their pairs)
+    const size_t tables = (size_t)p->n_omega * sizeof(double4) + (size_t)(2 * p->n_omega - 1) * sizeof(double2);
+    const size_t all = !split || !walk ? spec : ((spec + 15) & ~(size_t)15) + tables;
+    const bool fits = spectra && s.shm + col + all <= budget;
+    if ((walk || !split) && !fits) {
+        if (walk && !split && s.shm + tables <= budget) {
+            s.shm += tables;
+            s.tables_lds = 1;
+        }
+        return s;
+    }
     if (s.shm + col <= budget) {
         s.shm += col;
         s.columns_lds = 1;
-        const size_t spec = sizeof(double) * (size_t)walkers * p->n_omega;
-        // (a split walk: and the tables of the bins and their pairs)
-        const size_t all = !split || !walk ? spec
-                                           : ((spec + 15) & ~(size_t)15) + (size_t)p->n_omega * sizeof(double4) +
-                                                 (size_t)(2 * p->n_omega - 1) * sizeof(double2);
-        if (!(split && lanes == 4) && spectra && s.shm + all <= budget) {
+        if (!(split && lanes == 4) && fits) {
             s.shm += all;
             s.spectra_lds = 1;
         }
@@ -4292,6 +4324,7 @@ struct Launch {
     size_t shm;
     int cls = 0, mode = 0, threads = kThreads;  // sweeps only
     int wpb = 8;  // resyncs only
+    int lanes = 4, near = 0;  // sweeps only
 };
 
 template <typename R, int M>
@@ -4299,13 +4332,16 @@ void launch_sweep_batched_m(const Launch &L, const SweepArgs *jobs, hipStream_t 
 {
     const dim3 grid(L.blocks), thr(L.threads);
     if (L.mode == kSweepTraced)
-        hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepTraced>), grid, thr, L.shm, stream, jobs, L.first, L.n);
-    else if (L.mode == kSweepWalk)
-        hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepWalk>), grid, thr, L.shm, stream, jobs, L.first, L.n);
-    else if constexpr (M > 0)
-        hipLaunchKernelGGL((k_sweep_split_batched<R, M>), grid, thr, L.shm, stream, jobs, L.first, L.n);
-    else
-        hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepFast>), grid, thr, L.shm, stream, jobs, L.first, L.n);
+        hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepTraced, 4>), grid, thr, L.shm, stream, jobs, L.first, L.n);
+    else if (L.mode == kSweepWalk && L.lanes == 4)
+        hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepWalk, 4>), grid, thr, L.shm, stream, jobs, L.first, L.n);
+    else if constexpr (M > 0) {
+        if (L.mode == kSweepWalk)
+            hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepWalk, 8>), grid, thr, L.shm, stream, jobs, L.first, L.n);
+        else
+            hipLaunchKernelGGL((k_sweep_split_batched<R, M>), grid, thr, L.shm, stream, jobs, L.first, L.n, L.near);
+    } else
+        hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepFast, 4>), grid, thr, L.shm, stream, jobs, L.first, L.n);
 }
 
 void launch_sweep_batched(const Launch &L, const SweepArgs *jobs, hipStream_t stream)
@@ -4393,14 +4429,25 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
         L.kind = g / (3 * kBasisClasses);
         const bool walk = L.mode == kSweepWalk, split = L.mode == kSweepFast && L.cls != 0;
         L.threads = split ? 2 * kSweepThreads : kSweepThreads;
+        if (walk && L.cls != 0) {
+            // 8 lanes a walker, or 4 where 8 would leave a fifth of the last round
+            // of wavefronts, two a SIMD, unused (256 bins, one step: 24 jobs of 1024
+            // walkers 1.5 rounds, 1.54 against 1.71 ms; 1024 bins, 16 jobs of 4096
+            // walkers 4 rounds, 8.4 against 7.2 ms)
+            size_t waves = 0;
+            for (int i : idx) waves += ((size_t)act[i]->p->n_walkers + 7) / 8;
+            const size_t room = (size_t)2 * 4 * kCUs, rounds = (waves + room - 1) / room;
+            L.lanes = rounds > 1 && waves * 5 < rounds * room * 4 ? 4 : 8;
+        }
         std::vector<SweepArgs> sa;
         std::vector<int> first;
+        int reading = 0;  // workgroups that read their columns from memory
         for (int i : idx) {
             const sail_problem *p = act[i]->p;
             const sail_schedule &sc = act[i]->sc;
             // a split job whose columns would not fit takes fewer pairs of
             // wavefronts, hence fewer records (1024 FP64 bins: two)
-            SweepPlan s = plan_sweep(p, split, walk && L.cls != 0 ? 8 : 4, split ? 128 * pairs : L.threads,
+            SweepPlan s = plan_sweep(p, split, L.lanes, split ? 128 * pairs : L.threads,
                                      split ? kLdsBytes : kLdsBytes / 2, walk, false, sc.walk_len);
             for (int t = 64 * pairs; split && !s.columns_lds && t >= 128; t /= 2) {
                 const SweepPlan q = plan_sweep(p, true, 4, t, kLdsBytes, false, false, 0);
@@ -4416,9 +4463,11 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
                                          SweepParams{sc.eps0, sc.amp_p, sc.amp_avg, sc.amp_m, sc.walk_len}, s));
             first.push_back(L.blocks);
             L.blocks += sweep_blocks(p, s);
+            if (!s.columns_lds) reading += sweep_blocks(p, s);
             L.shm = std::max(L.shm, s.shm);
         }
         first.push_back(L.blocks);
+        L.near = 2 * reading > L.blocks;
         L.n = (int)idx.size();
         L.args = sg.put(sa.data(), sa.size());
         L.first = sg.put(first.data(), first.size());

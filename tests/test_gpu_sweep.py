@@ -96,3 +96,33 @@ def test_same_bits_for_every_plan(S, n_omega, n_tau, n_walkers, prec, walk, spre
 def test_basis_classes_against_oracle(S, n_omega, n_tau, spread):  # noqa: F811
     wl = _workload(n_omega, n_tau, 18, 20, spread)
     _anneal_lockstep(S, wl, 18, 11, 20, dict(branch_every=20, resync_every=10), T=np.geomspace(100.0, 1.0, 20))
+
+
+# jobs, bins, times, walkers, precision, walk steps: launches of many workgroups and their rules
+@pytest.mark.parametrize("jobs,n_omega,n_tau,n_walkers,prec,walk", [
+    (20, 1300, 17, 1100, 0, 0),  # columns in memory, more workgroups than compute units, a remainder
+    (3, 2556, 9, 70, 0, 0),      # room for the bins' table, not the pairs'
+    (3, 2556, 9, 70, 1, 0),
+    (4, 1100, 17, 300, 0, 0),    # one pair, and wider jobs as far as compute units last
+    (4, 1100, 17, 4000, 0, 0),   # more pairs than leave room for the columns
+    (24, 40, 12, 700, 0, 2),     # walks of four lanes
+    (24, 40, 12, 700, 1, 2),
+    (5, 40, 12, 700, 0, 2),      # of eight
+    (3, 2000, 9, 40, 0, 1),      # tables beside a walk's records: the bins' only
+])
+def test_same_bits_in_large_batches(S, jobs, n_omega, n_tau, n_walkers, prec, walk):  # noqa: F811
+    n = 2
+    wl = _workload(n_omega, n_tau, n_walkers, n)
+    sched = S.Schedule(np.geomspace(100.0, 1.0, n), branch_every=n, resync_every=n, walk_len=walk)
+
+    def problem(i):
+        gp = S.Problem(wl.omega, wl.tau, wl.Ft, wl.sigma, wl.m0, wl.m1)
+        gp.init_walkers(n_walkers, 11 + i, precision=prec)
+        return gp
+
+    batched = [problem(i) for i in range(jobs)]
+    S.Batch(batched).run([sched] * jobs, [0] * jobs, [1] * jobs)  # ends between resyncs
+    for i in sorted({0, 1, jobs // 2, jobs - 1}):
+        alone = problem(i)
+        alone.run(sched, 0, 1)
+        assert alone.state_export() == batched[i].state_export(), f"job {i}"
