@@ -154,7 +154,7 @@ struct SweepArgs {
     int amp_m;
     int chunk;            // basis dimensions per chunk as stored (a multiple of 16 bytes)
     int columns_lds;      // 1: the workgroup copies the columns to LDS
-    int tables_lds;       // walks of one wavefront, columns in memory: 1: it copies the bins' and pairs' table values
+    int tables_lds;       // columns in memory: it copies the table values of bins (1), of bins and pairs (2)
     int resident;         // split sweeps: bins of every spectrum, the first ones, that the workgroup keeps in LDS
     int lanes;            // lanes a walker takes (a batch's split sweeps: 4 or 16)
     int pairs;            // split sweeps: chain and stager wavefronts at work in a workgroup (any others leave)
@@ -446,14 +446,18 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         const double *bl = a.b + (size_t)lw * No;
         for (int j = c; j < nres && !stager; j += G) bsp[j] = bl[j];
     }
-    // a walk's bins are known late: their table values sit in LDS too
-    const bool tables = WALK && (SPLIT || (!LDSC && a.tables_lds));
-    double4 *bin_s = (double4 *)(LDSC ? spec + (((size_t)wpb * No + 1) & ~(size_t)1) : lds + wpb * RSTR);
+    // Table values of bins and pairs in LDS: of a split walk, whose bins are known
+    // late, and where the columns are in memory (a batch of problems' columns and
+    // tables would not stay in the caches; 32 jobs of 2556 bins, 300 walkers: with
+    // all table reads to one place a launch takes 3.36 instead of 4.42 ms)
+    constexpr bool TAB = (SPLIT && WALK) || !LDSC;
+    const bool bins_in = (SPLIT && WALK) || (TAB && a.tables_lds > 0), pairs_in = (SPLIT && WALK) || (TAB && a.tables_lds > 1);
+    double4 *bin_s = (double4 *)(spec + (LDSC ? ((size_t)wpb * No + 1) & ~(size_t)1 : 0));
     double2 *GH_s = (double2 *)(bin_s + No);
-    if (tables) {
+    if (bins_in)
         for (int i = threadIdx.x; i < No; i += nthr) bin_s[i] = bin[i];
+    if (pairs_in)
         for (int i = threadIdx.x; i < 2 * No - 1; i += nthr) GH_s[i] = GH[i];
-    }
     __syncthreads();
 
     // spectra in memory through a buffer resource: 32-bit offsets (the library
@@ -539,9 +543,15 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         double2 gh;
     };
     auto load_pair = [&](const int p, const int s, Pair &t) __attribute__((always_inline)) {
-        t.p = bin[p];
-        t.s = bin[s];
-        t.gh = GH[p + s];
+        if (TAB && bins_in) {
+            t.p = bin_s[p];
+            t.s = bin_s[s];
+        } else {
+            t.p = bin[p];
+            t.s = bin[s];
+        }
+        if (TAB && pairs_in) t.gh = GH_s[p + s];
+        else t.gh = GH[p + s];
     };
     // Deltas and walker-independent residue terms of the move (p, s, r): S1 =
     // sum_i w_i s_i^2 and S1 + S3 (S3 = sum_i c_i s_i); sum_i w_i K_pi K_si is
@@ -897,9 +907,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
                 const int p = dpp_swap<0xA0>(x), s = dpp_swap<0xF5>(x);  // quad_perm 0, 0, 2, 2 and 1, 1, 3, 3
                 rows(p, s, v);
                 Pair pr;
-                pr.p = bin_s[p];
-                pr.s = bin_s[s];
-                pr.gh = GH_s[p + s];
+                load_pair(p, s, pr);
                 const double bp = bsp[p], bs = bsp[s];
                 // the next proposal's words arrive meanwhile
                 const int qn = min(qq + 1, nq - 1);
@@ -1022,13 +1030,25 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         begin_sweep();
         if (c == 0) *width = yeps;
         barrier();
-        Rec v[2];
-        double next_bins;  // of the proposal after the next
+        // Columns are loaded AHEAD proposals before they are used, their bins read
+        // one proposal before that.  From memory they take longer than a proposal (32
+        // jobs of 1300 bins, 300 walkers, FP64: 932 ns a proposal one ahead, 780 ns three;
+        // alone, 5000 walkers, 389 and 345 ns); FP32 columns are one load a lane
+        // and do not gain (2556 bins: 4.20 against 4.49 ms a launch), and more than 24
+        // dimensions, or 16 lanes' unrolled batches, do not leave the registers.
+        constexpr int AHEAD = LDSC || sizeof(R) == 4 || M > 6 || G > 4 ? 1 : 3, V = AHEAD + 1;
+        static_assert(G % V == 0, "a batch turns the ring");
+        Rec v[V];
+        double next_bins;
         {
             // the first batch's bins and spectrum values
-            const double w0 = *bins_at(0, 0), own_bins = *bins_at(0, c);
-            next_bins = *bins_at(0, 1);
-            rows(__double2loint(w0), __double2hiint(w0), v[0]);
+            const double own_bins = *bins_at(0, c);
+#pragma unroll
+            for (int t = 0; t < AHEAD; ++t) {
+                const double w0 = *bins_at(0, t);
+                rows(__double2loint(w0), __double2hiint(w0), v[t]);
+            }
+            next_bins = *bins_at(0, AHEAD);
             load_next(own_bins);
         }
         for (;;) {
@@ -1041,11 +1061,11 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
                 const bool ends = q0 + G >= No;
                 // the batch's masks, read at its start, or at use (FP32, 16 lanes:
                 // 221 against 231 ns a proposal; FP64: 220 against 215)
-                constexpr bool AHEAD = G == 4 || sizeof(R) == 8;
+                constexpr bool HIT_AHEAD = G == 4 || sizeof(R) == 8;
                 uint64_t hit[G] = {};
                 if constexpr (!ALLB) {
                     const double own_bins = *bins_at(bn, c);
-                    if constexpr (AHEAD) {
+                    if constexpr (HIT_AHEAD) {
 #pragma unroll
                         for (int t = 0; t < G; ++t) hit[t] = uniform(hits[rs * G + t]);
                     }
@@ -1075,23 +1095,25 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
                 }
 #pragma unroll
                 for (int t = 0; t < G; ++t) {
-                    // the next proposal's columns (its bins were read a proposal
-                    // ago), its record, and the bins of the one after it
-                    Rec &cur = v[t & 1], &nx = v[(t + 1) & 1];
+                    // columns of a proposal to come (its bins were read a proposal
+                    // ago), the next one's record, and the bins of the one whose
+                    // columns are next
+                    Rec &cur = v[t % V], &nx = v[(t + 1) % V], &far = v[(t + AHEAD) % V];
                     // (FP32: the spectrum values before the next proposal's words,
                     // which the decision would else wait behind, 200 to 192 ns a
                     // proposal; FP64 is as fast either way)
                     constexpr bool EARLY = ALLB && sizeof(R) == 4;
                     const double bp = EARLY ? bsp[cur.p] : 0.0, bs = EARLY ? bsp[cur.s] : 0.0;
-                    rows(__double2loint(next_bins), __double2hiint(next_bins), nx);
+                    rows(__double2loint(next_bins), __double2hiint(next_bins), far);
                     fetch(t + 1 < G ? rec_at(rs, t + 1) : rec_at(rn, 0), nx);
-                    next_bins = t + 2 < G ? *bins_at(bsl, t + 2) : *bins_at(bn, t + 2 - G);
+                    constexpr int B = AHEAD + 1;
+                    next_bins = t + B < G ? *bins_at(bsl, t + B) : *bins_at(bn, t + B - G);
                     if constexpr (ALLB) {
                         if constexpr (EARLY) body(t, cur, bp, bs, 0);
                         else body(t, cur, bsp[cur.p], bsp[cur.s], 0);
                         wave_lds_sync();
                     } else {
-                        if constexpr (!AHEAD) hit[t] = uniform(hits[rs * G + t]);
+                        if constexpr (!HIT_AHEAD) hit[t] = uniform(hits[rs * G + t]);
                         body(t, cur, obp, obs, hit[t]);
                     }
                     // keep each proposal's code together (bounds register pressure)
@@ -1173,13 +1195,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
                         order();
                     }
                     rows(p, s, v);
-                    if (tables) {
-                        pr.p = bin_s[p];
-                        pr.s = bin_s[s];
-                        pr.gh = GH_s[p + s];
-                    } else {
-                        load_pair(p, s, pr);
-                    }
+                    load_pair(p, s, pr);
                     pair_terms(p, s, pr, v.rm1 + 1.0, v.dp, v.ds, v.s1, v.t);
                     body(qq, v, bp, bs, 0);
                     order();
@@ -3451,14 +3467,12 @@ SweepPlan plan_sweep(const sail_problem *p, bool split, int lanes, int threads, 
     if (basis_class(p->precision, p->dims(p->precision)) == 0) return s;
     const size_t spec = sizeof(double) * (size_t)walkers * p->n_omega;
     // (a split walk: and the tables of the bins and their pairs)
-    const size_t tables = (size_t)p->n_omega * sizeof(double4) + (size_t)(2 * p->n_omega - 1) * sizeof(double2);
+    const size_t bins = (size_t)p->n_omega * sizeof(double4), tables = bins + (size_t)(2 * p->n_omega - 1) * sizeof(double2);
     const size_t all = !split || !walk ? spec : ((spec + 15) & ~(size_t)15) + tables;
     const bool fits = spectra && s.shm + col + all <= budget;
-    if ((walk || !split) && !fits) {
-        if (walk && !split && s.shm + tables <= budget) {
-            s.shm += tables;
-            s.tables_lds = 1;
-        }
+    if ((walk || !split) ? !fits : s.shm + col > budget) {
+        s.tables_lds = s.shm + tables <= budget ? 2 : s.shm + bins <= budget ? 1 : 0;
+        s.shm += s.tables_lds == 2 ? tables : s.tables_lds == 1 ? bins : 0;
         return s;
     }
     if (s.shm + col <= budget) {
@@ -4441,25 +4455,56 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
         }
         std::vector<SweepArgs> sa;
         std::vector<int> first;
+        std::vector<SweepPlan> plans;
+        if (split) {
+            auto at = [&](int n) {
+                size_t b = 0;
+                for (int i : idx) b += ((size_t)act[i]->p->n_walkers + 16 * n - 1) / (16 * n);
+                return b;
+            };
+            // workgroups that have all of a compute unit's LDS must not outnumber
+            // the compute units, or the last ones wait for a whole round
+            int spread = 1;
+            while (spread < 4 && at(spread) > (size_t)kCUs) spread *= 2;
+            int total = 0;
+            for (int i : idx) {
+                const sail_problem *p = act[i]->p;
+                // a job whose columns would not fit takes fewer pairs of wavefronts,
+                // hence fewer records (1024 FP64 bins: two; one: 1100 bins, where the
+                // 4000 walkers of each of four jobs took four rounds, 2.28 ms, and take
+                // 1.41 ms with the columns in memory); without them
+                // in LDS, as many as share a compute unit's copy of the tables
+                SweepPlan s = plan_sweep(p, true, 4, 128 * pairs, kLdsBytes, false, false, 0);
+                for (int t = 64 * pairs; !s.columns_lds && t >= (spread > 1 ? 256 : 128); t /= 2) {
+                    const SweepPlan q = plan_sweep(p, true, 4, t, kLdsBytes, false, false, 0);
+                    if (q.columns_lds) s = q;
+                }
+                if (!s.columns_lds) s = plan_sweep(p, true, 4, 128 * spread, kLdsBytes, false, false, 0);
+                plans.push_back(s);
+                total += sweep_blocks(p, s);
+            }
+            for (size_t n = 0; n < idx.size(); ++n) {
+                const sail_problem *p = act[idx[n]]->p;
+                for (int t = 4 * 128; wide[idx[n]] && t >= 128; t /= 2) {
+                    const SweepPlan q = plan_sweep(p, true, 16, t, kLdsBytes, false, false, 0);
+                    const int with = total - sweep_blocks(p, plans[n]) + sweep_blocks(p, q);
+                    if (!q.columns_lds || (t == 128 && with > kCUs)) continue;
+                    total = with;
+                    plans[n] = q;
+                    break;
+                }
+            }
+        } else {
+            for (int i : idx)
+                plans.push_back(plan_sweep(act[i]->p, false, L.lanes, L.threads, kLdsBytes / 2, walk, false, act[i]->sc.walk_len));
+        }
         int reading = 0;  // workgroups that read their columns from memory
-        for (int i : idx) {
-            const sail_problem *p = act[i]->p;
-            const sail_schedule &sc = act[i]->sc;
-            // a split job whose columns would not fit takes fewer pairs of
-            // wavefronts, hence fewer records (1024 FP64 bins: two)
-            SweepPlan s = plan_sweep(p, split, L.lanes, split ? 128 * pairs : L.threads,
-                                     split ? kLdsBytes : kLdsBytes / 2, walk, false, sc.walk_len);
-            for (int t = 64 * pairs; split && !s.columns_lds && t >= 128; t /= 2) {
-                const SweepPlan q = plan_sweep(p, true, 4, t, kLdsBytes, false, false, 0);
-                if (q.columns_lds) s = q;
-            }
-            for (int t = 4 * 128; split && wide[i] && t >= 128; t /= 2) {
-                const SweepPlan q = plan_sweep(p, true, 16, t, kLdsBytes, false, false, 0);
-                if (!q.columns_lds) continue;
-                s = q;
-                break;
-            }
-            sa.push_back(make_sweep_args(p, act[i]->k, kend[i],
+        for (size_t n = 0; n < idx.size(); ++n) {
+            const BatchJob *job = act[idx[n]];
+            const sail_problem *p = job->p;
+            const sail_schedule &sc = job->sc;
+            const SweepPlan &s = plans[n];
+            sa.push_back(make_sweep_args(p, job->k, kend[idx[n]],
                                          SweepParams{sc.eps0, sc.amp_p, sc.amp_avg, sc.amp_m, sc.walk_len}, s));
             first.push_back(L.blocks);
             L.blocks += sweep_blocks(p, s);
