@@ -353,18 +353,33 @@ __device__ __forceinline__ void buffer_store_f64(__amdgpu_buffer_rsrc_t r, uint3
     __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, 0);
 }
 
-// One lane's chunk of a column: M values in 16-byte loads.
-template <typename R, int M>
+// One lane's chunk of a column: M values in 16-byte loads.  From memory, the last
+// one takes the values that are left: a full one would let its unused registers
+// overlap another load's, which then waits for it (FP32, 2556 bins x 5000 walkers: 455 to
+// 285 ns a proposal).  From LDS full ones are faster (ds_read_b96, FP32, 300 bins x
+// 3000 walkers: 211 to 229 ns).
+template <bool MEM, typename R, int M>
 __device__ __forceinline__ void load_chunk(const R *p, R (&v)[M])
 {
     constexpr int W = 16 / sizeof(R), MS = chunk_stride<R>(M);
     typedef R vec __attribute__((ext_vector_type(W)));
+    typedef R pair __attribute__((ext_vector_type(2)));
 #pragma unroll
     for (int i = 0; i < MS; i += W) {
-        const vec x = *(const vec *)(p + i);
+        if (!MEM || i + W <= M) {
+            const vec x = *(const vec *)(p + i);
 #pragma unroll
-        for (int t = 0; t < W; ++t)
-            if (i + t < M) v[i + t] = x[t];
+            for (int t = 0; t < W; ++t)
+                if (i + t < M) v[i + t] = x[t];
+        } else {
+            const R *q = (const R *)__builtin_assume_aligned(p + i, 16);
+            if (M - i >= 2) {
+                const pair x = *(const pair *)q;
+                v[i] = x[0];
+                v[i + 1] = x[1];
+            }
+            if ((M - i) % 2) v[M - 1] = q[M - 1 - i];
+        }
     }
 }
 
@@ -471,7 +486,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
 
     R phi[MR];
     R *phig = (R *)a.phi + ((size_t)lw * 4 + ch) * ms;
-    if constexpr (M > 0) load_chunk<R, MR>(phig, phi);
+    if constexpr (M > 0) load_chunk<false, R, MR>(phig, phi);
     double g = a.gsc[lw], chi2 = a.chi2[lw], rate = a.rate[lw], ginv = a.ginv[lw];
     double Q2 = 0.0;  // sum_i w_i Phi_i^2 of the walker, exact at each sweep's start
     int nacc = 0;
@@ -506,11 +521,11 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
             constexpr uint32_t st = (uint32_t)chunk_stride<R>(MR);
             const uint32_t po = (uint32_t)p * (4 * st) + (uint32_t)ch * st, so = (uint32_t)s * (4 * st) + (uint32_t)ch * st;
             if constexpr (LDSC) {
-                load_chunk<R, MR>(col_s + po, v.rp);
-                load_chunk<R, MR>(col_s + so, v.rs);
+                load_chunk<false, R, MR>(col_s + po, v.rp);
+                load_chunk<false, R, MR>(col_s + so, v.rs);
             } else {
-                load_chunk<R, MR>(colg + po, v.rp);
-                load_chunk<R, MR>(colg + so, v.rs);
+                load_chunk<true, R, MR>(colg + po, v.rp);
+                load_chunk<true, R, MR>(colg + so, v.rs);
             }
         }
     };
@@ -1033,10 +1048,10 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         // Columns are loaded AHEAD proposals before they are used, their bins read
         // one proposal before that.  From memory they take longer than a proposal (32
         // jobs of 1300 bins, 300 walkers, FP64: 932 ns a proposal one ahead, 780 ns three;
-        // alone, 5000 walkers, 389 and 345 ns); FP32 columns are one load a lane
-        // and do not gain (2556 bins: 4.20 against 4.49 ms a launch), and more than 24
-        // dimensions, or 16 lanes' unrolled batches, do not leave the registers.
-        constexpr int AHEAD = LDSC || sizeof(R) == 4 || M > 6 || G > 4 ? 1 : 3, V = AHEAD + 1;
+        // alone, 5000 walkers, 389 and 345 ns; FP32, 2556 bins, 5000 walkers 350 and 285
+        // ns).  More than 24 dimensions, or 16 lanes' unrolled batches, do not leave
+        // the registers for it.
+        constexpr int AHEAD = LDSC || M > 6 || G > 4 ? 1 : 3, V = AHEAD + 1;
         static_assert(G % V == 0, "a batch turns the ring");
         Rec v[V];
         double next_bins;
