@@ -4399,23 +4399,11 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
 
     // sweep groups, heaviest workgroups first
     std::vector<Launch> sweeps, resyncs, targets, smooths;
-    // pairs of wavefronts per split workgroup: four share a compute unit's LDS
-    // copy of the columns when workgroups abound; fewer when that would leave
-    // compute units idle (up to half as many workgroups again as compute units
-    // still pack well, longest first; 24 FP64 jobs of 20736 walkers, with the
-    // columns of 1024 bins in LDS beside two pairs: a round 27 ms, with four pairs
-    // for all 46 ms)
-    int pairs = 1;
-    auto groups_of = [&](int n) {
-        size_t b = 0;
-        for (const auto *j : act) b += ((size_t)j->p->n_walkers + 16 * n - 1) / (16 * n);
-        return b;
-    };
-    while (pairs < 4 && groups_of(pairs) > (size_t)kCUs * 3 / 2) pairs *= 2;
     // A round ends with its longest jobs.  While SIMDs would be left without a
     // chain, those take 16 lanes a walker (1024 bins: 283 to 220 ns a proposal),
     // longest first, where their columns fit in LDS beside the larger records
-    // (16 FP32 jobs of 9472 walkers, one round: 14.5 to 11.6 ms).
+    // (16 FP32 jobs of 9472 walkers, one round: 14.5 to 11.6 ms) and no compute unit
+    // gets a second workgroup for it.
     std::vector<char> wide(act.size(), 0);
     {
         int64_t simds = 4 * kCUs;
@@ -4457,7 +4445,7 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
         L.cls = (g / 3) % kBasisClasses;
         L.kind = g / (3 * kBasisClasses);
         const bool walk = L.mode == kSweepWalk, split = L.mode == kSweepFast && L.cls != 0;
-        L.threads = split ? 2 * kSweepThreads : kSweepThreads;
+        L.threads = split ? 0 : kSweepThreads;
         if (walk && L.cls != 0) {
             // 8 lanes a walker, or 4 where 8 would leave a fifth of the last round
             // of wavefronts, two a SIMD, unused (256 bins, one step: 24 jobs of 1024
@@ -4472,29 +4460,33 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
         std::vector<int> first;
         std::vector<SweepPlan> plans;
         if (split) {
+            // Pairs of wavefronts per workgroup: four share a compute unit's LDS copy
+            // of the columns when workgroups abound; fewer while the workgroups do
+            // not outnumber the compute units, each of which runs one (their
+            // registers, and often their LDS, leave no room for a second): 24
+            // FP64 jobs of 20736 walkers, with the columns of 1024 bins in LDS
+            // beside two pairs, a round 27 ms, with four pairs for all 46 ms; 32
+            // jobs of 512 bins, 300 walkers, two sweeps: 160 workgroups 377 us, 320
+            // of two pairs 581 us.
+            int pairs = 1;
             auto at = [&](int n) {
                 size_t b = 0;
                 for (int i : idx) b += ((size_t)act[i]->p->n_walkers + 16 * n - 1) / (16 * n);
                 return b;
             };
-            // workgroups that have all of a compute unit's LDS must not outnumber
-            // the compute units, or the last ones wait for a whole round
-            int spread = 1;
-            while (spread < 4 && at(spread) > (size_t)kCUs) spread *= 2;
+            while (pairs < 4 && at(pairs) > (size_t)kCUs) pairs *= 2;
             int total = 0;
             for (int i : idx) {
                 const sail_problem *p = act[i]->p;
-                // a job whose columns would not fit takes fewer pairs of wavefronts,
-                // hence fewer records (1024 FP64 bins: two; one: 1100 bins, where the
-                // 4000 walkers of each of four jobs took four rounds, 2.28 ms, and take
-                // 1.41 ms with the columns in memory); without them
-                // in LDS, as many as share a compute unit's copy of the tables
+                // a job whose columns would not fit takes two pairs, hence fewer
+                // records (1024 FP64 bins); not one of several, which leaves compute
+                // units idle for long (1100 bins, four jobs of 4000 walkers: 2.28 ms, and
+                // 1.41 ms with the columns in memory)
                 SweepPlan s = plan_sweep(p, true, 4, 128 * pairs, kLdsBytes, false, false, 0);
-                for (int t = 64 * pairs; !s.columns_lds && t >= (spread > 1 ? 256 : 128); t /= 2) {
+                for (int t = 64 * pairs; !s.columns_lds && t >= 256; t /= 2) {
                     const SweepPlan q = plan_sweep(p, true, 4, t, kLdsBytes, false, false, 0);
                     if (q.columns_lds) s = q;
                 }
-                if (!s.columns_lds) s = plan_sweep(p, true, 4, 128 * spread, kLdsBytes, false, false, 0);
                 plans.push_back(s);
                 total += sweep_blocks(p, s);
             }
@@ -4503,7 +4495,7 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
                 for (int t = 4 * 128; wide[idx[n]] && t >= 128; t /= 2) {
                     const SweepPlan q = plan_sweep(p, true, 16, t, kLdsBytes, false, false, 0);
                     const int with = total - sweep_blocks(p, plans[n]) + sweep_blocks(p, q);
-                    if (!q.columns_lds || (t == 128 && with > kCUs)) continue;
+                    if (!q.columns_lds || with > kCUs) continue;
                     total = with;
                     plans[n] = q;
                     break;
@@ -4525,6 +4517,7 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
             L.blocks += sweep_blocks(p, s);
             if (!s.columns_lds) reading += sweep_blocks(p, s);
             L.shm = std::max(L.shm, s.shm);
+            L.threads = std::max(L.threads, s.threads);
         }
         first.push_back(L.blocks);
         L.near = 2 * reading > L.blocks;
