@@ -152,7 +152,6 @@ struct SweepArgs {
     uint32_t key0, key1;
     double A, B, eps0, amp_p, amp_avg;
     int amp_m;
-    int chunk;            // basis dimensions per chunk as stored (a multiple of 16 bytes)
     int columns_lds;      // 1: the workgroup copies the columns to LDS
     int tables_lds;       // columns in memory: it copies the table values of bins (1), of bins and pairs (2)
     int resident;         // split sweeps: bins of every spectrum, the first ones, that the workgroup keeps in LDS
@@ -283,24 +282,24 @@ constexpr int64_t walk_split_stride(int walk_len) { return (int64_t)2 * 16 * (kW
 template <typename R>
 constexpr int chunk_stride(int m) { return sizeof(R) == 8 ? (m + 1) & ~1 : (m + 3) & ~3; }
 
-// The sweep kernels are built for these numbers of dimensions per chunk; a
-// larger basis runs the general variant (class 0).
-constexpr int kDims64[4] = {2, 4, 6, 8}, kDims32[4] = {2, 3, 4, 6};
-constexpr int kBasisClasses = 9;
+// The sweep kernels are built for these numbers of dimensions per chunk.  Decaying
+// kernels take up to 8; weights that turn the columns into separate Gaussians
+// more, which are held by 16 lanes, a quarter of a chunk each (96 bins, 96 x 4
+// dimensions at most, 1024 walkers: 235 ns a proposal, 3.3 us with a walker's
+// coordinates in memory, 470 ns with a recurrence along 80 times).  More than 4096
+// walkers leave a compute unit 16 at a time and stay behind the recurrence (8192: 760
+// against 540 us for 960 proposals).
+constexpr int kDims64[6] = {2, 4, 6, 8, 16, 24}, kDims32[5] = {2, 3, 4, 6, 16};
+constexpr int kBasisClasses = 25;
+constexpr bool wide_basis(int m) { return m > 8; }
 constexpr int kReadRows = 16;  // walkers whose reconstructions are read at once, at least
-// Dimensions per chunk for a basis of n dimensions.
+// Dimensions per chunk for a basis of n dimensions (or the most there are).
 int round_dims(int precision, int n)
 {
     const int need = n > 4 ? (n + 3) / 4 : 1;
-    for (int m : precision == SAIL_FP32 ? kDims32 : kDims64)
-        if (need <= m) return m;
-    return need;
-}
-int basis_class(int precision, int m)
-{
-    for (int v : precision == SAIL_FP32 ? kDims32 : kDims64)
-        if (m == v) return v;
-    return 0;
+    const int *m = precision == SAIL_FP32 ? kDims32 : kDims64, *last = m + (precision == SAIL_FP32 ? 4 : 5);
+    while (m < last && need > *m) ++m;
+    return *m;
 }
 
 size_t column_bytes(int n_omega, int chunk, size_t rsz) { return (size_t)n_omega * 4 * chunk * rsz; }
@@ -400,9 +399,8 @@ enum : int { kSweepFast = 0, kSweepTraced = 1, kSweepWalk = 2 };
 // the problem, `lds` is its LDS (records, then the columns if LDSC, then the
 // walkers' spectra if LDSB).  R is the precision of the residual loop (double:
 // the FP64 path, float: the FP32 variant); moves, positivity, thresholds and
-// chi^2 stay double.  M is the number of basis dimensions a chunk holds; M = 0
-// takes any number, with phi in memory (bases of more than 32 dimensions, which
-// only weights or grids far from a decaying kernel give).
+// chi^2 stay double.  M is the number of basis dimensions a chunk holds; a wide
+// basis (more than 8) takes 16 lanes, each with a quarter of a chunk.
 //
 // SPLIT: half of the workgroup's wavefronts run the walkers' chains, four lanes
 // a walker; the other half, one beside each on the same SIMD, draw and stage
@@ -415,15 +413,16 @@ template <typename R, int M, int G, bool LDSC, bool LDSB, int MODE, bool SPLIT>
 __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block, double *lds)
 {
     constexpr bool WALK = MODE == kSweepWalk, TRACE = MODE != kSweepFast;
-    constexpr int MR = M > 0 ? M : 1;
+    constexpr bool WIDE = wide_basis(M);
+    constexpr int CH = WIDE ? 16 : 4, MR = 4 * M / CH;  // lanes that share a walker's coordinates, dimensions in each
+    static_assert(!WIDE || G == 16, "a wide basis takes 16 lanes");
     const int RSTR = !SPLIT ? rec_stride(G, WALK) : WALK ? (int)walk_split_stride(a.walk_len) : split_stride(G);
-    static_assert(M > 0 || !LDSC, "the general variant reads its columns from memory");
     static_assert(!SPLIT || (WALK ? G == 16 && LDSB : G == 16 || G == 4), "split sweeps");
     constexpr bool ALLB = LDSB && (!SPLIT || G == 16);  // whole spectra in LDS; split sweeps keep the first bins there
     const int nthr = SPLIT ? 128 * a.pairs : (int)blockDim.x;
     if (SPLIT && (int)threadIdx.x >= nthr) return;
     const int lane = threadIdx.x & 63;
-    const int c = lane & (G - 1), ch = lane & 3;
+    const int c = lane & (G - 1), ch = lane & (CH - 1);
     // walkers of the workgroup, and this lane's among them
     const int half = nthr >> 1;
     const bool stager = SPLIT && (int)threadIdx.x >= half;
@@ -443,17 +442,18 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
     const double4 *bin = a.bin;
     const double2 *GH = a.GH;
     const double cC = a.C, w0x2 = 2.0 * a.w0, dW = a.dW;
-    const int ms = M > 0 ? chunk_stride<R>(MR) : a.chunk;  // stored dimensions per chunk
+    constexpr int st = chunk_stride<R>(MR), CVAL = CH * st;  // stored dimensions: of a lane, of a column
+    const int mine = WIDE ? (ch & 3) * (4 * st) + (ch >> 2) * st : ch * st;  // where this lane's are
 
     // records, columns and spectra in LDS
     double *myrec = lds + ws * RSTR;
     const R *colg = (const R *)a.col;
     R *col_s = (R *)(lds + wpb * RSTR + (SPLIT && !ALLB ? wpb / (64 / G) * split_hits(G) : 0));
     if constexpr (LDSC) {
-        const size_t n16 = (size_t)No * 4 * ms * sizeof(R) / 16;
+        const size_t n16 = (size_t)No * CVAL * sizeof(R) / 16;
         for (size_t i = threadIdx.x; i < n16; i += nthr) ((float4 *)col_s)[i] = ((const float4 *)colg)[i];
     }
-    double *spec = (double *)(col_s + (LDSC ? (size_t)No * 4 * ms : 0));
+    double *spec = (double *)(col_s + (LDSC ? (size_t)No * CVAL : 0));
     // the walker's spectrum, or its first bins and a slot for the others' stores
     const int nres = ALLB ? No : a.resident;
     double *bsp = spec + (size_t)ws * (ALLB ? No : nres + 1);
@@ -485,8 +485,8 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
     };
 
     R phi[MR];
-    R *phig = (R *)a.phi + ((size_t)lw * 4 + ch) * ms;
-    if constexpr (M > 0) load_chunk<false, R, MR>(phig, phi);
+    R *phig = (R *)a.phi + (size_t)lw * CVAL + mine;
+    load_chunk<false, R, MR>(phig, phi);
     double g = a.gsc[lw], chi2 = a.chi2[lw], rate = a.rate[lw], ginv = a.ginv[lw];
     double Q2 = 0.0;  // sum_i w_i Phi_i^2 of the walker, exact at each sweep's start
     int nacc = 0;
@@ -517,16 +517,13 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         asm("" : "+v"(p), "+v"(s));
         v.p = p;
         v.s = s;
-        if constexpr (M > 0) {
-            constexpr uint32_t st = (uint32_t)chunk_stride<R>(MR);
-            const uint32_t po = (uint32_t)p * (4 * st) + (uint32_t)ch * st, so = (uint32_t)s * (4 * st) + (uint32_t)ch * st;
-            if constexpr (LDSC) {
-                load_chunk<false, R, MR>(col_s + po, v.rp);
-                load_chunk<false, R, MR>(col_s + so, v.rs);
-            } else {
-                load_chunk<true, R, MR>(colg + po, v.rp);
-                load_chunk<true, R, MR>(colg + so, v.rs);
-            }
+        const uint32_t po = (uint32_t)p * CVAL + (uint32_t)mine, so = (uint32_t)s * CVAL + (uint32_t)mine;
+        if constexpr (LDSC) {
+            load_chunk<false, R, MR>(col_s + po, v.rp);
+            load_chunk<false, R, MR>(col_s + so, v.rs);
+        } else {
+            load_chunk<true, R, MR>(colg + po, v.rp);
+            load_chunk<true, R, MR>(colg + so, v.rs);
         }
     };
     // staging area of a walker: records of batch slot h, then the bins
@@ -670,17 +667,12 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         // only: the two residuals' product is what the basis leaves out.
         R sv[MR], acc = 0;
         const R dpr = (R)v.dp, dsr = (R)v.ds;
-        if constexpr (M > 0) {
 #pragma unroll
-            for (int t = 0; t < MR; ++t) {
-                sv[t] = fma(dpr, v.rp[t], dsr * v.rs[t]);
-                acc = t == 0 ? phi[t] * sv[t] : fma(phi[t], sv[t], acc);
-            }
-        } else {
-            const R *cp = colg + (size_t)(v.p * 4 + ch) * ms, *cs = colg + (size_t)(v.s * 4 + ch) * ms;
-            for (int t = 0; t < ms; ++t) acc = fma(phig[t], fma(dpr, cp[t], dsr * cs[t]), acc);
+        for (int t = 0; t < MR; ++t) {
+            sv[t] = fma(dpr, v.rp[t], dsr * v.rs[t]);
+            acc = t == 0 ? phi[t] * sv[t] : fma(phi[t], sv[t], acc);
         }
-        const double S2 = (double)group_sum<4>(acc);
+        const double S2 = (double)group_sum<CH>(acc);
         const double r2 = r + r;
         const double dchi2 = fma(rm1d, fma(r, Q2, chi2 - cC), fma(r2, S2, v.t));
         // r g, exactly rounded (r - 1 is exact, so g (r - 1) + g is g r): the
@@ -720,15 +712,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         }
         if constexpr (OWNED) accm |= am & own;
         if (__builtin_amdgcn_inverse_ballot_w64(am)) {
-            if constexpr (M == 0) {
-                const R *cp = colg + (size_t)(v.p * 4 + ch) * ms, *cs = colg + (size_t)(v.s * 4 + ch) * ms;
-                // (lanes without a walker compute on another's coordinates)
-                for (int t = 0; t < ms && valid; ++t) {
-                    const R s = fma(dpr, cp[t], dsr * cs[t]);
-                    if constexpr (sizeof(R) == 8) phig[t] = fma((R)r, phig[t], s);
-                    else phig[t] = phig[t] + fma((R)rm1d, phig[t], s);
-                }
-            } else if constexpr (sizeof(R) == 8) {
+            if constexpr (sizeof(R) == 8) {
                 // the three-operand FMA writes phi in place (the compiler's
                 // accumulating form lands in sv and needs a copy back each)
 #pragma unroll
@@ -800,13 +784,9 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         yeps = y * eps0;
         nacc = 0;
         double q2 = 0.0;
-        if constexpr (M > 0) {
 #pragma unroll
-            for (int t = 0; t < MR; ++t) q2 = fma((double)phi[t], (double)phi[t], q2);
-        } else {
-            for (int t = 0; t < ms; ++t) q2 = fma((double)phig[t], (double)phig[t], q2);
-        }
-        Q2 = group_sum<4>(q2);
+        for (int t = 0; t < MR; ++t) q2 = fma((double)phi[t], (double)phi[t], q2);
+        Q2 = group_sum<CH>(q2);
     };
     auto end_sweep = [&]() __attribute__((always_inline)) {
         rate = (1.0 - amp_avg) * rate + amp_avg * ((double)nacc / (double)No);
@@ -1049,9 +1029,8 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         // one proposal before that.  From memory they take longer than a proposal (32
         // jobs of 1300 bins, 300 walkers, FP64: 932 ns a proposal one ahead, 780 ns three;
         // alone, 5000 walkers, 389 and 345 ns; FP32, 2556 bins, 5000 walkers 350 and 285
-        // ns).  More than 24 dimensions, or 16 lanes' unrolled batches, do not leave
-        // the registers for it.
-        constexpr int AHEAD = LDSC || M > 6 || G > 4 ? 1 : 3, V = AHEAD + 1;
+        // ns).  As far as registers go: 8 FP64 values a lane two ahead, 16 lanes one.
+        constexpr int AHEAD = LDSC ? 1 : G == 4 ? (M > 6 ? 2 : 3) : sizeof(R) == 4 ? 3 : 1, V = AHEAD == 1 ? 2 : 4;
         static_assert(G % V == 0, "a batch turns the ring");
         Rec v[V];
         double next_bins;
@@ -1325,11 +1304,9 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         }
     }
     if (valid) {
-        if constexpr (M > 0) {
-            if (c < 4) {
+        if (c < CH) {
 #pragma unroll
-                for (int t = 0; t < MR; ++t) phig[t] = phi[t];
-            }
+            for (int t = 0; t < MR; ++t) phig[t] = phi[t];
         }
         if constexpr (LDSB) {
             wave_lds_sync();
@@ -1371,8 +1348,8 @@ __global__ __launch_bounds__(2 * kSweepThreads) void k_sweep_split16(SweepArgs a
 }
 
 // Many problems in one launch: problem q owns workgroups [first[q], first[q + 1]).
-// Traces (4 lanes a walker) and walks (8, or 4 in a large batch), columns and
-// spectra in memory.
+// Traces (4 lanes a walker) and walks (8, or 4 in a large batch), 16 in a wide
+// basis, columns and spectra in memory.
 template <typename R, int M, int MODE, int G>
 __global__ __launch_bounds__(kSweepThreads, 2) void k_sweep_batched(const SweepArgs *__restrict__ jobs,
                                                                    const int *__restrict__ first, int n_jobs)
@@ -1392,10 +1369,11 @@ __global__ __launch_bounds__(2 * kSweepThreads) void k_sweep_split_batched(const
     const int q = owner_of(first, n_jobs, b);
     const SweepArgs &a = jobs[q];
     const int block = b - first[q];
-    if (a.lanes == 16) {
+    if constexpr (wide_basis(M)) {
         if (a.columns_lds) sweep_block<R, M, 16, true, false, kSweepFast, true>(a, block, lds);
         else sweep_block<R, M, 16, false, false, kSweepFast, true>(a, block, lds);
     }
+    else if (a.lanes == 16) sweep_block<R, M, 16, true, false, kSweepFast, true>(a, block, lds);
     else if (a.resident) sweep_block<R, M, 4, true, true, kSweepFast, true>(a, block, lds);
     else if (a.columns_lds) sweep_block<R, M, 4, true, false, kSweepFast, true>(a, block, lds);
     else sweep_block<R, M, 4, false, false, kSweepFast, true>(a, block, lds);
@@ -3425,7 +3403,6 @@ SweepArgs make_sweep_args(const sail_problem *p, int k0, int k1, const SweepPara
     SweepArgs s;
     s.n_walkers = p->n_walkers;
     s.n_omega = p->n_omega;
-    s.chunk = p->chunk(p->precision);
     s.columns_lds = plan.columns_lds;
     s.tables_lds = plan.tables_lds;
     s.resident = plan.resident;
@@ -3479,7 +3456,6 @@ SweepPlan plan_sweep(const sail_problem *p, bool split, int lanes, int threads, 
                                          : (size_t)walkers * split_stride(lanes) + (size_t)walkers / (64 / lanes) * split_hits(lanes))};
     const size_t col = column_bytes(p->n_omega, p->chunk(p->precision),
                                     p->precision == SAIL_FP32 ? sizeof(float) : sizeof(double));
-    if (basis_class(p->precision, p->dims(p->precision)) == 0) return s;
     const size_t spec = sizeof(double) * (size_t)walkers * p->n_omega;
     // (a split walk: and the tables of the bins and their pairs)
     const size_t bins = (size_t)p->n_omega * sizeof(double4), tables = bins + (size_t)(2 * p->n_omega - 1) * sizeof(double2);
@@ -3537,22 +3513,23 @@ constexpr int kCUs = 256;
 SweepPlan plan_alone(const sail_problem *p, int mode, int walk_len)
 {
     const size_t n = (size_t)p->n_walkers;
-    const bool general = basis_class(p->precision, p->dims(p->precision)) == 0;
+    const int wide = wide_basis(p->dims(p->precision)) ? 16 : 0;  // lanes a wide basis takes
     auto sized = [&](bool split, int lanes, bool spectra) {
         const int most = split ? 2 * kSweepThreads : kSweepThreads, per = split ? 2 * lanes : lanes;
         int threads = split ? 128 : 64;
         while (threads < most && n * per > (size_t)threads * kCUs) threads *= 2;
         const size_t blocks = (n * per + threads - 1) / threads;
-        const size_t per_cu = std::min<size_t>(std::max<size_t>((blocks + kCUs - 1) / kCUs, 1), 4);
+        // (a split sweep's registers leave room for one workgroup of eight wavefronts)
+        const size_t per_cu = split ? 1 : std::min<size_t>(std::max<size_t>((blocks + kCUs - 1) / kCUs, 1), 4);
         return plan_sweep(p, split, lanes, threads, kLdsBytes / per_cu, mode == kSweepWalk, spectra, walk_len);
     };
-    if (mode == kSweepTraced || general) return sized(false, 4, false);
+    if (mode == kSweepTraced) return sized(false, wide ? wide : 4, false);
     // Walks: split, 16 lanes a walker, everything in LDS, if it fits; else all in
     // one wavefront, 8 lanes a walker (256 bins, 1024 walkers, 4 steps: a block
     // 3.5 ms against 6.4 ms, and 9.3 ms with the tables in memory).
     if (mode == kSweepWalk) {
         const SweepPlan w = sized(true, 16, true);
-        return w.spectra_lds ? w : sized(false, 8, true);
+        return w.spectra_lds ? w : sized(false, wide ? wide : 8, true);
     }
     if (n * 16 <= (size_t)kSweepThreads * kCUs) {
         const SweepPlan t = sized(true, 16, true);
@@ -3562,7 +3539,7 @@ SweepPlan plan_alone(const sail_problem *p, int mode, int walk_len)
         if (t.columns_lds) return t;
     }
     const SweepPlan s = sized(false, 16, true);
-    return s.spectra_lds ? s : sized(true, 4, false);
+    return s.spectra_lds ? s : sized(true, wide ? wide : 4, false);
 }
 
 template <typename R, int M, int G, bool LDSC, bool LDSB, int MODE>
@@ -3574,36 +3551,31 @@ void launch_sweep_k(const SweepArgs &a, int blocks, const SweepPlan &s, hipStrea
 template <typename R, int M>
 void launch_sweep_m(const SweepArgs &a, int blocks, const SweepPlan &s, int mode, hipStream_t stream)
 {
-    if (mode == kSweepTraced) return launch_sweep_k<R, M, 4, false, false, kSweepTraced>(a, blocks, s, stream);
-    if constexpr (M > 0) {
-        if (mode == kSweepWalk) {
-            if (s.split) {
-                hipLaunchKernelGGL((k_sweep_split16<R, M, true, true, kSweepWalk>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
-                return;
-            }
-            if (s.spectra_lds) return launch_sweep_k<R, M, 8, true, true, kSweepWalk>(a, blocks, s, stream);
-            return launch_sweep_k<R, M, 8, false, false, kSweepWalk>(a, blocks, s, stream);
-        }
-        if (s.split && s.lanes == 16) {
-            if (s.spectra_lds)
-                hipLaunchKernelGGL((k_sweep_split16<R, M, true, true, kSweepFast>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
-            else if (s.columns_lds)
-                hipLaunchKernelGGL((k_sweep_split16<R, M, true, false, kSweepFast>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
-            else
-                hipLaunchKernelGGL((k_sweep_split16<R, M, false, false, kSweepFast>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
-            return;
-        }
-        if (s.spectra_lds) return launch_sweep_k<R, M, 16, true, true, kSweepFast>(a, blocks, s, stream);
-        if (s.resident)
-            hipLaunchKernelGGL((k_sweep_split<R, M, true, true>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
-        else if (s.columns_lds)
-            hipLaunchKernelGGL((k_sweep_split<R, M, true, false>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
-        else
-            hipLaunchKernelGGL((k_sweep_split<R, M, false, false>), dim3(blocks), dim3(s.threads), s.shm, stream, a);
+    constexpr bool WIDE = wide_basis(M);
+    const dim3 grid(blocks), thr(s.threads);
+    if (mode == kSweepTraced) return launch_sweep_k<R, M, WIDE ? 16 : 4, false, false, kSweepTraced>(a, blocks, s, stream);
+    if (mode == kSweepWalk) {
+        if (s.split) hipLaunchKernelGGL((k_sweep_split16<R, M, true, true, kSweepWalk>), grid, thr, s.shm, stream, a);
+        else if (s.spectra_lds) launch_sweep_k<R, M, WIDE ? 16 : 8, true, true, kSweepWalk>(a, blocks, s, stream);
+        else launch_sweep_k<R, M, WIDE ? 16 : 8, false, false, kSweepWalk>(a, blocks, s, stream);
+        return;
+    }
+    if (s.spectra_lds) {
+        if (s.split) hipLaunchKernelGGL((k_sweep_split16<R, M, true, true, kSweepFast>), grid, thr, s.shm, stream, a);
+        else launch_sweep_k<R, M, 16, true, true, kSweepFast>(a, blocks, s, stream);
+        return;
+    }
+    // (spectra in memory: split; 16 lanes with the columns in LDS, or a wide basis)
+    if (s.lanes == 16 && s.columns_lds) {
+        hipLaunchKernelGGL((k_sweep_split16<R, M, true, false, kSweepFast>), grid, thr, s.shm, stream, a);
+    } else if constexpr (WIDE) {
+        hipLaunchKernelGGL((k_sweep_split16<R, M, false, false, kSweepFast>), grid, thr, s.shm, stream, a);
+    } else if (s.resident) {
+        hipLaunchKernelGGL((k_sweep_split<R, M, true, true>), grid, thr, s.shm, stream, a);
+    } else if (s.columns_lds) {
+        hipLaunchKernelGGL((k_sweep_split<R, M, true, false>), grid, thr, s.shm, stream, a);
     } else {
-        // the general variant: four lanes, phi and columns in memory
-        if (mode == kSweepWalk) return launch_sweep_k<R, M, 4, false, false, kSweepWalk>(a, blocks, s, stream);
-        launch_sweep_k<R, M, 4, false, false, kSweepFast>(a, blocks, s, stream);
+        hipLaunchKernelGGL((k_sweep_split<R, M, false, false>), grid, thr, s.shm, stream, a);
     }
 }
 
@@ -3614,13 +3586,12 @@ void with_basis_class(int precision, int cls, F &&f)
 #define SAIL_CASE(R, M) case M: f(R{}, std::integral_constant<int, M>{}); break;
     if (precision == SAIL_FP32) {
         switch (cls) {
-            SAIL_CASE(float, 2) SAIL_CASE(float, 3) SAIL_CASE(float, 4) SAIL_CASE(float, 6)
-            default: f(float{}, std::integral_constant<int, 0>{});
+            SAIL_CASE(float, 2) SAIL_CASE(float, 3) SAIL_CASE(float, 4) SAIL_CASE(float, 6) SAIL_CASE(float, 16)
         }
     } else {
         switch (cls) {
-            SAIL_CASE(double, 2) SAIL_CASE(double, 4) SAIL_CASE(double, 6) SAIL_CASE(double, 8)
-            default: f(double{}, std::integral_constant<int, 0>{});
+            SAIL_CASE(double, 2) SAIL_CASE(double, 4) SAIL_CASE(double, 6) SAIL_CASE(double, 8) SAIL_CASE(double, 16)
+            SAIL_CASE(double, 24)
         }
     }
 #undef SAIL_CASE
@@ -3646,7 +3617,7 @@ sail_status launch_sweep(sail_problem *p, int k0, int k1, const SweepParams &sp,
         p->ev_used++;
         SAIL_HIP(hipEventRecord(e0, stream));
     }
-    with_basis_class(p->precision, basis_class(p->precision, p->dims(p->precision)), [&](auto r, auto m) {
+    with_basis_class(p->precision, p->dims(p->precision), [&](auto r, auto m) {
         launch_sweep_m<decltype(r), decltype(m)::value>(a, blocks, s, mode, stream);
     });
     SAIL_HIP(hipGetLastError());
@@ -3678,10 +3649,10 @@ sail_status launch_sweep(sail_problem *p, int k0, int k1, const SweepParams &sp,
 // the sample.
 constexpr double kBasisTol64 = 1e-7, kBasisTolLeast = 2e-8, kBasisTol32 = 1e-4, kBasisGreedy = 1e-8;
 constexpr int kBasisSample = 64;
-// Vectors a footprint reckons with.  Decaying kernels give 5 to 25; weights that
-// turn the columns into separate Gaussians reach 67 when they span the whole
-// range of a double.
-constexpr int kBasisMost = 96;
+// Dimensions at most.  Decaying kernels give 5 to 25.  Weights that turn the columns
+// into separate Gaussians give some sqrt(32 W) / pi, W the range of omega tau, which is
+// below 1450 where the columns' norms fit a double: 73 (in FP32 56) computed there.
+constexpr int kBasisMost = 4 * kDims64[5];
 
 double dot(const double *x, const double *y, int n)
 {
@@ -3800,7 +3771,7 @@ public:
         std::vector<std::vector<double>> q = q_;
         const int dims = (int)q.size();
         // principal directions of the sampled columns (a basis of more vectors
-        // than the sweep takes in registers in any precision stays as it is)
+        // than columns of the first sample stays as it is)
         if (dims <= kBasisSample) {
             std::vector<std::vector<double>> rows(dims), r;
             for (int d = 0; d < dims; ++d)
@@ -3934,6 +3905,7 @@ sail_status build_tables(sail_problem *p)
         if (worst[d] <= tol * tol) dims64 = d;
         if (worst[d] <= kBasisTol32 * kBasisTol32) dims32 = d;
     }
+    if (dims64 > kBasisMost) return fail(SAIL_ENUMERIC, "the weighted columns span more than 96 dimensions");
     p->dims64 = round_dims(SAIL_FP64, dims64);
     p->dims32 = round_dims(SAIL_FP32, dims32);
     const int ec = p->echunk = chunk_stride<double>(p->dims64), kept = std::min(dims, 4 * p->dims64);
@@ -4198,7 +4170,7 @@ struct BatchJob {
     int k = 0, last = 0;
 };
 
-constexpr int kSweepGroups = 2 * 5 * 3;  // precisions x basis classes of each x modes
+constexpr int kSweepGroups = 2 * 6 * 3;  // precisions x basis classes of each x modes
 
 struct StageRing {
     static constexpr int kSlots = 4;
@@ -4360,17 +4332,18 @@ template <typename R, int M>
 void launch_sweep_batched_m(const Launch &L, const SweepArgs *jobs, hipStream_t stream)
 {
     const dim3 grid(L.blocks), thr(L.threads);
-    if (L.mode == kSweepTraced)
-        hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepTraced, 4>), grid, thr, L.shm, stream, jobs, L.first, L.n);
-    else if (L.mode == kSweepWalk && L.lanes == 4)
+    constexpr bool WIDE = wide_basis(M);
+    if (L.mode == kSweepFast) {
+        hipLaunchKernelGGL((k_sweep_split_batched<R, M>), grid, thr, L.shm, stream, jobs, L.first, L.n, L.near);
+    } else if (L.mode == kSweepTraced) {
+        hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepTraced, WIDE ? 16 : 4>), grid, thr, L.shm, stream, jobs, L.first, L.n);
+    } else if constexpr (WIDE) {
+        hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepWalk, 16>), grid, thr, L.shm, stream, jobs, L.first, L.n);
+    } else if (L.lanes == 4) {
         hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepWalk, 4>), grid, thr, L.shm, stream, jobs, L.first, L.n);
-    else if constexpr (M > 0) {
-        if (L.mode == kSweepWalk)
-            hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepWalk, 8>), grid, thr, L.shm, stream, jobs, L.first, L.n);
-        else
-            hipLaunchKernelGGL((k_sweep_split_batched<R, M>), grid, thr, L.shm, stream, jobs, L.first, L.n, L.near);
-    } else
-        hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepFast, 4>), grid, thr, L.shm, stream, jobs, L.first, L.n);
+    } else {
+        hipLaunchKernelGGL((k_sweep_batched<R, M, kSweepWalk, 8>), grid, thr, L.shm, stream, jobs, L.first, L.n);
+    }
 }
 
 void launch_sweep_batched(const Launch &L, const SweepArgs *jobs, hipStream_t stream)
@@ -4405,18 +4378,21 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
     // (16 FP32 jobs of 9472 walkers, one round: 14.5 to 11.6 ms) and no compute unit
     // gets a second workgroup for it.
     std::vector<char> wide(act.size(), 0);
+    // chain wavefronts of a problem at its fewest lanes a walker
+    auto least_lanes = [](const sail_problem *p) { return wide_basis(p->dims(p->precision)) ? 16 : 4; };
+    auto pairs_of = [&](const sail_problem *p) { return (p->n_walkers * least_lanes(p) + 63) / 64; };
     {
         int64_t simds = 4 * kCUs;
         std::vector<int> by(act.size());
         for (size_t i = 0; i < act.size(); ++i) {
             by[i] = (int)i;
-            simds -= (act[i]->p->n_walkers + 15) / 16;
+            simds -= pairs_of(act[i]->p);
         }
         std::stable_sort(by.begin(), by.end(), [&](int x, int y) {
             return (int64_t)act[x]->p->n_omega * (kend[x] - act[x]->k) > (int64_t)act[y]->p->n_omega * (kend[y] - act[y]->k);
         });
         for (int i : by) {
-            const int more = (act[i]->p->n_walkers + 3) / 4 - (act[i]->p->n_walkers + 15) / 16;
+            const int more = (act[i]->p->n_walkers + 3) / 4 - pairs_of(act[i]->p);
             if (more > simds) break;
             simds -= more;
             wide[i] = 1;
@@ -4428,7 +4404,7 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
     for (size_t i = 0; i < act.size(); ++i) {
         const sail_problem *p = act[i]->p;
         const int mode = act[i]->sc.walk_len > 0 ? kSweepWalk : sweep_traced(p, act[i]->k, kend[i]) ? kSweepTraced : kSweepFast;
-        group[i] = (p->precision * kBasisClasses + basis_class(p->precision, p->dims(p->precision))) * 3 + mode;
+        group[i] = (p->precision * kBasisClasses + p->dims(p->precision)) * 3 + mode;
     }
     for (int g = 0; g < 2 * kBasisClasses * 3; ++g) {
         std::vector<int> idx;
@@ -4444,9 +4420,10 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
         L.mode = g % 3;
         L.cls = (g / 3) % kBasisClasses;
         L.kind = g / (3 * kBasisClasses);
-        const bool walk = L.mode == kSweepWalk, split = L.mode == kSweepFast && L.cls != 0;
+        const bool walk = L.mode == kSweepWalk, split = L.mode == kSweepFast;
         L.threads = split ? 0 : kSweepThreads;
-        if (walk && L.cls != 0) {
+        L.lanes = least_lanes(act[idx[0]]->p);
+        if (walk && L.lanes == 4) {
             // 8 lanes a walker, or 4 where 8 would leave a fifth of the last round
             // of wavefronts, two a SIMD, unused (256 bins, one step: 24 jobs of 1024
             // walkers 1.5 rounds, 1.54 against 1.71 ms; 1024 bins, 16 jobs of 4096
@@ -4471,7 +4448,7 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
             int pairs = 1;
             auto at = [&](int n) {
                 size_t b = 0;
-                for (int i : idx) b += ((size_t)act[i]->p->n_walkers + 16 * n - 1) / (16 * n);
+                for (int i : idx) b += ((size_t)pairs_of(act[i]->p) + n - 1) / n;
                 return b;
             };
             while (pairs < 4 && at(pairs) > (size_t)kCUs) pairs *= 2;
@@ -4482,9 +4459,9 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
                 // records (1024 FP64 bins); not one of several, which leaves compute
                 // units idle for long (1100 bins, four jobs of 4000 walkers: 2.28 ms, and
                 // 1.41 ms with the columns in memory)
-                SweepPlan s = plan_sweep(p, true, 4, 128 * pairs, kLdsBytes, false, false, 0);
+                SweepPlan s = plan_sweep(p, true, L.lanes, 128 * pairs, kLdsBytes, false, false, 0);
                 for (int t = 64 * pairs; !s.columns_lds && t >= 256; t /= 2) {
-                    const SweepPlan q = plan_sweep(p, true, 4, t, kLdsBytes, false, false, 0);
+                    const SweepPlan q = plan_sweep(p, true, L.lanes, t, kLdsBytes, false, false, 0);
                     if (q.columns_lds) s = q;
                 }
                 plans.push_back(s);
@@ -4492,7 +4469,7 @@ sail_status batch_round(std::vector<BatchJob *> &jobs, StageRing &ring, SweepTim
             }
             for (size_t n = 0; n < idx.size(); ++n) {
                 const sail_problem *p = act[idx[n]]->p;
-                for (int t = 4 * 128; wide[idx[n]] && t >= 128; t /= 2) {
+                for (int t = 4 * 128; wide[idx[n]] && L.lanes == 4 && t >= 128; t /= 2) {
                     const SweepPlan q = plan_sweep(p, true, 16, t, kLdsBytes, false, false, 0);
                     const int with = total - sweep_blocks(p, plans[n]) + sweep_blocks(p, q);
                     if (!q.columns_lds || with > kCUs) continue;

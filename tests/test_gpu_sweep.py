@@ -91,11 +91,30 @@ def test_same_bits_for_every_plan(S, n_omega, n_tau, n_walkers, prec, walk, spre
         np.testing.assert_array_equal(alone.read_chi2(), gp.read_chi2(), err_msg=f"{name}: chi2")
 
 
+@pytest.mark.parametrize("n_omega,n_tau,spread", [(96, 120, 800.0), (96, 120, 1200.0)])
+def test_wide_bases_against_oracle(S, n_omega, n_tau, spread):  # noqa: F811
+    test_basis_classes_against_oracle(S, n_omega, n_tau, spread)
+
+
 @pytest.mark.parametrize("n_omega,n_tau,spread", [(60, 7, 0.0), (96, 80, 60.0), (96, 80, 150.0), (96, 80, 250.0),
                                                   (96, 80, 400.0)])
 def test_basis_classes_against_oracle(S, n_omega, n_tau, spread):  # noqa: F811
     wl = _workload(n_omega, n_tau, 18, 20, spread)
     _anneal_lockstep(S, wl, 18, 11, 20, dict(branch_every=20, resync_every=10), T=np.geomspace(100.0, 1.0, 20))
+
+
+# bases of more than 32 dimensions: 16 lanes a walker in every plan
+@pytest.mark.parametrize("n_omega,n_tau,n_walkers,prec,walk,spread", [
+    (96, 80, 4500, 0, 0, 400.0),   # more walkers than one a wavefront's quarter
+    (300, 128, 130, 0, 0, 400.0),  # columns in memory
+    (300, 128, 130, 1, 0, 400.0),
+    (60, 120, 33, 0, 0, 1100.0),   # as many dimensions as bins, 64 and less
+    (96, 120, 33, 0, 0, 1300.0),   # more than 64
+    (40, 80, 20, 0, 64, 400.0),    # a walk's steps leave no room for its tables
+    (96, 80, 1100, 1, 2, 400.0),
+])
+def test_same_bits_for_wide_bases(S, n_omega, n_tau, n_walkers, prec, walk, spread):  # noqa: F811
+    test_same_bits_for_every_plan(S, n_omega, n_tau, n_walkers, prec, walk, spread)
 
 
 # jobs, bins, times, walkers, precision, walk steps: launches of many workgroups and their rules
