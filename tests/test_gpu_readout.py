@@ -60,3 +60,25 @@ def test_read_outs_by_several_threads():
         together = list(pool.map(read, range(60)))
     for i, got in enumerate(together):
         np.testing.assert_array_equal(got, read(i), err_msg=str(i))
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n_omega,n_tau,n_walkers", [(3, 1, 2), (17, 16, 9), (40, 33, 2000), (300, 24, 2064), (700, 200, 1100)])
+def test_reconstructions_are_the_spectra_s(n_omega, n_tau, n_walkers, precision):
+    """F read one copy with the rates, or in passes of the kept rows, against
+    K a in 80 bits."""
+    from paper_1609_07936_amd import sail as S
+    tau = np.array([0.4]) if n_tau == 1 else W.uniform_tau(0.05, 1.6, n_tau)
+    tgt = W.Target([1.5, 4.0], [0.4, 0.8], [0.6, 0.4], 10.0)
+    wl = W.make("ro", 10.0, n_omega, tau, tgt, 1e-3, 3, n_walkers, 4, 1e2, 1.0, 100, 100, 5, n_quad=2000)
+    gp = S.Problem(wl.omega, wl.tau, wl.Ft, wl.sigma, wl.m0, wl.m1)
+    gp.init_walkers(n_walkers, 7, precision=precision)
+    gp.run(S.Schedule(np.full(4, 50.0)), 0, 3)
+    st = gp.read_state()
+    K = np.exp(-np.outer(wl.omega, wl.tau).astype(np.longdouble)) * ((wl.omega[1] - wl.omega[0]) / (2.0 * np.pi))
+    # positive terms: a rounding each for the scale, the column, the product and the sum, and the loop precision's
+    u = 2.0 ** -53
+    np.testing.assert_allclose(st["F"], (st["a"].astype(np.longdouble) @ K).astype(float), atol=0,
+                               rtol=(n_omega + 8) * u + (2.0 ** -24 if precision else 0.0))
+    blob = gp.state_export()
+    np.testing.assert_array_equal(np.frombuffer(blob[-8 - 8 * n_walkers:-8]), st["rate"])
