@@ -166,3 +166,67 @@ def test_autotuned_layouts_do_not_vary(S):
                 assert gp.autotune_layout(wl.n_walkers, precision, alone=alone) == 16
                 gp.init_walkers(wl.n_walkers, 1, precision=precision)
                 assert gp.layout() == (4, 16)
+
+
+# plans of their own: one workgroup's LDS, spectra in memory, four lanes; more dimensions
+@pytest.mark.parametrize("n_omega,n_tau,n_walkers,w_max,tau_hi", [(64, 32, 64, 10.0, 1.6), (998, 33, 700, 10.0, 1.6),
+                                                                  (130, 40, 8197, 10.0, 1.6), (40, 24, 33, 25.0, 4.0)])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_carried_coordinates_follow_the_spectra(S, n_omega, n_tau, n_walkers, w_max, tau_hi, precision):
+    """Between resyncs the coordinates that the sweep carries are the spectra's,
+    as a resync takes them, up to the roundings of the accepted moves; the
+    traced sweep carries the same ones bit for bit, and its flags give the
+    acceptance rate."""
+    import torch
+    wl = _workload(n_omega, n_tau, n_walkers, w_max, tau_hi)
+    n = 5
+    sched = S.Schedule(np.full(100, 50.0))
+    a, b = _problem(S, wl, precision), _problem(S, wl, precision)
+    a.run(sched, 0, n)
+    d = torch.zeros((n_walkers, n, n_omega), dtype=torch.float64, device="cuda")
+    f = torch.zeros((n_walkers, n, n_omega), dtype=torch.uint8, device="cuda")
+    b.set_trace(0, n, d.data_ptr(), f.data_ptr())
+    b.run(sched, 0, n)
+    torch.cuda.synchronize()
+    blob = a.state_export()
+    assert blob == b.state_export()
+    accepted = (f.cpu().numpy() & 1).sum(axis=2)
+    rate = np.ones(n_walkers)
+    for k in range(n):
+        rate = (1.0 - 0.1) * rate + 0.1 * (accepted[:, k] / n_omega)
+    np.testing.assert_array_equal(a.read_state()["rate"], rate)
+    assert accepted.sum() > 0
+    other = bytearray(blob)
+    other[-1] ^= 0xFF
+    b.state_import(bytes(other))  # taken by its spectra
+    K = np.exp(-np.outer(wl.omega, wl.tau)) * ((wl.omega[1] - wl.omega[0]) / (2.0 * np.pi)) / wl.sigma
+    size = a.read_state()["a"].sum(axis=1).max() * np.sqrt((K * K).sum(axis=1)).max()
+    u = 2.0 ** -24 if precision else 2.0 ** -53
+    # a move rounds phi and two columns' terms once each, and the spectrum's two values and scale
+    bound = (16.0 * accepted.sum(axis=1).max() + n_omega + 64) * u * size
+    err = np.abs(_coordinates(blob) - _coordinates(b.state_export())).max()
+    print(f"{n_omega}x{n_tau}x{n_walkers}: {err / size:.1e} of the norm, bound {bound / size:.1e}", flush=True)
+    assert 0.0 < err <= bound
+
+
+def test_fp32_residue_changes_late_in_a_segment(S):
+    """The FP32 loop's residue changes forty sweeps after a resync, in lockstep
+    with the FP64 oracle: within 1e-5 of their condition scale, as right after
+    one."""
+    import oracle as O
+    import torch
+    wl, n, seed = _workload(64, 32, 24), 40, 11
+    T = np.geomspace(30.0, 0.01, n)
+    gp = _problem(S, wl, 1, seed)
+    d = torch.zeros((24, n, 64), dtype=torch.float64, device="cuda")
+    f = torch.zeros((24, n, 64), dtype=torch.uint8, device="cuda")
+    gp.set_trace(0, n, d.data_ptr(), f.data_ptr())
+    gp.run(S.Schedule(T), 0, n)
+    torch.cuda.synchronize()
+    g_f = f.cpu().numpy()
+    an = O.Anneal(O.Problem(wl.omega, wl.tau, wl.Ft, wl.sigma, wl.m0, wl.m1), O.Schedule(T), 24, seed)
+    out = an.run(0, n, trace=(0, n), replay=g_f, band=1e-5)
+    assert out["hard_mismatch"] == 0, out["first_mismatch"]
+    err = np.abs(d.cpu().numpy() - out["dchi2"]) / np.maximum(out["cond"], 1e-300)
+    print(f"worst over the first sweep {err[:, 0].max():.1e}, over the last {err[:, -1].max():.1e}", flush=True)
+    assert err.max() <= 1e-5
