@@ -484,7 +484,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         else return buffer_load_f64(b_rs, brow + ((uint32_t)j << 3));
     };
 
-    R phi[MR];
+    R phi[MR], lost = 0;  // lost: FP32, of a sweep's additions to phi[0]
     R *phig = (R *)a.phi + (size_t)lw * CVAL + mine;
     load_chunk<false, R, MR>(phig, phi);
     double g = a.gsc[lw], chi2 = a.chi2[lw], rate = a.rate[lw], ginv = a.ginv[lw];
@@ -719,10 +719,20 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
                 for (int t = 0; t < MR; ++t) asm("v_fma_f64 %0, %1, %0, %2" : "+v"(phi[t]) : "v"(r), "v"(sv[t]));
             } else {
                 // FP32: r - 1 rounds to FP32 with a relative error far smaller
-                // than r would, so the change is formed first
+                // than r would, so the change is formed first.  What an addition to a
+                // lane's first value, the largest by far (the basis is in principal
+                // directions), loses is carried to the next one until the sweep ends:
+                // without, residue changes fifty sweeps after a resync were off by
+                // 8.6e-8 of their condition scale (rms, 512 bins x 128 times), with it
+                // by 1.5e-8, and by 3.7e-8 with FP32 values per time, whose roundings
+                // averaged (512 bins x 16384 walkers, block 18.3 to 18.6 ms)
                 const R rm1 = (R)rm1d;
 #pragma unroll
-                for (int t = 0; t < MR; ++t) phi[t] = phi[t] + fma(rm1, phi[t], sv[t]);
+                for (int t = 0; t < MR; ++t) {
+                    const R y = fma(rm1, phi[t], t == 0 ? sv[t] + lost : sv[t]), sum = phi[t] + y;
+                    if (t == 0) lost = y - (sum - phi[t]);
+                    phi[t] = sum;
+                }
             }
             asm("v_fma_f64 %0, %1, %0, %2" : "+v"(Q2) : "v"(r * r), "v"(fma(r2, S2, v.s1)));
             chi2 = chi2 + dchi2;
@@ -786,6 +796,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         double q2 = 0.0;
 #pragma unroll
         for (int t = 0; t < MR; ++t) q2 = fma((double)phi[t], (double)phi[t], q2);
+        lost = 0;
         Q2 = group_sum<CH>(q2);
     };
     auto end_sweep = [&]() __attribute__((always_inline)) {
