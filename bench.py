@@ -98,13 +98,24 @@ def matched(median_a: float, median_b: float, rel: float = 0.05) -> bool:
 
 
 def sweep_source_digest() -> str:
-    """sha256 prefix of the sweep kernel's source: sail.hip from its start to
-    the end of k_sweep_batched (the helpers, the sweep and its wrappers)."""
+    """sha256 prefix of the sweep kernels' source: sail.hip from its start to
+    the end of the last wrapper, k_sweep_split_batched (the helpers, the sweep
+    and its kernels)."""
     import hashlib
     text = open(os.path.join(ROOT, "paper_1609_07936_amd", "csrc", "sail.hip"), "rb").read()
-    i = text.index(b"void k_sweep_batched(")
+    i = text.index(b"void k_sweep_split_batched(")
     j = text.index(b"\n}\n", i) + 3
     return hashlib.sha256(text[:j]).hexdigest()[:16]
+
+
+def proposal_flops(S, wl, precision: int) -> float:
+    """Flops the sweep spends on a proposal's residue change: two columns in the
+    basis scaled and added (3 a coordinate), their product with the walker (2)
+    and the update of an accepted move (2 to 3); 8 per stored coordinate, the
+    padding included."""
+    p = S.Problem(wl.omega, wl.tau, wl.Ft, wl.sigma, wl.m0, wl.m1)
+    p.init_walkers(2, 1, precision=precision)
+    return 8.0 * int(np.frombuffer(p.state_export(), dtype="<i4", count=8)[7])
 
 
 def measured_lds(workload: str, avg_launch_ms: float):
@@ -324,7 +335,8 @@ def batched_line(args) -> dict:
     sweep_ms, launches = batch.sweep_timing(reset=True)
     swept = steps * per_step
     proposals = sum(wl.n_walkers * wl.omega.size for wl in jobs) * swept
-    flops = 8.0 * sum(wl.n_walkers * wl.omega.size * wl.tau.size for wl in jobs) * swept
+    direct = 8.0 * sum(wl.n_walkers * wl.omega.size * wl.tau.size for wl in jobs) * swept
+    flops = sum(proposal_flops(S, wl, S.SAIL_FP32) * wl.n_walkers * wl.omega.size for wl in jobs) * swept
     achieved = flops / (sweep_ms * 1e-3) / 1e12
     rel = np.array([np.median(gp.read_chi2(stream=stream)) / gp.chi2_unit for gp in probs])
     plain = None
@@ -366,12 +378,13 @@ def batched_line(args) -> dict:
             "at_sweep": swept,
         },
         "roofline": {
-            "kernel": "k_sweep_batched<float>",
-            "bound": "alu",
+            "kernel": "k_sweep_split_batched<float>",
+            "bound": "latency of the walkers' serial chains, spectrum traffic",
             "achieved": achieved,
             "peak": FP32_PEAK_TFLOPS,
             "unit": "TFLOP/s",
             "frac": achieved / FP32_PEAK_TFLOPS,
+            "summed_over_times_tflops": direct / (sweep_ms * 1e-3) / 1e12,
             "traffic": measured_traffic(args.workload),
             "traffic_unit": "bytes per launch (FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
             "avg_launch_ms": sweep_ms / launches,
@@ -464,8 +477,9 @@ def served_line(args) -> dict:
     first, second = lat[sub < args.duration / 2], lat[sub >= args.duration / 2]
     span = max(r["t_done"] for r in ok) - t_base
     prop = sum(wl.n_walkers * wl.omega.size * wl.n_sweeps for wl, r in zip(jobs, res) if r["status"] == 0)
-    flops = 8.0 * sum(wl.n_walkers * wl.omega.size * wl.tau.size * wl.n_sweeps for wl, r in zip(jobs, res)
-                      if r["status"] == 0)
+    done = [wl for wl, r in zip(jobs, res) if r["status"] == 0]
+    direct = 8.0 * sum(wl.n_walkers * wl.omega.size * wl.tau.size * wl.n_sweeps for wl in done)
+    flops = sum(proposal_flops(S, wl, S.SAIL_FP32) * wl.n_walkers * wl.omega.size * wl.n_sweeps for wl in done)
     rel = np.array([r["chi2_median"] / r["chi2_unit"] for r in ok])
     achieved = flops / (st["sweep_ms"] * 1e-3) / 1e12
     line = {
@@ -501,8 +515,10 @@ def served_line(args) -> dict:
         "speedup_over_plain_fp64": {"solves_per_s": (len(ok) / span) / plain["solves_per_s"]},
         "failed": len(res) - len(ok),
         "quality": {"final_chi2_over_chi2_0_median_over_jobs": float(np.median(rel))},
-        "roofline": {"kernel": "k_sweep_batched<float>", "bound": "alu", "achieved": achieved,
+        "roofline": {"kernel": "k_sweep_split_batched<float>",
+                     "bound": "latency of the walkers' serial chains, spectrum traffic", "achieved": achieved,
                      "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / FP32_PEAK_TFLOPS,
+                     "summed_over_times_tflops": direct / (st["sweep_ms"] * 1e-3) / 1e12,
                      "traffic": None, "avg_launch_ms": st["sweep_ms"] / max(1, st["sweep_launches"]),
                      "launches": st["sweep_launches"]},
         "server": st,
@@ -548,8 +564,7 @@ def band(args):
     spec = gp.read_spectrum(stream=stream)
     chi2 = gp.read_chi2(stream=stream)
     left, right = wl.omega < 1.5, wl.omega >= 1.5
-    flops = 8.0 * wl.tau.size * proposals
-    achieved = flops / (sweep_ms * 1e-3) / 1e12
+    achieved = proposal_flops(S, wl, S.SAIL_FP64) * proposals / (sweep_ms * 1e-3) / 1e12
     line = {
         "metric": "walker proposals/s at matched final chi2",
         "value": proposals / elapsed,
@@ -581,8 +596,11 @@ def band(args):
             "final_chi2_over_chi2_0_median": float(np.median(chi2) / gp.chi2_unit),
             "at_sweep": SWEEPS_PER_STEP * steps,
         },
-        "roofline": {"kernel": "k_sweep<double>", "bound": "alu", "achieved": achieved, "peak": FP64_PEAK_TFLOPS,
-                     "unit": "TFLOP/s", "frac": achieved / FP64_PEAK_TFLOPS, "traffic": None,
+        "roofline": {"kernel": "k_sweep_split16<double>", "bound": "latency of the walkers' serial chains",
+                     "achieved": achieved, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
+                     "frac": achieved / FP64_PEAK_TFLOPS,
+                     "summed_over_times_tflops": 8.0 * wl.tau.size * proposals / (sweep_ms * 1e-3) / 1e12,
+                     "traffic": None,
                      "avg_launch_ms": sweep_ms / launches, "launches": launches,
                      "sweep_share_of_step": sweep_ms / (elapsed * 1e3)},
     }
@@ -681,10 +699,12 @@ def main():
             "final_chi2_over_chi2_0_min": float(chi2_final.min() / gp.chi2_unit),
             "final_at_sweep": n_sweeps_total,
         })
-    # roofline of the sweep kernel: 8 N_tau algorithmic flops per proposal
-    flops_per_launch = 8.0 * wl.tau.size * wl.n_walkers * wl.omega.size * (SWEEPS_PER_STEP * steps / launches)
+    # the sweep kernel: what it computes, and the 8 N_tau flops per proposal that
+    # the residue change takes summed over the times
+    proposals_per_launch = wl.n_walkers * wl.omega.size * (SWEEPS_PER_STEP * steps / launches)
     avg_ms = sweep_ms / launches
-    achieved = flops_per_launch / (avg_ms * 1e-3) / 1e12
+    achieved = (proposal_flops(S, wl, S.SAIL_FP32 if fp32 else S.SAIL_FP64) * proposals_per_launch /
+                (avg_ms * 1e-3) / 1e12)
     peak = FP32_PEAK_TFLOPS if fp32 else FP64_PEAK_TFLOPS
     line = {
         "metric": "walker proposals/s at matched final chi2",
@@ -714,12 +734,13 @@ def main():
         },
         "quality": quality,
         "roofline": {
-            "kernel": "k_sweep<float>" if fp32 else "k_sweep<double>",
-            "bound": "alu",
+            "kernel": "k_sweep_split<float>" if fp32 else "k_sweep_split<double>",
+            "bound": "latency of the walkers' serial chains, spectrum traffic",
             "achieved": achieved,
             "peak": peak,
             "unit": "TFLOP/s",
             "frac": achieved / peak,
+            "summed_over_times_tflops": 8.0 * wl.tau.size * proposals_per_launch / (avg_ms * 1e-3) / 1e12,
             "traffic": measured_traffic(args.workload),
             "traffic_unit": "bytes per launch (FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
             "lds": measured_lds(args.workload, avg_ms),

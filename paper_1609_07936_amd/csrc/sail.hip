@@ -15,7 +15,7 @@
 //     walker's coordinates phi of sqrt(wh) Phi in that basis, and sums over
 //     tau become sums over the basis.
 //   * A walker occupies G lanes of a wavefront; lane c holds chunk c mod 4 of
-//     phi in registers.  The residue change is taken from its expansion, whose
+//     phi in registers (a quarter of it where the basis is wide).  The residue change is taken from its expansion, whose
 //     only sum that needs the walker is sum_i w_i Phi_i s_i = phi . sigma with
 //     sigma = dp C_p + ds C_s (C_j: column j in the basis; four chunk sums and
 //     a two-step butterfly, so every lane ends with the same bits and takes the
@@ -488,7 +488,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
     R *phig = (R *)a.phi + (size_t)lw * CVAL + mine;
     load_chunk<false, R, MR>(phig, phi);
     double g = a.gsc[lw], chi2 = a.chi2[lw], rate = a.rate[lw], ginv = a.ginv[lw];
-    double Q2 = 0.0;  // sum_i w_i Phi_i^2 of the walker, exact at each sweep's start
+    double Q2 = 0.0;  // sum_i w_i Phi_i^2 of the walker, from its coordinates at each sweep's start
     int nacc = 0;
     int k = a.k0, q0 = 0;
     double Tabs = 0.0, yeps = 0.0, thr_T = 0.0;  // temperature and move width of sweep k, thr_tol T
@@ -656,7 +656,8 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         // F' = r F + s with s_i = dp K_pi + ds K_si.  The residue change
         // sum_i w_i ((Phi'_i - Phit_i)^2 - (Phi_i - Phit_i)^2) expands into
         //   (r - 1) (r Q2 + chi^2 - C) + 2 r S2 + S1 + S3,
-        // Q2 = sum_i w_i Phi_i^2 (the walker's, exact at each sweep's start and
+        // Q2 = sum_i w_i Phi_i^2 (the walker's, from its coordinates at each sweep's
+        // start, short of it by what the basis leaves of Phi, squared, and
         // carried through the accepted moves), S2 = sum_i w_i Phi_i s_i =
         // phi . sigma (the only sum that needs the walker), and S1 =
         // sum_i w_i s_i^2, S3 = sum_i c_i s_i from tables (staged);
@@ -803,7 +804,8 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         rate = (1.0 - amp_avg) * rate + amp_avg * ((double)nacc / (double)No);
     };
     // the records are private to this wavefront: a wavefront-level ordering
-    // point is enough (SAIL_SWEEP_SYNC=1 selects a workgroup barrier)
+    // point is enough (SAIL_SWEEP_SYNC=1 selects a workgroup barrier; split sweeps,
+    // whose records pass between wavefronts, have one there always)
     auto order = [&]() __attribute__((always_inline)) {
         if (wg_sync) __syncthreads();
         else wave_lds_sync();
@@ -1438,8 +1440,8 @@ __device__ __forceinline__ T wave_reduce(T v, Op op)
 }
 
 // --------------------------------------------------------------------------
-// Resync: fold the lazy scale, optionally renormalise both sums, recompute
-// Phi = E b, G and chi^2 (one workgroup per walker).
+// Resync: imprint or smooth, fold the lazy scale, optionally renormalise both
+// sums, recompute the walkers' coordinates and chi^2 (8 or 16 walkers a workgroup).
 // --------------------------------------------------------------------------
 struct ResyncArgs {
     int n_omega, n_tau;
@@ -1538,7 +1540,7 @@ __device__ __forceinline__ void columns_product(const double *sb, const int ld, 
 // chi^2; the basis coordinates are stored in the loop precision R.  A walker's
 // sums are taken in the same order for either WPB.  8 walkers leave half of a
 // tile's rows idle but twice the workgroups.  512 bins, 144 columns, 16384 walkers:
-// 96 us, 25 TFLOP/s (165 us on the vector units, which an LDS read per FMA held
+// 93 us, 26 TFLOP/s (165 us on the vector units, which an LDS read per FMA held
 // back); 64 walkers of 64 bins 11 us (19), mostly latency.
 template <typename R, int WPB>
 __device__ __forceinline__ void resync_block(const ResyncArgs &a, const int block, double *sh)
@@ -2077,8 +2079,8 @@ __device__ __forceinline__ int branch_m(double xi, double w, double y, int n)
 // a chain of counts, each a handful of instructions per walker and a
 // reduction over the workgroup, so a small population takes few wavefronts
 // (their barrier is what a count waits for; one wavefront needs none) and few
-// walkers per thread (64 walkers, one event: 1250 us with 1024 threads of 16,
-// 261 us with one wavefront; the parallel search's evaluations: 38 to 17 us at
+// walkers per thread (64 walkers, one event in one workgroup: 1250 us with 1024
+// threads of 16 walkers, 480 us with one wavefront; the spread search's evaluations: 38 to 17 us at
 // 1024 walkers, 43 to 29 us at 3001; a batch of 64 mixed events: 1290 to 769 us).  The shape follows from
 // the population alone, so an event has the same bits however it is run.
 struct BranchShape {
@@ -2125,8 +2127,8 @@ __device__ __forceinline__ T branch_reduce(T v, T (*slots)[WAVES], int &par, Op 
     return r;
 }
 
-// The fixed Delta search of one problem spread over many workgroups (64 walkers:
-// 480 us in one workgroup, 260 us spread; two events of a small solve):
+// The fixed Delta search of one problem spread over many workgroups (64 walkers,
+// an event: 480 us in one workgroup, 110 us of kernels spread):
 // each round evaluates, in parallel, every Delta the search could visit next
 // (the bracketing powers d0 2^j; then kTreeLevels levels of the bisection
 // tree, each node's Delta derived from the round's bracket by the search's own
@@ -2793,7 +2795,7 @@ __global__ void k_zero_u64(int n, unsigned long long *v)
 }
 
 // Smallest and largest of n values, one workgroup (16384 values: 28 us with 256
-// threads, 5 us with 1024; latency, four values in flight per thread).
+// threads, 9 to 12 us with 1024; latency, four values in flight per thread).
 __global__ __launch_bounds__(kMinMaxThreads) void k_minmax(int n, const double *v, double *out)
 {
     __shared__ double red[kMinMaxThreads / 64];
@@ -4189,8 +4191,8 @@ int segment_end(const sail_schedule *sc, int k, int last)
 
 // --------------------------------------------------------------------------
 // Many problems advanced together.  A round takes every unfinished job to
-// its next resync boundary: one sweep launch per (precision, tau points per
-// lane) holds the workgroups of all of them, then one launch each for the
+// its next resync boundary: one sweep launch per (precision, basis class, mode)
+// holds the workgroups of all of them, then one launch each for the
 // renormalising resync, the branching solves and the imprint + target resync
 // of the jobs that reached such a boundary.  Every job runs exactly the
 // kernels' per-problem code on its own state, so its result is bit-identical

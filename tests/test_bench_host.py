@@ -54,3 +54,23 @@ def test_lds_figures_from_the_committed_summary():
         assert r["bytes_per_launch"] > 0 and r["ceiling"] > 0
         assert abs(r["achieved"] - r["bytes_per_launch"] / (ms * 1e-3) / 1e12) < 1e-9
         assert abs(r["frac"] - r["achieved"] / r["ceiling"]) < 1e-12
+
+
+def test_sweep_digest_covers_every_sweep_kernel(tmp_path, monkeypatch):
+    """The digest that admits the committed profiles covers the kernel of the
+    shared launches, whose profile is among them, to its end."""
+    import re
+    src = tmp_path / "paper_1609_07936_amd" / "csrc"
+    src.mkdir(parents=True)
+    text = open(os.path.join(ROOT, "paper_1609_07936_amd", "csrc", "sail.hip")).read()
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+
+    def digest(t):
+        (src / "sail.hip").write_text(t)
+        return bench.sweep_source_digest()
+
+    last = max(m.end() for m in re.finditer(r"void k_sweep\w*\(", text))
+    body = text.index("sweep_block<", last)
+    assert digest(text[:body] + " " + text[body:]) != digest(text)
+    end = text.index("\n}\n", body) + 3
+    assert digest(text[:end] + "// more\n" + text[end:]) == digest(text)
