@@ -21,7 +21,8 @@
  *    ABI.  On an error the call changes no state (one exception:
  *    sail_walkers_init, see there), and sail_last_error() returns a message
  *    for the calling thread.
- *  - A problem is used from one host thread at a time.  Work is enqueued on
+ *  - A problem is used from one host thread at a time (read-outs by several
+ *    threads between its runs take turns).  Work is enqueued on
  *    the HIP stream passed as `stream` (NULL means the null stream); calls
  *    that return host data synchronise that stream.
  */
@@ -135,9 +136,9 @@ sail_status sail_walkers_init(sail_problem_t p, int n_walkers, uint64_t seed, in
  * A sweep is n_omega proposals per walker.  After sweep k, if (k + 1) is a
  * multiple of resync_every every walker is renormalised to both sum rules and
  * its F and chi^2 recomputed; if (k + 1) is a multiple of branch_every the
- * branching event (k + 1) / branch_every - 1 follows (Sec. 2.5; with 256
- * walkers or more its Delta search runs over many workgroups, with the
- * same result).  Stages may be run in several calls; the random stream
+ * branching event (k + 1) / branch_every - 1 follows (Sec. 2.5; its Delta
+ * search runs over many workgroups, a batch's in one, with the same
+ * result).  Stages may be run in several calls; the random stream
  * depends only on the global sweep, proposal and walker indices. */
 sail_status sail_run_schedule(sail_problem_t p, const sail_schedule *sched, int first_sweep, int n_sweeps,
                               void *stream);
@@ -235,7 +236,9 @@ sail_status sail_read_chi2_hist_noalloc(sail_problem_t p, int n_bins, double lo,
 
 /* Walker state, every pointer host and optional (NULL skips it):
  *   a     [n_walkers][n_omega] spectra a_j (scale folded in)
- *   F     [n_walkers][n_tau] reconstructions F(tau_i)
+ *   F     [n_walkers][n_tau] reconstructions F(tau_i) = sum_j a_j K(omega_j,
+ *         tau_i), rounded to the loop precision (what the sweep carries in
+ *         their place is in sail_state_export)
  *   rate  [n_walkers] running acceptance rates */
 sail_status sail_read_state(sail_problem_t p, double *a, double *F, double *rate, void *stream);
 
@@ -306,7 +309,7 @@ sail_status sail_state_import(sail_problem_t p, const void *buf, size_t bytes, v
  * sail_run_schedule on that problem alone: the results are bit-identical.
  * The problems advance in rounds, each taking every unfinished problem to
  * its next resync boundary in one shared sweep launch (per precision and
- * lane layout), followed by shared launches of the resyncs, the branching
+ * sweep kernel), followed by shared launches of the resyncs, the branching
  * solves and the imprints that fall due.  Problems may sit at different
  * sweeps and have different sizes, walker counts, precisions and schedules.
  * Traced sweeps (sail_set_trace) are refused.  Validation happens before any
@@ -423,9 +426,8 @@ sail_status sail_layout(sail_problem_t p, int *lanes_per_walker, int *tau_per_la
 /* Requests tau points per lane for the next sail_walkers_init: 4, 8 or 16
  * for FP64, 8, 16 or 32 for FP32, 0 for the library's choice (16).  A
  * request the precision does not take falls back to the choice.  It sets the
- * nominal layout (sail_layout), hence the padding of the reconstructions'
- * rows in device memory; results and speed do not depend on it.  Any other
- * value: SAIL_EINVAL. */
+ * nominal layout (sail_layout); results and speed do not depend on it.  Any
+ * other value: SAIL_EINVAL. */
 sail_status sail_set_tau_per_lane(sail_problem_t p, int tau_per_lane);
 
 /* Chooses the tau points per lane for this problem at n_walkers walkers and
