@@ -288,16 +288,17 @@ constexpr int chunk_stride(int m) { return sizeof(R) == 8 ? (m + 1) & ~1 : (m + 
 // dimensions at most, 1024 walkers: 235 ns a proposal, 3.3 us with a walker's
 // coordinates in memory, 470 ns with a recurrence along 80 times).  More than 4096
 // walkers leave a compute unit 16 at a time and stay behind the recurrence (8192: 760
-// against 540 us for 960 proposals).
-constexpr int kDims64[6] = {2, 4, 6, 8, 16, 24}, kDims32[5] = {2, 3, 4, 6, 16};
-constexpr int kBasisClasses = 25;
+// against 540 us for 960 proposals).  The widest (500 bins, 512 times, 1024 walkers, FP64):
+// four sweeps 0.98 ms, 15.8 with the coordinates in memory, 1.31 with the recurrence.
+constexpr int kDims64[7] = {2, 4, 6, 8, 16, 24, 32}, kDims32[6] = {2, 3, 4, 6, 16, 24};
+constexpr int kBasisClasses = 33;
 constexpr bool wide_basis(int m) { return m > 8; }
 constexpr int kReadRows = 16;  // walkers whose reconstructions are read at once, at least
 // Dimensions per chunk for a basis of n dimensions (or the most there are).
 int round_dims(int precision, int n)
 {
     const int need = n > 4 ? (n + 3) / 4 : 1;
-    const int *m = precision == SAIL_FP32 ? kDims32 : kDims64, *last = m + (precision == SAIL_FP32 ? 4 : 5);
+    const int *m = precision == SAIL_FP32 ? kDims32 : kDims64, *last = m + (precision == SAIL_FP32 ? 5 : 6);
     while (m < last && need > *m) ++m;
     return *m;
 }
@@ -356,11 +357,12 @@ __device__ __forceinline__ void buffer_store_f64(__amdgpu_buffer_rsrc_t r, uint3
 // one takes the values that are left: a full one would let its unused registers
 // overlap another load's, which then waits for it (FP32, 2556 bins x 5000 walkers: 455 to
 // 285 ns a proposal).  From LDS full ones are faster (ds_read_b96, FP32, 300 bins x
-// 3000 walkers: 211 to 229 ns).
-template <bool MEM, typename R, int M>
+// 3000 walkers: 211 to 229 ns).  Quarters of a chunk that end within 16 bytes (FP32, 24
+// dimensions a chunk) are loaded by 8.
+template <bool MEM, typename R, int M, int BYTES = 16>
 __device__ __forceinline__ void load_chunk(const R *p, R (&v)[M])
 {
-    constexpr int W = 16 / sizeof(R), MS = chunk_stride<R>(M);
+    constexpr int W = BYTES / sizeof(R), MS = (M + W - 1) / W * W;
     typedef R vec __attribute__((ext_vector_type(W)));
     typedef R pair __attribute__((ext_vector_type(2)));
 #pragma unroll
@@ -442,7 +444,8 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
     const double4 *bin = a.bin;
     const double2 *GH = a.GH;
     const double cC = a.C, w0x2 = 2.0 * a.w0, dW = a.dW;
-    constexpr int st = chunk_stride<R>(MR), CVAL = CH * st;  // stored dimensions: of a lane, of a column
+    constexpr int st = WIDE ? MR : chunk_stride<R>(MR), CVAL = CH * st;  // stored dimensions: of a lane, of a column
+    constexpr int LB = st * sizeof(R) % 16 ? 8 : 16;                     // bytes of a load
     const int mine = WIDE ? (ch & 3) * (4 * st) + (ch >> 2) * st : ch * st;  // where this lane's are
 
     // records, columns and spectra in LDS
@@ -486,7 +489,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
 
     R phi[MR], lost = 0;  // lost: FP32, of a sweep's additions to phi[0]
     R *phig = (R *)a.phi + (size_t)lw * CVAL + mine;
-    load_chunk<false, R, MR>(phig, phi);
+    load_chunk<false, R, MR, LB>(phig, phi);
     double g = a.gsc[lw], chi2 = a.chi2[lw], rate = a.rate[lw], ginv = a.ginv[lw];
     double Q2 = 0.0;  // sum_i w_i Phi_i^2 of the walker, from its coordinates at each sweep's start
     int nacc = 0;
@@ -519,11 +522,11 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         v.s = s;
         const uint32_t po = (uint32_t)p * CVAL + (uint32_t)mine, so = (uint32_t)s * CVAL + (uint32_t)mine;
         if constexpr (LDSC) {
-            load_chunk<false, R, MR>(col_s + po, v.rp);
-            load_chunk<false, R, MR>(col_s + so, v.rs);
+            load_chunk<false, R, MR, LB>(col_s + po, v.rp);
+            load_chunk<false, R, MR, LB>(col_s + so, v.rs);
         } else {
-            load_chunk<true, R, MR>(colg + po, v.rp);
-            load_chunk<true, R, MR>(colg + so, v.rs);
+            load_chunk<true, R, MR, LB>(colg + po, v.rp);
+            load_chunk<true, R, MR, LB>(colg + so, v.rs);
         }
     };
     // staging area of a walker: records of batch slot h, then the bins
@@ -1042,8 +1045,9 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int block,
         // one proposal before that.  From memory they take longer than a proposal (32
         // jobs of 1300 bins, 300 walkers, FP64: 932 ns a proposal one ahead, 780 ns three;
         // alone, 5000 walkers, 389 and 345 ns; FP32, 2556 bins, 5000 walkers 350 and 285
-        // ns).  As far as registers go: 8 FP64 values a lane two ahead, 16 lanes one.
-        constexpr int AHEAD = LDSC ? 1 : G == 4 ? (M > 6 ? 2 : 3) : sizeof(R) == 4 ? 3 : 1, V = AHEAD == 1 ? 2 : 4;
+        // ns).  As far as registers go: 8 FP64 values a lane two ahead, 16 lanes of FP64
+        // or of more than 64 dimensions one.
+        constexpr int AHEAD = LDSC ? 1 : G == 4 ? (M > 6 ? 2 : 3) : sizeof(R) == 4 && M <= 16 ? 3 : 1, V = AHEAD == 1 ? 2 : 4;
         static_assert(G % V == 0, "a batch turns the ring");
         Rec v[V];
         double next_bins;
@@ -3621,11 +3625,12 @@ void with_basis_class(int precision, int cls, F &&f)
     if (precision == SAIL_FP32) {
         switch (cls) {
             SAIL_CASE(float, 2) SAIL_CASE(float, 3) SAIL_CASE(float, 4) SAIL_CASE(float, 6) SAIL_CASE(float, 16)
+            SAIL_CASE(float, 24)
         }
     } else {
         switch (cls) {
             SAIL_CASE(double, 2) SAIL_CASE(double, 4) SAIL_CASE(double, 6) SAIL_CASE(double, 8) SAIL_CASE(double, 16)
-            SAIL_CASE(double, 24)
+            SAIL_CASE(double, 24) SAIL_CASE(double, 32)
         }
     }
 #undef SAIL_CASE
@@ -3684,9 +3689,12 @@ sail_status launch_sweep(sail_problem *p, int k0, int k1, const SweepParams &sp,
 constexpr double kBasisTol64 = 1e-7, kBasisTolLeast = 2e-8, kBasisTol32 = 1e-4, kBasisGreedy = 1e-8;
 constexpr int kBasisSample = 64;
 // Dimensions at most.  Decaying kernels give 5 to 25.  Weights that turn the columns
-// into separate Gaussians give some sqrt(32 W) / pi, W the range of omega tau, which is
-// below 1450 where the columns' norms fit a double: 73 (in FP32 56) computed there.
-constexpr int kBasisMost = 4 * kDims64[5];
+// into separate Gaussians give most.  Equally wide ones are some sqrt(32 W) / pi, W the
+// range of omega tau, which is below 1450 where the columns' norms fit a double: 73 (in
+// FP32 56) computed there; ones that widen with tau are more: 107 (78) the most that a
+// search over such weights found.
+constexpr int kBasisMost = 4 * kDims64[6], kBasisMost32 = 4 * kDims32[5];
+constexpr int kBasisReckoned = 96;  // in footprints
 
 double dot(const double *x, const double *y, int n)
 {
@@ -3769,8 +3777,9 @@ public:
     }
 
     // extends the selection until it spans the sample to kBasisGreedy, and
-    // returns it rotated: [vectors][n_tau], orthonormal
-    std::vector<std::vector<double>> vectors()
+    // returns it rotated: [vectors][n_tau], orthonormal; more vectors than columns of
+    // the first sample only if `turn`
+    std::vector<std::vector<double>> vectors(bool turn)
     {
         const int n = p_->n_tau, most = std::min(p_->n_omega, n);
         while ((int)q_.size() < most) {
@@ -3804,9 +3813,8 @@ public:
         }
         std::vector<std::vector<double>> q = q_;
         const int dims = (int)q.size();
-        // principal directions of the sampled columns (a basis of more vectors
-        // than columns of the first sample stays as it is)
-        if (dims <= kBasisSample) {
+        // principal directions of the sampled columns
+        if (dims <= kBasisSample || turn) {
             std::vector<std::vector<double>> rows(dims), r;
             for (int d = 0; d < dims; ++d)
                 for (const auto &v : column_) rows[d].push_back(dot(q_[d].data(), v.data(), n));
@@ -3911,8 +3919,9 @@ sail_status build_tables(sail_problem *p)
     const int ns = std::min(No, kBasisSample);
     for (int i = 0; i < ns; ++i) sample.take((int)((int64_t)i * (No - 1) / std::max(1, ns - 1)));
     std::vector<double> got(kBasisPass + No), worst;
-    for (;;) {
-        q = sample.vectors();
+    int dims64, dims32;
+    for (bool turn = false;;) {
+        q = sample.vectors(turn);
         loaded = -1;
         // what every column holds from each vector on, last vectors first
         const int dims = (int)q.size();
@@ -3932,16 +3941,21 @@ sail_status build_tables(sail_problem *p)
         bool more = false;
         const int want = std::min<int>((int)out.size(), 16);
         for (int i = 0; i < want; ++i) more |= sample.take(out[(size_t)i * out.size() / want]);
-        if (!more) break;
+        if (more) continue;
+        dims64 = dims32 = dims;
+        for (int d = dims - 1; d >= 1; --d) {
+            const double tol = d <= 4 * kDims64[0] ? kBasisTolLeast : kBasisTol64;
+            if (worst[d] <= tol * tol) dims64 = d;
+            if (worst[d] <= kBasisTol32 * kBasisTol32) dims32 = d;
+        }
+        // (500 bins, 512 times under weights whose columns widen along tau: 106 and 99
+        // as selected, 98 and 72 rotated)
+        if ((dims64 <= kBasisMost && dims32 <= kBasisMost32) || turn) break;
+        turn = true;
     }
     const int dims = (int)q.size();
-    int dims64 = dims, dims32 = dims;
-    for (int d = dims - 1; d >= 1; --d) {
-        const double tol = d <= 4 * kDims64[0] ? kBasisTolLeast : kBasisTol64;
-        if (worst[d] <= tol * tol) dims64 = d;
-        if (worst[d] <= kBasisTol32 * kBasisTol32) dims32 = d;
-    }
-    if (dims64 > kBasisMost) return fail(SAIL_ENUMERIC, "the weighted columns span more than 96 dimensions");
+    if (dims64 > kBasisMost || dims32 > kBasisMost32)
+        return fail(SAIL_ENUMERIC, "the weighted columns span too many dimensions");
     p->dims64 = round_dims(SAIL_FP64, dims64);
     p->dims32 = round_dims(SAIL_FP32, dims32);
     const int ec = p->echunk = chunk_stride<double>(p->dims64), kept = std::min(dims, 4 * p->dims64);
@@ -4101,12 +4115,12 @@ size_t max_padding(int n_tau, int precision)
 }
 
 // Device bytes of a problem's tables, each rounded as the allocator rounds it;
-// the basis has at most min(n_tau, n_omega, kBasisMost) dimensions.
+// the basis of min(n_tau, n_omega, kBasisReckoned) dimensions at most.
 size_t table_bytes(int n_omega, int n_tau, int precision)
 {
     const size_t rsz = precision == SAIL_FP32 ? sizeof(float) : sizeof(double);
     const size_t No = (size_t)n_omega;
-    const int most = std::min(std::min(n_tau, n_omega), kBasisMost);
+    const int most = std::min(std::min(n_tau, n_omega), kBasisReckoned);
     const size_t d64 = 4 * (size_t)chunk_stride<double>(round_dims(SAIL_FP64, most));
     const size_t d32 = 4 * (size_t)chunk_stride<float>(round_dims(SAIL_FP32, most));
     return sizeof(double) * (6 * No + No * (n_tau + d64) + (5 + kBasisPass) * (size_t)n_tau + kBasisPass + 2 * (2 * No - 1)) +

@@ -7,6 +7,7 @@ spread the columns over more dimensions (the wider classes, and the general
 one of any number) are compared with the oracle, to the parity tests' bars.
 """
 import dataclasses
+import sys
 
 import numpy as np
 import pytest
@@ -101,6 +102,30 @@ def test_wide_bases_against_oracle(S, n_omega, n_tau, spread):  # noqa: F811
 def test_basis_classes_against_oracle(S, n_omega, n_tau, spread):  # noqa: F811
     wl = _workload(n_omega, n_tau, 18, 20, spread)
     _anneal_lockstep(S, wl, 18, 11, 20, dict(branch_every=20, resync_every=10), T=np.geomspace(100.0, 1.0, 20))
+
+
+def _widening(n_walkers, n_sweeps, prec=0):
+    """Weights that turn 500 columns along 512 times into Gaussians which widen
+    along tau, the most dimensions of a grid: 98 (FP32: 72) in principal
+    directions, 106 (99) as selected.  With prec 1 half the range, scaled so that the
+    columns fit a float: 77 in FP32."""
+    w_max, tau = 1675.0 / (1 + prec), np.linspace(0.0, 4.0, 512)
+    tgt = W.Target([0.15 * w_max, 0.4 * w_max], [0.04 * w_max, 0.08 * w_max], [0.6, 0.4], w_max)
+    wl = W.make("widening", w_max, 500, tau, tgt, 1e-3, 3, n_walkers, n_sweeps, 1e2, 1.0, n_sweeps, n_sweeps, 5,
+                n_quad=4000)
+    slope = np.cumsum((tau / 4.0 + 0.042) ** -1.934)
+    slope = w_max * (slope[-1] - slope) / (slope[-1] - slope[0])
+    v = np.cumsum(slope) * (tau[1] - tau[0])
+    v -= v[-1] - 75.0 if prec else 0.5 * (v[0] + v[-1])
+    return dataclasses.replace(wl, sigma=np.exp(-np.clip(v, -340.0, 340.0)))
+
+
+@pytest.mark.parametrize("n_walkers,prec,walk", [(130, 0, 0), (130, 1, 0), (37, 0, 3), (4500, 1, 0)])
+def test_same_bits_for_the_widest_basis(S, monkeypatch, n_walkers, prec, walk):  # noqa: F811
+    plain = _workload
+    monkeypatch.setattr(sys.modules[__name__], "_workload", lambda o, t, w, n, spread=0.0: (
+        _widening(w, n, prec) if spread else plain(o, t, w, n)))
+    test_same_bits_for_every_plan(S, 500, 512, n_walkers, prec, walk, 1.0)
 
 
 # bases of more than 32 dimensions: 16 lanes a walker in every plan
